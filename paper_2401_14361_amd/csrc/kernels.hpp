@@ -98,8 +98,6 @@ struct moei_eamc {
     unsigned long long* d_cand = nullptr;   // [B_max][workgroups][2] per-workgroup winners (dot, norm)
     int32_t* d_cand_idx = nullptr;          // [B_max][workgroups] their trace indices
     unsigned* d_ticket = nullptr;           // [B_max] arrival counters of the final pick
-    // priority scratch
-    unsigned long long* d_keys = nullptr;  // [2][L*E] sort keys (prefetch, evict)
 };
 
 namespace moei {

@@ -1201,7 +1201,6 @@ extern "C" int moei_eamc_create(const moei_model_desc* desc, int32_t n_cap, int3
     c->n_cap = n_cap;
     c->cell_bytes = cell_bytes;
     c->lsplit_max = desc->L < 32 ? desc->L : 32;
-    const size_t LE = (size_t)desc->L * desc->E;
     hipError_t e = hipMalloc(&c->d_traces, cells(c) * cell_bytes);
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_norm2, (size_t)n_cap * 8);
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_part, (size_t)kMaxMatchBatch * c->lsplit_max * n_cap * 8);
@@ -1210,7 +1209,6 @@ extern "C" int moei_eamc_create(const moei_model_desc* desc, int32_t n_cap, int3
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_cand_idx, (size_t)kMaxMatchBatch * n_blk_max * 4);
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_ticket, (size_t)kMaxMatchBatch * 4);
     if (e == hipSuccess) e = hipMemset(c->d_ticket, 0, (size_t)kMaxMatchBatch * 4);
-    if (e == hipSuccess) e = hipMalloc((void**)&c->d_keys, 2 * LE * 8);
     if (e != hipSuccess) {
         moei_eamc_destroy(c);
         MOEI_FAIL(MOEI_ENOMEM, "moei_eamc_create: device allocation failed: %s", hipGetErrorString(e));
@@ -1227,7 +1225,6 @@ extern "C" int moei_eamc_destroy(moei_eamc* c) {
     (void)hipFree(c->d_cand);
     (void)hipFree(c->d_cand_idx);
     (void)hipFree(c->d_ticket);
-    (void)hipFree(c->d_keys);
     delete c;
     return MOEI_OK;
 }

@@ -347,6 +347,30 @@ def test_expert_priority(m, N, L, E, B, cb):
         np.testing.assert_allclose(V, rV, rtol=1e-6, atol=0)
 
 
+# rows wider than the registers of a lane, one cell, the most cells the LDS holds, the largest batch with
+# repeated picks and a token without picks (-1)
+@pytest.mark.parametrize("N,L,E,B", [(9, 3, 300, 16), (3, 1, 1, 1), (4, 10, 2048, 2), (30, 20, 65, 9)])
+def test_expert_priority_row_widths_and_batches(m, N, L, E, B):
+    rng = np.random.default_rng(N + L + E)
+    T = (rng.integers(0, 9, size=(N, L, E)) * (rng.random((N, L, E)) < 0.5)).astype(np.int32)
+    desc = m.ModelDesc(L, E, 1, 0, 8, 8, m.WDTYPE_BF16, 0, EPS)
+    eamc = m.Eamc(desc, N, 4)
+    eamc.load(T)
+    res = rng.random((L, E)) < 0.5
+    slot_of = np.where(res.reshape(-1), np.arange(L * E), -1).astype(np.int32)
+    for cur in (0, L - 1):
+        best = rng.integers(-1, N, size=B).astype(np.int32)
+        cur_idx = rng.integers(-1, E, size=(B, 5)).astype(np.int32)
+        out = m.expert_priority(eamc, dev(best), cur, dev(slot_of), EPS, dev(cur_idx))
+        P, V, pf, n_pf, ev, n_ev = [o.cpu().numpy() for o in out]
+        rP, rV, rpf, rev = O.expert_priority(O.aggregate_matches(T, best), cur, res, EPS,
+                                             [cur * E + int(j) for j in cur_idx.reshape(-1) if j >= 0])
+        assert pf[:int(n_pf[0])].tolist() == rpf and ev[:int(n_ev[0])].tolist() == rev
+        np.testing.assert_allclose(P, rP, rtol=1e-6, atol=0)
+        np.testing.assert_allclose(V, rV, rtol=1e-6, atol=0)
+    eamc.close()
+
+
 def test_expert_priority_worked_example(m):
     # Sec. 4.7 example: EAM [[1,2],[0,3],[0,3]]; E[2,2] (0-based (1,1)) is kept, (1,0) and (2,0) go first
     T = np.array([[[1, 2], [0, 3], [0, 3]]], dtype=np.int32)
