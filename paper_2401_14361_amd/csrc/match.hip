@@ -837,7 +837,7 @@ __global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) {
             if (a.best_sim) a.best_sim[b] = r.idx >= 0 ? (float)cosine(r.dot, nq, r.nt) : 0.f;
             s_best[0] = r.idx;
         }
-        if (a.do_score) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best, true);
+        if (a.do_score) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best);
         return;
     }
     // several workgroups: publish this one's winner, the last to arrive finishes
@@ -869,7 +869,7 @@ __global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) {
         a.ticket[b] = 0;  // ready for the next launch on this stream
         s_best[0] = fin.idx;
     }
-    if (a.do_score) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best, true);
+    if (a.do_score) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best);
 }
 
 // ---- the m most similar traces of ONE query, most similar first (ties: lowest index)
@@ -1033,7 +1033,7 @@ __global__ void __launch_bounds__(kPickThreads) eamc_topm_kernel(TopmArgs a) {
             });
         if (tid == 0) *a.ticket = 0;  // ready for the next launch on this stream
     }
-    if (a.do_score) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best, true);
+    if (a.do_score) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best);
 }
 
 struct Plan {

@@ -1,5 +1,5 @@
-// Scoring of every (layer, expert) cell from the matched traces: shared by the stand-alone
-// priority kernel and by the match kernel's finishing workgroup (fused layer step).
+// Scoring of every (layer, expert) cell from the matched traces by the workgroup that finishes the
+// match (fused layer step).
 #pragma once
 
 #include "kernels.hpp"
@@ -49,10 +49,6 @@ __device__ __forceinline__ uint32_t cell_at(const void* traces, int cell_bytes, 
                            : (uint32_t) reinterpret_cast<const uint16_t*>(traces)[i];
 }
 
-// Called by all kScoreThreads threads of ONE workgroup: scores for every cell, a 64-bit sort
-// key per cell and list (kNone where the cell is not a candidate) and the two candidate
-// counts.  One wavefront per layer row.  s_n[2] and s_best[kMaxMatchBatch] are LDS; with
-// best_in_lds the caller has already put the matched trace indices (-1 = none) there.
 // A copy of the keys in LDS for the head selection (models of up to kKeyLdsCells cells): the
 // selection then needs no second trip to memory.
 constexpr int kKeyLdsCells = 2048;
@@ -60,70 +56,63 @@ struct KeyLds {
     u64 k[2][kKeyLdsCells];
 };
 
-__device__ __forceinline__ void score_cells(const ScoreArgs& a, int* s_n, int* s_best, bool best_in_lds, u64* kp,
-                                            u64* kv, KeyLds* lds_keys) {
+// Called by all kScoreThreads threads of ONE workgroup: scores for every cell, a 64-bit sort
+// key per cell and list (kNone where the cell is not a candidate) and the two candidate
+// counts.  One wavefront per layer row, two of its rows on their way at a time (the trip to the
+// matched cells is what a row costs, and beside the streaming FFN it is a long one).  s_n[2] and
+// s_best[kMaxMatchBatch] are LDS; the caller has put the matched trace indices (-1 = none) into s_best.
+__device__ __forceinline__ void score_cells(const ScoreArgs& a, int* s_n, const int* s_best, u64* kp, u64* kv,
+                                            KeyLds* lds_keys) {
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wv = tid / kWave;
     const int L = a.L, E = a.E, l = a.cur_layer;
     if (tid < 2) s_n[tid] = 0;
-    if (!best_in_lds && tid < a.B) {
-        const int n = a.best[tid];
-        s_best[tid] = (n >= 0 && n < a.N) ? n : -1;
-    }
     __syncthreads();
     constexpr int kPerLane = 4;  // cells of a row held in registers (rows up to 256 wide)
-    int my_ev = 0, my_pf = 0;
-    for (int i = wv; i < L; i += kScoreThreads / kWave) {
-        // all of the row's loads go out together: matched cells, residency, current picks
+    struct Row {
         u64 tv[kPerLane];
         int sv[kPerLane];
-        u64 rsum = 0;
-        for (int r = 0; r * kWave < E; ++r) {
-            const int j = lane + r * kWave;
-            u64 t = 0;
-            int slot = -1;
-            if (j < E) {
-                for (int b = 0; b < a.B; ++b) {
-                    const int n = s_best[b];
-                    if (n >= 0) t += cell_at(a.traces, a.cell_bytes, ((size_t)i * a.n_cap + n) * E + j);
-                }
-                if (r < kPerLane) slot = a.slot_of[(size_t)i * E + j];
-            }
-            if (r < kPerLane) {
-                tv[r] = t;
-                sv[r] = slot;
-            }
-            rsum += t;
+        u64 rsum;
+        int cur;  // lane m holds pick m of the current layer (used for row l only)
+    };
+    int my_ev = 0, my_pf = 0;
+    auto cell_sum = [&](int i, int j) {
+        u64 t = 0;
+        for (int b = 0; b < a.B; ++b) {
+            const int n = s_best[b];
+            if (n >= 0) t += cell_at(a.traces, a.cell_bytes, ((size_t)i * a.n_cap + n) * E + j);
         }
-        int cur = -1;  // lane m holds pick m of the current layer (used for row l only)
-        if (i == l && lane < a.n_cur) cur = a.cur_idx[lane];
-        const u64 R = wave_sum_u64_dpp(rsum);
-        const double den = (double)(R ? R : 1ull) * (double)L;
-        for (int r = 0; r * kWave < E; ++r) {
+        return t;
+    };
+    // all of a row's loads go out together: matched cells, residency, current picks
+    auto load_row = [&](int i, Row& w) {
+        w.rsum = 0;
+#pragma unroll
+        for (int r = 0; r < kPerLane; ++r) {
             const int j = lane + r * kWave;
-            u64 t = 0;
-            int slot = -1;
-            if (r < kPerLane) {
-                t = tv[r];
-                slot = sv[r];
-            } else if (j < E) {
-                for (int b = 0; b < a.B; ++b) {
-                    const int n = s_best[b];
-                    if (n >= 0) t += cell_at(a.traces, a.cell_bytes, ((size_t)i * a.n_cap + n) * E + j);
-                }
-                slot = a.slot_of[(size_t)i * E + j];
-            }
+            w.tv[r] = j < E ? cell_sum(i, j) : 0;
+            w.sv[r] = j < E ? a.slot_of[(size_t)i * E + j] : -1;
+            w.rsum += w.tv[r];
+        }
+        for (int j = lane + kPerLane * kWave; j < E; j += kWave) w.rsum += cell_sum(i, j);
+        w.cur = -1;
+        if (i == l && lane < a.n_cur) w.cur = a.cur_idx[lane];
+    };
+    auto score_row = [&](int i, const Row& w) {
+        const u64 R = wave_sum_u64_dpp(w.rsum);
+        const double den = (double)(R ? R : 1ull) * (double)L;
+        auto score = [&](int j, u64 t, int slot) {
             // is expert j one of the current picks?  (all 64 lanes take part in the shuffles)
             bool excluded = false;
             if (i == l) {
                 for (int m0 = 0; m0 < a.n_cur; m0 += kWave) {
-                    int c = cur;
+                    int c = w.cur;
                     if (m0 > 0) c = (m0 + lane < a.n_cur) ? a.cur_idx[m0 + lane] : -1;
                     const int lim = min(kWave, a.n_cur - m0);
                     for (int m = 0; m < lim; ++m) excluded |= (__shfl(c, m, kWave) == j);
                 }
             }
-            if (j >= E) continue;
+            if (j >= E) return;
             const size_t f = (size_t)i * E + j;
             const double td = (double)t;
             const double v = ((td + a.eps) * (double)(L - i)) / den;
@@ -145,7 +134,22 @@ __device__ __forceinline__ void score_cells(const ScoreArgs& a, int* s_n, int* s
             }
             my_pf += is_pf;
             my_ev += is_ev;
+        };
+#pragma unroll
+        for (int r = 0; r < kPerLane; ++r)
+            if (r * kWave < E) score(lane + r * kWave, w.tv[r], w.sv[r]);  // uniform
+        for (int r = kPerLane; r * kWave < E; ++r) {
+            const int j = lane + r * kWave;
+            score(j, j < E ? cell_sum(i, j) : 0, j < E ? a.slot_of[(size_t)i * E + j] : -1);
         }
+    };
+    constexpr int kWaves = kScoreThreads / kWave;
+    for (int i = wv; i < L; i += 2 * kWaves) {
+        Row w0, w1;
+        load_row(i, w0);
+        if (i + kWaves < L) load_row(i + kWaves, w1);
+        score_row(i, w0);
+        if (i + kWaves < L) score_row(i + kWaves, w1);
     }
     if (my_pf) atomicAdd(&s_n[0], my_pf);
     if (my_ev) atomicAdd(&s_n[1], my_ev);
@@ -202,76 +206,92 @@ __device__ __forceinline__ KeyId wave_keyid_min(KeyId v) {
     return KeyId{((u64)mh << 32) | ml, (int)mi};
 }
 
-constexpr int kSelWaves = 4;                     // wavefronts that search one list (one per SIMD)
+constexpr int kSelWaves = 8;                     // wavefronts that search one list: half of the workgroup
 constexpr int kSelThreads = kSelWaves * kWave;
-constexpr int kSelOwn = 8;                       // keys a lane keeps in registers (models of up to 2048 cells)
+constexpr int kSelOwnSmall = 4;                  // keys a lane keeps in registers (models of up to 2,048 cells) ...
+constexpr int kSelOwnLarge = 20;                 // ... and of up to 10,240 cells
 constexpr int kHeadMax = 96;                     // most entries of a head (picks + prefetch candidates)
+static_assert(2 * kSelThreads == kScoreThreads, "both lists are searched at once");
 struct HeadLds {
     u64 key[2][kSelWaves][kHeadMax];
     int id[2][kSelWaves][kHeadMax];
 };
 
+// The h smallest (key, flat id) pairs of the calling wavefront's cells ltid, ltid + 512, ... of one list,
+// ascending, to okey / oid: h rounds of a DPP arg-min, no barrier - what remains after a round is what
+// lies after its winner, and only the lane that held the winner looks through its cells again.  OWN:
+// keys of a lane held in registers, all requested together (0: read again each time).
+template <int OWN>
+__device__ __forceinline__ void wave_head(const u64* keys, int LE, int ltid, int lane, int want, u64* okey, int* oid) {
+    u64 mine[OWN > 0 ? OWN : 1];
+#pragma unroll
+    for (int r = 0; r < OWN; ++r) {
+        const int f = ltid + r * kSelThreads;
+        mine[r] = f < LE ? keys[f] : kNone;
+    }
+    bool have_last = false;
+    KeyId last{0, -1};
+    KeyId cur{kNone, 0x7fffffff};
+    bool cur_valid = false;  // this lane's best remaining cell is known
+    for (int round = 0; round < want; ++round) {
+        if (!cur_valid) {
+            cur = KeyId{kNone, 0x7fffffff};
+            auto consider = [&](u64 k, int f) {
+                if (k == kNone) return;
+                if (have_last && (k < last.k || (k == last.k && f <= last.id))) return;
+                cur = keyid_min(cur, KeyId{k, f});
+            };
+            if constexpr (OWN > 0) {
+#pragma unroll
+                for (int r = 0; r < OWN; ++r) consider(mine[r], ltid + r * kSelThreads);
+            } else {
+                for (int f = ltid; f < LE; f += kSelThreads) consider(keys[f], f);
+            }
+            cur_valid = true;
+        }
+        const KeyId w = wave_keyid_min(cur);
+        if (lane == 0) {
+            okey[round] = w.k;
+            oid[round] = w.id;
+        }
+        last = w;
+        have_last = true;
+        if (cur.id == w.id) cur_valid = false;  // this lane's best has been taken: look for its next one
+    }
+}
+
 // All kScoreThreads threads of the scoring workgroup call, after score_cells (whose closing barrier
-// has made the keys visible).  Wavefronts 0..3 search the prefetch list, 4..7 the eviction list, the
-// others only meet the barrier.  Lane t of a list's 256 owns cells t, t + 256, ...  First every
-// wavefront extracts the h smallest (key, flat id) pairs of its own cells - h rounds of a DPP arg-min,
-// no barrier: what remains after a round is what lies after its winner - then the list's first
-// wavefront extracts the h smallest of the 4 h candidates the same way.
+// has made the keys visible).  Wavefronts 0..7 search the prefetch list, 8..15 the eviction list.
+// First every wavefront extracts the h smallest pairs of its own cells, then the list's first
+// wavefront the h smallest of those 8 h candidates the same way.
 // Writes pf_order[0 .. min(h_pf, n_pf)) and ev_order[0 .. min(h_ev, n_ev)).
+// A chain of dependent steps, so what counts is their number: with four wavefronts a list and keys in
+// registers for up to 2,048 cells only, every round over 9,440 cells was one more trip to memory per
+// 256 of them, and the finishing workgroup of the match took 80.6 us beside the streaming FFN; now 42.1 (59 x 160 cells, two
+// rows of a wavefront on their way at a time included).
 __device__ __forceinline__ void select_heads(const ScoreArgs& a, const u64* kp, const u64* kv, const int* s_n, HeadLds& hl) {
     const int tid = threadIdx.x;
     const int LE = a.L * a.E;
-    const int list = tid / kSelThreads;          // 0, 1: searching; >= 2: idle
+    const int list = tid / kSelThreads;
     const int ltid = tid % kSelThreads;
     const int lane = tid & (kWave - 1), lwave = ltid / kWave;
-    const bool active = list < 2;
     const u64* keys = list == 0 ? kp : kv;
     int32_t* out = list == 0 ? a.pf_order : a.ev_order;
     int32_t* host_out = list == 0 ? a.host_pf_head : a.host_ev_head;
-    int want = 0;
-    if (active) want = list == 0 ? min(a.h_pf, s_n[0]) : min(a.h_ev, s_n[1]);
-    want = min(want, kHeadMax);
+    const int want = min(list == 0 ? min(a.h_pf, s_n[0]) : min(a.h_ev, s_n[1]), kHeadMax);
     if (want > 0) {  // uniform over the wavefront
-        const bool in_regs = LE <= kSelOwn * kSelThreads;
-        u64 mine[kSelOwn];
-#pragma unroll
-        for (int r = 0; r < kSelOwn; ++r) {
-            const int f = ltid + r * kSelThreads;
-            mine[r] = (in_regs && f < LE) ? keys[f] : kNone;
-        }
-        bool have_last = false;
-        KeyId last{0, -1};
-        KeyId cur{kNone, 0x7fffffff};
-        bool cur_valid = false;  // this lane's best remaining cell is known
-        for (int round = 0; round < want; ++round) {
-            if (!cur_valid) {
-                cur = KeyId{kNone, 0x7fffffff};
-                auto consider = [&](u64 k, int f) {
-                    if (k == kNone) return;
-                    if (have_last && (k < last.k || (k == last.k && f <= last.id))) return;
-                    cur = keyid_min(cur, KeyId{k, f});
-                };
-                if (in_regs) {
-#pragma unroll
-                    for (int r = 0; r < kSelOwn; ++r) consider(mine[r], ltid + r * kSelThreads);
-                } else {
-                    for (int f = ltid; f < LE; f += kSelThreads) consider(keys[f], f);
-                }
-                cur_valid = true;
-            }
-            const KeyId w = wave_keyid_min(cur);
-            if (lane == 0) {
-                hl.key[list][lwave][round] = w.k;
-                hl.id[list][lwave][round] = w.id;
-            }
-            last = w;
-            have_last = true;
-            if (cur.id == w.id) cur_valid = false;  // this lane's best has been taken: look for its next one
-        }
+        u64* okey = hl.key[list][lwave];
+        int* oid = hl.id[list][lwave];
+        if (LE <= kSelOwnSmall * kSelThreads)
+            wave_head<kSelOwnSmall>(keys, LE, ltid, lane, want, okey, oid);
+        else if (LE <= kSelOwnLarge * kSelThreads)
+            wave_head<kSelOwnLarge>(keys, LE, ltid, lane, want, okey, oid);
+        else
+            wave_head<0>(keys, LE, ltid, lane, want, okey, oid);
     }
     __syncthreads();
     if (want > 0 && lwave == 0) {
-        // 4 * want candidates, lane-major: candidate c = wave * want + round sits in lane c % 64
+        // 8 * want candidates, lane-major: candidate c = wave * want + round sits in lane c % 64
         constexpr int kPer = (kSelWaves * kHeadMax + kWave - 1) / kWave;
         const int total = kSelWaves * want;
         KeyId cand[kPer];
@@ -286,10 +306,11 @@ __device__ __forceinline__ void select_heads(const ScoreArgs& a, const u64* kp, 
             KeyId cur{kNone, 0x7fffffff};
 #pragma unroll
             for (int r = 0; r < kPer; ++r) {
-                const KeyId c = cand[r];
-                if (c.k == kNone) continue;
-                if (have_last && (c.k < last.k || (c.k == last.k && c.id <= last.id))) continue;
-                cur = keyid_min(cur, c);
+                if (r * kWave < total) {  // uniform
+                    const KeyId c = cand[r];
+                    const bool taken = have_last && (c.k < last.k || (c.k == last.k && c.id <= last.id));
+                    if (c.k != kNone && !taken) cur = keyid_min(cur, c);
+                }
             }
             const KeyId w = wave_keyid_min(cur);
             if (lane == 0 && w.k != kNone) {
@@ -303,12 +324,11 @@ __device__ __forceinline__ void select_heads(const ScoreArgs& a, const u64* kp, 
 }
 
 // Scoring, then the heads of the orders when the caller has asked for them.
-__device__ __forceinline__ void score_and_heads(const ScoreArgs& a, HeadLds& hl, KeyLds& kl, int* s_n, int* s_best,
-                                                bool best_in_lds) {
+__device__ __forceinline__ void score_and_heads(const ScoreArgs& a, HeadLds& hl, KeyLds& kl, int* s_n, const int* s_best) {
     const int LE = a.L * a.E;
     const bool heads = a.h_pf > 0 || a.h_ev > 0;
     const bool in_lds = heads && LE <= kKeyLdsCells;
-    score_cells(a, s_n, s_best, best_in_lds, a.keys, a.keys + LE, in_lds ? &kl : nullptr);
+    score_cells(a, s_n, s_best, a.keys, a.keys + LE, in_lds ? &kl : nullptr);
     if (heads) select_heads(a, in_lds ? kl.k[0] : a.keys, in_lds ? kl.k[1] : a.keys + LE, s_n, hl);
 }
 

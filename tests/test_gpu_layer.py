@@ -449,3 +449,30 @@ def test_full_size_deepseek_v2_slice_steps(m):
     cfg = mi.get_config("C4")
     cfg = cfg.scaled(L=cfg.S // cfg.E)
     _replay(m, cfg, cfg.L * cfg.E, 1, 12, 2)
+
+
+# the heads of the orders from keys in LDS, from 4 and from 20 keys per lane, and read again each time; rows of
+# one and of several wavefronts' width
+@pytest.mark.parametrize("L,E", [(3, 700), (33, 62), (60, 170), (5, 2048)])
+def test_heads_of_the_orders_over_many_cells(m, L, E):
+    rng = np.random.default_rng(L * E)
+    k, depth, H, I, N = 3, 5, 64, 8, 40
+    desc = m.ModelDesc(L, E, k, 0, H, I, m.WDTYPE_BF16, 0, EPS)
+    T = (rng.integers(0, 30, size=(N, L, E)) * (rng.random((N, L, E)) < 0.3)).astype(np.int32)
+    eamc = m.Eamc(desc, N, 4)
+    eamc.load(T)
+    cache = m.Cache(desc, L * E // 2, pinned(np.zeros((2, 3 * H * I), dtype=np.uint16)))
+    cache.reset(L * E // 2)
+    cache.set_prefetch(depth)
+    d_eam = dev(T[7].copy())
+    y = torch.empty(H, dtype=torch.float32, device="cuda")
+    W, x = dev(np.zeros((E, H), dtype=np.uint16)), dev(np.zeros(H, dtype=np.uint16))
+    for layer in (0, L - 2):
+        bias = dev(rng.standard_normal(E).astype(np.float32))
+        res = cache.get_slots().reshape(L, E) >= 0
+        idx, best, _ = m.moe_decode_layer(cache, eamc, d_eam, layer, W, bias, x, y)
+        pf_head, ev_head = cache.last_heads()
+        _, _, rpf, rev = O.expert_priority(T[best].astype(np.int64), layer, res, EPS, [layer * E + int(j) for j in idx])
+        assert ev_head.tolist() == rev[:k + depth] and pf_head.tolist() == rpf[:depth]
+    cache.close()
+    eamc.close()
