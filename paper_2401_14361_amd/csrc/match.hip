@@ -873,7 +873,10 @@ __global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) {
 }
 
 // ---- the m most similar traces of ONE query, most similar first (ties: lowest index)
-constexpr int kTopmPerThread = 4;  // candidates a thread of the finishing workgroup may hold
+constexpr int kTopmPerThread = 4;   // candidates a thread of the finishing workgroup may hold
+constexpr int kTopmMax = 16;        // largest m
+constexpr int kTopmRankAll = kPickWaves * kTopmMax;  // candidates that are ranked against each other at once
+constexpr int kTopmLds = kTopmPerThread * kPickWaves * kTopmMax;  // what one pass over kTopmPerThread per thread leaves
 
 struct TopmArgs {
     const u64* part;   // [n_lsplit][n_cap]
@@ -890,150 +893,235 @@ struct TopmArgs {
     ScoreArgs sc;
 };
 
-// m rounds of "best of the workgroup, then retire it".  Every wavefront keeps its own winner in
-// LDS; after a round only the wavefront that held the overall winner searches again, the others'
-// winners stand.  `local_best()` is the calling thread's best remaining candidate, `retire(idx)`
-// removes a candidate from the calling thread, `emit(r, w)` is called by thread 0 with winner r.
-template <typename LocalBest, typename Retire, typename Emit>
-__device__ __forceinline__ void extract_top(int m, u64* s_dot, u64* s_nt, int* s_idx, int* s_win, LocalBest local_best,
-                                            Retire retire, Emit emit) {
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    bool stale = true;  // uniform over the wavefront: its LDS entry must be recomputed
-    for (int r = 0; r < m; ++r) {
-        if (stale) {
-            const Best wb = wave_pick(local_best());
-            if (lane == 0) {
-                s_dot[wv] = wb.dot;
-                s_nt[wv] = wb.nt;
-                s_idx[wv] = wb.idx;
-            }
-            stale = false;
-        }
-        __syncthreads();
-        if (wv == 0) {
-            Best w = make_best(0, 1, -1);
-            if (lane < kPickWaves && s_idx[lane] >= 0) w = make_best(s_dot[lane], s_nt[lane], s_idx[lane]);
-            w = wave_pick(w);
-            if (lane == 0) {
-                *s_win = w.idx;
-                emit(r, w);
-            }
-        }
-        __syncthreads();
-        const int win = *s_win;
-        if (win >= 0) {
-            retire(win);
-            stale = s_idx[wv] == win;  // LDS read, the same in every lane
-        }
-    }
+struct TopLds {
+    u64 dot[kTopmLds];
+    u64 nt[kTopmLds];
+    double key[kTopmLds];
+    int idx[kTopmLds];
+    int rank[kTopmRankAll];
+    int n_valid;
+};
+
+// A candidate's place is the number of candidates that come before it: independent comparisons, where
+// m rounds of an arg-max are m chains of dependent exchanges.  The comparison looks at the keys' high
+// words (positive doubles order like their bit patterns); only a pair whose high words differ by at
+// most one is looked at again, with whole keys and, within 2^-48, exactly.
+__device__ __forceinline__ unsigned key_hi(double key) { return (unsigned)((u64)__double_as_longlong(key) >> 32); }
+__device__ __forceinline__ bool close_hi(unsigned o, unsigned me) { return o - me + 1u <= 2u; }
+// Does candidate o come before candidate me?  (two different candidates that exist)
+__device__ __forceinline__ bool comes_before(const Best& o, const Best& me) {
+    const int c = cmp_sim(o, me);
+    return c > 0 || (c == 0 && o.idx < me.idx);
 }
 
-// grid (workgroups over traces): each workgroup extracts the m best of its 1024 traces by m
-// rounds of the exact pick; the last workgroup to arrive extracts the m best of all winners.
+__device__ __forceinline__ void top_put(TopLds& t, int i, const Best& b) {
+    t.dot[i] = b.dot;
+    t.nt[i] = b.nt;
+    t.key[i] = b.key;
+    t.idx[i] = b.idx;
+}
+__device__ __forceinline__ Best top_get(const TopLds& t, int i) {
+    Best b;
+    b.dot = t.dot[i];
+    b.nt = t.nt[i];
+    b.key = t.key[i];
+    b.idx = t.idx[i];
+    return b;
+}
+
+// The m first of a wavefront's 64 candidates (one per lane, idx -1: none), in order, to entries
+// at .. at + m of t; entries that stay free get idx -1.
+__device__ __forceinline__ void wave_top(const Best& me, int m, TopLds& t, int at) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const unsigned hi = key_hi(me.key);  // 0 for a lane without a candidate: before nobody
+    const u64 valid = __ballot(me.idx >= 0);
+    int rank = 0;
+    u64 unclear = 0;
+#pragma unroll
+    for (int j = 0; j < kWave; ++j) {
+        const unsigned o = (unsigned)__builtin_amdgcn_readlane((int)hi, j);
+        rank += o > hi ? 1 : 0;
+        unclear |= __ballot(close_hi(o, hi)) & ~(1ull << j);  // (a pair that is close sets both its lanes' bits)
+    }
+    for (u64 left = unclear & valid; left; left &= left - 1) {
+        const int j = __ffsll((long long)left) - 1;
+        const Best o = best_lane(me, j);
+        const unsigned ohi = key_hi(o.key);
+        if (close_hi(ohi, hi) && j != lane && me.idx >= 0) rank += (comes_before(o, me) ? 1 : 0) - (ohi > hi ? 1 : 0);
+    }
+    if (me.idx >= 0 && rank < m) top_put(t, at + rank, me);
+    if (lane >= __popcll(valid) && lane < m) t.idx[at + lane] = -1;
+}
+
+// The m first of the `count` candidates in t: while there are more than kTopmRankAll, every 64 of
+// them are cut down to their m first; then all are ranked against each other, the comparisons of one
+// candidate shared by as many threads as there are for it.  All threads of the workgroup call;
+// emit(r, best) is called once for each r < m by some thread (best.idx = -1: no such trace).
+template <typename Emit>
+__device__ __forceinline__ void block_top(TopLds& t, int count, int m, Emit emit) {
+    const int tid = threadIdx.x, wv = tid / kWave;
+    const Best none = make_best(0, 1, -1);
+    __syncthreads();
+    while (count > kTopmRankAll) {  // count <= kPickThreads: a candidate per thread
+        const Best me = tid < count && t.idx[tid] >= 0 ? top_get(t, tid) : none;
+        __syncthreads();
+        const int groups = (count + kWave - 1) / kWave;
+        if (wv < groups) wave_top(me, m, t, wv * m);  // uniform over the wavefront
+        __syncthreads();
+        count = groups * m;
+    }
+    if (tid < count) t.rank[tid] = 0;
+    if (tid == 0) t.n_valid = 0;
+    __syncthreads();
+    // thread = (candidate c, slice of the others), padded to whole wavefronts so that a slice is uniform
+    const int cpad = (count + kWave - 1) / kWave * kWave;
+    const int slices = kPickThreads / cpad;
+    const int c = tid % cpad, sl = tid / cpad;
+    if (sl < slices) {  // uniform over the wavefront
+        const Best me = c < count && t.idx[c] >= 0 ? top_get(t, c) : none;
+        const unsigned hi = key_hi(me.key);
+        const int per = (count + slices - 1) / slices;
+        const int o1 = min(count, (sl + 1) * per);
+        int rank = 0;
+#pragma unroll 4
+        for (int o = sl * per; o < o1; ++o) {
+            const unsigned ohi = key_hi(t.key[o]);
+            const int oidx = t.idx[o];
+            const bool close = close_hi(ohi, hi) & (oidx >= 0) & (oidx != me.idx);
+            rank += ((ohi > hi) & (oidx >= 0) & !close) ? 1 : 0;
+            if (__ballot(close) != 0ull) {
+                if (close && comes_before(top_get(t, o), me)) ++rank;
+            }
+        }
+        if (me.idx >= 0) {
+            if (rank) atomicAdd(&t.rank[c], rank);
+            if (sl == 0) atomicAdd(&t.n_valid, 1);
+        }
+    }
+    __syncthreads();
+    if (tid < count && t.idx[tid] >= 0 && t.rank[tid] < m) emit(t.rank[tid], top_get(t, tid));
+    if (tid >= t.n_valid && tid < m) emit(tid, none);
+}
+
+// grid (workgroups over traces): each workgroup finds the m best of its 1024 traces; the last
+// workgroup to arrive finds the m best of all winners.  A chain of dependent steps on few compute
+// units: m rounds of a workgroup-wide exact arg-max (two barriers and two chains of exchanges
+// each, twice over) took 39.7 us at 10,000 traces and m = 8, ranking takes 16.0 us.
 __global__ void __launch_bounds__(kPickThreads) eamc_topm_kernel(TopmArgs a) {
-    __shared__ u64 s_dot[kPickWaves];
-    __shared__ u64 s_nt[kPickWaves];
-    __shared__ int s_idx[kPickWaves];
+    __shared__ u64 s_red[kPickWaves];
     __shared__ u64 s_nq;
     __shared__ unsigned s_ticket;
-    __shared__ int s_win;
     __shared__ int s_sn[2];
     __shared__ int s_best[kMaxMatchBatch];
-    __shared__ HeadLds s_heads;
-    __shared__ KeyLds s_keys;
+    __shared__ u64 s_wdot[kTopmMax], s_wnt[kTopmMax];
+    __shared__ int s_widx[kTopmMax];
+    struct Scoring {
+        HeadLds heads;
+        KeyLds keys;
+    };
+    __shared__ __align__(16) unsigned char s_mem[sizeof(TopLds) > sizeof(Scoring) ? sizeof(TopLds) : sizeof(Scoring)];
+    TopLds& s_top = *reinterpret_cast<TopLds*>(s_mem);        // the search ...
+    Scoring& s_score = *reinterpret_cast<Scoring*>(s_mem);    // ... then the scoring
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wv = tid / kWave;
     const bool single = gridDim.x == 1;
 
+    // One trace per thread; its partial dot products and norm travel together with the query cells.
+    const int n = blockIdx.x * kPickChunk + tid;
+    const bool have = n < a.N;
+    u64 dot = 0, nt = 1;
+    if (have) {
+        const u64* pp = a.part + n;
+        nt = a.norm2[n];
+        int s = 0;
+        for (; s + 4 <= a.n_lsplit; s += 4) {  // the split partials are independent loads: four at a time
+            const u64 v0 = pp[(size_t)s * a.n_cap], v1 = pp[(size_t)(s + 1) * a.n_cap];
+            const u64 v2 = pp[(size_t)(s + 2) * a.n_cap], v3 = pp[(size_t)(s + 3) * a.n_cap];
+            dot += (v0 + v1) + (v2 + v3);
+        }
+        for (; s < a.n_lsplit; ++s) dot += pp[(size_t)s * a.n_cap];
+    }
     u64 nq = 0;
     for (int i = tid; i < a.LE; i += kPickThreads) {
         u64 v = (uint32_t)a.q[i];
         nq += v * v;
     }
     nq = wave_sum_u64_dpp(nq);
-    if (lane == 0) s_dot[wv] = nq;
+    if (lane == 0) s_red[wv] = nq;
     __syncthreads();
     if (tid == 0) {
         u64 t = 0;
-        for (int i = 0; i < kPickWaves; ++i) t += s_dot[i];
+        for (int i = 0; i < kPickWaves; ++i) t += s_red[i];
         s_nq = t;
     }
     __syncthreads();
     nq = s_nq;
 
     Best me = make_best(0, 1, -1);
-    const int n = blockIdx.x * kPickChunk + tid;  // one trace per thread
-    if (n < a.N) {
-        const u64* pp = a.part + n;
-        u64 dot = 0;
-        for (int s = 0; s < a.n_lsplit; ++s) dot += pp[(size_t)s * a.n_cap];
-        const u64 nt = a.norm2[n];
+    if (have) {
         if (a.sims) a.sims[n] = (float)cosine(dot, nq, nt);
         me = make_best(dot, nt, n);
     }
-    extract_top(
-        a.m, s_dot, s_nt, s_idx, &s_win, [&]() { return me; },
-        [&](int win) {
-            if (me.idx == win) me = make_best(0, 1, -1);
-        },
-        [&](int r, const Best& w) {
-            if (single) {
-                a.top[r] = w.idx;
-                if (a.top_sim) a.top_sim[r] = w.idx >= 0 ? (float)cosine(w.dot, nq, w.nt) : 0.f;
-                s_best[r] = w.idx;
-            } else {
-                const size_t ci = (size_t)blockIdx.x * a.m + r;
-                a.cand[ci * 2] = w.dot;
-                a.cand[ci * 2 + 1] = w.nt;
-                a.cand_idx[ci] = w.idx;
-            }
+    auto finish = [&](int r, const Best& w) {
+        a.top[r] = w.idx;
+        if (a.top_sim) a.top_sim[r] = w.idx >= 0 ? (float)cosine(w.dot, nq, w.nt) : 0.f;
+        s_best[r] = w.idx;
+    };
+    wave_top(me, a.m, s_top, wv * a.m);
+    if (single) {
+        block_top(s_top, kPickWaves * a.m, a.m, finish);
+    } else {
+        block_top(s_top, kPickWaves * a.m, a.m, [&](int r, const Best& w) {
+            s_wdot[r] = w.dot;
+            s_wnt[r] = w.nt;
+            s_widx[r] = w.idx;
         });
-    if (!single) {
-        if (tid == 0) {
+        __syncthreads();
+        if (wv == 0) {  // one wavefront stores the workgroup's winners, so one fence covers them all
+            if (lane < a.m) {
+                const size_t ci = (size_t)blockIdx.x * a.m + lane;
+                a.cand[ci * 2] = s_wdot[lane];
+                a.cand[ci * 2 + 1] = s_wnt[lane];
+                a.cand_idx[ci] = s_widx[lane];
+            }
             __threadfence();
-            s_ticket = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lane == 0) s_ticket = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
         if (s_ticket != gridDim.x - 1) return;
         if (tid == 0) __threadfence();
         __syncthreads();
         const int total = (int)gridDim.x * a.m;  // the host keeps this within kTopmPerThread per thread
-        Best mine[kTopmPerThread];
-#pragma unroll
-        for (int u = 0; u < kTopmPerThread; ++u) {
-            const int i = tid + u * kPickThreads;
-            mine[u] = make_best(0, 1, -1);
-            if (i < total) {
-                const int idx = __hip_atomic_load(&a.cand_idx[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (idx >= 0) {
-                    const u64 d = __hip_atomic_load(&a.cand[(size_t)i * 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    const u64 t = __hip_atomic_load(&a.cand[(size_t)i * 2 + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    mine[u] = make_best(d, t, idx);
-                }
+        auto winner = [&](int i) {
+            Best b = make_best(0, 1, -1);
+            const int idx = __hip_atomic_load(&a.cand_idx[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (idx >= 0) {
+                const u64 d = __hip_atomic_load(&a.cand[(size_t)i * 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const u64 t = __hip_atomic_load(&a.cand[(size_t)i * 2 + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                b = make_best(d, t, idx);
             }
+            return b;
+        };
+        int count = total;
+        if (total <= kTopmRankAll) {
+            if (tid < total) {
+                top_put(s_top, tid, winner(tid));
+            }
+        } else {
+            const int groups = (total + kWave - 1) / kWave;
+            for (int g = wv; g < groups; g += kPickWaves) {  // uniform over the wavefront
+                const int i = g * kWave + lane;
+                wave_top(i < total ? winner(i) : make_best(0, 1, -1), a.m, s_top, g * a.m);
+            }
+            count = groups * a.m;
         }
-        __syncthreads();  // the first phase is done with the LDS winners
-        extract_top(
-            a.m, s_dot, s_nt, s_idx, &s_win,
-            [&]() {
-                Best loc = mine[0];
-#pragma unroll
-                for (int u = 1; u < kTopmPerThread; ++u) loc = pick(loc, mine[u]);
-                return loc;
-            },
-            [&](int win) {
-#pragma unroll
-                for (int u = 0; u < kTopmPerThread; ++u)
-                    if (mine[u].idx == win) mine[u] = make_best(0, 1, -1);
-            },
-            [&](int r, const Best& w) {
-                a.top[r] = w.idx;
-                if (a.top_sim) a.top_sim[r] = w.idx >= 0 ? (float)cosine(w.dot, nq, w.nt) : 0.f;
-                s_best[r] = w.idx;
-            });
+        block_top(s_top, count, a.m, finish);
         if (tid == 0) *a.ticket = 0;  // ready for the next launch on this stream
     }
-    if (a.do_score) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best);
+    if (a.do_score) {
+        __syncthreads();  // the matched traces are in LDS; the search's LDS is free
+        score_and_heads(a.sc, s_score.heads, s_score.keys, s_sn, s_best);
+    }
 }
 
 struct Plan {

@@ -56,6 +56,15 @@ def test_topm_shapes_ties_and_short_collections(m, N, L, E, cell_bytes):
     _check_topm(m, T, q, cell_bytes, (1, 2, 5, 16))
 
 
+# winners of many workgroups: up to 256 of them are ranked at once, more are cut down first, over 1,024 twice
+@pytest.mark.parametrize("N,mm", [(16 * 1024, 16), (16 * 1024 + 1, 16), (65 * 1024, 16), (33 * 1024 - 5, 8)])
+def test_topm_winners_of_many_workgroups(m, N, mm):
+    rng = np.random.default_rng(N)
+    T = rng.integers(0, 50, size=(N, 1, 4)).astype(np.int32)   # small counts: many exact and many close similarities
+    T[::997] = 0
+    _check_topm(m, T, rng.integers(1, 50, size=(1, 4)).astype(np.int32), 4, (mm,))
+
+
 def test_topm_many_equal_similarities(m):
     # few distinct cell values: most similarities coincide exactly, the order is the index order
     rng = np.random.default_rng(5)
