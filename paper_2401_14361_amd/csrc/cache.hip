@@ -692,8 +692,8 @@ extern "C" int moe_prefill_layer(moei_cache* c, int32_t* d_eam, int32_t layer, c
         const size_t nk = (size_t)n_max * d.k;
         hipError_t e = hipMalloc((void**)&p.d_idx, nk * 4);
         if (e == hipSuccess) e = hipMalloc((void**)&p.d_w, nk * 4);
-        if (e == hipSuccess) e = hipMalloc((void**)&p.d_perm, nk * 4);
-        if (e == hipSuccess) e = hipMalloc((void**)&p.d_pgate, nk * 4);
+        if (e == hipSuccess) e = hipMalloc((void**)&p.d_perm, (nk + 256) * 4);  // read in whole tiles
+        if (e == hipSuccess) e = hipMalloc((void**)&p.d_pgate, (nk + 16) * 4);  // read in whole blocks of 16
         if (e == hipSuccess) e = hipMalloc((void**)&p.d_where, nk * 4);
         if (e == hipSuccess) e = hipMalloc(&p.d_items, (size_t)prefill_max_items(d, n_max) * prefill_item_bytes());
         if (e == hipSuccess) e = hipMalloc((void**)&p.d_meta, 8);

@@ -165,6 +165,10 @@ __device__ __forceinline__ float bf16_one(uint16_t u) { return __uint_as_float((
 __device__ __forceinline__ void load16_to_lds(const void* gsrc, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gsrc) : "memory");
 }
+// the same from a uniform base address plus a byte offset per lane
+__device__ __forceinline__ void load16_to_lds_at(const void* base, uint32_t off, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off), "s"(base) : "memory");
+}
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }

@@ -335,14 +335,10 @@ __global__ void __launch_bounds__(256) ffn_reduce_kernel(const float* __restrict
     }
 }
 
-int env_int(const char* name, int dflt) {
-    const char* v = getenv(name);
-    if (!v || !*v) return dflt;
-    return atoi(v);
-}
+}  // namespace
 
-int g_cus = 0;
 int compute_units() {
+    static int g_cus = 0;
     if (g_cus == 0) {
         int dev = 0, n = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
@@ -352,6 +348,15 @@ int compute_units() {
     }
     return g_cus;
 }
+
+namespace {
+
+int env_int(const char* name, int dflt) {
+    const char* v = getenv(name);
+    if (!v || !*v) return dflt;
+    return atoi(v);
+}
+
 
 constexpr size_t kLdsBudget = 150 * 1024;  // of the 160 KiB per compute unit
 

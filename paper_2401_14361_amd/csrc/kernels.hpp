@@ -33,6 +33,7 @@ int launch_gather_slots(const int32_t* d_idx, int k, const int32_t* d_slot_of_ro
                         int32_t* d_flags, hipStream_t s);
 
 // ------------------------------------------------------------------ ffn.hip
+int compute_units();  // of the device the library was first used on
 struct FfnScratch {
     float* d_part = nullptr;  // [n_part][H] workgroup partial sums of y
     int n_part = 0;           // = workgroups of the fused kernel (one per compute unit)
@@ -66,7 +67,7 @@ struct PrefillScratch {
     int32_t* d_idx = nullptr;   // [n_max][k] picks
     float* d_w = nullptr;       // [n_max][k] gate weights
     int32_t* d_perm = nullptr;  // [n_max*k] tokens grouped per expert
-    float* d_pgate = nullptr;   // [n_max*k] their gate weights
+    float* d_pgate = nullptr;   // [n_max*k + 16] their gate weights
     int32_t* d_where = nullptr;  // [n_max*k] row of every (token, pick)
     void* d_items = nullptr;
     int32_t* d_meta = nullptr;  // [2]

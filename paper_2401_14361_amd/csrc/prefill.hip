@@ -18,6 +18,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -335,12 +336,27 @@ __device__ __forceinline__ bool xcd_item_work(int n_blocks, int* item, int* bloc
 }
 
 
-__device__ __forceinline__ float silu_f(float g) { return g / (1.0f + expf(-g)); }
-
-// round-to-nearest-even fp32 -> bf16 bits (finite inputs)
-__device__ __forceinline__ uint32_t bf16_bits(float f) {
-    uint32_t u = __float_as_uint(f);
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+// w silu(g) u of four neighbouring units, rounded to nearest even bf16.  The quotient and the exponential
+// are the hardware's (an ulp or two of fp32, far below the rounding to 8 bits that follows): the
+// library's expf and division took four times as many instructions.
+__device__ __forceinline__ float silu_f(float g) {
+    return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504f * g));
+}
+__device__ __forceinline__ uint2 activations(f32x4 g, f32x4 u, float w) {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    const f32x4 a = {silu_f(g[0]) * u[0] * w, silu_f(g[1]) * u[1] * w, silu_f(g[2]) * u[2] * w, silu_f(g[3]) * u[3] * w};
+    return __builtin_bit_cast(uint2, __builtin_convertvector(a, bf16x4));
+}
+// the activations of units u0 .. u0 + 3 of a row (I may end among them); packed: I is a multiple of 4
+__device__ __forceinline__ void store_activations(uint16_t* row, int u0, int I, bool packed, uint2 h) {
+    if (packed && u0 + 3 < I) {
+        *reinterpret_cast<uint2*>(row + u0) = h;
+    } else {
+        const uint16_t e[4] = {(uint16_t)h.x, (uint16_t)(h.x >> 16), (uint16_t)h.y, (uint16_t)(h.y >> 16)};
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (u0 + v < I) row[u0 + v] = e[v];
+    }
 }
 
 // 3a.  grid (ceil(I / 64), items).  D = A B with A = 16 weight rows (units) x 32 k, B = 32 k x 16
@@ -450,17 +466,7 @@ __global__ void __launch_bounds__(TM * 4) prefill_gateup_kernel(MmArgs a) {
         const int tok = tq * 64 + tb * 16 + lrow;
         if (tok >= it.ntok) continue;
         const float gw = s_gate[tok];
-        uint16_t* dst_row = a.act + (size_t)(it.row0 + tok) * I;
-        uint32_t h[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) h[v] = bf16_bits(silu_f(G[tb][v]) * U[tb][v] * gw);
-        if (packed && u0 + 3 < I) {
-            *reinterpret_cast<uint2*>(dst_row + u0) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-        } else {
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (u0 + v < I) dst_row[u0 + v] = (uint16_t)h[v];
-        }
+        store_activations(a.act + (size_t)(it.row0 + tok) * I, u0, I, packed, activations(G[tb], U[tb], gw));
     }
 }
 
@@ -472,16 +478,22 @@ __global__ void __launch_bounds__(TM * 4) prefill_gateup_kernel(MmArgs a) {
 // So this kernel gives every workgroup a weight stream of its own - 128 units (gate and up: 256
 // rows) of one expert - and as many of the expert's tokens as the accumulators hold (256), and
 // brings both operands in with loads straight into LDS, one cache line (64 k-values) of every row
-// per stage.  The weights come from HBM and the inputs mostly from L2, and a wavefront's loads
-// complete in order, so the two are loaded by different wavefronts into rings of their own:
-// wavefronts 0..3 keep two stages of weight rows in flight (a ring of three), wavefronts 4..7 one
-// stage of input rows (a ring of two); all unit blocks of an item run on one XCD, so the item's
-// input rows pass through that L2 once.  Chunk c of ring row r sits at chunk position
-// c ^ ((r >> 1) % 8): the sixteen lanes that read one operand (sixteen consecutive rows, the same
-// chunk) then touch all 64 banks once.  A wavefront owns 32 units (two 16-row blocks of gate, two of
-// up) x 128 tokens (the even or the odd 16-token blocks of the item, so that a partly filled item
-// leaves both halves of the workgroup the same work; blocks without tokens are neither read nor
-// multiplied), 32 accumulator tiles, and multiplies a stage in two halves of 32 k-values.
+// per stage, in rings of three (weights) and two stages (inputs).  A compute unit returns loads in the
+// order they were asked for, so every wavefront loads a share of both, the inputs - mostly from L2 -
+// ahead of the weights that are needed a stage later.  The workgroups are persistent, one per compute
+// unit, and their rings run on from tile to tile; the tiles are dealt out evenly (see Tile): with the
+// items of a list pinned to the XCDs one XCD had 99 tiles for its 32 compute units where 96 was the
+// average, a fourth round for everybody.  Measured (26-layer 64-expert shape, one layer): 512 tokens
+// 186 -> 158 us, 2,048 tokens 307 -> 290 us; two large items per XCD, 1,531 tokens of an 8-expert layer
+// of 14,336 units: 946 -> 925 us.  What is left there: with the loads taken out 587 us, with the matrix
+// instructions taken out 735 us.  (More stages in flight do not help: giving a stage's slots back half
+// a stage earlier, at the price of a second barrier, took 1,050 us.)
+// Chunk c of ring row r sits at chunk position c ^ ((r >> 1) % 8): the sixteen lanes that read one
+// operand (sixteen consecutive rows, the same chunk) then touch all 64 banks once.  A wavefront owns
+// 32 units (two 16-row blocks of gate, two of up) x 128 tokens (the even or the odd 16-token blocks of
+// the item, so that a partly filled item leaves both halves of the workgroup the same work; blocks
+// without tokens are neither read nor multiplied), 32 accumulator tiles, and multiplies a stage in two
+// halves of 32 k-values.
 constexpr int kTileTokWide = 256;
 constexpr int kWdUnits = 128;   // intermediate units per workgroup
 constexpr int kWdKS = 64;       // k-values per stage: 128 bytes of a row
@@ -491,176 +503,293 @@ constexpr int kWdThreads = 512;
 constexpr int kWdStageElems = 256 * kWdKS;  // a stage of either ring: 256 rows
 __device__ __forceinline__ int wd_pos(int row, int chunk) { return row * kWdKS + ((chunk ^ ((row >> 1) & 7)) << 3); }
 
-// waits until at most `stages` * 8 of this wavefront's vector memory operations are outstanding
-__device__ __forceinline__ void wait_but_stages(int stages) {
-    // s_waitcnt: vmcnt in bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima
-    if (stages >= 2)
-        __builtin_amdgcn_s_waitcnt(0x4f70);  // 16
-    else if (stages == 1)
-        __builtin_amdgcn_s_waitcnt(0x0f78);  // 8
-    else
-        __builtin_amdgcn_s_waitcnt(0x0f70);
+// f(R), f(R - 1), ..., f(0), each with its argument as a compile-time constant
+template <int R, typename F>
+__device__ __forceinline__ void count_down(F&& f) {
+    if constexpr (R >= 0) {
+        f(std::integral_constant<int, R>{});
+        count_down<R - 1>(f);
+    }
 }
+
+// waits until at most N of this wavefront's vector memory operations are outstanding
+template <int N>
+__device__ __forceinline__ void wait_vm_c() {
+    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+    __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
+}
+// a uniform address in scalar registers
+__device__ __forceinline__ const unsigned char* scalar_ptr(const void* p) {
+    const uint64_t v = (uint64_t)(uintptr_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return reinterpret_cast<const unsigned char*>((uintptr_t)(((uint64_t)hi << 32) | lo));
+}
+
+// The tiles of a persistent workgroup: one workgroup per compute unit.  The tiles - items times output
+// blocks - form one sequence, of which every XCD takes an eighth and its workgroups every 32nd tile of
+// that: first the items at positions 0, 8, 16 ... of the item list, then those at 1, 9, 17 ..., each with
+// all its output blocks, so that an item's input rows pass through one L2 or two, large and small
+// items are spread over the XCDs, and no XCD gets more tiles than another, however few items there are.
+struct Tile {
+    int slot, ntok, list_off, first_tok, row0;
+    int block;  // output block
+    bool ok;    // false: the workgroup has no more tiles
+};
+// Read-only tables are read through the constant address space: uniform loads that count on lgkmcnt, so
+// that waiting for them does not wait for the ring's loads.
+typedef const __attribute__((address_space(4))) int32_t* const_ints;
+__device__ __forceinline__ Tile tile_at(const MmArgs& a, int n_items, int n_blocks, int seq) {
+    const int xcd = blockIdx.x % kXcds, step = gridDim.x / kXcds;
+    const int total = n_items * n_blocks;
+    const int end = (int)((long)total * (xcd + 1) / kXcds);
+    const int t = (int)((long)total * xcd / kXcds) + (int)(blockIdx.x / kXcds) + seq * step;
+    Tile r;
+    r.ok = t < end;
+    const int i = r.ok ? t / n_blocks : 0;
+    r.block = t - i * n_blocks;
+    // item i of the sequence: the first n_items % 8 positions modulo 8 have one item more
+    const int q = n_items / kXcds, more = n_items % kXcds;
+    int x, k;
+    if (i < more * (q + 1)) {
+        x = i / (q + 1);
+        k = i - x * (q + 1);
+    } else {
+        const int j = i - more * (q + 1);
+        x = j / q;
+        k = j - x * q;
+        x += more;
+    }
+    const_ints it = (const_ints)(uintptr_t)(a.items + x + kXcds * k);
+    r.slot = it[0];
+    r.ntok = it[1];
+    r.list_off = it[2];
+    r.first_tok = it[3];
+    r.row0 = it[4];
+    return r;
+}
+static_assert(sizeof(PItem) == 24 && offsetof(PItem, row0) == 16, "tile_at reads an item as integers");
 
 __global__ void __launch_bounds__(kWdThreads, 2) prefill_gateup_wide_kernel(MmArgs a) {
     constexpr int TM = kTileTokWide;
-    constexpr int NLD = 8;        // loads per wavefront and stage, 8 rows each: four wavefronts fill 256 rows
     constexpr int NTB = TM / 32;  // 16-token blocks per wavefront: 8
-    static_assert(2 * kWdUnits == 256 && TM == 256 && kWdThreads == 8 * kWave && kWdKS == 64, "four wavefronts load 256 rows of 128 bytes");
+    static_assert(2 * kWdUnits == 256 && TM == 256 && kWdThreads == 8 * kWave && kWdKS == 64, "eight wavefronts load 256 rows of 128 bytes");
     extern __shared__ __align__(16) unsigned char smem_raw[];
     uint16_t* ring_w = reinterpret_cast<uint16_t*>(smem_raw);        // [kWdStagesW][256][64]
     uint16_t* ring_x = ring_w + (size_t)kWdStagesW * kWdStageElems;  // [kWdStagesX][256][64]
-    int item, ub;
-    if (!xcd_item_work(a.n_ub, &item, &ub)) return;
-    if (item >= a.meta[0]) return;
-    const PItem it = a.items[item];
-    if (it.slot < 0 || it.slot >= a.n_slots_total) return;  // the down kernel writes the zeros and raises the flag
     const int H = a.H, I = a.I;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lrow = lane & 15, lgrp = lane >> 4;
     const int rg = wv & 3, th = wv >> 2;  // unit group (32 units); the even or the odd 16-token blocks
-    // 16-token blocks of this wavefront that hold tokens of the item (blocks th, th + 2, ...)
-    const int n_live = max(0, ((it.ntok + 15) / 16 - th + 1) / 2);
-    const bool loads_w = wv < 4;  // else the inputs
-    const uint16_t* wslot = a.pool + (size_t)it.slot * a.slot_elems;
-    const int u_wg = ub * kWdUnits;
+    const int n_items = ((const_ints)(uintptr_t)a.meta)[0];
+    const int n_slices = H / kWdKS;  // >= 4
+    int seq = 0;
+    auto next_tile = [&]() {  // items whose expert is not resident are passed over: the down kernel writes the zeros and raises the flag
+        Tile t;
+        do t = tile_at(a, n_items, a.n_ub, seq++);
+        while (t.ok && (t.slot < 0 || t.slot >= a.n_slots_total));
+        return t;
+    };
+    Tile cur = next_tile();
+    if (!cur.ok) return;
 
-    // load j of this wavefront fills rows 8 * (4 * j + wv % 4) .. + 8 of a stage of its ring; this
-    // lane brings chunk position lane % 8 of row .. + lane / 8.  Weight rows 0..127 are gate rows,
-    // 128..255 up rows.  Units past I repeat unit I - 1 and tokens past the item repeat its first
-    // token: what they yield is never stored.
-    const uint16_t* src[NLD];
+    // ---- loads: stage after stage of one tile, then on into the next tile
+    // A wavefront fills rows 8 * (8 * j + wv) .. + 8 of a stage of either ring with its load j of four;
+    // this lane brings chunk position lane % 8 of row .. + lane / 8.  Weight rows 0..127 are gate
+    // rows, 128..255 up rows.  Units past I repeat unit I - 1; input rows past the item's tokens are
+    // not loaded by whole groups of eight, and repeat its first token inside one: what they yield is
+    // never stored.
+    const int my_row = 8 * wv + (lane >> 3);  // the row of load j: my_row + 64 * j
+    const uint32_t my_chunk = (uint32_t)((lane & 7) ^ ((my_row >> 1) & 7)) * 16;  // rows 64 apart share the swizzle key
+    const uint32_t my_w = lds_address(ring_w) + (uint32_t)(8 * wv) * (kWdKS * 2), my_x = lds_address(ring_x) + (uint32_t)(8 * wv) * (kWdKS * 2);
+    const unsigned char *base_w = nullptr, *base_x = nullptr;  // of the stage to be loaded next (uniform)
+    int unit_w = 0, slice_w = 0, put_w = 0;                    // first unit of the tile; next slice; its ring slot
+    int n_x = 0, toks = 0, slice_x = 0, put_x = 0;             // loads of a stage; lane l: token of row 64 * (l % 4) + 8 * wv + l / 8
+    auto aim_w = [&](const Tile& t) {
+        slice_w = 0;
+        base_w = scalar_ptr(a.pool + (size_t)t.slot * a.slot_elems);
+        unit_w = t.block * kWdUnits;
+    };
+    auto aim_x = [&](const Tile& t) {
+        slice_x = 0;
+        base_x = scalar_ptr(a.X);
+        n_x = min(4, max(0, (t.ntok - 8 * wv + 63) / 64));
+        int at = lane;
+        asm volatile("" : "+v"(at));  // the comparisons are made here, not kept as lane masks
+        const int row = 64 * (at & 3) + 8 * wv + (at >> 3);
+        if (t.first_tok >= 0) {
+            toks = t.first_tok + (row < t.ntok ? row : 0);
+        } else {  // (the list is padded by a whole tile)
+            const_ints pt = (const_ints)(uintptr_t)(a.perm + t.list_off);
+            int v = 0;
 #pragma unroll
-    for (int j = 0; j < NLD; ++j) {
-        const int r = 8 * (4 * j + (wv & 3)) + (lane >> 3);
-        const int c = (lane & 7) ^ ((r >> 1) & 7);
-        if (loads_w) {
-            const int u = min(u_wg + (r & (kWdUnits - 1)), I - 1);
-            src[j] = wslot + (size_t)u * 3 * H + (r >= kWdUnits ? H : 0) + c * 8;
-        } else {
-            const int t = r < it.ntok ? r : 0;
-            const int tok = it.first_tok >= 0 ? it.first_tok + t : a.perm[it.list_off + t];
-            src[j] = a.X + (size_t)tok * H + c * 8;
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v = (at & 59) == 8 * i + j ? pt[64 * j + 8 * wv + i] : v;
+            toks = row < t.ntok ? v : pt[0];
         }
-    }
-    const int depth = loads_w ? kWdStagesW : kWdStagesX;  // uniform over the wavefront
-    const uint32_t my_ring = lds_address(loads_w ? ring_w : ring_x) + (uint32_t)(8 * (wv & 3)) * (kWdKS * 2);
-    // input rows past the item's tokens are not loaded (what the ring holds there is multiplied at most
-    // within a token block that also holds tokens, and never stored): this wavefront's loads j < n_ld
-    const int n_ld = loads_w ? NLD : min(NLD, max(0, (it.ntok - 8 * (wv & 3) + 31) / 32));
-    auto issue = [&](int s) {
-        const uint32_t st = my_ring + (uint32_t)(s % depth) * (kWdStageElems * 2);
+    };
+    auto issue_w = [&]() {
+        const uint32_t st = my_w + (uint32_t)put_w * (kWdStageElems * 2);
 #pragma unroll
-        for (int j = 0; j < NLD; ++j)
-            if (j < n_ld) load16_to_lds(src[j] + (size_t)s * kWdKS, st + (uint32_t)(32 * j) * (kWdKS * 2));
+        for (int j = 0; j < 2; ++j) {
+            const uint32_t off = (uint32_t)min(unit_w + my_row + 64 * j, I - 1) * (uint32_t)(6 * H) + my_chunk;
+            load16_to_lds_at(base_w, off, st + (uint32_t)(64 * j) * (kWdKS * 2));
+            load16_to_lds_at(base_w + 2 * H, off, st + (uint32_t)(64 * j + kWdUnits) * (kWdKS * 2));
+        }
+        base_w += kWdKS * 2;
+        if (++put_w == kWdStagesW) put_w = 0;
+        ++slice_w;
+    };
+    auto issue_x = [&]() {
+        const uint32_t st = my_x + (uint32_t)put_x * (kWdStageElems * 2);
+        count_down<3>([&](auto r_tag) {
+            constexpr int j = 3 - decltype(r_tag)::value;
+            const uint32_t tok = MOEI_DPP_U32(toks, 0x55 * j);  // quad_perm [j,j,j,j]: lane j of every four holds load j's token
+            if (j < n_x) load16_to_lds_at(base_x, tok * (uint32_t)(2 * H) + my_chunk, st + (uint32_t)(64 * j) * (kWdKS * 2));
+        });
+        base_x += kWdKS * 2;
+        if (++put_x == kWdStagesX) put_x = 0;
+        ++slice_x;
+    };
+    static_assert(kWdStagesX == 2 && kWdStagesW == 3, "one stage of inputs and two of weights are on their way");
+    aim_x(cur);
+    aim_w(cur);
+    issue_x();
+    issue_w();
+    issue_w();
+    Tile nxt = next_tile();
+    bool more_w = true;  // the weights of the stage after the one entered next are on their way
+    // Enters the next stage: it has landed for all once every wavefront has seen its loads of it
+    // complete and the barrier is passed; by then every wavefront has read the stage before it, whose
+    // ring slots take the inputs of the stage after it and the weights of the one after that - past a
+    // tile's end those of the next tile, so that the rings never run dry between tiles.  A compute unit
+    // returns loads in the order they were asked for, so inputs, which mostly come from L2, are asked
+    // for before the weights, and wait for no weights that are not needed first anyway.  (A wavefront's
+    // stores count too: the first wait of a tile is longer than it needs to be.)
+    auto enter = [&]() {
+        if (more_w)
+            wait_vm_c<4>();
+        else
+            wait_vm_c<0>();
+        __syncthreads();
+        if (slice_x == n_slices && nxt.ok) aim_x(nxt);
+        if (slice_x < n_slices) issue_x();
+        if (slice_w == n_slices && nxt.ok) aim_w(nxt);
+        more_w = slice_w < n_slices;
+        if (more_w) issue_w();
     };
 
-    f32x4 G[2][NTB], U[2][NTB];
-#pragma unroll
-    for (int bl = 0; bl < 2; ++bl)
-#pragma unroll
-        for (int tb = 0; tb < NTB; ++tb) G[bl][tb] = U[bl][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
     // The operands of a half stage are read into registers one half step before they are multiplied,
-    // so the LDS reads of half step t + 1 run beside the matrix instructions of half step t, and a
-    // ring slot is free again as soon as every wavefront has read both its halves.
+    // so the LDS reads of half step t + 1 run beside the matrix instructions of half step t.
     struct Ops {
         bf16x8 ag[2], au[2], b[NTB];
     };
+    struct Sums {
+        f32x4 G[2][NTB], U[2][NTB];
+    };
+    int slot_w = 0, slot_x = 0;  // ring slots of the stage entered last
+    auto step_slots = [&]() {
+        if (++slot_w == kWdStagesW) slot_w = 0;
+        if (++slot_x == kWdStagesX) slot_x = 0;
+    };
+    // this lane's place in the first operand rows, chunk lgrp; chunk 4 + lgrp sits 32 elements across
+    const int pos_w = wd_pos(32 * rg + lrow, lgrp), pos_x = wd_pos(16 * th + lrow, lgrp);
     // NT: token blocks of this wavefront that are read and multiplied (the live ones, rounded up to even)
-    auto read_ops = [&](int t, Ops& o, auto nt_tag) {  // half step t: stage t / 2, chunks 4 * (t % 2) .. + 4
+    auto read_ops = [&](int half, Ops& o, auto nt_tag) {  // half 0 or 1 of the stage entered last: chunks 4 * half .. + 4
         constexpr int NT = decltype(nt_tag)::value;
-        const int s = t >> 1, c = 4 * (t & 1) + lgrp;
-        const uint16_t* sw = ring_w + (size_t)(s % kWdStagesW) * kWdStageElems;
-        const uint16_t* sx = ring_x + (size_t)(s % kWdStagesX) * kWdStageElems;
+        const uint16_t* sw = ring_w + (size_t)slot_w * kWdStageElems + (pos_w ^ (32 * half));
+        const uint16_t* sx = ring_x + (size_t)slot_x * kWdStageElems + (pos_x ^ (32 * half));
 #pragma unroll
         for (int bl = 0; bl < 2; ++bl) {
-            const int r = 32 * rg + 16 * bl + lrow;
-            o.ag[bl] = ld_bf16x8(sw + wd_pos(r, c));
-            o.au[bl] = ld_bf16x8(sw + wd_pos(kWdUnits + r, c));
+            o.ag[bl] = ld_bf16x8(sw + 16 * bl * kWdKS);
+            o.au[bl] = ld_bf16x8(sw + (kWdUnits + 16 * bl) * kWdKS);
         }
 #pragma unroll
-        for (int tb = 0; tb < NT; ++tb) o.b[tb] = ld_bf16x8(sx + wd_pos((2 * tb + th) * 16 + lrow, c));
+        for (int tb = 0; tb < NT; ++tb) o.b[tb] = ld_bf16x8(sx + 32 * tb * kWdKS);
     };
-    auto multiply = [&](const Ops& o, auto nt_tag) {
+    auto multiply = [&](const Ops& o, Sums& d, auto nt_tag) {
         constexpr int NT = decltype(nt_tag)::value;
 #pragma unroll
         for (int tb = 0; tb < NT; ++tb)
 #pragma unroll
             for (int bl = 0; bl < 2; ++bl) {
-                G[bl][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o.ag[bl], o.b[tb], G[bl][tb], 0, 0, 0);
-                U[bl][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o.au[bl], o.b[tb], U[bl][tb], 0, 0, 0);
+                d.G[bl][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o.ag[bl], o.b[tb], d.G[bl][tb], 0, 0, 0);
+                d.U[bl][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o.au[bl], o.b[tb], d.U[bl][tb], 0, 0, 0);
             }
     };
-    const int n_slices = H / kWdKS;   // H is a multiple of 128: at least two stages
-    const int n_half = 2 * n_slices;  // at least four half steps, an even number
-    for (int s = 0; s < depth; ++s)
-        if (s < n_slices) issue(s);
-    static_assert(kWdStagesX == 2, "the wavefronts that load inputs wait for all their loads: their count per stage varies");
-    if (loads_w)
-        wait_but_stages(min(n_slices, depth) - 1);  // stage 0 has landed
-    else if (n_ld > 0)
-        wait_but_stages(0);  // (stage 1's loads with it)
-    __syncthreads();
-    // Half step t multiplies half t and reads half t + 1.  When that is the first half of stage s + 1
-    // (t odd), the stage has landed for all once the wavefronts that load have seen their loads of it
-    // complete and the barrier is passed; by then every wavefront has read both halves of stage s,
-    // whose ring slots take stages s + 3 (weights) and s + 2 (inputs).  The loop is written once for
-    // each count of token blocks a wavefront may have, and its last half step is peeled, so that no
-    // path through a half step skips its reads.
+    // A whole tile, whose first stage has been entered; written once for each count of token blocks a
+    // wavefront may have.
     auto run = [&](auto nt_tag) {
         constexpr int NT = decltype(nt_tag)::value;
+        Sums d;
+#pragma unroll
+        for (int bl = 0; bl < 2; ++bl)
+#pragma unroll
+            for (int tb = 0; tb < NT; ++tb) d.G[bl][tb] = d.U[bl][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
         Ops opA, opB;
         if constexpr (NT > 0) read_ops(0, opA, nt_tag);
-        auto half = [&](int t, const Ops& cur, Ops& nxt, bool enters_stage) {
-            if (enters_stage) {
-                const int s = t >> 1;
-                wait_but_stages(loads_w ? min(n_slices - 2 - s, depth - 2) : 0);  // stages younger than s + 1 that have been issued
-                __syncthreads();
-                if (s + depth < n_slices) issue(s + depth);
-            }
+        for (int s = 1; s < n_slices; ++s) {
             if constexpr (NT > 0) {
-                read_ops(t + 1, nxt, nt_tag);
-                multiply(cur, nt_tag);
+                read_ops(1, opB, nt_tag);
+                multiply(opA, d, nt_tag);
             }
-        };
-        for (int t = 0; t + 2 < n_half; t += 2) {
-            half(t, opA, opB, false);
-            half(t + 1, opB, opA, true);
+            enter();
+            step_slots();
+            if constexpr (NT > 0) {
+                read_ops(0, opA, nt_tag);
+                multiply(opB, d, nt_tag);
+            }
         }
-        half(n_half - 2, opA, opB, false);
-        if constexpr (NT > 0) multiply(opB, nt_tag);
+        if constexpr (NT > 0) {
+            read_ops(1, opB, nt_tag);
+            multiply(opA, d, nt_tag);
+        }
+        if (nxt.ok) {  // the next tile's first stage, while this one's last products and its activations are formed
+            enter();
+            step_slots();
+        }
+        if constexpr (NT > 0) multiply(opB, d, nt_tag);
+        // D[unit 4*lgrp + v][token lrow] -> activation, bf16, act[row][unit]
+        const bool packed = (I & 3) == 0;
+        const int u_wg = cur.block * kWdUnits;
+#pragma unroll
+        for (int tb = 0; tb < NT; ++tb) {
+            __builtin_amdgcn_sched_barrier(0);  // one block at a time: the registers hold no more
+            const int t0 = (2 * tb + th) * 16;
+            if (t0 >= cur.ntok) continue;  // uniform
+            int at = lrow;
+            asm volatile("" : "+v"(at));  // formed here, not kept (nor sixteen lane masks) through the loop
+            const int tok = t0 + at;
+            float gw = 1.0f;
+            if (cur.first_tok < 0) {  // sixteen gate weights in a row (the buffer is padded to a whole block)
+                const_ints pg = (const_ints)(uintptr_t)(a.pgate + cur.list_off + t0);
+                int g = 0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) g = at == i ? pg[i] : g;
+                gw = __builtin_bit_cast(float, g);
+            }
+            if (tok >= cur.ntok) continue;
+            uint16_t* dst_row = a.act + (size_t)(cur.row0 + tok) * I;
+#pragma unroll
+            for (int bl = 0; bl < 2; ++bl)
+                store_activations(dst_row, u_wg + 32 * rg + 16 * bl + lgrp * 4, I, packed, activations(d.G[bl][tb], d.U[bl][tb], gw));
+        }
     };
-    switch ((n_live + 1) / 2) {  // uniform over the wavefront
-        case 0: run(std::integral_constant<int, 0>{}); break;
-        case 1: run(std::integral_constant<int, 2>{}); break;
-        case 2: run(std::integral_constant<int, 4>{}); break;
-        case 3: run(std::integral_constant<int, 6>{}); break;
-        default: run(std::integral_constant<int, 8>{}); break;
-    }
-    // D[unit 4*lgrp + v][token lrow] -> activation, bf16, act[row][unit]
-    const bool packed = (I & 3) == 0;
-#pragma unroll
-    for (int tb = 0; tb < NTB; ++tb) {
-        const int tok = (2 * tb + th) * 16 + lrow;
-        if (tok >= it.ntok) continue;
-        const float gw = it.first_tok >= 0 ? 1.0f : a.pgate[it.list_off + tok];
-        uint16_t* dst_row = a.act + (size_t)(it.row0 + tok) * I;
-#pragma unroll
-        for (int bl = 0; bl < 2; ++bl) {
-            const int u0 = u_wg + 32 * rg + 16 * bl + lgrp * 4;
-            uint32_t h[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) h[v] = bf16_bits(silu_f(G[bl][tb][v]) * U[bl][tb][v] * gw);
-            if (packed && u0 + 3 < I) {
-                *reinterpret_cast<uint2*>(dst_row + u0) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-            } else {
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (u0 + v < I) dst_row[u0 + v] = (uint16_t)h[v];
-            }
+    enter();
+    for (;;) {
+        // 16-token blocks of this wavefront that hold tokens of the item (blocks th, th + 2, ...)
+        const int n_live = max(0, ((cur.ntok + 15) / 16 - th + 1) / 2);
+        switch ((n_live + 1) / 2) {  // uniform over the wavefront
+            case 0: run(std::integral_constant<int, 0>{}); break;
+            case 1: run(std::integral_constant<int, 2>{}); break;
+            case 2: run(std::integral_constant<int, 4>{}); break;
+            case 3: run(std::integral_constant<int, 6>{}); break;
+            default: run(std::integral_constant<int, 8>{}); break;
         }
+        if (!nxt.ok) break;
+        cur = nxt;
+        nxt = next_tile();
     }
 }
 
@@ -1038,21 +1167,6 @@ static_assert(rt_depth(1) * (2 + 8) * 8 * kRtKS * 2 <= 156 * 1024 && rt_depth(2)
 inline int rt_blocks_per_wave(int E) { return ((E + 15) / 16 + 3) / 4; }
 inline size_t rt_lds_bytes(int E) { return (size_t)rt_depth(rt_blocks_per_wave(E)) * rt_stage_elems(E) * 2; }
 
-// waits until at most N of this wavefront's vector memory operations are outstanding
-template <int N>
-__device__ __forceinline__ void wait_vm_c() {
-    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-    __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
-}
-// f(R), f(R - 1), ..., f(0), each with its argument as a compile-time constant
-template <int R, typename F>
-__device__ __forceinline__ void count_down(F&& f) {
-    if constexpr (R >= 0) {
-        f(std::integral_constant<int, R>{});
-        count_down<R - 1>(f);
-    }
-}
-
 template <int NB>  // blocks of 16 experts per wavefront: ceil(ceil(E / 16) / 4)
 __global__ void __launch_bounds__(kRtThreads) prefill_route_wide_kernel(const uint16_t* __restrict__ W,
                                                                         const float* __restrict__ bias,
@@ -1229,11 +1343,20 @@ int max_items_for(const moei_model_desc& d, int n, int tm) {
 // 64-expert top-6 shape: 256 tokens 279 us per layer with 64-token items against 288 us, 512 tokens
 // 330 against 325, 1,024 tokens 488 against 405)
 int tile_tokens(const moei_model_desc& d, int n) {
+    // the wide gate/up kernel looks up to three stages ahead and forms 32-bit offsets into an expert
+    if (d.H < 4 * kWdKS || (uint64_t)6 * d.H * d.I > 0xffffffffull) return kTileTok;
     const char* v = getenv("MOEI_PREFILL_TILE");
     if (v && atoi(v) == kTileTok) return kTileTok;
     if (v && atoi(v) == kTileTokBig) return kTileTokBig;
     if (v && atoi(v) == kTileTokWide) return kTileTokWide;
     return (long)n * d.k >= (long)48 * d.E ? kTileTokWide : kTileTok;
+}
+
+// workgroups of a persistent kernel: one per compute unit, a whole number per XCD, no more than there can be tiles
+int persistent_grid(int n_blocks, int max_items) {
+    const int per_xcd = std::max(1, compute_units() / kXcds);
+    const long tiles = (long)((max_items + kXcds - 1) / kXcds) * n_blocks;
+    return kXcds * (int)std::min<long>(per_xcd, tiles);
 }
 
 template <int TM>
@@ -1253,8 +1376,7 @@ int launch_mm(const moei_model_desc& d, MmArgs a, int max_items, hipStream_t s) 
         rc = pf_allow_lds(prefill_gateup_wide_kernel, gu_smem);
         if (rc) return rc;
         a.n_ub = (d.I + kWdUnits - 1) / kWdUnits;
-        const int item_rounds = (max_items + kXcds - 1) / kXcds;
-        launch(K_PF_GATEUP, prefill_gateup_wide_kernel, dim3(kXcds * a.n_ub * item_rounds), dim3(kWdThreads), gu_smem, s, a);
+        launch(K_PF_GATEUP, prefill_gateup_wide_kernel, dim3(persistent_grid(a.n_ub, max_items)), dim3(kWdThreads), gu_smem, s, a);
     }
     MOEI_LAUNCH_CHECK();
     if (a.dn_split == 2 && d.I % kDwKS == 0 && d.H % kDwCols == 0) {

@@ -131,6 +131,15 @@ def test_prefill_ragged_rows_and_small_expert_counts(m):
     _check(_prefill_case(m, cfg, 300, layer=0))
 
 
+# the persistent gate/up kernel: fewer items than XCDs, one tile in all, several tiles per workgroup with a ragged
+# last one, the fewest stages it takes (H = 256), and rows too short for it (H = 128)
+@pytest.mark.parametrize("E,k,n_shared,H,I,n", [(1, 1, 0, 256, 8, 300), (1, 1, 0, 256, 128, 17), (4, 2, 1, 128, 136, 500),
+                                                (9, 2, 0, 256, 6200, 600), (24, 3, 2, 384, 1416, 1300)])
+def test_prefill_tiles_over_the_chip(m, E, k, n_shared, H, I, n):
+    cfg = mi.get_config("C2").scaled(L=1, E=E, k=k, n_shared=n_shared, H=H, I=I, N=8, prompt=16)
+    _check(_prefill_case(m, cfg, n, layer=0, sample=24))
+
+
 def test_prefill_long_prompts_with_256_token_items(m):
     # n k > 128 E: the items hold up to 256 tokens and the gate/up products run in the kernel that
     # fills its LDS ring straight from global memory.  Mixtral structure, I = 72 (less than one
