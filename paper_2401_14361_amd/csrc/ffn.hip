@@ -43,18 +43,18 @@ struct FfnArgs {
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + expf(-g)); }
 
 // Adds the wavefronts' y rows in wavefront order and writes the workgroup's partial row.
-// Rows go through LDS `ygroup` at a time; `store_my_row` writes the calling wavefront's.
+// Rows (`row` floats apart) go through LDS `ygroup` at a time; `store_my_row` writes the calling wavefront's.
 template <typename Store>
-__device__ __forceinline__ void block_sum_rows(float* yp, int H, int waves, int ygroup, int wv, float* out,
+__device__ __forceinline__ void block_sum_rows(float* yp, int H, int row, int waves, int ygroup, int wv, float* out,
                                                Store store_my_row) {
     const int tid = threadIdx.x, nthr = blockDim.x;
     for (int g0 = 0; g0 < waves; g0 += ygroup) {
-        if (wv >= g0 && wv < g0 + ygroup) store_my_row(yp + (size_t)(wv - g0) * H);
+        if (wv >= g0 && wv < g0 + ygroup) store_my_row(yp + (size_t)(wv - g0) * row);
         __syncthreads();
         const int ng = min(ygroup, waves - g0);
         for (int c = tid; c < H; c += nthr) {
             float s = g0 == 0 ? 0.f : out[c];  // each column is owned by one thread across rounds
-            for (int k = 0; k < ng; ++k) s += yp[(size_t)k * H + c];
+            for (int k = 0; k < ng; ++k) s += yp[(size_t)k * row + c];
             out[c] = s;
         }
         __syncthreads();
@@ -66,7 +66,11 @@ __device__ __forceinline__ void block_sum_rows(float* yp, int H, int waves, int 
 // wavefront keeps a rolling window of PF loads in flight: each step consumes the oldest
 // load and issues the one PF steps ahead, across unit boundaries, so its stream never
 // drains.  grid = one workgroup per compute unit, block = waves * 64 threads,
-// LDS = x (H floats) + ygroup y rows.
+// LDS = x (NCH chunks of floats) + ygroup y rows of that length.
+// TAIL: H is any multiple of 16 bytes of up to NCH chunks.  The lanes past the end of the last chunk
+// read its first piece (the same for all of them) and add nothing, so a row costs what its chunks cost.
+// (The kernel for any H below reads two or four bytes a lane and keeps its sums in LDS: with H = 1,792 a token of
+// seven layers, four experts of 910 units each, took 958 us with it and takes 165 us.)
 template <int NCH>
 struct StreamShape {
     static constexpr int kSteps = 3 * NCH;
@@ -77,7 +81,7 @@ struct StreamShape {
     static constexpr int kMaxWaves = NCH <= 4 ? 16 : (NCH <= 10 ? 12 : 8);
 };
 
-template <typename WT, int NCH>
+template <typename WT, int NCH, bool TAIL>
 __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fused_kernel(FfnArgs a) {
     using V = WVec<WT>;
     using Raw = typename V::raw;
@@ -88,7 +92,7 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
     static_assert(STEPS % PF == 0, "the window must divide the steps of a unit");
     extern __shared__ __align__(16) float smem[];
     float* xs = smem;
-    float* yp = smem + a.H;
+    float* yp = smem + NCH * CW;
     constexpr bool kPacked = std::is_same<WT, uint16_t>::value;  // bf16: x stays bf16 in LDS, products by v_dot2c_f32_bf16
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     // the wavefront index in a scalar register: unit ids, slot ids and base addresses are
@@ -117,7 +121,11 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
     auto step_off = [&](int s) -> int {
         return s < 2 * NCH ? ((s & 1) ? H : 0) + (s >> 1) * CW : 2 * H + (s - 2 * NCH) * CW;
     };
-    auto ld = [&](size_t unit, int off) -> Raw { return V::load_once(pool + unit + off + lane_off); };
+    // is load step s of the last chunk, which lanes from `lanes_in` on lie past the end of?
+    auto last_chunk = [](int s) { return TAIL && (s < 2 * NCH ? s >> 1 : s - 2 * NCH) == NCH - 1; };
+    const bool lane_in = !TAIL || (NCH - 1) * CW + lane * N < H;
+    const unsigned tail_off = lane_in ? lane_off : 0u;
+    auto ld = [&](size_t unit, int s) -> Raw { return V::load_once(pool + unit + step_off(s) + (last_chunk(s) ? tail_off : lane_off)); };
 
     float acc[NCH * N];
 #pragma unroll
@@ -141,7 +149,8 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
     uint4 xv0 = make_uint4(0u, 0u, 0u, 0u), xv1 = xv0, xv2 = xv0, xv3 = xv0;
     if constexpr (kPacked) {
         // a piece past the row is read as the row's last one (and not stored)
-        auto piece = [&](int u) { return reinterpret_cast<const uint4*>(a.x)[min(tid + u * (int)blockDim.x, NCH * kWave - 1)]; };
+        const int n_pieces = TAIL ? H / N : NCH * kWave;
+        auto piece = [&](int u) { return reinterpret_cast<const uint4*>(a.x)[min(tid + u * (int)blockDim.x, n_pieces - 1)]; };
         xv0 = piece(0);
         if constexpr (kXRounds > 1) xv1 = piece(1);
         if constexpr (kXRounds > 2) xv2 = piece(2);
@@ -158,13 +167,13 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
         gate = a.gate_w[e];
         if (any) p = unit_off(slot0, t - e * I, ok);
 #pragma unroll
-        for (int s = 0; s < PF; ++s) win[s] = ld(p, step_off(s));
+        for (int s = 0; s < PF; ++s) win[s] = ld(p, s);
     }
     if constexpr (kPacked) {
         uint4* dst = reinterpret_cast<uint4*>(xs);
         auto put = [&](int u, uint4 v) {
             const int c = tid + u * (int)blockDim.x;
-            if (c < NCH * kWave) dst[c] = v;
+            if (c < NCH * kWave) dst[c] = !TAIL || c * N < H ? v : make_uint4(0u, 0u, 0u, 0u);
         };
         put(0, xv0);
         if constexpr (kXRounds > 1) put(1, xv1);
@@ -172,6 +181,8 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
         if constexpr (kXRounds > 3) put(3, xv3);
     } else {
         stage_as_f32(reinterpret_cast<const WT*>(a.x), xs, H);
+        if constexpr (TAIL)
+            for (int c = H + tid; c < NCH * CW; c += blockDim.x) xs[c] = 0.f;
     }
     if (tid < a.n_act) {
         s_slot[tid] = my_slot;
@@ -195,6 +206,7 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
         for (int s = 0; s < STEPS; ++s) {
             const Raw cur = win[s % PF];
             if (s < 2 * NCH) {
+                const float before = (s & 1) == 0 ? g : u;
                 if constexpr (kPacked) {
                     if ((s & 1) == 0) xp = reinterpret_cast<const uint4*>(xs)[(s >> 1) * kWave + lane];
                     if ((s & 1) == 0)
@@ -211,6 +223,12 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
                     } else {
                         u = V::dot(cur, xf, u);
                     }
+                }
+                if (last_chunk(s)) {  // a lane past the row's end adds nothing (its columns of y are never stored)
+                    if ((s & 1) == 0)
+                        g = lane_in ? g : before;
+                    else
+                        u = lane_in ? u : before;
                 }
             } else {
                 if (s == 2 * NCH) {
@@ -231,9 +249,10 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
             // hoisting refills and growing the window.
             __builtin_amdgcn_sched_barrier(0);
             if (s + PF < STEPS)
-                win[s % PF] = ld(p, step_off(s + PF));
+                win[s % PF] = ld(p, s + PF);
             else
-                win[s % PF] = ld(more ? pn : 0, more ? step_off(s + PF - STEPS) : 0);
+                win[s % PF] = V::load_once(pool + (more ? pn + step_off(s + PF - STEPS) : 0) +
+                                           (last_chunk(s + PF - STEPS) ? tail_off : lane_off));
             __builtin_amdgcn_sched_barrier(0);
         }
         t = tn;
@@ -243,7 +262,7 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
     }
     __syncthreads();  // the LDS behind the y rows held the slot ids until here
     float* out = a.part + (size_t)blockIdx.x * H;
-    block_sum_rows(yp, H, a.waves, a.ygroup, wv, out, [&](float* row) {
+    block_sum_rows(yp, H, NCH * CW, a.waves, a.ygroup, wv, out, [&](float* row) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
@@ -409,33 +428,55 @@ int launch_ffn_typed(FfnArgs a, bool fast, int grid, float* d_y, hipStream_t s) 
     using V = WVec<WT>;
     const int H = a.H;
     int rc = MOEI_OK;
-    const int nch = H / (kWave * V::N);
+    const int nch = (H + kWave * V::N - 1) / (kWave * V::N);
     const size_t row = (size_t)H * sizeof(float);
     if (fast) {
-#define MOEI_FFN_CASE(N_)                                                                            \
-    case N_: {                                                                                       \
-        a.waves = plan_waves(a.n_act * a.I, grid, StreamShape<N_>::kMaxWaves);                       \
-        int yg = (int)((kLdsBudget - row) / row);                                                    \
-        a.ygroup = yg < 1 ? 1 : (yg > a.waves ? a.waves : yg);                                       \
-        const size_t smem = row * (1 + a.ygroup);                                                    \
-        rc = allow_big_lds(ffn_fused_kernel<WT, N_>, smem);                                          \
-        if (rc) return rc;                                                                           \
-        launch(K_FFN_FUSED, ffn_fused_kernel<WT, N_>, dim3(grid), dim3(a.waves * kWave), smem, s, a); \
-        break;                                                                                       \
+#define MOEI_FFN_CASE(N_, TAIL_)                                                                        \
+    case N_: {                                                                                         \
+        a.waves = plan_waves(a.n_act * a.I, grid, StreamShape<N_>::kMaxWaves);                         \
+        const size_t padded = (size_t)N_ * kWave * V::N * sizeof(float);                               \
+        int yg = (int)((kLdsBudget - padded) / padded);                                                \
+        a.ygroup = yg < 1 ? 1 : (yg > a.waves ? a.waves : yg);                                         \
+        const size_t smem = padded * (1 + a.ygroup);                                                   \
+        rc = allow_big_lds(ffn_fused_kernel<WT, N_, TAIL_>, smem);                                     \
+        if (rc) return rc;                                                                             \
+        launch(K_FFN_FUSED, ffn_fused_kernel<WT, N_, TAIL_>, dim3(grid), dim3(a.waves * kWave), smem, s, a); \
+        break;                                                                                         \
     }
-        switch (nch) {
-            MOEI_FFN_CASE(1)
-            MOEI_FFN_CASE(2)
-            MOEI_FFN_CASE(3)
-            MOEI_FFN_CASE(4)
-            MOEI_FFN_CASE(5)
-            MOEI_FFN_CASE(6)
-            MOEI_FFN_CASE(8)
-            MOEI_FFN_CASE(10)
-            MOEI_FFN_CASE(12)
-            MOEI_FFN_CASE(16)
+        // whole chunks, for the counts of chunks that configurations have; any other row through TAIL
+        const int whole = H % (kWave * V::N) == 0 ? nch : 0;
+        switch (whole) {
+            MOEI_FFN_CASE(1, false)
+            MOEI_FFN_CASE(2, false)
+            MOEI_FFN_CASE(3, false)
+            MOEI_FFN_CASE(4, false)
+            MOEI_FFN_CASE(5, false)
+            MOEI_FFN_CASE(6, false)
+            MOEI_FFN_CASE(8, false)
+            MOEI_FFN_CASE(10, false)
+            MOEI_FFN_CASE(12, false)
+            MOEI_FFN_CASE(16, false)
             default:
-                fast = false;
+                switch ((uintptr_t)a.x % 16 == 0 ? nch : 0) {
+                    MOEI_FFN_CASE(1, true)
+                    MOEI_FFN_CASE(2, true)
+                    MOEI_FFN_CASE(3, true)
+                    MOEI_FFN_CASE(4, true)
+                    MOEI_FFN_CASE(5, true)
+                    MOEI_FFN_CASE(6, true)
+                    MOEI_FFN_CASE(7, true)
+                    MOEI_FFN_CASE(8, true)
+                    MOEI_FFN_CASE(9, true)
+                    MOEI_FFN_CASE(10, true)
+                    MOEI_FFN_CASE(11, true)
+                    MOEI_FFN_CASE(12, true)
+                    MOEI_FFN_CASE(13, true)
+                    MOEI_FFN_CASE(14, true)
+                    MOEI_FFN_CASE(15, true)
+                    MOEI_FFN_CASE(16, true)
+                    default:
+                        fast = false;
+                }
         }
 #undef MOEI_FFN_CASE
     }
@@ -952,7 +993,7 @@ int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_
     const int wb = d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4;
     const int n = 16 / wb;
     static const bool force_generic = env_int("MOEI_FFN_GENERIC", 0) != 0;
-    const bool fast = (d.H % (kWave * n) == 0) && ((uintptr_t)d_pool % 16 == 0) && ((slot_elems * wb) % 16 == 0) &&
+    const bool fast = (d.H % n == 0) && ((uintptr_t)d_pool % 16 == 0) && ((slot_elems * wb) % 16 == 0) &&
                       !force_generic;
     if (d.wdtype == MOEI_WDTYPE_BF16) return launch_ffn_typed<uint16_t>(a, fast, scr.n_part, d_y, s);
     return launch_ffn_typed<float>(a, fast, scr.n_part, d_y, s);

@@ -423,6 +423,26 @@ def test_expert_ffn_shapes(m, wdtype, H, I):
     cache.close()
 
 
+# rows that end inside a chunk of 64 lanes x 16 bytes: one lane in the last chunk, one short of it, chunk counts
+# without a kernel for whole chunks, the longest row and one too long; few and many units
+@pytest.mark.parametrize("wdtype,H,I", [("bf16", 8, 3), ("bf16", 504, 77), ("bf16", 520, 33), ("bf16", 1792, 910),
+                                        ("bf16", 2880, 301), ("bf16", 4616, 40), ("bf16", 7160, 9), ("bf16", 8184, 5),
+                                        ("bf16", 8200, 5), ("fp32", 4, 3), ("fp32", 260, 50), ("fp32", 2044, 211),
+                                        ("fp32", 2816, 213), ("fp32", 4092, 7)])
+def test_expert_ffn_rows_that_end_inside_a_chunk(m, wdtype, H, I):
+    cfg = mi.get_config("C1").scaled(H=H, I=I, wdtype=wdtype, L=2, n_shared=1, k=3, E=8)
+    err, cache = _ffn_case(m, cfg, 5, [3, 0, 4, 5 + 1], [0.5, 0.3, 0.2, 1.0], seed=H + I)
+    assert err <= FFN_TOL_FP32ACC, err
+    # a token that is not 16-byte aligned takes the kernel for any row: the same sums in another order
+    slots, gates = dev(np.array([3, 0, 4], np.int32)), dev(np.array([0.5, 0.3, 0.2], np.float32))
+    buf = torch.zeros(H + 1, dtype=cache.slot_tensor(0).dtype, device="cuda")
+    buf[1:] = torch.randn(H, device="cuda").to(buf.dtype)
+    y0 = m.expert_ffn_gemv(cache, slots, gates, buf[1:].clone())
+    y1 = m.expert_ffn_gemv(cache, slots, gates, buf[1:])
+    assert rel_max_err(y1.cpu().numpy(), y0.cpu().numpy().astype(np.float64)) <= FFN_TOL_FP32ACC
+    cache.close()
+
+
 def test_expert_ffn_edge_cases(m):
     cfg = mi.get_config("C1").scaled(H=128, I=256, wdtype="bf16", L=1, n_shared=0, k=2, E=4)
     err, cache = _ffn_case(m, cfg, 3, [1], [1.0], seed=1)
