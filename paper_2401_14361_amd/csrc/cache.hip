@@ -47,6 +47,7 @@ struct Pinned {
     float best_sim;
     int32_t n_list[2];  // n_pf, n_ev
     int32_t flags;
+    int32_t matches[2 * kMaxMatchBatch];  // d_best and d_best_sim, for moei_cache_last_matches
     int32_t best_seq;  // number of the step whose `best` is in place (written by the scoring workgroup after it)
 };
 
@@ -130,7 +131,7 @@ struct moei_cache {
     float* d_gate = nullptr;
     int32_t* d_best = nullptr;  // [kMaxMatchBatch] matched traces of the last step, most similar first
     int match_m = 1;            // traces aggregated by the layer step's prediction
-    float* d_best_sim = nullptr;
+    float* d_best_sim = nullptr;  // [kMaxMatchBatch] their similarities, behind d_best
     float *d_P = nullptr, *d_V = nullptr;
     unsigned long long* d_keys = nullptr;  // [2][L*E] sort keys of the last step (prefetch, eviction)
     int32_t *d_pf_head = nullptr, *d_ev_head = nullptr;  // leading entries of the orders, selected by the step itself
@@ -204,7 +205,6 @@ extern "C" int moei_cache_destroy(moei_cache* c) {
     (void)hipFree(c->d_slot_ids);
     (void)hipFree(c->d_gate);
     (void)hipFree(c->d_best);
-    (void)hipFree(c->d_best_sim);
     (void)hipFree(c->d_P);
     (void)hipFree(c->d_V);
     (void)hipFree(c->d_keys);
@@ -263,8 +263,8 @@ int cache_alloc(moei_cache* c) {
     MOEI_DMALLOC(c->d_w, (size_t)kMaxAct * 4);
     MOEI_DMALLOC(c->d_slot_ids, (size_t)kMaxAct * 4);
     MOEI_DMALLOC(c->d_gate, (size_t)kMaxAct * 4);
-    MOEI_DMALLOC(c->d_best, kMaxMatchBatch * 4);
-    MOEI_DMALLOC(c->d_best_sim, kMaxMatchBatch * 4);
+    MOEI_DMALLOC(c->d_best, 2 * kMaxMatchBatch * 4);
+    c->d_best_sim = reinterpret_cast<float*>(c->d_best + kMaxMatchBatch);
     MOEI_DMALLOC(c->d_P, LE * 4);
     MOEI_DMALLOC(c->d_V, LE * 4);
     MOEI_DMALLOC(c->d_keys, 2 * LE * 8);
@@ -992,10 +992,14 @@ extern "C" int moei_cache_last_matches(moei_cache* c, int32_t* h_top, float* h_t
                                        void* stream) {
     MOEI_REQUIRE(c && h_m, "moei_cache_last_matches: null pointer");
     MOEI_REQUIRE(cap >= c->match_m, "moei_cache_last_matches: room for %d entries, %d needed", cap, c->match_m);
-    MOEI_HIP(hipStreamSynchronize(as_stream(stream)));
+    // one copy behind what the caller's stream holds, and one wait for both: a program that reads the
+    // matches once a token pays for each trip to the device (two blocking copies behind two waits before)
+    hipStream_t s = as_stream(stream);
     MOEI_HIP(hipStreamSynchronize(c->side_stream));
-    if (h_top) MOEI_HIP(hipMemcpy(h_top, c->d_best, (size_t)c->match_m * 4, hipMemcpyDeviceToHost));
-    if (h_top_sim) MOEI_HIP(hipMemcpy(h_top_sim, c->d_best_sim, (size_t)c->match_m * 4, hipMemcpyDeviceToHost));
+    MOEI_HIP(hipMemcpyAsync(c->pin->matches, c->d_best, sizeof(c->pin->matches), hipMemcpyDeviceToHost, s));
+    MOEI_HIP(hipStreamSynchronize(s));
+    if (h_top) memcpy(h_top, c->pin->matches, (size_t)c->match_m * 4);
+    if (h_top_sim) memcpy(h_top_sim, c->pin->matches + kMaxMatchBatch, (size_t)c->match_m * 4);
     *h_m = c->match_m;
     return MOEI_OK;
 }
