@@ -50,7 +50,8 @@ struct PItem {
     int32_t list_off;   // routed: position of the item's first token in perm / pgate
     int32_t first_tok;  // shared expert: tokens first_tok .. first_tok + ntok - 1 with weight 1; else -1
     int32_t row0;       // the item's first row of the activation / contribution buffers
-    int32_t once;       // the expert has no other item: its weights are read once (non-temporal loads)
+    int32_t first;      // position of the expert's first item in the list ...
+    int32_t n;          // ... and how many it has: the items of an expert follow each other
 };
 
 // ------------------------------------------------------------------ 1. routing of n tokens
@@ -143,7 +144,6 @@ struct GroupArgsP {
     PItem* items;
     int32_t* meta;  // [0] = items in all, [1] = routed items
     int32_t* flags;
-    int spread_shared;  // list the items so that all items of a shared expert fall on one XCD of the wide kernels
 };
 
 constexpr int kXcds = 8;  // workgroups are handed to the chip's 8 XCDs in turn
@@ -250,27 +250,17 @@ __global__ void __launch_bounds__(kGrpThreads) prefill_group_kernel(GroupArgsP g
     const int slot = g.slot_of_row[e];
     if (cnt > 0 && slot < 0 && tid == 0) atomicOr(g.flags, 2);
     // the shared experts' items come first in the list: they are full, and the matrix kernels' grids
-    // start with the list's head, so the longest workgroups are not the last to start.  For the wide
-    // kernels, which run item p on XCD p % 8, item `tile` of shared expert s sits at position
-    // s + 8 * tile instead (and the routed items fill the other positions in their order): all items of
-    // a shared expert then run on one XCD, several of them at a time, and its weights pass through
-    // that L2 once for them.  (Needs at most 8 shared experts and enough routed items to leave no gap.)
+    // start with the list's head, so the longest workgroups are not the last to start
     const int tiles = (g.n + g.TM - 1) / g.TM;
     const int n_sh_items = g.n_shared * tiles;
-    const int free8 = kXcds - g.n_shared;  // routed positions per block of 8 among the first 8 * tiles
-    const bool spread = g.spread_shared && g.n_shared > 0 && g.n_shared <= kXcds && n_routed >= tiles * free8;
-    for (int it = tid; it * g.TM < cnt; it += kGrpThreads) {
-        const int r = ioff + it;  // number of this item among the routed ones
-        int p = n_sh_items + r;
-        if (spread && r < tiles * free8) p = kXcds * (r / free8) + g.n_shared + r % free8;
-        g.items[p] = PItem{slot, min(g.TM, cnt - it * g.TM), off + it * g.TM, -1, off + it * g.TM, cnt <= g.TM};
-    }
+    const int first = n_sh_items + ioff;
+    for (int it = tid; it * g.TM < cnt; it += kGrpThreads)
+        g.items[first + it] = PItem{slot, min(g.TM, cnt - it * g.TM), off + it * g.TM, -1, off + it * g.TM, first, (cnt + g.TM - 1) / g.TM};
     if (e == 0) {
         for (int q = tid; q < n_sh_items; q += kGrpThreads) {
             const int s = q / tiles, tile = q - s * tiles;
-            g.items[spread ? s + kXcds * tile : q] =
-                PItem{g.shared_base + s, min(g.TM, g.n - tile * g.TM), 0, tile * g.TM, g.n * g.k + s * g.n + tile * g.TM,
-                      tiles == 1};
+            g.items[q] = PItem{g.shared_base + s, min(g.TM, g.n - tile * g.TM), 0, tile * g.TM, g.n * g.k + s * g.n + tile * g.TM,
+                               s * tiles, tiles};
         }
         if (tid == 0) {
             g.meta[0] = n_routed + g.n_shared * tiles;
@@ -310,6 +300,8 @@ struct MmArgs {
     int32_t* flags;
     int n_ub;  // gate/up: blocks of 64 (wide kernel: 128) units;  down: blocks of 512 columns
     int n_cb;
+    int cus;       // compute units of an XCD
+    int n_shared, sh_tiles;  // shared experts, and how many items each has
     int dn_split;  // the down kernel takes an item in this many parts of TM tokens (items of the wide tile: 2)
 };
 
@@ -326,15 +318,60 @@ __device__ __forceinline__ bool xcd_work(int n_blocks, int* item, int* block) {
     return *block < n_blocks;
 }
 
-// The other way round, for the kernel whose workgroups each stream weights of their own: all output
-// blocks of an item on one XCD, so that the item's input rows come through that L2 once.
-__device__ __forceinline__ bool xcd_item_work(int n_blocks, int* item, int* block) {
-    const int v = blockIdx.x, xcd = v % kXcds, w = v / kXcds;
-    *block = w % n_blocks;
-    *item = xcd + kXcds * (w / n_blocks);
-    return true;
+// The wide gate/up kernel's tiles - items times unit blocks - form one sequence: an expert's items one
+// after the other in every unit block, block after block.  A tile's weights then pass through an L2 for
+// all of the expert's items at a time, if the workgroups that take neighbouring tiles run side by side on
+// one XCD: an XCD takes as many tiles in a row as it has compute units.  The list runs from the items
+// with the most tokens down, so every second XCD takes its tiles from the end: tiles that are bound by
+// their products and tiles that are bound by their weights run at the same time.  What is left for a last,
+// partly filled round is spread over the XCDs evenly.  Measured against items dealt to the XCDs whole, their
+// tiles in item order: 1,531 tokens of an 8-expert layer of 14,336 units (two items each) 1,305 -> 1,261
+// us a layer, kernel 925 -> 890 us; 512 and 2,048 tokens of the 64-expert shape the same.
+// Number of the w-th tile of an XCD (`total`: it has none).
+__device__ __forceinline__ int tile_of_xcd(int total, int xcd, int w, int cus) {
+    const int round = w / cus, done = round * kXcds * cus, left = total - done;
+    if (left >= kXcds * cus) {
+        const int full = total / (kXcds * cus) * kXcds, c = round * (kXcds / 2) + xcd / 2;
+        return (xcd % 2 ? full - 1 - c : c) * cus + w % cus;
+    }
+    const int first = left * xcd / kXcds, t = first + w % cus;
+    return left > 0 && t < left * (xcd + 1) / kXcds ? done + t : total;
 }
-
+// The wide down kernel runs an item whole on one XCD, position p of its order on XCD p % 8.  Item `tile` of
+// shared expert s is at position s + 8 * tile there: the items of a shared expert run on one XCD, several
+// at a time, and its weights pass through that L2 once for them; the routed items fill the other
+// positions in the list's order.  (Needs at most 8 shared experts and enough routed items to leave no gap.)
+__device__ __forceinline__ int item_at(const MmArgs& a, int p, int n_routed) {
+    const int free8 = kXcds - a.n_shared;  // routed positions per block of 8 among the first 8 * tiles
+    if (a.n_shared == 0 || free8 < 0 || n_routed < a.sh_tiles * free8 || p >= kXcds * a.sh_tiles) return p;
+    const int s = p % kXcds;
+    return s < a.n_shared ? s * a.sh_tiles + p / kXcds : a.n_shared * a.sh_tiles + p / kXcds * free8 + s - a.n_shared;
+}
+// Read-only tables are read through the constant address space: uniform loads that count on lgkmcnt, so
+// that waiting for them does not wait for a ring's loads.
+typedef const __attribute__((address_space(4))) int32_t* const_ints;
+static_assert(sizeof(PItem) == 28 && offsetof(PItem, row0) == 16 && offsetof(PItem, first) == 20 && offsetof(PItem, n) == 24,
+              "tile_at reads an item as integers");
+struct Tile {
+    int slot, ntok, list_off, first_tok, row0;
+    int block;  // unit block
+    bool ok;    // false: there is no such tile
+};
+__device__ __forceinline__ Tile tile_at(const MmArgs& a, int n_items, int n_blocks, int t) {
+    Tile r{-1, 0, 0, -1, 0, 0, t < n_items * n_blocks};
+    if (!r.ok) return r;  // uniform
+    const_ints it = (const_ints)(uintptr_t)(a.items + t / n_blocks);  // an item of the tile's expert
+    const int first = it[5], n = it[6];
+    const int q = t - first * n_blocks;
+    r.block = q / n;
+    it = (const_ints)(uintptr_t)(a.items + first + q % n);
+    r.slot = it[0];
+    r.ntok = it[1];
+    r.list_off = it[2];
+    r.first_tok = it[3];
+    r.row0 = it[4];
+    return r;
+}
 
 // w silu(g) u of four neighbouring units, rounded to nearest even bf16.  The quotient and the exponential
 // are the hardware's (an ulp or two of fp32, far below the rounding to 8 bits that follows): the
@@ -410,7 +447,7 @@ __global__ void __launch_bounds__(TM * 4) prefill_gateup_kernel(MmArgs a) {
 #pragma unroll
         for (int j = 0; j < NW; ++j) {
             const int kk = s * kGuKS + ((tid + kMmThreads * j) % VPR) * 8;
-            wst[j] = kk < H ? (it.once ? load_once_16(wsrc[j] + s * kGuKS) : *reinterpret_cast<const uint4*>(wsrc[j] + s * kGuKS))
+            wst[j] = kk < H ? (it.n == 1 ? load_once_16(wsrc[j] + s * kGuKS) : *reinterpret_cast<const uint4*>(wsrc[j] + s * kGuKS))
                             : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
@@ -481,7 +518,7 @@ __global__ void __launch_bounds__(TM * 4) prefill_gateup_kernel(MmArgs a) {
 // per stage, in rings of three (weights) and two stages (inputs).  A compute unit returns loads in the
 // order they were asked for, so every wavefront loads a share of both, the inputs - mostly from L2 -
 // ahead of the weights that are needed a stage later.  The workgroups are persistent, one per compute
-// unit, and their rings run on from tile to tile; the tiles are dealt out evenly (see Tile): with the
+// unit, and their rings run on from tile to tile; the tiles are dealt out evenly (see tile_of_xcd): with the
 // items of a list pinned to the XCDs one XCD had 99 tiles for its 32 compute units where 96 was the
 // average, a fourth round for everybody.  Measured (26-layer 64-expert shape, one layer): 512 tokens
 // 186 -> 158 us, 2,048 tokens 307 -> 290 us; two large items per XCD, 1,531 tokens of an 8-expert layer
@@ -525,50 +562,6 @@ __device__ __forceinline__ const unsigned char* scalar_ptr(const void* p) {
     return reinterpret_cast<const unsigned char*>((uintptr_t)(((uint64_t)hi << 32) | lo));
 }
 
-// The tiles of a persistent workgroup: one workgroup per compute unit.  The tiles - items times output
-// blocks - form one sequence, of which every XCD takes an eighth and its workgroups every 32nd tile of
-// that: first the items at positions 0, 8, 16 ... of the item list, then those at 1, 9, 17 ..., each with
-// all its output blocks, so that an item's input rows pass through one L2 or two, large and small
-// items are spread over the XCDs, and no XCD gets more tiles than another, however few items there are.
-struct Tile {
-    int slot, ntok, list_off, first_tok, row0;
-    int block;  // output block
-    bool ok;    // false: the workgroup has no more tiles
-};
-// Read-only tables are read through the constant address space: uniform loads that count on lgkmcnt, so
-// that waiting for them does not wait for the ring's loads.
-typedef const __attribute__((address_space(4))) int32_t* const_ints;
-__device__ __forceinline__ Tile tile_at(const MmArgs& a, int n_items, int n_blocks, int seq) {
-    const int xcd = blockIdx.x % kXcds, step = gridDim.x / kXcds;
-    const int total = n_items * n_blocks;
-    const int end = (int)((long)total * (xcd + 1) / kXcds);
-    const int t = (int)((long)total * xcd / kXcds) + (int)(blockIdx.x / kXcds) + seq * step;
-    Tile r;
-    r.ok = t < end;
-    const int i = r.ok ? t / n_blocks : 0;
-    r.block = t - i * n_blocks;
-    // item i of the sequence: the first n_items % 8 positions modulo 8 have one item more
-    const int q = n_items / kXcds, more = n_items % kXcds;
-    int x, k;
-    if (i < more * (q + 1)) {
-        x = i / (q + 1);
-        k = i - x * (q + 1);
-    } else {
-        const int j = i - more * (q + 1);
-        x = j / q;
-        k = j - x * q;
-        x += more;
-    }
-    const_ints it = (const_ints)(uintptr_t)(a.items + x + kXcds * k);
-    r.slot = it[0];
-    r.ntok = it[1];
-    r.list_off = it[2];
-    r.first_tok = it[3];
-    r.row0 = it[4];
-    return r;
-}
-static_assert(sizeof(PItem) == 24 && offsetof(PItem, row0) == 16, "tile_at reads an item as integers");
-
 __global__ void __launch_bounds__(kWdThreads, 2) prefill_gateup_wide_kernel(MmArgs a) {
     constexpr int TM = kTileTokWide;
     constexpr int NTB = TM / 32;  // 16-token blocks per wavefront: 8
@@ -586,7 +579,7 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_gateup_wide_kernel(MmAr
     int seq = 0;
     auto next_tile = [&]() {  // items whose expert is not resident are passed over: the down kernel writes the zeros and raises the flag
         Tile t;
-        do t = tile_at(a, n_items, a.n_ub, seq++);
+        do t = tile_at(a, n_items, a.n_ub, tile_of_xcd(n_items * a.n_ub, blockIdx.x % kXcds, blockIdx.x / kXcds + seq++ * a.cus, a.cus));
         while (t.ok && (t.slot < 0 || t.slot >= a.n_slots_total));
         return t;
     };
@@ -851,7 +844,7 @@ __global__ void __launch_bounds__(TM * 4, 2) prefill_down_kernel(MmArgs a) {  //
     auto load_w = [&](int k0, uint4* dst) {  // units k0 + 8*lgrp + j (clamped: their activations are zero)
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            dst[j] = it.once ? load_once_16(wd + (size_t)min(k0 + lgrp * 8 + j, I - 1) * 3 * H)
+            dst[j] = it.n == 1 ? load_once_16(wd + (size_t)min(k0 + lgrp * 8 + j, I - 1) * 3 * H)
                             : *reinterpret_cast<const uint4*>(wd + (size_t)min(k0 + lgrp * 8 + j, I - 1) * 3 * H);
     };
 
@@ -958,10 +951,10 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_down_wide_kernel(MmArgs
     extern __shared__ __align__(16) unsigned char smem_raw[];
     uint16_t* ring_w = reinterpret_cast<uint16_t*>(smem_raw);         // [kDwStagesW][64][256]
     uint16_t* ring_a = ring_w + (size_t)kDwStagesW * kDwStageElemsW;  // [kDwStagesA][256][64], chunks swizzled
-    int item, cb;
-    xcd_item_work(a.n_cb, &item, &cb);
-    if (item >= a.meta[0]) return;
-    const PItem it = a.items[item];
+    // all column blocks of an item on one XCD, all items of a shared expert on one XCD too
+    const int pos = blockIdx.x % kXcds + kXcds * (blockIdx.x / kXcds / a.n_cb), cb = blockIdx.x / kXcds % a.n_cb;
+    if (pos >= a.meta[0]) return;
+    const PItem it = a.items[item_at(a, pos, a.meta[1])];
     const int H = a.H, I = a.I;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -1352,12 +1345,7 @@ int tile_tokens(const moei_model_desc& d, int n) {
     return (long)n * d.k >= (long)48 * d.E ? kTileTokWide : kTileTok;
 }
 
-// workgroups of a persistent kernel: one per compute unit, a whole number per XCD, no more than there can be tiles
-int persistent_grid(int n_blocks, int max_items) {
-    const int per_xcd = std::max(1, compute_units() / kXcds);
-    const long tiles = (long)((max_items + kXcds - 1) / kXcds) * n_blocks;
-    return kXcds * (int)std::min<long>(per_xcd, tiles);
-}
+int cus_per_xcd() { return std::max(1, compute_units() / kXcds); }
 
 template <int TM>
 int launch_mm(const moei_model_desc& d, MmArgs a, int max_items, hipStream_t s) {
@@ -1376,7 +1364,7 @@ int launch_mm(const moei_model_desc& d, MmArgs a, int max_items, hipStream_t s) 
         rc = pf_allow_lds(prefill_gateup_wide_kernel, gu_smem);
         if (rc) return rc;
         a.n_ub = (d.I + kWdUnits - 1) / kWdUnits;
-        launch(K_PF_GATEUP, prefill_gateup_wide_kernel, dim3(persistent_grid(a.n_ub, max_items)), dim3(kWdThreads), gu_smem, s, a);
+        launch(K_PF_GATEUP, prefill_gateup_wide_kernel, dim3(kXcds * a.cus), dim3(kWdThreads), gu_smem, s, a);
     }
     MOEI_LAUNCH_CHECK();
     if (a.dn_split == 2 && d.I % kDwKS == 0 && d.H % kDwCols == 0) {
@@ -1443,8 +1431,7 @@ int launch_prefill(const moei_model_desc& d, const PrefillScratch& ps, const voi
     MOEI_LAUNCH_CHECK();
     const int tm = tile_tokens(d, n);
     GroupArgsP g{ps.d_idx, ps.d_w, n, d.k, d.E, d.n_shared, tm, d_slot_of_row, shared_base, d_eam_row, ps.d_perm,
-                 ps.d_pgate, ps.d_where, reinterpret_cast<PItem*>(ps.d_items), ps.d_meta, d_flags,
-                 tm == kTileTokWide};
+                 ps.d_pgate, ps.d_where, reinterpret_cast<PItem*>(ps.d_items), ps.d_meta, d_flags};
     launch(K_FFN_GROUP, prefill_group_kernel, dim3(d.E), dim3(kGrpThreads), (size_t)d.E * sizeof(int), s, g);
     MOEI_LAUNCH_CHECK();
     // the number of items is known on the device only: the grids cover the largest possible count
@@ -1452,7 +1439,7 @@ int launch_prefill(const moei_model_desc& d, const PrefillScratch& ps, const voi
     MmArgs a{reinterpret_cast<const uint16_t*>(d_pool), slot_elems, n_slots_total,
              reinterpret_cast<const PItem*>(ps.d_items), ps.d_meta, reinterpret_cast<const uint16_t*>(d_X), ps.d_perm,
              ps.d_pgate, ps.d_act, ps.d_yc, d.H, d.I, d_flags, 0, (d.H + kDnCols - 1) / kDnCols,
-             tm == kTileTokWide ? 2 : 1};
+             cus_per_xcd(), d.n_shared, (n + tm - 1) / tm, tm == kTileTokWide ? 2 : 1};
     rc = tm == kTileTok ? launch_mm<kTileTok>(d, a, max_items, s) : launch_mm<kTileTokBig>(d, a, max_items, s);
     if (rc) return rc;
     launch(K_PF_REDUCE, prefill_reduce_kernel, dim3(n), dim3(256), 0, s, (const float*)ps.d_yc,
