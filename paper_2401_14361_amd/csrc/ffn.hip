@@ -546,6 +546,7 @@ __device__ __forceinline__ int build_items(const GroupArgs& a, GroupItem* s_item
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int n_pick = a.B * a.k;
     float* s_pickw = reinterpret_cast<float*>(s_pick + n_pick);
+    const int row_slot = tid < a.E ? a.slot_of_row[tid] : -1;  // on its way with the picks
     for (int p = tid; p < n_pick; p += blockDim.x) {
         int e = a.idx[p];
         if (e < 0 || e >= a.E) e = -1;  // a token without picks (no softmax exists for its logits)
@@ -573,7 +574,7 @@ __device__ __forceinline__ int build_items(const GroupArgs& a, GroupItem* s_item
     if (tid < 256) {
         int slot = -1, ntok = tid < a.E ? sc->cnt[tid] : 0;
         if (ntok > 0) {
-            slot = a.slot_of_row[tid];
+            slot = row_slot;
             if (slot < 0) {  // not resident: contributes nothing, flagged
                 if (publish) atomicOr(a.flags, 2);
                 ntok = 0;
@@ -646,6 +647,7 @@ struct GroupedFfnArgs {
     const void* x;  // [B][H]
     float* part;    // [workgroups][seg_max][TB][H]
     int H, I;
+    int cost;  // rows that an item's start counts for
     int seg_max;
 };
 
@@ -654,11 +656,25 @@ struct GroupedShape {
     static constexpr int kTB = NCH <= 4 ? 4 : 1;  // y accumulators per token must fit the register file
 };
 
-// The activated items' intermediate units form one row space of n_items * I rows; workgroup g
-// takes the contiguous range [total*g/G, total*(g+1)/G).  A range crosses at most
-// ceil(n_items / G) item boundaries, so it is cut into at most that many + 1 segments, each
+// The activated items' intermediate units form one row space of n_items * (I + cost) rows, the first
+// `cost` of an item standing for what its start costs a workgroup (the window drains, the partial rows of
+// the item before are added up, the inputs are staged, the window fills: about as long as 180 KB of
+// weights take); workgroup g takes the contiguous range [total*g/G, total*(g+1)/G).  A range crosses at
+// most ceil(n_items / G) item boundaries, so it is cut into at most that many + 1 segments, each
 // inside one item; a segment yields one partial y row per token of the item.
+// (With even shares of the units alone the workgroups that change items ended last: a layer step of three
+// requests over 10,000 traces took 125.3 us, now 121.9; of sixteen, bound by the 934 MB it streams, 251.)
 __device__ __host__ inline long grouped_range_begin(long total, int g, int G) { return total * g / G; }
+__host__ inline int grouped_cost(int H, int wb) { return (180 * 1024 + 3 * H * wb - 1) / (3 * H * wb); }
+// The next segment of a range: rows r0 .. r1 of `item` (none: r0 == r1); *row moves past it.
+__device__ __forceinline__ void grouped_segment(long* row, long end, int I, int cost, int* item, int* r0, int* r1) {
+    *item = (int)(*row / (I + cost));
+    const int c0 = (int)(*row - (long)*item * (I + cost));
+    const int c1 = (int)min((long)(I + cost), c0 + (end - *row));
+    *row += c1 - c0;
+    *r0 = max(0, c0 - cost);
+    *r1 = max(0, c1 - cost);
+}
 
 __host__ inline int grouped_seg_max(int max_items, int G) { return (max_items + G - 1) / G + 1; }
 
@@ -686,7 +702,7 @@ __global__ void __launch_bounds__((kGroupedWaves * kWave)) ffn_grouped_kernel(Gr
     const unsigned lane_off = (unsigned)lane * N;
     int* s_pick = reinterpret_cast<int*>(s_items + a.max_items);  // [2][B*k]
     const int n_items = build_items(a.grp, s_items, s_pick, &s_is, blockIdx.x == 0);
-    const long total = (long)n_items * I;
+    const long total = (long)n_items * (I + a.cost);
     const long R0 = grouped_range_begin(total, blockIdx.x, gridDim.x);
     const long R1 = grouped_range_begin(total, blockIdx.x + 1, gridDim.x);
     auto scalar = [](size_t v) -> size_t {
@@ -701,10 +717,9 @@ __global__ void __launch_bounds__((kGroupedWaves * kWave)) ffn_grouped_kernel(Gr
 
     int seg = 0;
     for (long row = R0; row < R1 && seg < a.seg_max; ++seg) {  // uniform over the workgroup
-        const int item = (int)(row / I);
-        const int r0 = (int)(row - (long)item * I);
-        const int r1 = (int)min((long)I, r0 + (R1 - row));
-        row += r1 - r0;
+        int item, r0, r1;
+        grouped_segment(&row, R1, I, a.cost, &item, &r0, &r1);
+        if (r0 == r1) continue;
         const GroupItem it = s_items[item];
         // this wavefront's rows of the segment: r0 + wv, r0 + wv + 8, ...
         const int nr = (r1 - r0 - wv + kGroupedWaves - 1) / kGroupedWaves;  // may be <= 0
@@ -821,7 +836,7 @@ __global__ void __launch_bounds__((kGroupedWaves * kWave)) ffn_grouped_kernel(Gr
 __global__ void __launch_bounds__(256) ffn_grouped_reduce_kernel(const float* __restrict__ part,
                                                                  const GroupItem* __restrict__ items,
                                                                  const int32_t* __restrict__ n_items, int tb, int I,
-                                                                 int H, int n_blocks, int seg_max,
+                                                                 int cost, int H, int n_blocks, int seg_max,
                                                                  float* __restrict__ y) {
     extern __shared__ __align__(16) int32_t s_rows[];  // partial row of each segment for this token, or -1
     __shared__ float s_sum[32][32];
@@ -830,17 +845,16 @@ __global__ void __launch_bounds__(256) ffn_grouped_reduce_kernel(const float* __
     const int n = n_blocks * seg_max;
     int32_t* s_list = s_rows + n;  // the rows that exist, in segment order
     const int b = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const long total = (long)*n_items * I;
+    const long total = (long)*n_items * (I + cost);
     for (int g = tid; g < n_blocks; g += 256) {
         long row = grouped_range_begin(total, g, n_blocks);
         const long R1 = grouped_range_begin(total, g + 1, n_blocks);
         for (int seg = 0; seg < seg_max; ++seg) {
             int entry = -1;
             if (row < R1) {
-                const int item = (int)(row / I);
-                const int r0 = (int)(row - (long)item * I);
-                row += min((long)I, r0 + (R1 - row)) - r0;
-                for (int j = 0; j < items[item].ntok; ++j)
+                int item, r0, r1;
+                grouped_segment(&row, R1, I, cost, &item, &r0, &r1);
+                for (int j = 0; r0 < r1 && j < items[item].ntok; ++j)
                     if (items[item].tok[j] == b) entry = (g * seg_max + seg) * tb + j;
             }
             s_rows[g * seg_max + seg] = entry;
@@ -1040,7 +1054,7 @@ int launch_grouped_typed(const moei_model_desc& d, GroupedFfnArgs ga, int B, flo
 #undef MOEI_GROUPED_CASE
     launch(K_FFN_REDUCE, ffn_grouped_reduce_kernel, dim3(d.H / 32, B), dim3(256),
            (size_t)2 * grid * ga.seg_max * sizeof(int32_t), s, (const float*)ga.part, (const GroupItem*)ga.grp.items,
-           (const int32_t*)ga.grp.n_items, ga.grp.tb, d.I, d.H, grid, ga.seg_max, d_y);
+           (const int32_t*)ga.grp.n_items, ga.grp.tb, d.I, ga.cost, d.H, grid, ga.seg_max, d_y);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
 }
@@ -1060,7 +1074,7 @@ int launch_expert_ffn_grouped(const moei_model_desc& d, const void* d_pool, size
         MOEI_FAIL(MOEI_EINVAL, "expert_ffn_grouped: H = %d must be a multiple of %d", d.H, kWave * n);
     GroupArgs gr{d_idx, d_w, d_slot_of_row, B, d.k, d.E, d.n_shared, shared_base, 0,
                  reinterpret_cast<GroupItem*>(d_items), d_n_items, d_flags};
-    GroupedFfnArgs ga{d_pool, slot_elems, gr, grouped_max_items(d), d_x, d_part, d.H, d.I, 0};
+    GroupedFfnArgs ga{d_pool, slot_elems, gr, grouped_max_items(d), d_x, d_part, d.H, d.I, grouped_cost(d.H, wb), 0};
     if (d.wdtype == MOEI_WDTYPE_BF16) return launch_grouped_typed<uint16_t>(d, ga, B, d_y, s);
     return launch_grouped_typed<float>(d, ga, B, d_y, s);
 }

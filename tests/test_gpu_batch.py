@@ -156,6 +156,16 @@ def test_batched_ffn_at_the_item_builders_limits(m):
     _ffn_only_case(m, cfg, B, idx, w)
 
 
+# shares of the units in which an item's start weighs more than its units: one item over all workgroups, and
+# many items of one unit
+@pytest.mark.parametrize("E,k,n_shared,B,I", [(1, 1, 0, 1, 5), (1, 1, 0, 4, 130), (200, 4, 2, 16, 1)])
+def test_batched_ffn_items_shorter_than_their_start(m, E, k, n_shared, B, I):
+    cfg = mi.get_config("C5").scaled(L=1, E=E, k=k, n_shared=n_shared, H=512, I=I, N=8, prompt=16)
+    rng = np.random.default_rng(E + I)
+    idx = np.stack([rng.choice(E, size=k, replace=False) for _ in range(B)]).astype(np.int32)
+    _ffn_only_case(m, cfg, B, idx, rng.random((B, k)).astype(np.float32))
+
+
 def test_batched_ffn_rejects_more_experts_than_the_item_builder_takes(m):
     cfg = mi.get_config("C5").scaled(L=1, E=260, k=2, n_shared=0, N=4, prompt=4, H=256, I=4, wdtype="fp32")
     desc = m.ModelDesc.from_config(cfg)
