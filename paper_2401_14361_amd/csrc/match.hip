@@ -983,7 +983,6 @@ __device__ __forceinline__ void block_top(TopLds& t, int count, int m, Emit emit
         const int per = (count + slices - 1) / slices;
         const int o1 = min(count, (sl + 1) * per);
         int rank = 0;
-#pragma unroll 4
         for (int o = sl * per; o < o1; ++o) {
             const unsigned ohi = key_hi(t.key[o]);
             const int oidx = t.idx[o];

@@ -6,7 +6,7 @@
 //                             same summation order as the decode routing, so the same bits)
 //   2. prefill_group_kernel   histogram of the picks -> EAM row; tokens grouped per expert in
 //                             ascending token order, cut into items of <= 64 (long prompts: 256) tokens
-//   3. prefill_gateup_kernel, prefill_down_kernel
+//   3. prefill_gateup_kernel, prefill_down_kernel (long prompts: the _wide_ kernels)
 //                             grouped SwiGLU expert FFN on the matrix cores as two tiled products
 //                             per item; an expert's weights pass once per item
 //   4. prefill_reduce_kernel  y[t] = sum of the token's rows, in pick order
@@ -522,7 +522,7 @@ __global__ void __launch_bounds__(TM * 4) prefill_gateup_kernel(MmArgs a) {
 // items of a list pinned to the XCDs one XCD had 99 tiles for its 32 compute units where 96 was the
 // average, a fourth round for everybody.  Measured (26-layer 64-expert shape, one layer): 512 tokens
 // 186 -> 158 us, 2,048 tokens 307 -> 290 us; two large items per XCD, 1,531 tokens of an 8-expert layer
-// of 14,336 units: 946 -> 925 us.  What is left there: with the loads taken out 587 us, with the matrix
+// of 14,336 units: 946 -> 925 us, and 890 with the tiles in the order of tile_of_xcd.  What is left there: with the loads taken out 587 us, with the matrix
 // instructions taken out 735 us.  (More stages in flight do not help: giving a stage's slots back half
 // a stage earlier, at the price of a second barrier, took 1,050 us.)
 // Chunk c of ring row r sits at chunk position c ^ ((r >> 1) % 8): the sixteen lanes that read one

@@ -28,7 +28,10 @@ constexpr int kRankThreads = 256;
 // number of candidates that sort before it (smaller key; among the lower ids also an equal one).
 // Measured (26 x 64 cells, beside the library's other kernels): one scoring workgroup and a ranking
 // launch took 12.7 + 9.2 us for 3 or 8 traces and 22.8 + 9.3 us for 16 traces and 96 picks; this
-// kernel takes 9.5 and 15.8 us.
+// kernel takes 9.5 and 15.8 us.  More loads in flight do not help: flat over the cells, two
+// cells of 16 traces of a thread at once, it took 11.2 and 16.5 us; of those 3.5 us are the launch, 2.6 us
+// the ranking and, at 16 traces, 5.6 us the misses on 26 x 16 rows that lie all over the collection (every
+// cell taken from one trace: 11.1 us).  Fewer workgroups rank longer (64 a list: 13.3 and 19.1 us).
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderPerLane = 4;   // cells of a row held in registers (rows up to 256 wide)
 constexpr int kOrderTraces = 8;    // traces whose cells are requested together
