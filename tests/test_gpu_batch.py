@@ -157,8 +157,9 @@ def test_batched_ffn_at_the_item_builders_limits(m):
 
 
 # shares of the units in which an item's start weighs more than its units: one item over all workgroups, and
-# many items of one unit
-@pytest.mark.parametrize("E,k,n_shared,B,I", [(1, 1, 0, 1, 5), (1, 1, 0, 4, 130), (200, 4, 2, 16, 1)])
+# many items of one unit; items that divide the workgroups, and items that do not
+@pytest.mark.parametrize("E,k,n_shared,B,I", [(1, 1, 0, 1, 5), (1, 1, 0, 4, 130), (200, 4, 2, 16, 1),
+                                              (8, 8, 0, 1, 70), (3, 3, 0, 2, 70)])
 def test_batched_ffn_items_shorter_than_their_start(m, E, k, n_shared, B, I):
     cfg = mi.get_config("C5").scaled(L=1, E=E, k=k, n_shared=n_shared, H=512, I=I, N=8, prompt=16)
     rng = np.random.default_rng(E + I)
