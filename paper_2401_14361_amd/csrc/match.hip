@@ -752,7 +752,6 @@ struct PickArgs {
     int32_t* best;
     float* best_sim;
     float* sims;
-    int do_score;   // the finishing workgroup also scores the matched trace (B = 1)
     ScoreArgs sc;
 };
 
@@ -777,6 +776,10 @@ __device__ __forceinline__ Best block_pick(Best me, u64* s_dot, u64* s_nt, int* 
 
 // grid (workgroups over traces, B): sums the layer-split partial dots, writes similarities,
 // picks the workgroup's best trace; the last workgroup to arrive picks among the winners.
+// SCORE: the finishing workgroup also scores the matched trace (B = 1).  A search alone has a kernel of
+// its own: with the scoring in it 97 scalar registers were spilled, and a match over 10,000 traces took
+// 22.8 us for one query and 26.7 for eight instead of 22.1 and 25.8.
+template <bool SCORE>
 __global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) {
     __shared__ u64 s_dot[kPickWaves];
     __shared__ u64 s_nt[kPickWaves];
@@ -828,8 +831,8 @@ __global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) {
     Best r = block_pick(me, s_dot, s_nt, s_idx);
     __shared__ int s_sn[2];
     __shared__ int s_best[kMaxMatchBatch];
-    __shared__ HeadLds s_heads;
-    __shared__ KeyLds s_keys;
+    __shared__ std::conditional_t<SCORE, HeadLds, char> s_heads;
+    __shared__ std::conditional_t<SCORE, KeyLds, char> s_keys;
     if (gridDim.x == 1) {
         if (tid == 0) {
             a.best[b] = r.idx;
@@ -837,7 +840,7 @@ __global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) {
             if (a.best_sim) a.best_sim[b] = r.idx >= 0 ? (float)cosine(r.dot, nq, r.nt) : 0.f;
             s_best[0] = r.idx;
         }
-        if (a.do_score) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best);
+        if constexpr (SCORE) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best);
         return;
     }
     // several workgroups: publish this one's winner, the last to arrive finishes
@@ -869,7 +872,7 @@ __global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) {
         a.ticket[b] = 0;  // ready for the next launch on this stream
         s_best[0] = fin.idx;
     }
-    if (a.do_score) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best);
+    if constexpr (SCORE) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best);
 }
 
 // ---- the m most similar traces of ONE query, most similar first (ties: lowest index)
@@ -889,7 +892,6 @@ struct TopmArgs {
     int32_t* top;       // [m], -1 beyond the stored traces
     float* top_sim;     // [m] or null
     float* sims;        // [N] or null
-    int do_score;       // the finishing workgroup also scores the aggregate of the m traces
     ScoreArgs sc;
 };
 
@@ -1006,6 +1008,8 @@ __device__ __forceinline__ void block_top(TopLds& t, int count, int m, Emit emit
 // workgroup to arrive finds the m best of all winners.  A chain of dependent steps on few compute
 // units: m rounds of a workgroup-wide exact arg-max (two barriers and two chains of exchanges
 // each, twice over) took 39.7 us at 10,000 traces and m = 8, ranking takes 16.0 us.
+// SCORE: the finishing workgroup also scores the aggregate of the m traces.
+template <bool SCORE>
 __global__ void __launch_bounds__(kPickThreads) eamc_topm_kernel(TopmArgs a) {
     __shared__ u64 s_red[kPickWaves];
     __shared__ u64 s_nq;
@@ -1117,7 +1121,7 @@ __global__ void __launch_bounds__(kPickThreads) eamc_topm_kernel(TopmArgs a) {
         block_top(s_top, count, a.m, finish);
         if (tid == 0) *a.ticket = 0;  // ready for the next launch on this stream
     }
-    if (a.do_score) {
+    if constexpr (SCORE) {
         __syncthreads();  // the matched traces are in LDS; the search's LDS is free
         score_and_heads(a.sc, s_score.heads, s_score.keys, s_sn, s_best);
     }
@@ -1554,8 +1558,8 @@ int launch_match(const moei_eamc* c, const int32_t* d_eam, int B, int layer_hi, 
     if (rc) return rc;
     const int n_blk = c->N > 0 ? (c->N + kPickChunk - 1) / kPickChunk : 1;
     PickArgs pa{c->d_part, c->d_norm2, d_eam, n_lsplit, c->n_cap, c->N, L * E, c->d_cand, c->d_cand_idx,
-                c->d_ticket, d_best, d_best_sim, d_sims, score != nullptr, score ? *score : ScoreArgs{}};
-    launch(K_MATCH_ARGMAX, eamc_pick_kernel, dim3(n_blk, B), dim3(kPickThreads), 0, s, pa);
+                c->d_ticket, d_best, d_best_sim, d_sims, score ? *score : ScoreArgs{}};
+    launch(K_MATCH_ARGMAX, score ? eamc_pick_kernel<true> : eamc_pick_kernel<false>, dim3(n_blk, B), dim3(kPickThreads), 0, s, pa);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
 }
@@ -1572,8 +1576,8 @@ int launch_match_topm(const moei_eamc* c, const int32_t* d_eam, int layer_hi, in
     int rc = launch_dots(c, d_eam, 1, layer_hi, &n_lsplit, s);
     if (rc) return rc;
     TopmArgs ta{c->d_part, c->d_norm2, d_eam, n_lsplit, c->n_cap, c->N, L * E, m, c->d_cand, c->d_cand_idx,
-                c->d_ticket, d_top, d_top_sim, d_sims, score != nullptr, score ? *score : ScoreArgs{}};
-    launch(K_MATCH_ARGMAX, eamc_topm_kernel, dim3(n_blk), dim3(kPickThreads), 0, s, ta);
+                c->d_ticket, d_top, d_top_sim, d_sims, score ? *score : ScoreArgs{}};
+    launch(K_MATCH_ARGMAX, score ? eamc_topm_kernel<true> : eamc_topm_kernel<false>, dim3(n_blk), dim3(kPickThreads), 0, s, ta);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
 }
