@@ -233,6 +233,41 @@ def test_prefill_full_width_2048_token_prompt_with_256_token_items(m):
     _check(o)
 
 
+def _round_bf16(v):
+    step = np.exp2(np.floor(np.log2(np.abs(v))) - 7)
+    return np.round(v / step) * step   # half to even
+
+
+@pytest.mark.parametrize("tile", [64, 128, 256])
+def test_prefill_activations_round_from_fp32_accuracy(m, tile, monkeypatch):
+    # one expert, one-hot tokens and a unit W_down: Y[t][u] is the bf16 activation silu(g) u of one pair (g, u) of
+    # stored weights.  It has to be a rounding of a value within 3 x 2^-23 of the exact one: expf 2^-23, then the sum, the
+    # quotient and the product 2^-24 each.  Gates down to where the reciprocal of 1 + exp(-g) leaves the normal range.
+    monkeypatch.setenv("MOEI_PREFILL_TILE", str(tile))
+    n = 256
+    desc = m.ModelDesc(1, 1, 1, 0, n, n, m.WDTYPE_BF16, 0, 2.0 ** -20)
+    rng = np.random.default_rng(tile)
+    bf16 = lambda v: torch.from_numpy(v.astype(np.float32)).to(torch.bfloat16)
+    g = bf16(np.where(rng.random((n, n)) < 0.8, rng.uniform(-88.6, 0, (n, n)), rng.uniform(0, 20, (n, n))))
+    gd = g.double().numpy()
+    silu = gd / (1 + np.exp(-gd))
+    u = bf16(rng.choice([-1.0, 1.0], (n, n)) * rng.uniform(1, 2, (n, n)) *
+             np.exp2(rng.integers(-3, 4, (n, n)) - np.floor(np.log2(np.abs(silu) + 1e-300)).clip(-120, 120)))
+    cache = m.Cache(desc, 1)
+    W = torch.stack([g, u, torch.eye(n, dtype=torch.bfloat16)], dim=1)   # [unit][gate row, up row, down column][H]
+    cache.slot_tensor(0).copy_(W.reshape(-1).cuda())
+    cache.reset(1)
+    eam = torch.zeros((1, 1), dtype=torch.int32, device="cuda")
+    X = torch.eye(n, dtype=torch.bfloat16, device="cuda")
+    Y = m.moe_prefill_layer(cache, eam, 0, torch.zeros((1, n), dtype=torch.bfloat16, device="cuda"), None, X)
+    got = Y.cpu().numpy().astype(np.float64).T   # [unit][token], as the weights
+    exact = silu * u.double().numpy()
+    ends = np.stack([_round_bf16(exact * (1 - 3 * 2.0 ** -23)), _round_bf16(exact * (1 + 3 * 2.0 ** -23))])
+    wrong = (got != ends[0]) & (got != ends[1]) & (exact != 0)
+    assert not wrong.any(), (int(wrong.sum()), [(gd[i, j], exact[i, j], got[i, j]) for i, j in np.argwhere(wrong)[:5]])
+    cache.close()
+
+
 def test_prefill_edge_cases(m):
     cfg = mi.get_config("C2").scaled(L=2, H=256, I=64, N=8, prompt=16)
     desc = m.ModelDesc.from_config(cfg)
