@@ -167,6 +167,14 @@ def test_prefill_every_item_size_on_one_prompt(m, tile, monkeypatch):
     _check(_prefill_case(m, cfg, 9, layer=0))
 
 
+@pytest.mark.parametrize("tile", [64, 128, 256])
+def test_prefill_every_item_size_on_the_shortest_rows(m, tile, monkeypatch):
+    # H = 128: one slice of the kernels that stage through registers; a wish for 256-token items is met by 64
+    monkeypatch.setenv("MOEI_PREFILL_TILE", str(tile))
+    cfg = mi.get_config("C2").scaled(L=1, E=8, k=2, H=128, I=200, N=8, prompt=16)
+    _check(_prefill_case(m, cfg, 410, layer=0, sample=40))
+
+
 @pytest.mark.parametrize("E,k,n", [(40, 4, 1030), (100, 6, 1027), (160, 6, 1100), (256, 8, 1277)])
 def test_prefill_long_prompt_routing_over_expert_counts(m, E, k, n):
     # prompts of 512 tokens and more form their logits in the routing kernel that runs on the matrix
