@@ -451,9 +451,9 @@ def test_full_size_deepseek_v2_slice_steps(m):
     _replay(m, cfg, cfg.L * cfg.E, 1, 12, 2)
 
 
-# the heads of the orders from keys in LDS, from 4 and from 20 keys per lane, and read again each time; rows of
-# one and of several wavefronts' width
-@pytest.mark.parametrize("L,E", [(3, 700), (33, 62), (60, 170), (5, 2048)])
+# the heads of the orders from keys in LDS (up to 2,048 cells), from 20 keys per lane (up to 10,240), and read again
+# each time; rows of one and of several wavefronts' width
+@pytest.mark.parametrize("L,E", [(8, 256), (3, 700), (33, 62), (60, 170), (5, 2048), (65, 170), (6, 2048)])
 def test_heads_of_the_orders_over_many_cells(m, L, E):
     rng = np.random.default_rng(L * E)
     k, depth, H, I, N = 3, 5, 64, 8, 40
