@@ -81,7 +81,8 @@ def _prefill_case(m, cfg, n, layer, n_unique=None, resident=None, sample=None, n
     Y, idx, w = m.moe_prefill_layer(cache, d_eam, layer, dev(W), dev(req.bias[layer]), dev(X_dev), want_picks=True)
     torch.cuda.synchronize()
     ref_eam = eam0.astype(np.int64).copy()
-    expert_of = lambda f: split_expert(cfg, bank[f % n_unique])
+    none = np.zeros_like(bank[0])   # what an expert that is not resident contributes
+    expert_of = lambda f: split_expert(cfg, none if resident is not None and f >= resident else bank[f % n_unique])
     shared_of = lambda l: [split_expert(cfg, shared[l * cfg.n_shared + s]) for s in range(cfg.n_shared)]
     rows_y = None
     if sample is None:
@@ -139,6 +140,27 @@ def test_prefill_ragged_rows_and_small_expert_counts(m):
 def test_prefill_tiles_over_the_chip(m, E, k, n_shared, H, I, n):
     cfg = mi.get_config("C2").scaled(L=1, E=E, k=k, n_shared=n_shared, H=H, I=I, N=8, prompt=16)
     _check(_prefill_case(m, cfg, n, layer=0, sample=24))
+
+
+# long prompts (the persistent gate/up kernel, several tiles per workgroup) with experts that are not resident: their
+# items lie between the others', at the head of the list too, their tiles are passed over while the rings run on, and
+# their rows are zero; and with none resident at all
+@pytest.mark.parametrize("n_shared,H,I,resident", [(0, 512, 4160, 6), (0, 512, 4160, 12), (2, 512, 4160, 6), (2, 384, 1400, 12),
+                                                   (0, 512, 4160, 0)])
+def test_prefill_long_prompt_with_experts_that_are_not_resident(m, n_shared, H, I, resident):
+    cfg = mi.get_config("C2").scaled(L=1, E=24, k=3, n_shared=n_shared, H=H, I=I, N=8, prompt=16)
+    o = _prefill_case(m, cfg, 1300, layer=0, resident=resident, sample=40)
+    by_count = np.argsort(-np.bincount(o["ridx"].reshape(-1), minlength=24), kind="stable")
+    assert resident == 0 or (by_count[:8] < resident).any() and (by_count[:8] >= resident).any()
+    assert resident != 6 or by_count[0] >= resident     # the first items of the list are absent ones
+    assert o["flags"] & 2 and not o["flags"] & 4 and o["finite"]
+    assert (o["idx"] == o["ridx"]).all() and (o["eam"] == o["ream"]).all()
+    if resident == 0:
+        assert not o["Y"].any()
+        return
+    assert rel_max_err(o["Y"], o["rY"]) <= FFN_TOL_BF16_ACT
+    for t in range(o["Y"].shape[0]):
+        assert not o["rY"][t].any() and not o["Y"][t].any() or rel_max_err(o["Y"][t], o["rY"][t]) <= FFN_TOL, t
 
 
 def test_prefill_long_prompts_with_256_token_items(m):
