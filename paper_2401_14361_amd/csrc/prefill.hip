@@ -52,6 +52,7 @@ struct PItem {
     int32_t row0;       // the item's first row of the activation / contribution buffers
     int32_t first;      // position of the expert's first item in the list ...
     int32_t n;          // ... and how many it has: the items of an expert follow each other
+    int32_t last;       // tokens of the last of them (the others are full)
 };
 
 // ------------------------------------------------------------------ 1. routing of n tokens
@@ -254,13 +255,15 @@ __global__ void __launch_bounds__(kGrpThreads) prefill_group_kernel(GroupArgsP g
     const int tiles = (g.n + g.TM - 1) / g.TM;
     const int n_sh_items = g.n_shared * tiles;
     const int first = n_sh_items + ioff;
-    for (int it = tid; it * g.TM < cnt; it += kGrpThreads)
-        g.items[first + it] = PItem{slot, min(g.TM, cnt - it * g.TM), off + it * g.TM, -1, off + it * g.TM, first, (cnt + g.TM - 1) / g.TM};
+    const int n_it = (cnt + g.TM - 1) / g.TM;
+    for (int it = tid; it < n_it; it += kGrpThreads)
+        g.items[first + it] = PItem{slot, min(g.TM, cnt - it * g.TM), off + it * g.TM, -1, off + it * g.TM, first, n_it,
+                                    cnt - (n_it - 1) * g.TM};
     if (e == 0) {
         for (int q = tid; q < n_sh_items; q += kGrpThreads) {
             const int s = q / tiles, tile = q - s * tiles;
             g.items[q] = PItem{g.shared_base + s, min(g.TM, g.n - tile * g.TM), 0, tile * g.TM, g.n * g.k + s * g.n + tile * g.TM,
-                               s * tiles, tiles};
+                               s * tiles, tiles, g.n - (tiles - 1) * g.TM};
         }
         if (tid == 0) {
             g.meta[0] = n_routed + g.n_shared * tiles;
@@ -280,6 +283,7 @@ __global__ void __launch_bounds__(kGrpThreads) prefill_group_kernel(GroupArgsP g
 // w % 4 (16 units / 128 columns) for tokens 64 * (w / 4) .. + 64.
 constexpr int kTileTok = 64;      // tokens per item for short prompts: four 16-token blocks
 constexpr int kTileTokBig = 128;  // for long prompts
+constexpr int kTileTokWide = 256; // for long prompts, the _wide_ kernels
 constexpr int kGuUnits = 64;   // 3a: intermediate units per workgroup, 16 per wavefront
 constexpr int kGuKS = 128;     // 3a: k-slice of inputs and weight rows in LDS
 constexpr int kDnCols = 512;   // 3b: output columns per workgroup, 128 per wavefront
@@ -322,20 +326,30 @@ __device__ __forceinline__ bool xcd_work(int n_blocks, int* item, int* block) {
 // after the other in every unit block, block after block.  A tile's weights then pass through an L2 for
 // all of the expert's items at a time, if the workgroups that take neighbouring tiles run side by side on
 // one XCD: an XCD takes as many tiles in a row as it has compute units.  The list runs from the items
-// with the most tokens down, so every second XCD takes its tiles from the end: tiles that are bound by
-// their products and tiles that are bound by their weights run at the same time.  What is left for a last,
-// partly filled round is spread over the XCDs evenly.  Measured against items dealt to the XCDs whole, their
-// tiles in item order: 1,531 tokens of an 8-expert layer of 14,336 units (two items each) 1,305 -> 1,261
-// us a layer, kernel 925 -> 890 us; 512 and 2,048 tokens of the 64-expert shape the same.
-// Number of the w-th tile of an XCD (`total`: it has none).
-__device__ __forceinline__ int tile_of_xcd(int total, int xcd, int w, int cus) {
-    const int round = w / cus, done = round * kXcds * cus, left = total - done;
-    if (left >= kXcds * cus) {
-        const int full = total / (kXcds * cus) * kXcds, c = round * (kXcds / 2) + xcd / 2;
-        return (xcd % 2 ? full - 1 - c : c) * cus + w % cus;
+// with the most tokens down, so half of the XCDs take their tiles from the end: tiles that are bound by
+// their products and tiles that are bound by their weights run at the same time.  The halves change places
+// from round to round, and a last, partly filled round goes first to the XCDs that had one light round more and
+// there to the workgroups with the lightest tiles: dealt out by number alone the even XCDs had the heavy half
+// of the list, and the second tiles went to the workgroups with the heaviest first ones (67 experts of 448 units,
+// 1,053 tokens, 310 tiles: kernel 48.5 us, 34.5 dealt like this and without the waits named at tile_at and at
+// row_of_lanes; 34.0 with a workgroup per tile and no order at all).
+// Number of the tile that workgroup `me` of an XCD takes in round `round` of its tiles (`total`: none); `full`: rounds that
+// are full on all XCDs.
+__device__ __forceinline__ int tile_of_xcd(int total, int full, int xcd, int me, int round, int cus) {
+    const int half = xcd / 2, left = total - full * kXcds * cus;
+    if (round < full) {
+        const int c = round * (kXcds / 2) + half;
+        return ((xcd + round) % 2 ? full * kXcds - 1 - c : c) * cus + me;
     }
-    const int first = left * xcd / kXcds, t = first + w % cus;
-    return left > 0 && t < left * (xcd + 1) / kXcds ? done + t : total;
+    if (round > full) return total;
+    int b = left * xcd / kXcds, e = left * (xcd + 1) / kXcds;
+    if (full % 2) {
+        const int odd = min(left, kXcds / 2 * cus), rest = left - odd;
+        b = xcd % 2 ? odd * half / 4 : odd + rest * half / 4;
+        e = xcd % 2 ? odd * (half + 1) / 4 : odd + rest * (half + 1) / 4;
+    }
+    const int t = b + cus - 1 - me;
+    return t < e ? total - left + t : total;
 }
 // The wide down kernel runs an item whole on one XCD, position p of its order on XCD p % 8.  Item `tile` of
 // shared expert s is at position s + 8 * tile there: the items of a shared expert run on one XCD, several
@@ -350,26 +364,30 @@ __device__ __forceinline__ int item_at(const MmArgs& a, int p, int n_routed) {
 // Read-only tables are read through the constant address space: uniform loads that count on lgkmcnt, so
 // that waiting for them does not wait for a ring's loads.
 typedef const __attribute__((address_space(4))) int32_t* const_ints;
-static_assert(sizeof(PItem) == 28 && offsetof(PItem, row0) == 16 && offsetof(PItem, first) == 20 && offsetof(PItem, n) == 24,
+static_assert(sizeof(PItem) == 32 && offsetof(PItem, row0) == 16 && offsetof(PItem, first) == 20 && offsetof(PItem, n) == 24 &&
+                  offsetof(PItem, last) == 28,
               "tile_at reads an item as integers");
 struct Tile {
     int slot, ntok, list_off, first_tok, row0;
     int block;  // unit block
-    bool ok;    // false: there is no such tile
+    int ok;     // 0: there is no such tile
 };
-__device__ __forceinline__ Tile tile_at(const MmArgs& a, int n_items, int n_blocks, int t) {
-    Tile r{-1, 0, 0, -1, 0, 0, t < n_items * n_blocks};
+// One trip to memory: the expert's item that is found at the tile's place tells where the tile's own item is.  (Reading
+// that one too was a second trip a tile.)
+__device__ __forceinline__ Tile tile_at(const MmArgs& a, int total, int n_blocks, int t) {
+    Tile r{-1, 0, 0, -1, 0, 0, t < total};
     if (!r.ok) return r;  // uniform
-    const_ints it = (const_ints)(uintptr_t)(a.items + t / n_blocks);  // an item of the tile's expert
-    const int first = it[5], n = it[6];
-    const int q = t - first * n_blocks;
-    r.block = q / n;
-    it = (const_ints)(uintptr_t)(a.items + first + q % n);
+    const int p = t / n_blocks;
+    const_ints it = (const_ints)(uintptr_t)(a.items + p);
+    const int first = it[5], n = it[6], q = t - first * n_blocks;
+    r.block = n == 1 ? q : q / n;
+    const int i = q - r.block * n, ahead = (first + i - p) * kTileTokWide;
+    const bool routed = it[3] < 0;
     r.slot = it[0];
-    r.ntok = it[1];
-    r.list_off = it[2];
-    r.first_tok = it[3];
-    r.row0 = it[4];
+    r.ntok = i == n - 1 ? it[7] : kTileTokWide;
+    r.list_off = it[2] + (routed ? ahead : 0);
+    r.first_tok = routed ? -1 : it[3] + ahead;
+    r.row0 = it[4] + ahead;
     return r;
 }
 
@@ -535,17 +553,21 @@ __global__ void __launch_bounds__(TM * 4) prefill_gateup_kernel(MmArgs a) {
 // unit, and their rings run on from tile to tile; the tiles are dealt out evenly (see tile_of_xcd): with the
 // items of a list pinned to the XCDs one XCD had 99 tiles for its 32 compute units where 96 was the
 // average, a fourth round for everybody.  Measured (26-layer 64-expert shape, one layer): 512 tokens
-// 186 -> 158 us, 2,048 tokens 307 -> 290 us; two large items per XCD, 1,531 tokens of an 8-expert layer
-// of 14,336 units: 946 -> 925 us, and 890 with the tiles in the order of tile_of_xcd.  What is left there: with the loads taken out 587 us, with the matrix
+// 178 us with a workgroup per tile, 152 like this; 4,000 tokens 465 and 441; 1,531 tokens of an 8-expert
+// layer of 14,336 units: 946 and 890 us.  What is left there: with the loads taken out 587 us, with the matrix
 // instructions taken out 735 us.  (More stages in flight do not help: giving a stage's slots back half
 // a stage earlier, at the price of a second barrier, took 1,050 us.)
+// A workgroup has few tiles, often one, so what a tile costs besides its products counts as much as they
+// do: one trip to the cache each for its item, its list of tokens (into lanes at once, put_lanes) and its gate weights (a
+// block ahead, row_of_lanes).  With chains of trips there instead, prompts of one or two tiles a workgroup took
+// longer than with a workgroup per tile: 2,000 tokens of 4 experts of 8 units 26.6 us against 21.1, now 19.7; 738 tokens of 9
+// experts of 440 units, H = 2,688, 73.8 against 65.3, now 64.9; 1,024 tokens of 64 experts, H = 256, 61.6 against 50.2, now 40.9.
 // Chunk c of ring row r sits at chunk position c ^ ((r >> 1) % 8): the sixteen lanes that read one
 // operand (sixteen consecutive rows, the same chunk) then touch all 64 banks once.  A wavefront owns
 // 32 units (two 16-row blocks of gate, two of up) x 128 tokens (the even or the odd 16-token blocks of
 // the item, so that a partly filled item leaves both halves of the workgroup the same work; blocks
 // without tokens are neither read nor multiplied), 32 accumulator tiles, and multiplies a stage in two
 // halves of 32 k-values.
-constexpr int kTileTokWide = 256;
 constexpr int kWdUnits = 128;   // intermediate units per workgroup
 constexpr int kWdKS = 64;       // k-values per stage: 128 bytes of a row
 constexpr int kWdStagesW = 3;   // ring of weight stages
@@ -576,6 +598,32 @@ __device__ __forceinline__ const unsigned char* scalar_ptr(const void* p) {
     return reinterpret_cast<const unsigned char*>((uintptr_t)(((uint64_t)hi << 32) | lo));
 }
 
+// word i of eight uniform ones -> lane 8 * i + J.  (Written as a select by the lane's number the compiler made a branch of
+// each word, its load inside and waited for: 32 trips to the cache a tile, one after the other.)
+template <int J>
+__device__ __forceinline__ void put_lanes(int& v, const_ints w) {
+    asm("v_writelane_b32 %0, %1, %9\n\tv_writelane_b32 %0, %2, 8 + %9\n\tv_writelane_b32 %0, %3, 16 + %9\n\tv_writelane_b32 %0, %4, 24 + %9\n\t"
+        "v_writelane_b32 %0, %5, 32 + %9\n\tv_writelane_b32 %0, %6, 40 + %9\n\tv_writelane_b32 %0, %7, 48 + %9\n\tv_writelane_b32 %0, %8, 56 + %9\n\t"
+        "s_nop 3"
+        : "+v"(v)
+        : "s"(w[0]), "s"(w[1]), "s"(w[2]), "s"(w[3]), "s"(w[4]), "s"(w[5]), "s"(w[6]), "s"(w[7]), "n"(J));
+}
+// Sixteen uniform words -> word lane % 16 in every lane.  (A chain of selects by the lane's number takes three
+// instructions a word: a lane mask and one scalar operand are all that one of them may read.)
+__device__ __forceinline__ float row_of_lanes(const int* w) {
+    int v = w[0];
+    asm("v_writelane_b32 %0, %1, 1\n\tv_writelane_b32 %0, %2, 2\n\tv_writelane_b32 %0, %3, 3\n\tv_writelane_b32 %0, %4, 4\n\t"
+        "v_writelane_b32 %0, %5, 5\n\tv_writelane_b32 %0, %6, 6\n\tv_writelane_b32 %0, %7, 7\n\tv_writelane_b32 %0, %8, 8\n\t"
+        "v_writelane_b32 %0, %9, 9\n\tv_writelane_b32 %0, %10, 10\n\tv_writelane_b32 %0, %11, 11\n\tv_writelane_b32 %0, %12, 12\n\t"
+        "v_writelane_b32 %0, %13, 13\n\tv_writelane_b32 %0, %14, 14\n\tv_writelane_b32 %0, %15, 15\n\ts_nop 3"
+        : "+v"(v)
+        : "s"(w[1]), "s"(w[2]), "s"(w[3]), "s"(w[4]), "s"(w[5]), "s"(w[6]), "s"(w[7]), "s"(w[8]), "s"(w[9]), "s"(w[10]), "s"(w[11]),
+          "s"(w[12]), "s"(w[13]), "s"(w[14]), "s"(w[15]));
+    v = __builtin_amdgcn_permlane16_swap(v, v, false, false)[0];  // lanes 16..31 take lanes 0..15
+    v = __builtin_amdgcn_permlane32_swap(v, v, false, false)[0];  // lanes 32..63 take lanes 0..31
+    return __builtin_bit_cast(float, v);
+}
+
 __global__ void __launch_bounds__(kWdThreads, 2) prefill_gateup_wide_kernel(MmArgs a) {
     constexpr int TM = kTileTokWide;
     constexpr int NTB = TM / 32;  // 16-token blocks per wavefront: 8
@@ -590,14 +638,15 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_gateup_wide_kernel(MmAr
     const int rg = wv & 3, th = wv >> 2;  // unit group (32 units); the even or the odd 16-token blocks
     const int n_items = ((const_ints)(uintptr_t)a.meta)[0];
     const int n_slices = H / kWdKS;  // >= 4
-    int seq = 0;
-    auto next_tile = [&]() {  // items whose expert is not resident are passed over: the down kernel writes the zeros and raises the flag
-        Tile t;
-        do t = tile_at(a, n_items, a.n_ub, tile_of_xcd(n_items * a.n_ub, blockIdx.x % kXcds, blockIdx.x / kXcds + seq++ * a.cus, a.cus));
-        while (t.ok && (t.slot < 0 || t.slot >= a.n_slots_total));
-        return t;
+    const int total = n_items * a.n_ub, full = total / (kXcds * a.cus);
+    int round = 0;
+    auto next_tile = [&]() { return tile_at(a, total, a.n_ub, tile_of_xcd(total, full, blockIdx.x % kXcds, blockIdx.x / kXcds, round++, a.cus)); };
+    // items whose expert is not resident are passed over: the down kernel writes the zeros and raises the flag
+    auto resident = [&](Tile& t) {
+        while (t.ok && (t.slot < 0 || t.slot >= a.n_slots_total)) t = next_tile();
     };
     Tile cur = next_tile();
+    resident(cur);
     if (!cur.ok) return;
 
     // ---- loads: stage after stage of one tile, then on into the next tile
@@ -610,12 +659,15 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_gateup_wide_kernel(MmAr
     const uint32_t my_chunk = (uint32_t)((lane & 7) ^ ((my_row >> 1) & 7)) * 16;  // rows 64 apart share the swizzle key
     const uint32_t my_w = lds_address(ring_w) + (uint32_t)(8 * wv) * (kWdKS * 2), my_x = lds_address(ring_x) + (uint32_t)(8 * wv) * (kWdKS * 2);
     const unsigned char *base_w = nullptr, *base_x = nullptr;  // of the stage to be loaded next (uniform)
-    int unit_w = 0, slice_w = 0, put_w = 0;                    // first unit of the tile; next slice; its ring slot
-    int n_x = 0, toks = 0, slice_x = 0, put_x = 0;             // loads of a stage; lane l: token of row 64 * (l % 4) + 8 * wv + l / 8
+    // what a stage's loads are formed from, an addition or two each
+    uint32_t off_w = 0, off_x = 0;       // byte offset of this lane's first weight row; lane l: of the input row of row 64 * (l % 4) + 8 * wv + l / 8
+    int slice_w = 0, put_w = 0;          // next slice; its ring slot
+    int n_x = 0, slice_x = 0, put_x = 0; // loads of a stage
+    const uint32_t end_w = (uint32_t)(I - 1) * (uint32_t)(6 * H);  // the last unit's
     auto aim_w = [&](const Tile& t) {
         slice_w = 0;
         base_w = scalar_ptr(a.pool + (size_t)t.slot * a.slot_elems);
-        unit_w = t.block * kWdUnits;
+        off_w = (uint32_t)min(t.block * kWdUnits + my_row, I - 1) * (uint32_t)(6 * H);
     };
     auto aim_x = [&](const Tile& t) {
         slice_x = 0;
@@ -625,22 +677,23 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_gateup_wide_kernel(MmAr
         asm volatile("" : "+v"(at));  // the comparisons are made here, not kept as lane masks
         const int row = 64 * (at & 3) + 8 * wv + (at >> 3);
         if (t.first_tok >= 0) {
-            toks = t.first_tok + (row < t.ntok ? row : 0);
+            off_x = (uint32_t)(t.first_tok + (row < t.ntok ? row : 0)) * (uint32_t)(2 * H);
         } else {  // (the list is padded by a whole tile)
             const_ints pt = (const_ints)(uintptr_t)(a.perm + t.list_off);
             int v = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v = (at & 59) == 8 * i + j ? pt[64 * j + 8 * wv + i] : v;
-            toks = row < t.ntok ? v : pt[0];
+            put_lanes<0>(v, pt + 8 * wv);
+            put_lanes<1>(v, pt + 64 + 8 * wv);
+            put_lanes<2>(v, pt + 128 + 8 * wv);
+            put_lanes<3>(v, pt + 192 + 8 * wv);
+            v = __builtin_amdgcn_update_dpp(v, v, 0x114, 0xf, 0xa, false);  // row_shr:4 into lanes 8i + 4 .. 8i + 7
+            off_x = (uint32_t)(row < t.ntok ? v : pt[0]) * (uint32_t)(2 * H);
         }
     };
     auto issue_w = [&]() {
         const uint32_t st = my_w + (uint32_t)put_w * (kWdStageElems * 2);
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const uint32_t off = (uint32_t)min(unit_w + my_row + 64 * j, I - 1) * (uint32_t)(6 * H) + my_chunk;
+            const uint32_t off = (j == 0 ? off_w : min(off_w + (uint32_t)(64 * 6 * H), end_w)) + my_chunk;
             load16_to_lds_at(base_w, off, st + (uint32_t)(64 * j) * (kWdKS * 2));
             load16_to_lds_at(base_w + 2 * H, off, st + (uint32_t)(64 * j + kWdUnits) * (kWdKS * 2));
         }
@@ -648,24 +701,32 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_gateup_wide_kernel(MmAr
         if (++put_w == kWdStagesW) put_w = 0;
         ++slice_w;
     };
+    auto load_x = [&](uint32_t st, auto j_tag) {
+        constexpr int j = decltype(j_tag)::value;  // quad_perm [j,j,j,j]: lane j of every four holds load j's row
+        const uint32_t row = (uint32_t)__builtin_amdgcn_mov_dpp((int)off_x, 0x55 * j, 0xf, 0xf, true);
+        load16_to_lds_at(base_x, row + my_chunk, st + (uint32_t)(64 * j) * (kWdKS * 2));
+    };
     auto issue_x = [&]() {
         const uint32_t st = my_x + (uint32_t)put_x * (kWdStageElems * 2);
-        count_down<3>([&](auto r_tag) {
-            constexpr int j = 3 - decltype(r_tag)::value;
-            const uint32_t tok = MOEI_DPP_U32(toks, 0x55 * j);  // quad_perm [j,j,j,j]: lane j of every four holds load j's token
-            if (j < n_x) load16_to_lds_at(base_x, tok * (uint32_t)(2 * H) + my_chunk, st + (uint32_t)(64 * j) * (kWdKS * 2));
-        });
+        if (n_x == 4) {  // no branch between the loads
+            count_down<3>([&](auto r_tag) { load_x(st, std::integral_constant<int, 3 - decltype(r_tag)::value>{}); });
+        } else {
+            count_down<2>([&](auto r_tag) {
+                constexpr int j = 2 - decltype(r_tag)::value;
+                if (j < n_x) load_x(st, std::integral_constant<int, j>{});
+            });
+        }
         base_x += kWdKS * 2;
         if (++put_x == kWdStagesX) put_x = 0;
         ++slice_x;
     };
     static_assert(kWdStagesX == 2 && kWdStagesW == 3, "one stage of inputs and two of weights are on their way");
-    aim_x(cur);
     aim_w(cur);
+    issue_w();  // on its way while the list of tokens is read
+    aim_x(cur);
     issue_x();
     issue_w();
-    issue_w();
-    Tile nxt = next_tile();
+    Tile nxt = next_tile();  // (looked at in a tile's second stage: by then its words have arrived)
     bool more_w = true;  // the weights of the stage after the one entered next are on their way
     // Enters the next stage: it has landed for all once every wavefront has seen its loads of it
     // complete and the barrier is passed; by then every wavefront has read the stage before it, whose
@@ -747,16 +808,28 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_gateup_wide_kernel(MmAr
                 read_ops(0, opA, nt_tag);
                 multiply(opB, d, nt_tag);
             }
+            if (s == 1) resident(nxt);  // (first needed when the last stage but one is entered; there are at least four)
         }
         if constexpr (NT > 0) {
             read_ops(1, opB, nt_tag);
             multiply(opA, d, nt_tag);
         }
+        // Gate weights of a block of sixteen tokens, asked for one block ahead (the buffer is padded to a whole block; a
+        // shared expert's tokens have none, what is read is not used)
+        int g16[16];
+        auto ask_gates = [&](int tb) {
+            const_ints pg = (const_ints)(uintptr_t)(a.pgate + cur.list_off + min((2 * tb + th) * 16, (cur.ntok - 1) & ~15));
+#pragma unroll
+            for (int i = 0; i < 16; ++i) g16[i] = pg[i];
+        };
         if (nxt.ok) {  // the next tile's first stage, while this one's last products and its activations are formed
             enter();
             step_slots();
         }
-        if constexpr (NT > 0) multiply(opB, d, nt_tag);
+        if constexpr (NT > 0) {
+            ask_gates(0);
+            multiply(opB, d, nt_tag);
+        }
         // D[unit 4*lgrp + v][token lrow] -> activation, bf16, act[row][unit]
         const bool packed = (I & 3) == 0;
         const int u_wg = cur.block * kWdUnits;
@@ -765,17 +838,12 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_gateup_wide_kernel(MmAr
             __builtin_amdgcn_sched_barrier(0);  // one block at a time: the registers hold no more
             const int t0 = (2 * tb + th) * 16;
             if (t0 >= cur.ntok) continue;  // uniform
+            const float gw = cur.first_tok < 0 ? row_of_lanes(g16) : 1.0f;
+            if (tb + 1 < NT) ask_gates(tb + 1);
+            __builtin_amdgcn_sched_barrier(0);
             int at = lrow;
-            asm volatile("" : "+v"(at));  // formed here, not kept (nor sixteen lane masks) through the loop
+            asm volatile("" : "+v"(at));  // formed here, not kept through the loop
             const int tok = t0 + at;
-            float gw = 1.0f;
-            if (cur.first_tok < 0) {  // sixteen gate weights in a row (the buffer is padded to a whole block)
-                const_ints pg = (const_ints)(uintptr_t)(a.pgate + cur.list_off + t0);
-                int g = 0;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) g = at == i ? pg[i] : g;
-                gw = __builtin_bit_cast(float, g);
-            }
             if (tok >= cur.ntok) continue;
             uint16_t* dst_row = a.act + (size_t)(cur.row0 + tok) * I;
 #pragma unroll
@@ -1356,7 +1424,7 @@ int tile_tokens(const moei_model_desc& d, int n) {
     // the wide gate/up kernel looks up to three stages ahead and forms 32-bit offsets into an expert.  Nothing is
     // lost on the shorter rows: H = 128, 64 experts of 6,144 units, 1,000 tokens 372 us a layer with 64-token items
     // (4,000 tokens 874) against 420 (968) with a kernel of 256-token items that took them
-    if (d.H < 4 * kWdKS || (uint64_t)6 * d.H * d.I > 0xffffffffull) return kTileTok;
+    if (d.H < 4 * kWdKS || (uint64_t)6 * d.H * (d.I + 64) > 0xffffffffull) return kTileTok;
     if (v && atoi(v) == kTileTokWide) return kTileTokWide;
     return (long)n * d.k >= (long)48 * d.E ? kTileTokWide : kTileTok;
 }

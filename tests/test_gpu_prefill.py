@@ -133,10 +133,11 @@ def test_prefill_ragged_rows_and_small_expert_counts(m):
 
 
 # the persistent gate/up kernel: fewer items than XCDs, one tile in all (no next tile, a partly filled item), several
-# tiles per workgroup with a ragged last one, the fewest stages it takes (H = 256); a prompt (17 tokens) and rows
-# (H = 128) too short for it
+# tiles per workgroup with a ragged last one, the fewest stages it takes (H = 256); one and three full rounds of tiles
+# before a last one that some or all of the XCDs share; a prompt (17 tokens) and rows (H = 128) too short for it
 @pytest.mark.parametrize("E,k,n_shared,H,I,n", [(1, 1, 0, 256, 8, 300), (1, 1, 0, 256, 128, 49), (1, 1, 0, 256, 128, 17),
-                                                (4, 2, 1, 128, 136, 500), (9, 2, 0, 256, 6200, 600), (24, 3, 2, 384, 1416, 1300)])
+                                                (4, 2, 1, 128, 136, 500), (9, 2, 0, 256, 6200, 600), (24, 3, 2, 384, 1416, 1300),
+                                                (16, 2, 0, 256, 2168, 800), (24, 3, 2, 256, 3000, 1300), (2, 2, 2, 384, 2048, 2000)])
 def test_prefill_tiles_over_the_chip(m, E, k, n_shared, H, I, n):
     cfg = mi.get_config("C2").scaled(L=1, E=E, k=k, n_shared=n_shared, H=H, I=I, N=8, prompt=16)
     _check(_prefill_case(m, cfg, n, layer=0, sample=24))
