@@ -445,6 +445,7 @@ __global__ void __launch_bounds__(TM * 4) prefill_gateup_kernel(MmArgs a) {
     if (item >= a.meta[0]) return;
     const PItem it = a.items[item];
     if (it.slot < 0 || it.slot >= a.n_slots_total) return;  // the down kernel writes the zeros and raises the flag
+    const bool once = it.n == 1;  // the expert has no other item: its weights are read once (non-temporal loads)
     const int H = a.H, I = a.I;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -476,11 +477,12 @@ __global__ void __launch_bounds__(TM * 4) prefill_gateup_kernel(MmArgs a) {
     const int n_slices = (H + kGuKS - 1) / kGuKS;
     uint4 xst[NX], wst[NW];
     auto fetch = [&](int s) {
+        if (once) {  // one branch for all of them (H is a whole number of slices)
 #pragma unroll
-        for (int j = 0; j < NW; ++j) {
-            const int kk = s * kGuKS + ((tid + kMmThreads * j) % VPR) * 8;
-            wst[j] = kk < H ? (it.n == 1 ? load_once_16(wsrc[j] + s * kGuKS) : *reinterpret_cast<const uint4*>(wsrc[j] + s * kGuKS))
-                            : make_uint4(0, 0, 0, 0);
+            for (int j = 0; j < NW; ++j) wst[j] = load_once_16(wsrc[j] + s * kGuKS);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NW; ++j) wst[j] = *reinterpret_cast<const uint4*>(wsrc[j] + s * kGuKS);
         }
 #pragma unroll
         for (int j = 0; j < NX; ++j) {
@@ -884,6 +886,7 @@ __global__ void __launch_bounds__(TM * 4, 2) prefill_down_kernel(MmArgs a) {  //
     it.row0 += part * TM;  // this workgroup's TM tokens of the item
     it.ntok = min(TM, it.ntok - part * TM);
     if (it.ntok <= 0) return;
+    const bool once = it.n == 1;  // the expert has no other item: its weights are read once (non-temporal loads)
     const int H = a.H, I = a.I;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -924,10 +927,14 @@ __global__ void __launch_bounds__(TM * 4, 2) prefill_down_kernel(MmArgs a) {  //
         for (int j = 0; j < NV; ++j) *reinterpret_cast<uint4*>(dst + (size_t)RPJ * j * kTileK) = stage[j];
     };
     auto load_w = [&](int k0, uint4* dst) {  // units k0 + 8*lgrp + j (clamped: their activations are zero)
+        auto row = [&](int j) { return wd + (size_t)min(k0 + lgrp * 8 + j, I - 1) * 3 * H; };
+        if (once) {  // one branch for the eight of them
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            dst[j] = it.n == 1 ? load_once_16(wd + (size_t)min(k0 + lgrp * 8 + j, I - 1) * 3 * H)
-                            : *reinterpret_cast<const uint4*>(wd + (size_t)min(k0 + lgrp * 8 + j, I - 1) * 3 * H);
+            for (int j = 0; j < 8; ++j) dst[j] = load_once_16(row(j));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) dst[j] = *reinterpret_cast<const uint4*>(row(j));
+        }
     };
 
     f32x4 Y[4][8];
