@@ -56,8 +56,9 @@ def test_topm_shapes_ties_and_short_collections(m, N, L, E, cell_bytes):
     _check_topm(m, T, q, cell_bytes, (1, 2, 5, 16))
 
 
-# winners of many workgroups: up to 256 of them are ranked at once, more are cut down first, over 1,024 twice
-@pytest.mark.parametrize("N,mm", [(16 * 1024, 16), (16 * 1024 + 1, 16), (65 * 1024, 16), (33 * 1024 - 5, 8)])
+# winners of many workgroups: up to 256 of them are ranked at once, more are cut down first, over 1,024 twice; one
+# trace comes from the kernel of the plain match
+@pytest.mark.parametrize("N,mm", [(16 * 1024, 16), (16 * 1024 + 1, 16), (65 * 1024, 16), (33 * 1024 - 5, 8), (65 * 1024, 1), (0, 1), (0, 3)])
 def test_topm_winners_of_many_workgroups(m, N, mm):
     rng = np.random.default_rng(N)
     T = rng.integers(0, 50, size=(N, 1, 4)).astype(np.int32)   # small counts: many exact and many close similarities
