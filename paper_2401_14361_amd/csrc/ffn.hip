@@ -69,8 +69,8 @@ __device__ __forceinline__ void block_sum_rows(float* yp, int H, int row, int wa
 // LDS = x (NCH chunks of floats) + ygroup y rows of that length.
 // TAIL: H is any multiple of 16 bytes of up to NCH chunks.  The lanes past the end of the last chunk
 // read its first piece (the same for all of them) and add nothing, so a row costs what its chunks cost.
-// (The kernel for any H below reads two or four bytes a lane and keeps its sums in LDS: with H = 1,792 a token of
-// seven layers, four experts of 910 units each, took 958 us with it and takes 165 us.)
+// (The kernel for any H below reads two or four bytes a lane and keeps its sums in LDS: a call of four experts of
+// 910 units, H = 1,792, takes 59.6 us with it and 17.4 with this one; eight of 301, H = 2,880, 90.7 and 16.4.)
 template <int NCH>
 struct StreamShape {
     static constexpr int kSteps = 3 * NCH;
@@ -662,8 +662,10 @@ struct GroupedShape {
 // weights take); workgroup g takes the contiguous range [total*g/G, total*(g+1)/G).  A range crosses at
 // most ceil(n_items / G) item boundaries, so it is cut into at most that many + 1 segments, each
 // inside one item; a segment yields one partial y row per token of the item.
-// (With even shares of the units alone the workgroups that change items ended last: a layer step of three
-// requests over 10,000 traces took 125.3 us, now 121.9; of sixteen, bound by the 934 MB it streams, 251.)
+// (With even shares of the units alone the workgroups that change items ended last.  A call of 2 / 3 / 4 / 8 requests of
+// the 64-expert shape (1,408 units, two shared experts) took 49.8 / 65.9 / 81.8 / 125.7 us, now 48.5 / 63.9 / 80.2 / 124.1; of
+// sixteen, 54 items that leave few workgroups in one of them alone, 181.8 either way.  Shorter items gain more: 1 / 3 / 8 / 16
+// requests of 32 experts of 700 units, H = 1,024, 17.3 / 23.1 / 35.6 / 42.7 and 14.9 / 21.0 / 32.0 / 40.0.)
 // Where the items divide the workgroups nobody changes items and every share is the same as it is: there a
 // start counts nothing (one request, 8 items: 34.4 us with it, 33.5 without).
 __device__ __host__ inline long grouped_range_begin(long total, int g, int G) { return total * g / G; }

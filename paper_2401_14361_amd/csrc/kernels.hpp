@@ -66,7 +66,7 @@ struct PrefillScratch {
     int n_max = 0;              // tokens the buffers are sized for
     int32_t* d_idx = nullptr;   // [n_max][k] picks
     float* d_w = nullptr;       // [n_max][k] gate weights
-    int32_t* d_perm = nullptr;  // [n_max*k] tokens grouped per expert
+    int32_t* d_perm = nullptr;  // [n_max*k + 256] tokens grouped per expert
     float* d_pgate = nullptr;   // [n_max*k + 16] their gate weights
     int32_t* d_where = nullptr;  // [n_max*k] row of every (token, pick)
     void* d_items = nullptr;

@@ -1007,7 +1007,7 @@ __device__ __forceinline__ void block_top(TopLds& t, int count, int m, Emit emit
 // grid (workgroups over traces): each workgroup finds the m best of its 1024 traces; the last
 // workgroup to arrive finds the m best of all winners.  A chain of dependent steps on few compute
 // units: m rounds of a workgroup-wide exact arg-max (two barriers and two chains of exchanges
-// each, twice over) took 39.7 us at 10,000 traces and m = 8, ranking takes 16.0 us.
+// each, twice over) took 39.7 us at 10,000 traces and m = 8, ranking takes 15.3 us.
 // SCORE: the finishing workgroup also scores the aggregate of the m traces.
 template <bool SCORE>
 __global__ void __launch_bounds__(kPickThreads) eamc_topm_kernel(TopmArgs a) {

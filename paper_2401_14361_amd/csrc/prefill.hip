@@ -1421,9 +1421,11 @@ namespace {
 int max_items_for(const moei_model_desc& d, int n, int tm) {
     return (n * d.k + tm - 1) / tm + d.E + d.n_shared * ((n + tm - 1) / tm);
 }
-// tokens per item: the wide kernels' 256 once the average expert holds 48 tokens (measured on the
-// 64-expert top-6 shape: 256 tokens 279 us per layer with 64-token items against 288 us, 512 tokens
-// 330 against 325, 1,024 tokens 488 against 405)
+// tokens per item: the wide kernels' 256 once the average expert holds 48 tokens, which is where their first form
+// became the faster one on the 64-expert top-6 shape.  Their present form does so at 33 there (us a layer with 64- and with
+// 256-token items, 24 / 32 / 40 / 48 / 96 tokens an expert: 252 / 263 / 282 / 292 / 417 and 261 / 264 / 268 / 277 / 332), and
+// below 16 for other shapes (16 tokens an expert: the same with H = 1,024 154 and 132, H = 4,096 453 and 432; 8 experts of
+// 14,336 units, H = 4,096, 921 and 570): the line could be lower for them, most of all with few experts.
 int tile_tokens(const moei_model_desc& d, int n) {
     const char* v = getenv("MOEI_PREFILL_TILE");
     if (v && atoi(v) == kTileTok) return kTileTok;
