@@ -777,9 +777,9 @@ __device__ __forceinline__ Best block_pick(Best me, u64* s_dot, u64* s_nt, int* 
 // grid (workgroups over traces, B): sums the layer-split partial dots, writes similarities,
 // picks the workgroup's best trace; the last workgroup to arrive picks among the winners.
 // SCORE: the finishing workgroup also scores the matched trace (B = 1).  A search alone has a kernel of
-// its own: with the scoring in it 97 scalar registers were spilled, and a match over 10,000 traces took
+// its own: with the scoring in it scalar registers were spilled, and a match over 10,000 traces took
 // 22.8 us for one query and 26.7 for eight instead of 22.1 and 25.8.
-template <bool SCORE>
+template <Scoring SCORE>
 __global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) {
     __shared__ u64 s_dot[kPickWaves];
     __shared__ u64 s_nt[kPickWaves];
@@ -831,8 +831,7 @@ __global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) {
     Best r = block_pick(me, s_dot, s_nt, s_idx);
     __shared__ int s_sn[2];
     __shared__ int s_best[kMaxMatchBatch];
-    __shared__ std::conditional_t<SCORE, HeadLds, char> s_heads;
-    __shared__ std::conditional_t<SCORE, KeyLds, char> s_keys;
+    __shared__ std::conditional_t<SCORE == Scoring::none, char, ScoreLds<SCORE == Scoring::large>> s_score;
     if (gridDim.x == 1) {
         if (tid == 0) {
             a.best[b] = r.idx;
@@ -840,39 +839,37 @@ __global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) {
             if (a.best_sim) a.best_sim[b] = r.idx >= 0 ? (float)cosine(r.dot, nq, r.nt) : 0.f;
             s_best[0] = r.idx;
         }
-        if constexpr (SCORE) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best);
-        return;
-    }
-    // several workgroups: publish this one's winner, the last to arrive finishes
-    const size_t cbase = (size_t)b * gridDim.x;
-    if (tid == 0) {
-        a.cand[(cbase + blockIdx.x) * 2] = r.dot;
-        a.cand[(cbase + blockIdx.x) * 2 + 1] = r.nt;
-        a.cand_idx[cbase + blockIdx.x] = r.idx;
-        __threadfence();
-        s_ticket = __hip_atomic_fetch_add(&a.ticket[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (s_ticket != gridDim.x - 1) return;
-    if (tid == 0) __threadfence();  // one acquire for the workgroup (the winners are read past the caches anyway)
-    __syncthreads();
-    Best fin = make_best(0, 1, -1);
-    for (int i = tid; i < (int)gridDim.x; i += kPickThreads) {
-        const int idx = __hip_atomic_load(&a.cand_idx[cbase + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (idx >= 0) {
-            const u64 d = __hip_atomic_load(&a.cand[(cbase + i) * 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const u64 t = __hip_atomic_load(&a.cand[(cbase + i) * 2 + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            fin = pick(fin, make_best(d, t, idx));
+    } else {  // several workgroups: publish this one's winner, the last to arrive finishes
+        const size_t cbase = (size_t)b * gridDim.x;
+        if (tid == 0) {
+            a.cand[(cbase + blockIdx.x) * 2] = r.dot;
+            a.cand[(cbase + blockIdx.x) * 2 + 1] = r.nt;
+            a.cand_idx[cbase + blockIdx.x] = r.idx;
+            __threadfence();
+            s_ticket = __hip_atomic_fetch_add(&a.ticket[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (s_ticket != gridDim.x - 1) return;
+        if (tid == 0) __threadfence();  // one acquire for the workgroup (the winners are read past the caches anyway)
+        __syncthreads();
+        Best fin = make_best(0, 1, -1);
+        for (int i = tid; i < (int)gridDim.x; i += kPickThreads) {
+            const int idx = __hip_atomic_load(&a.cand_idx[cbase + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (idx >= 0) {
+                const u64 d = __hip_atomic_load(&a.cand[(cbase + i) * 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const u64 t = __hip_atomic_load(&a.cand[(cbase + i) * 2 + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                fin = pick(fin, make_best(d, t, idx));
+            }
+        }
+        fin = block_pick(fin, s_dot, s_nt, s_idx);
+        if (tid == 0) {
+            a.best[b] = fin.idx;
+            if (a.best_sim) a.best_sim[b] = fin.idx >= 0 ? (float)cosine(fin.dot, nq, fin.nt) : 0.f;
+            a.ticket[b] = 0;  // ready for the next launch on this stream
+            s_best[0] = fin.idx;
         }
     }
-    fin = block_pick(fin, s_dot, s_nt, s_idx);
-    if (tid == 0) {
-        a.best[b] = fin.idx;
-        if (a.best_sim) a.best_sim[b] = fin.idx >= 0 ? (float)cosine(fin.dot, nq, fin.nt) : 0.f;
-        a.ticket[b] = 0;  // ready for the next launch on this stream
-        s_best[0] = fin.idx;
-    }
-    if constexpr (SCORE) score_and_heads(a.sc, s_heads, s_keys, s_sn, s_best);
+    if constexpr (SCORE != Scoring::none) score_and_heads<SCORE == Scoring::large>(a.sc, s_score, s_sn, s_best);
 }
 
 // ---- the m most similar traces of ONE query, most similar first (ties: lowest index)
@@ -1009,7 +1006,7 @@ __device__ __forceinline__ void block_top(TopLds& t, int count, int m, Emit emit
 // units: m rounds of a workgroup-wide exact arg-max (two barriers and two chains of exchanges
 // each, twice over) took 39.7 us at 10,000 traces and m = 8, ranking takes 15.3 us.
 // SCORE: the finishing workgroup also scores the aggregate of the m traces.
-template <bool SCORE>
+template <Scoring SCORE>
 __global__ void __launch_bounds__(kPickThreads) eamc_topm_kernel(TopmArgs a) {
     __shared__ u64 s_red[kPickWaves];
     __shared__ u64 s_nq;
@@ -1018,13 +1015,9 @@ __global__ void __launch_bounds__(kPickThreads) eamc_topm_kernel(TopmArgs a) {
     __shared__ int s_best[kMaxMatchBatch];
     __shared__ u64 s_wdot[kTopmMax], s_wnt[kTopmMax];
     __shared__ int s_widx[kTopmMax];
-    struct Scoring {
-        HeadLds heads;
-        KeyLds keys;
-    };
-    __shared__ __align__(16) unsigned char s_mem[sizeof(TopLds) > sizeof(Scoring) ? sizeof(TopLds) : sizeof(Scoring)];
-    TopLds& s_top = *reinterpret_cast<TopLds*>(s_mem);        // the search ...
-    Scoring& s_score = *reinterpret_cast<Scoring*>(s_mem);    // ... then the scoring
+    using Lds = std::conditional_t<SCORE == Scoring::none, char, ScoreLds<SCORE == Scoring::large>>;
+    __shared__ __align__(16) unsigned char s_mem[sizeof(TopLds) > sizeof(Lds) ? sizeof(TopLds) : sizeof(Lds)];
+    TopLds& s_top = *reinterpret_cast<TopLds*>(s_mem);  // the search, then the scoring
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wv = tid / kWave;
     const bool single = gridDim.x == 1;
@@ -1121,9 +1114,9 @@ __global__ void __launch_bounds__(kPickThreads) eamc_topm_kernel(TopmArgs a) {
         block_top(s_top, count, a.m, finish);
         if (tid == 0) *a.ticket = 0;  // ready for the next launch on this stream
     }
-    if constexpr (SCORE) {
+    if constexpr (SCORE != Scoring::none) {
         __syncthreads();  // the matched traces are in LDS; the search's LDS is free
-        score_and_heads(a.sc, s_score.heads, s_score.keys, s_sn, s_best);
+        score_and_heads<SCORE == Scoring::large>(a.sc, *reinterpret_cast<Lds*>(s_mem), s_sn, s_best);
     }
 }
 
@@ -1559,7 +1552,9 @@ int launch_match(const moei_eamc* c, const int32_t* d_eam, int B, int layer_hi, 
     const int n_blk = c->N > 0 ? (c->N + kPickChunk - 1) / kPickChunk : 1;
     PickArgs pa{c->d_part, c->d_norm2, d_eam, n_lsplit, c->n_cap, c->N, L * E, c->d_cand, c->d_cand_idx,
                 c->d_ticket, d_best, d_best_sim, d_sims, score ? *score : ScoreArgs{}};
-    launch(K_MATCH_ARGMAX, score ? eamc_pick_kernel<true> : eamc_pick_kernel<false>, dim3(n_blk, B), dim3(kPickThreads), 0, s, pa);
+    launch(K_MATCH_ARGMAX,
+           !score ? eamc_pick_kernel<Scoring::none> : L * E <= kKeyLdsCells ? eamc_pick_kernel<Scoring::small> : eamc_pick_kernel<Scoring::large>,
+           dim3(n_blk, B), dim3(kPickThreads), 0, s, pa);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
 }
@@ -1580,7 +1575,9 @@ int launch_match_topm(const moei_eamc* c, const int32_t* d_eam, int layer_hi, in
     if (rc) return rc;
     TopmArgs ta{c->d_part, c->d_norm2, d_eam, n_lsplit, c->n_cap, c->N, L * E, m, c->d_cand, c->d_cand_idx,
                 c->d_ticket, d_top, d_top_sim, d_sims, score ? *score : ScoreArgs{}};
-    launch(K_MATCH_ARGMAX, score ? eamc_topm_kernel<true> : eamc_topm_kernel<false>, dim3(n_blk), dim3(kPickThreads), 0, s, ta);
+    launch(K_MATCH_ARGMAX,
+           !score ? eamc_topm_kernel<Scoring::none> : L * E <= kKeyLdsCells ? eamc_topm_kernel<Scoring::small> : eamc_topm_kernel<Scoring::large>,
+           dim3(n_blk), dim3(kPickThreads), 0, s, ta);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
 }

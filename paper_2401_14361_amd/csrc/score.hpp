@@ -2,6 +2,8 @@
 // match (fused layer step).
 #pragma once
 
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace moei {
@@ -49,8 +51,11 @@ __device__ __forceinline__ uint32_t cell_at(const void* traces, int cell_bytes, 
                            : (uint32_t) reinterpret_cast<const uint16_t*>(traces)[i];
 }
 
-// A copy of the keys in LDS for the head selection (models of up to kKeyLdsCells cells): the
-// selection then needs no second trip to memory.
+// What the workgroup that finishes a match does besides: nothing, or the scoring of a model of up to / of more than
+// kKeyLdsCells cells.
+enum class Scoring { none, small, large };
+// Models of up to kKeyLdsCells cells (LARGE = false) keep a copy of the keys in LDS for the head selection, which
+// then needs no second trip to memory.
 constexpr int kKeyLdsCells = 2048;
 struct KeyLds {
     u64 k[2][kKeyLdsCells];
@@ -58,9 +63,10 @@ struct KeyLds {
 
 // Called by all kScoreThreads threads of ONE workgroup: scores for every cell, a 64-bit sort
 // key per cell and list (kNone where the cell is not a candidate) and the two candidate
-// counts.  One wavefront per layer row, two of its rows on their way at a time (the trip to the
+// counts.  One wavefront per layer row, the next row's loads out before a row is scored (the trip to the
 // matched cells is what a row costs, and beside the streaming FFN it is a long one).  s_n[2] and
 // s_best[kMaxMatchBatch] are LDS; the caller has put the matched trace indices (-1 = none) into s_best.
+template <bool LARGE>
 __device__ __forceinline__ void score_cells(const ScoreArgs& a, int* s_n, const int* s_best, u64* kp, u64* kv,
                                             KeyLds* lds_keys) {
     const int tid = threadIdx.x;
@@ -84,19 +90,28 @@ __device__ __forceinline__ void score_cells(const ScoreArgs& a, int* s_n, const 
         }
         return t;
     };
-    // all of a row's loads go out together: matched cells, residency, current picks
+    // all of a row's loads go out together: current picks, residency, matched cells (these last: their sum over
+    // the traces is waited for)
     auto load_row = [&](int i, Row& w) {
+        w.cur = -1;
+        if (i == l && lane < a.n_cur) w.cur = a.cur_idx[lane];
+#pragma unroll
+        for (int r = 0; r < kPerLane; ++r) {
+            const int j = lane + r * kWave;
+            w.sv[r] = -1;
+            if (r * kWave < E && j < E) w.sv[r] = a.slot_of[(size_t)i * E + j];
+        }
         w.rsum = 0;
 #pragma unroll
         for (int r = 0; r < kPerLane; ++r) {
             const int j = lane + r * kWave;
-            w.tv[r] = j < E ? cell_sum(i, j) : 0;
-            w.sv[r] = j < E ? a.slot_of[(size_t)i * E + j] : -1;
-            w.rsum += w.tv[r];
+            w.tv[r] = 0;
+            if (r * kWave < E) {  // uniform
+                if (j < E) w.tv[r] = cell_sum(i, j);
+                w.rsum += w.tv[r];
+            }
         }
         for (int j = lane + kPerLane * kWave; j < E; j += kWave) w.rsum += cell_sum(i, j);
-        w.cur = -1;
-        if (i == l && lane < a.n_cur) w.cur = a.cur_idx[lane];
     };
     auto score_row = [&](int i, const Row& w) {
         const u64 R = wave_sum_u64_dpp(w.rsum);
@@ -128,7 +143,7 @@ __device__ __forceinline__ void score_cells(const ScoreArgs& a, int* s_n, const 
             const u64 key_v = is_ev ? (u64)__double_as_longlong(v) : kNone;
             kp[f] = key_p;
             kv[f] = key_v;
-            if (lds_keys) {
+            if constexpr (!LARGE) {
                 lds_keys->k[0][f] = key_p;
                 lds_keys->k[1][f] = key_v;
             }
@@ -144,12 +159,12 @@ __device__ __forceinline__ void score_cells(const ScoreArgs& a, int* s_n, const 
         }
     };
     constexpr int kWaves = kScoreThreads / kWave;
-    for (int i = wv; i < L; i += 2 * kWaves) {
-        Row w0, w1;
-        load_row(i, w0);
-        if (i + kWaves < L) load_row(i + kWaves, w1);
-        score_row(i, w0);
-        if (i + kWaves < L) score_row(i + kWaves, w1);
+    Row row;
+    for (int i = wv - kWaves; i < L; i += kWaves) {  // (the code of a row stands here once)
+        Row next;
+        if (i + kWaves < L) load_row(i + kWaves, next);
+        if (i >= 0) score_row(i, row);
+        row = next;
     }
     if (my_pf) atomicAdd(&s_n[0], my_pf);
     if (my_ev) atomicAdd(&s_n[1], my_ev);
@@ -206,27 +221,34 @@ __device__ __forceinline__ KeyId wave_keyid_min(KeyId v) {
     return KeyId{((u64)mh << 32) | ml, (int)mi};
 }
 
-constexpr int kSelWaves = 8;                     // wavefronts that search one list: half of the workgroup
-constexpr int kSelThreads = kSelWaves * kWave;
-constexpr int kSelOwnSmall = 4;                  // keys a lane keeps in registers (models of up to 2,048 cells) ...
-constexpr int kSelOwnLarge = 20;                 // ... and of up to 10,240 cells
+// Wavefronts that search one list, and keys a lane keeps in registers: up to kKeyLdsCells cells four (one per SIMD) and 8;
+// up to 10,240 cells eight (half of the workgroup) and 20.  See select_heads.
+template <bool LARGE>
+struct Sel {
+    static constexpr int kWaves = LARGE ? 8 : 4;
+    static constexpr int kThreads = kWaves * kWave;
+    static constexpr int kOwn = LARGE ? 20 : 8;
+};
 constexpr int kHeadMax = 96;                     // most entries of a head (picks + prefetch candidates)
-static_assert(2 * kSelThreads == kScoreThreads, "both lists are searched at once");
-struct HeadLds {
-    u64 key[2][kSelWaves][kHeadMax];
-    int id[2][kSelWaves][kHeadMax];
+static_assert(2 * Sel<true>::kThreads <= kScoreThreads, "both lists are searched at once");
+static_assert(Sel<false>::kOwn * Sel<false>::kThreads >= kKeyLdsCells, "a small model's keys fit the registers");
+template <bool LARGE>
+struct ScoreLds {
+    u64 key[2][Sel<LARGE>::kWaves][kHeadMax];
+    int id[2][Sel<LARGE>::kWaves][kHeadMax];
+    std::conditional_t<LARGE, char, KeyLds> cells;
 };
 
-// The h smallest (key, flat id) pairs of the calling wavefront's cells ltid, ltid + 512, ... of one list,
+// The h smallest (key, flat id) pairs of the calling wavefront's cells ltid, ltid + STRIDE, ... of one list,
 // ascending, to okey / oid: h rounds of a DPP arg-min, no barrier - what remains after a round is what
 // lies after its winner, and only the lane that held the winner looks through its cells again.  OWN:
 // keys of a lane held in registers, all requested together (0: read again each time).
-template <int OWN>
+template <int STRIDE, int OWN>
 __device__ __forceinline__ void wave_head(const u64* keys, int LE, int ltid, int lane, int want, u64* okey, int* oid) {
     u64 mine[OWN > 0 ? OWN : 1];
 #pragma unroll
     for (int r = 0; r < OWN; ++r) {
-        const int f = ltid + r * kSelThreads;
+        const int f = ltid + r * STRIDE;
         mine[r] = f < LE ? keys[f] : kNone;
     }
     bool have_last = false;
@@ -243,9 +265,9 @@ __device__ __forceinline__ void wave_head(const u64* keys, int LE, int ltid, int
             };
             if constexpr (OWN > 0) {
 #pragma unroll
-                for (int r = 0; r < OWN; ++r) consider(mine[r], ltid + r * kSelThreads);
+                for (int r = 0; r < OWN; ++r) consider(mine[r], ltid + r * STRIDE);
             } else {
-                for (int f = ltid; f < LE; f += kSelThreads) consider(keys[f], f);
+                for (int f = ltid; f < LE; f += STRIDE) consider(keys[f], f);
             }
             cur_valid = true;
         }
@@ -261,15 +283,19 @@ __device__ __forceinline__ void wave_head(const u64* keys, int LE, int ltid, int
 }
 
 // All kScoreThreads threads of the scoring workgroup call, after score_cells (whose closing barrier
-// has made the keys visible).  Wavefronts 0..7 search the prefetch list, 8..15 the eviction list.
-// First every wavefront extracts the h smallest pairs of its own cells, then the list's first
-// wavefront the h smallest of those 8 h candidates the same way.
+// has made the keys visible).  The first kWaves wavefronts search the prefetch list, the next as many the eviction
+// list, others only meet the barrier.  First every wavefront extracts the h smallest pairs of its own cells, then the
+// list's first wavefront the h smallest of those kWaves h candidates the same way.
 // Writes pf_order[0 .. min(h_pf, n_pf)) and ev_order[0 .. min(h_ev, n_ev)).
-// A chain of dependent steps, so what counts is their number: with four wavefronts a list and keys in
-// registers for up to 2,048 cells only, every round over 9,440 cells was one more trip to memory per
-// 256 of them, and the finishing workgroup of the match took 80.6 us beside the streaming FFN; now 42.1 (59 x 160 cells, two
-// rows of a wavefront on their way at a time included).
-__device__ __forceinline__ void select_heads(const ScoreArgs& a, const u64* kp, const u64* kv, const int* s_n, HeadLds& hl) {
+// A chain of dependent steps, so what counts is their number: with four wavefronts a list and eight keys in
+// registers, every round over 9,440 cells was one more trip to memory per 256 of them, and the finishing workgroup of the
+// match took 60.8 us (59 x 160 cells, heads of 6 and 0 entries), 260 with a prefetch depth of 32; with eight and 20 keys 34.0
+// and 90.1.  Few cells are searched by four: with eight a list has twice the candidates to merge (26 x 64 cells, depth 32: 55.0
+// us, with four 47.0), and both forms in one kernel are more than twice the instructions to fetch (4 x 8 cells 9.0 us, in a
+// kernel of their own 8.4; 32 x 8 cells 16.0 and 15.2).
+template <bool LARGE>
+__device__ __forceinline__ void select_heads(const ScoreArgs& a, const u64* kp, const u64* kv, const int* s_n, ScoreLds<LARGE>& hl) {
+    constexpr int kSelWaves = Sel<LARGE>::kWaves, kSelThreads = Sel<LARGE>::kThreads, kOwn = Sel<LARGE>::kOwn;
     const int tid = threadIdx.x;
     const int LE = a.L * a.E;
     const int list = tid / kSelThreads;
@@ -278,20 +304,18 @@ __device__ __forceinline__ void select_heads(const ScoreArgs& a, const u64* kp, 
     const u64* keys = list == 0 ? kp : kv;
     int32_t* out = list == 0 ? a.pf_order : a.ev_order;
     int32_t* host_out = list == 0 ? a.host_pf_head : a.host_ev_head;
-    const int want = min(list == 0 ? min(a.h_pf, s_n[0]) : min(a.h_ev, s_n[1]), kHeadMax);
+    const int want = list > 1 ? 0 : min(list == 0 ? min(a.h_pf, s_n[0]) : min(a.h_ev, s_n[1]), kHeadMax);
     if (want > 0) {  // uniform over the wavefront
         u64* okey = hl.key[list][lwave];
         int* oid = hl.id[list][lwave];
-        if (LE <= kSelOwnSmall * kSelThreads)
-            wave_head<kSelOwnSmall>(keys, LE, ltid, lane, want, okey, oid);
-        else if (LE <= kSelOwnLarge * kSelThreads)
-            wave_head<kSelOwnLarge>(keys, LE, ltid, lane, want, okey, oid);
+        if (!LARGE || LE <= kOwn * kSelThreads)
+            wave_head<kSelThreads, kOwn>(keys, LE, ltid, lane, want, okey, oid);
         else
-            wave_head<0>(keys, LE, ltid, lane, want, okey, oid);
+            wave_head<kSelThreads, 0>(keys, LE, ltid, lane, want, okey, oid);
     }
     __syncthreads();
     if (want > 0 && lwave == 0) {
-        // 8 * want candidates, lane-major: candidate c = wave * want + round sits in lane c % 64
+        // kSelWaves * want candidates, lane-major: candidate c = wave * want + round sits in lane c % 64
         constexpr int kPer = (kSelWaves * kHeadMax + kWave - 1) / kWave;
         const int total = kSelWaves * want;
         KeyId cand[kPer];
@@ -323,13 +347,18 @@ __device__ __forceinline__ void select_heads(const ScoreArgs& a, const u64* kp, 
     }
 }
 
-// Scoring, then the heads of the orders when the caller has asked for them.
-__device__ __forceinline__ void score_and_heads(const ScoreArgs& a, HeadLds& hl, KeyLds& kl, int* s_n, const int* s_best) {
-    const int LE = a.L * a.E;
-    const bool heads = a.h_pf > 0 || a.h_ev > 0;
-    const bool in_lds = heads && LE <= kKeyLdsCells;
-    score_cells(a, s_n, s_best, a.keys, a.keys + LE, in_lds ? &kl : nullptr);
-    if (heads) select_heads(a, in_lds ? kl.k[0] : a.keys, in_lds ? kl.k[1] : a.keys + LE, s_n, hl);
+// Scoring, then the heads of the orders when the caller has asked for them.  LARGE: more than kKeyLdsCells cells.
+template <bool LARGE>
+__device__ __forceinline__ void score_and_heads(const ScoreArgs& a, ScoreLds<LARGE>& sl, int* s_n, const int* s_best) {
+    const u64 *kp = a.keys, *kv = a.keys + a.L * a.E;
+    if constexpr (LARGE) {
+        score_cells<LARGE>(a, s_n, s_best, a.keys, a.keys + a.L * a.E, nullptr);
+    } else {
+        score_cells<LARGE>(a, s_n, s_best, a.keys, a.keys + a.L * a.E, &sl.cells);
+        kp = sl.cells.k[0];
+        kv = sl.cells.k[1];
+    }
+    if (a.h_pf > 0 || a.h_ev > 0) select_heads<LARGE>(a, kp, kv, s_n, sl);
 }
 
 #endif

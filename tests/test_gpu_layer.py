@@ -476,3 +476,35 @@ def test_heads_of_the_orders_over_many_cells(m, L, E):
         assert ev_head.tolist() == rev[:k + depth] and pf_head.tolist() == rpf[:depth]
     cache.close()
     eamc.close()
+
+
+# both kernels of a fused step's scoring (up to 2,048 cells, more) behind the pick of one and of several traces, finished
+# by the only workgroup of the search and by the last of two
+@pytest.mark.parametrize("L,E", [(4, 8), (32, 64), (11, 187)])
+@pytest.mark.parametrize("N,matches", [(40, 3), (1100, 1), (1100, 16)])
+def test_heads_of_the_orders_from_several_matches(m, L, E, N, matches):
+    rng = np.random.default_rng(L * E + N + matches)
+    k, depth, H, I = 3, 32, 64, 8
+    desc = m.ModelDesc(L, E, k, 0, H, I, m.WDTYPE_BF16, 0, EPS)
+    T = (rng.integers(0, 30, size=(N, L, E)) * (rng.random((N, L, E)) < 0.3)).astype(np.int32)
+    eamc = m.Eamc(desc, N, 4)
+    eamc.load(T)
+    S = max(L * E // 2, 2 * k)
+    cache = m.Cache(desc, S, pinned(np.zeros((2, 3 * H * I), dtype=np.uint16)))
+    cache.reset(S)
+    cache.set_prefetch(depth)
+    cache.set_match_count(matches)
+    d_eam = dev(T[7].copy())
+    y = torch.empty(H, dtype=torch.float32, device="cuda")
+    W, x = dev(np.zeros((E, H), dtype=np.uint16)), dev(np.zeros(H, dtype=np.uint16))
+    for layer in (0, L - 2):
+        bias = dev(rng.standard_normal(E).astype(np.float32))
+        res = cache.get_slots().reshape(L, E) >= 0
+        idx, best, _ = m.moe_decode_layer(cache, eamc, d_eam, layer, W, bias, x, y)
+        top = cache.last_matches()[0]
+        assert top.tolist() == O.eamc_match_topm(T, d_eam.cpu().numpy(), matches)[0] and best == top[0]
+        pf_head, ev_head = cache.last_heads()
+        _, _, rpf, rev = O.expert_priority(O.aggregate_matches(T, top), layer, res, EPS, [layer * E + int(j) for j in idx])
+        assert ev_head.tolist() == rev[:k + depth] and pf_head.tolist() == rpf[:depth]
+    cache.close()
+    eamc.close()
