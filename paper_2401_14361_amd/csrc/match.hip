@@ -780,7 +780,7 @@ __device__ __forceinline__ Best block_pick(Best me, u64* s_dot, u64* s_nt, int* 
 // its own: with the scoring in it scalar registers were spilled, and a match over 10,000 traces took
 // 22.8 us for one query and 26.7 for eight instead of 22.1 and 25.8.
 template <Scoring SCORE>
-__global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) {
+__device__ __forceinline__ void pick_traces(const PickArgs& a) {
     __shared__ u64 s_dot[kPickWaves];
     __shared__ u64 s_nt[kPickWaves];
     __shared__ int s_idx[kPickWaves];
@@ -870,6 +870,16 @@ __global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) {
         }
     }
     if constexpr (SCORE != Scoring::none) score_and_heads<SCORE == Scoring::large>(a.sc, s_score, s_sn, s_best);
+}
+// The scoring kernels run beside the FFN that streams an expert's weights.  At most four of their wavefronts to a SIMD asks
+// for so many registers that they don't share a compute unit with a workgroup of that FFN but run on those it leaves
+// free: beside it a trip to memory waits behind its loads (pick and scores of 32 x 8 cells beside two experts of 14,336 units
+// 54.7 us, 20.2 on a unit of their own; the step 121.3 and 119.7 us).
+#define MOEI_OWN_UNIT __attribute__((amdgpu_waves_per_eu(4, 4)))
+__global__ void __launch_bounds__(kPickThreads) eamc_pick_kernel(PickArgs a) { pick_traces<Scoring::none>(a); }
+template <Scoring SCORE>
+__global__ void __launch_bounds__(kPickThreads) MOEI_OWN_UNIT eamc_pick_score_kernel(PickArgs a) {
+    pick_traces<SCORE>(a);
 }
 
 // ---- the m most similar traces of ONE query, most similar first (ties: lowest index)
@@ -1007,7 +1017,7 @@ __device__ __forceinline__ void block_top(TopLds& t, int count, int m, Emit emit
 // each, twice over) took 39.7 us at 10,000 traces and m = 8, ranking takes 15.3 us.
 // SCORE: the finishing workgroup also scores the aggregate of the m traces.
 template <Scoring SCORE>
-__global__ void __launch_bounds__(kPickThreads) eamc_topm_kernel(TopmArgs a) {
+__device__ __forceinline__ void pick_topm(const TopmArgs& a) {
     __shared__ u64 s_red[kPickWaves];
     __shared__ u64 s_nq;
     __shared__ unsigned s_ticket;
@@ -1118,6 +1128,11 @@ __global__ void __launch_bounds__(kPickThreads) eamc_topm_kernel(TopmArgs a) {
         __syncthreads();  // the matched traces are in LDS; the search's LDS is free
         score_and_heads<SCORE == Scoring::large>(a.sc, *reinterpret_cast<Lds*>(s_mem), s_sn, s_best);
     }
+}
+__global__ void __launch_bounds__(kPickThreads) eamc_topm_kernel(TopmArgs a) { pick_topm<Scoring::none>(a); }
+template <Scoring SCORE>
+__global__ void __launch_bounds__(kPickThreads) MOEI_OWN_UNIT eamc_topm_score_kernel(TopmArgs a) {
+    pick_topm<SCORE>(a);
 }
 
 struct Plan {
@@ -1553,7 +1568,7 @@ int launch_match(const moei_eamc* c, const int32_t* d_eam, int B, int layer_hi, 
     PickArgs pa{c->d_part, c->d_norm2, d_eam, n_lsplit, c->n_cap, c->N, L * E, c->d_cand, c->d_cand_idx,
                 c->d_ticket, d_best, d_best_sim, d_sims, score ? *score : ScoreArgs{}};
     launch(K_MATCH_ARGMAX,
-           !score ? eamc_pick_kernel<Scoring::none> : L * E <= kKeyLdsCells ? eamc_pick_kernel<Scoring::small> : eamc_pick_kernel<Scoring::large>,
+           !score ? eamc_pick_kernel : L * E <= kKeyLdsCells ? eamc_pick_score_kernel<Scoring::small> : eamc_pick_score_kernel<Scoring::large>,
            dim3(n_blk, B), dim3(kPickThreads), 0, s, pa);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
@@ -1576,7 +1591,7 @@ int launch_match_topm(const moei_eamc* c, const int32_t* d_eam, int layer_hi, in
     TopmArgs ta{c->d_part, c->d_norm2, d_eam, n_lsplit, c->n_cap, c->N, L * E, m, c->d_cand, c->d_cand_idx,
                 c->d_ticket, d_top, d_top_sim, d_sims, score ? *score : ScoreArgs{}};
     launch(K_MATCH_ARGMAX,
-           !score ? eamc_topm_kernel<Scoring::none> : L * E <= kKeyLdsCells ? eamc_topm_kernel<Scoring::small> : eamc_topm_kernel<Scoring::large>,
+           !score ? eamc_topm_kernel : L * E <= kKeyLdsCells ? eamc_topm_score_kernel<Scoring::small> : eamc_topm_score_kernel<Scoring::large>,
            dim3(n_blk), dim3(kPickThreads), 0, s, ta);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
