@@ -235,6 +235,8 @@ int moei_cache_error_flags(moei_cache* c, int32_t* h_flags, void* stream);
  * One MoE layer of one decode iteration for one request:
  *   logits = W_r x + b -> top-k -> EAM row update -> (EAMC match -> priorities) on a
  *   side stream, while Alg. 1 retrieval and the expert FFNs run on `stream`.
+ * An asynchronous step over a short collection has the match and the priorities on `stream` too, beside
+ * the FFNs in one launch; the calls below that wait for them take either kind into account.
  * d_router_w[E][H] in wdtype, d_router_bias[E] fp32 or NULL, d_eam[L][E] int32.
  * The eviction order used for this layer's misses is the one computed from the EAM
  * that already contains this layer's routing.

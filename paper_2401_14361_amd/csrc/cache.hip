@@ -11,6 +11,7 @@
 
 #include "kernels.hpp"
 #include "score.hpp"
+#include "step_match.hpp"
 
 namespace moei {
 
@@ -109,6 +110,12 @@ struct moei_cache {
     int32_t* d_flags = nullptr;
     unsigned* d_ticket = nullptr;
     hipStream_t copy_stream = nullptr, side_stream = nullptr;
+    // scratch of the steps that match beside the experts (step_match.hpp)
+    u64* d_step_cand = nullptr;
+    int32_t* d_step_idx = nullptr;
+    unsigned* d_step_ticket = nullptr;
+    hipStream_t match_stream = nullptr;  // the stream that holds the last step's match (match_on_stream), its caller's
+    bool match_on_stream = false;
     hipEvent_t ev_copy = nullptr, ev_routed = nullptr, ev_side = nullptr, ev_main = nullptr;
     hipEvent_t ev_match[kRing] = {};             // end of the side chain of the last step with this parity;
                                                   // ev_side aliases the most recent of the two
@@ -191,6 +198,9 @@ extern "C" int moei_cache_destroy(moei_cache* c) {
     (void)hipFree(c->d_slot_of);
     (void)hipFree(c->d_flags);
     (void)hipFree(c->d_ticket);
+    (void)hipFree(c->d_step_cand);
+    (void)hipFree(c->d_step_idx);
+    (void)hipFree(c->d_step_ticket);
     ffn_scratch_free(&c->ffn);
     (void)hipFree(c->d_items);
     (void)hipFree(c->d_n_items);
@@ -254,6 +264,9 @@ int cache_alloc(moei_cache* c) {
     MOEI_DMALLOC(c->d_slot_of, LE * 4);
     MOEI_DMALLOC(c->d_flags, 4);
     MOEI_DMALLOC(c->d_ticket, 4);
+    MOEI_DMALLOC(c->d_step_cand, (size_t)kStepMatchMaxBlocks * 2 * sizeof(u64));
+    MOEI_DMALLOC(c->d_step_idx, (size_t)kStepMatchMaxBlocks * 4);
+    MOEI_DMALLOC(c->d_step_ticket, 4);
     MOEI_DMALLOC(c->d_logits, (size_t)d.E * 4);
     for (int r = 0; r < kRing; ++r) {
         MOEI_DMALLOC(c->d_idx2[r], (size_t)kMaxAct * 4);
@@ -277,6 +290,7 @@ int cache_alloc(moei_cache* c) {
 #undef MOEI_DMALLOC
     MOEI_HIP(hipMemset(c->d_flags, 0, 4));
     MOEI_HIP(hipMemset(c->d_ticket, 0, 4));
+    MOEI_HIP(hipMemset(c->d_step_ticket, 0, 4));
     MOEI_HIP(hipMemset(c->d_n_pf, 0, 4));
     MOEI_HIP(hipMemset(c->d_n_ev, 0, 4));
     MOEI_HIP(hipMemset(c->d_best, 0xff, kMaxMatchBatch * 4));
@@ -364,6 +378,7 @@ extern "C" int moei_cache_reset(moei_cache* c, int32_t n_resident) {
                  "moei_cache_reset: n_resident = %d outside [0, min(S, L*E)]", n_resident);
     MOEI_HIP(hipDeviceSynchronize());
     c->side_pending = false;
+    c->match_on_stream = false;
     c->plan_pending = false;
     for (int r = 0; r < kRing; ++r) c->match_pending[r] = false;
     std::fill(c->slot_of.begin(), c->slot_of.end(), -1);
@@ -384,6 +399,7 @@ extern "C" int moei_cache_reset(moei_cache* c, int32_t n_resident) {
     }
     MOEI_HIP(hipMemset(c->d_flags, 0, 4));
     MOEI_HIP(hipMemset(c->d_ticket, 0, 4));
+    MOEI_HIP(hipMemset(c->d_step_ticket, 0, 4));
     return upload_slot_table(c);
 }
 
@@ -637,7 +653,7 @@ extern "C" int expert_ffn_gemv(moei_cache* c, const int32_t* d_slot_ids, const f
                  n_act, c->ffn.n_act_max);
     MOEI_REQUIRE(n_act == 0 || (d_slot_ids && d_gate_w), "expert_ffn_gemv: null slot ids or gate weights");
     return launch_expert_ffn(c->d, c->d_pool, c->slot_elems, c->n_total, c->ffn, d_slot_ids, d_gate_w, n_act, d_x, d_y,
-                             c->d_flags, as_stream(stream));
+                             c->d_flags, nullptr, 0, as_stream(stream));
 }
 
 extern "C" int expert_ffn_gemv_static(moei_cache* c, const int32_t* d_slot_ids, const float* d_gate_w, int32_t n_act,
@@ -776,6 +792,17 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
     // of recent steps: it only must not overwrite a set that the step kRing steps back still
     // reads (a wait that has long been satisfied unless the side stream falls far behind).
     c->parity = (c->parity + 1) % kRing;
+    // An asynchronous step over a collection that a few workgroups read while the experts stream matches and scores
+    // inside that launch: nothing goes to the side stream.  (A plan that the host carries out needs the side
+    // stream's event, an aggregate of several traces its kernels.)
+    const int match_blocks = sync_mode || plan_prefetch || c->match_m != 1 || !expert_ffn_takes_match(d, c->d_pool, c->slot_elems, d_x)
+                                 ? 0
+                                 : step_match_blocks(eamc, d, c->ffn.n_free);
+    if (match_blocks > 0 && c->side_pending) {  // an earlier step's match on the side stream writes the same results: it goes first
+        MOEI_HIP(hipStreamWaitEvent(s, c->ev_side, 0));
+        c->side_pending = false;
+        for (int r = 0; r < kRing; ++r) c->match_pending[r] = false;
+    }
     if (c->match_pending[c->parity]) MOEI_HIP(hipStreamWaitEvent(s, c->ev_match[c->parity], 0));
     // The asynchronous step picks its slots on the device, so the host cannot tell which
     // prefetch copies it depends on: the stream waits for all that are still unsettled (none in
@@ -817,24 +844,10 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
     }
     rc = launch_route_fused(ra, d.wdtype, s);
     if (rc) return rc;
-    MOEI_HIP(hipEventRecord(c->ev_routed, s));
-    // Asynchronous step: the expert FFNs go onto the main stream right behind the routing,
-    // before any side-stream work is enqueued, so that neither the host-side enqueue time of
-    // the match nor a captured graph's branch placement comes between routing and FFN.
-    if (!sync_mode) {
-        rc = launch_expert_ffn(d, c->d_pool, c->slot_elems, c->n_total, c->ffn, c->d_slot_ids, c->d_gate,
-                               k + d.n_shared, d_x, d_y, c->d_flags, s);
-        if (rc) return rc;
-    }
-
-    // side stream: EAMC match and priorities from the EAM that now holds this layer's routing
-    hipStream_t side = c->side_stream;
-    MOEI_HIP(hipStreamWaitEvent(side, c->ev_routed, 0));
-    // match and scoring in one launch sequence (the workgroup that finishes the match scores
-    // the matched trace), then the two orders
+    // match and scoring (the workgroup that finishes the match scores the matched trace), then the heads of the two orders:
     // Alg. 1 takes the victims from the head of the eviction order (one per miss at most) and prefetching
-    // looks at `depth` candidates: the step computes those heads; the complete orders are ranked from the
-    // step's keys when moei_cache_last_step asks for them
+    // looks at `depth` candidates; the complete orders are ranked from the step's keys when
+    // moei_cache_last_step asks for them
     ScoreArgs sc = make_score_args(eamc, c->d_best, c->match_m, layer, c->d_slot_of, d.eps, c->d_idx, k, c->d_P,
                                    c->d_V, c->d_n_pf, c->d_n_ev);
     sc.keys = c->d_keys;
@@ -844,6 +857,27 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
     sc.h_ev = k + c->pf_depth;
     c->last_h_pf = sc.h_pf;
     c->last_h_ev = sc.h_ev;
+    c->match_on_stream = match_blocks > 0;
+    if (match_blocks > 0) {
+        const StepMatchArgs ma{match_blocks, eamc->d_norm2, d_snap, c->d_step_cand, c->d_step_idx, c->d_step_ticket, c->d_best,
+                               c->d_best_sim, sc};
+        c->match_stream = s;
+        return launch_expert_ffn(d, c->d_pool, c->slot_elems, c->n_total, c->ffn, c->d_slot_ids, c->d_gate, k + d.n_shared, d_x, d_y,
+                                 c->d_flags, &ma, step_match_lds(eamc, match_blocks), s);
+    }
+    MOEI_HIP(hipEventRecord(c->ev_routed, s));
+    // Asynchronous step: the expert FFNs go onto the main stream right behind the routing,
+    // before any side-stream work is enqueued, so that neither the host-side enqueue time of
+    // the match nor a captured graph's branch placement comes between routing and FFN.
+    if (!sync_mode) {
+        rc = launch_expert_ffn(d, c->d_pool, c->slot_elems, c->n_total, c->ffn, c->d_slot_ids, c->d_gate,
+                               k + d.n_shared, d_x, d_y, c->d_flags, nullptr, 0, s);
+        if (rc) return rc;
+    }
+
+    // side stream: EAMC match and priorities from the EAM that now holds this layer's routing
+    hipStream_t side = c->side_stream;
+    MOEI_HIP(hipStreamWaitEvent(side, c->ev_routed, 0));
     if (sync_mode || plan_prefetch) {  // what the host reads goes straight into pinned memory: no copies behind the kernels
         sc.host_best = &c->pin_dev->best;
         sc.host_n = c->pin_dev->n_list;
@@ -922,7 +956,7 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
         // slots they take - but not for this layer's experts, whose slots they never touch)
         if (do_prefetch) MOEI_HIP(hipEventRecord(c->ev_main, s));
         rc = launch_expert_ffn(d, c->d_pool, c->slot_elems, c->n_total, c->ffn, c->d_slot_ids, c->d_gate, k + d.n_shared,
-                               d_x, d_y, c->d_flags, s);
+                               d_x, d_y, c->d_flags, nullptr, 0, s);
         if (rc) return rc;
         if (do_prefetch) {
             if (!side_done) MOEI_HIP(hipEventSynchronize(c->ev_side));
@@ -952,11 +986,25 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
     return MOEI_OK;
 }
 
+namespace {
+// The host waits for the last step's match, except for what the caller's own wait for `s` covers.  The match of a step that
+// holds it on its caller's stream is as far as that stream; a stream that has been destroyed since has drained.
+int wait_for_match(moei_cache* c, hipStream_t s) {
+    if (c->side_pending) MOEI_HIP(hipStreamSynchronize(c->side_stream));
+    if (c->match_on_stream && c->match_stream != s && hipStreamSynchronize(c->match_stream) != hipSuccess) {
+        (void)hipGetLastError();
+        MOEI_HIP(hipDeviceSynchronize());
+    }
+    return MOEI_OK;
+}
+}  // namespace
+
 extern "C" int moei_cache_last_heads(moei_cache* c, int32_t* h_pf_head, int32_t cap_pf, int32_t* h_n_pf_head,
                                      int32_t* h_ev_head, int32_t cap_ev, int32_t* h_n_ev_head, void* stream) {
     MOEI_REQUIRE(c && h_n_pf_head && h_n_ev_head, "moei_cache_last_heads: null pointer");
+    int rc = wait_for_match(c, as_stream(stream));
+    if (rc) return rc;
     MOEI_HIP(hipStreamSynchronize(as_stream(stream)));
-    MOEI_HIP(hipStreamSynchronize(c->side_stream));
     int32_t n_pf = 0, n_ev = 0;
     MOEI_HIP(hipMemcpy(&n_pf, c->d_n_pf, 4, hipMemcpyDeviceToHost));
     MOEI_HIP(hipMemcpy(&n_ev, c->d_n_ev, 4, hipMemcpyDeviceToHost));
@@ -995,7 +1043,8 @@ extern "C" int moei_cache_last_matches(moei_cache* c, int32_t* h_top, float* h_t
     // one copy behind what the caller's stream holds, and one wait for both: a program that reads the
     // matches once a token pays for each trip to the device (two blocking copies behind two waits before)
     hipStream_t s = as_stream(stream);
-    MOEI_HIP(hipStreamSynchronize(c->side_stream));
+    int rc = wait_for_match(c, s);
+    if (rc) return rc;
     MOEI_HIP(hipMemcpyAsync(c->pin->matches, c->d_best, sizeof(c->pin->matches), hipMemcpyDeviceToHost, s));
     MOEI_HIP(hipStreamSynchronize(s));
     if (h_top) memcpy(h_top, c->pin->matches, (size_t)c->match_m * 4);
@@ -1011,6 +1060,15 @@ extern "C" int moei_cache_join(moei_cache* c, void* stream) {
         if (rc) return rc;
     }
     if (c->side_pending) MOEI_HIP(hipStreamWaitEvent(as_stream(stream), c->ev_side, 0));
+    if (c->match_on_stream && c->match_stream != as_stream(stream)) {
+        hipError_t e = hipEventRecord(c->ev_routed, c->match_stream);
+        if (e == hipSuccess) {
+            MOEI_HIP(hipStreamWaitEvent(as_stream(stream), c->ev_routed, 0));
+        } else {
+            int rc = wait_for_match(c, as_stream(stream));
+            if (rc) return rc;
+        }
+    }
     if (c->n_pending > 0) {  // prefetch copies that no stream has waited for yet
         for (int t = 0; t < c->S; ++t) {
             int rc = settle_pending(c, t, as_stream(stream));
@@ -1025,9 +1083,14 @@ extern "C" int moei_cache_sync(moei_cache* c) {
     MOEI_HIP(hipStreamSynchronize(c->side_stream));
     MOEI_HIP(hipStreamSynchronize(c->copy_stream));
     MOEI_HIP(hipStreamSynchronize(c->pf_stream));
+    if (c->match_on_stream) {
+        int rc = wait_for_match(c, c->side_stream);  // (never the stream that holds it)
+        if (rc) return rc;
+    }
     std::fill(c->slot_pending.begin(), c->slot_pending.end(), 0);
     c->n_pending = 0;
     c->side_pending = false;
+    c->match_on_stream = false;
     for (int r = 0; r < kRing; ++r) c->match_pending[r] = false;
     return MOEI_OK;
 }
@@ -1036,10 +1099,11 @@ extern "C" int moei_cache_last_step(moei_cache* c, float* h_gate_w, float* h_bes
                                     float* h_evict, int32_t* h_pf_order, int32_t* h_n_pf, int32_t* h_ev_order,
                                     int32_t* h_n_ev, void* stream) {
     MOEI_REQUIRE(c, "moei_cache_last_step: null pointer");
+    int rc = wait_for_match(c, as_stream(stream));
+    if (rc) return rc;
     MOEI_HIP(hipStreamSynchronize(as_stream(stream)));
-    MOEI_HIP(hipStreamSynchronize(c->side_stream));
     if (h_pf_order || h_ev_order) {  // the step selected the heads only: the complete orders are ranked from its keys now
-        int rc = launch_priority_rank(c->d, c->d_keys, c->d_n_pf, c->d_n_ev, c->d_pf_order, c->d_ev_order, c->side_stream);
+        rc = launch_priority_rank(c->d, c->d_keys, c->d_n_pf, c->d_n_ev, c->d_pf_order, c->d_ev_order, c->side_stream);
         if (rc) return rc;
         MOEI_HIP(hipStreamSynchronize(c->side_stream));
     }

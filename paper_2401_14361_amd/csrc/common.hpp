@@ -182,6 +182,10 @@ __device__ __forceinline__ void wait_vm_fence() {
 // waits until the wavefront's LDS reads have returned (before their LDS is written again by such a load)
 __device__ __forceinline__ void wait_lds_fence() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// A barrier for what the workgroup exchanges through LDS alone: unlike __syncthreads it does not wait until the stores to
+// global memory before it have arrived (1 - 2 us each time while other workgroups stream).
+__device__ __forceinline__ void barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 #endif  // __HIPCC__
 
 }  // namespace moei

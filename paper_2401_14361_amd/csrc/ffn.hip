@@ -17,9 +17,11 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "step_match.hpp"
 #include "wtypes.hpp"
 
 namespace moei {
@@ -33,11 +35,13 @@ struct FfnArgs {
     const int32_t* slot_ids;
     const float* gate_w;
     const void* x;
-    float* part;  // [gridDim.x][H] workgroup partial sums
+    float* part;  // [n_wg][H] workgroup partial sums
+    int n_wg;     // workgroups that stream; the launch's others match and score (StepMatchArgs)
     int H, I, n_act;
     int waves;    // wavefronts per workgroup
     int ygroup;   // wavefronts whose y rows fit in LDS together
     int32_t* flags;
+    StepMatchArgs match;
 };
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + expf(-g)); }
@@ -91,6 +95,10 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
     constexpr int PF = StreamShape<NCH>::kWindow;
     static_assert(STEPS % PF == 0, "the window must divide the steps of a unit");
     extern __shared__ __align__(16) float smem[];
+    if ((int)blockIdx.x >= a.n_wg) {  // a workgroup that matches and scores beside the ones that stream
+        step_match(a.match, blockIdx.x - a.n_wg, reinterpret_cast<unsigned char*>(smem));
+        return;
+    }
     float* xs = smem;
     float* yp = smem + NCH * CW;
     constexpr bool kPacked = std::is_same<WT, uint16_t>::value;  // bf16: x stays bf16 in LDS, products by v_dot2c_f32_bf16
@@ -99,7 +107,7 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
     // then scalar too
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int H = a.H, I = a.I;
-    const int W = gridDim.x * a.waves;
+    const int W = a.n_wg * a.waves;
     const int NT = a.n_act * I;
     const WT* pool = reinterpret_cast<const WT*>(a.pool);
     const unsigned lane_off = (unsigned)lane * N;  // this lane's elements inside a chunk
@@ -135,7 +143,7 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
     // unit t -> wavefront t mod W, numbered wavefront-major (w = wv * workgroups + workgroup): when
     // the units do not fill the last round, every compute unit keeps most of its wavefronts busy
     // instead of whole workgroups running out of work
-    int t = wv * gridDim.x + blockIdx.x;
+    int t = wv * a.n_wg + blockIdx.x;
     float gate = 0.f, gate_n = 0.f;
     bool ok = false, ok_n = false;
     size_t p = 0;
@@ -379,17 +387,17 @@ int env_int(const char* name, int dflt) {
 
 constexpr size_t kLdsBudget = 150 * 1024;  // of the 160 KiB per compute unit
 
-// Wavefronts per workgroup: the count in [4, max_waves] that wastes the fewest unit slots when
+// Wavefronts per workgroup: the count in [min_waves, max_waves] that wastes the fewest unit slots when
 // n_units are dealt out to blocks * waves wavefronts (ties go to more wavefronts).
-int plan_waves(int n_units, int blocks, int max_waves) {
+int plan_waves(int n_units, int blocks, int max_waves, int min_waves) {
     static const int forced = env_int("MOEI_FFN_WAVES", 0);  // the environment is read once per process
-    if (forced >= 1 && forced <= max_waves) return forced;
+    if (forced >= min_waves && forced <= max_waves) return forced;
     // a layer step repeats the same shape call after call: the last plan is kept
-    static int memo_key[3] = {-1, -1, -1}, memo_val = 0;
-    if (memo_key[0] == n_units && memo_key[1] == blocks && memo_key[2] == max_waves) return memo_val;
+    static int memo_key[4] = {-1, -1, -1, -1}, memo_val = 0;
+    if (memo_key[0] == n_units && memo_key[1] == blocks && memo_key[2] == max_waves && memo_key[3] == min_waves) return memo_val;
     int best = max_waves;
     double best_eff = -1.0;
-    for (int m = max_waves; m >= (max_waves < 4 ? 1 : 4); --m) {
+    for (int m = max_waves; m >= min_waves; --m) {
         long per = ((long)n_units + (long)blocks * m - 1) / ((long)blocks * m);
         double eff = (double)n_units / ((double)per * blocks * m);
         if (eff > best_eff + 1e-9) {
@@ -400,6 +408,7 @@ int plan_waves(int n_units, int blocks, int max_waves) {
     memo_key[0] = n_units;
     memo_key[1] = blocks;
     memo_key[2] = max_waves;
+    memo_key[3] = min_waves;
     memo_val = best;
     return best;
 }
@@ -424,7 +433,7 @@ int allow_big_lds(K kernel, size_t bytes) {
 }
 
 template <typename WT>
-int launch_ffn_typed(FfnArgs a, bool fast, int grid, float* d_y, hipStream_t s) {
+int launch_ffn_typed(FfnArgs a, bool fast, int grid, size_t match_lds, float* d_y, hipStream_t s) {
     using V = WVec<WT>;
     const int H = a.H;
     int rc = MOEI_OK;
@@ -433,14 +442,14 @@ int launch_ffn_typed(FfnArgs a, bool fast, int grid, float* d_y, hipStream_t s) 
     if (fast) {
 #define MOEI_FFN_CASE(N_, TAIL_)                                                                        \
     case N_: {                                                                                         \
-        a.waves = plan_waves(a.n_act * a.I, grid, StreamShape<N_>::kMaxWaves);                         \
+        a.waves = plan_waves(a.n_act * a.I, grid, StreamShape<N_>::kMaxWaves, a.match.n_blocks > 0 ? 8 : 4); \
         const size_t padded = (size_t)N_ * kWave * V::N * sizeof(float);                               \
         int yg = (int)((kLdsBudget - padded) / padded);                                                \
         a.ygroup = yg < 1 ? 1 : (yg > a.waves ? a.waves : yg);                                         \
-        const size_t smem = padded * (1 + a.ygroup);                                                   \
+        const size_t smem = std::max(padded * (1 + a.ygroup), match_lds);                              \
         rc = allow_big_lds(ffn_fused_kernel<WT, N_, TAIL_>, smem);                                     \
         if (rc) return rc;                                                                             \
-        launch(K_FFN_FUSED, ffn_fused_kernel<WT, N_, TAIL_>, dim3(grid), dim3(a.waves * kWave), smem, s, a); \
+        launch(K_FFN_FUSED, ffn_fused_kernel<WT, N_, TAIL_>, dim3(grid + a.match.n_blocks), dim3(a.waves * kWave), smem, s, a); \
         break;                                                                                         \
     }
         // whole chunks, for the counts of chunks that configurations have; any other row through TAIL
@@ -481,6 +490,7 @@ int launch_ffn_typed(FfnArgs a, bool fast, int grid, float* d_y, hipStream_t s) 
 #undef MOEI_FFN_CASE
     }
     if (!fast) {
+        if (a.match.n_blocks > 0) MOEI_FAIL(MOEI_EINVAL, "expert FFN: H = %d takes no match beside it", H);
         int m = (int)((kLdsBudget - row) / row);
         if (m > 8) m = 8;
         if (m < 1) MOEI_FAIL(MOEI_ECAPACITY, "expert_ffn_gemv: H = %d does not fit the LDS staging", H);
@@ -930,6 +940,7 @@ int ffn_scratch_alloc(const moei_model_desc& d, int n_act_max, FfnScratch* out) 
     int reserve = env_int("MOEI_RESERVE_CUS", 24);
     if (reserve < 0 || reserve > compute_units() / 2) reserve = 0;
     out->n_part = compute_units() - reserve;
+    out->n_free = reserve;
     float* unused = nullptr;  // the static scratch of expert_ffn_gemv_static: address looked up at set-up
     int rc = static_part_ptr(&unused);
     if (rc) return rc;
@@ -989,13 +1000,29 @@ int launch_expert_ffn_static(const moei_model_desc& d, const void* d_pool, size_
     int rc = static_part_ptr(&scr.d_part);
     if (rc) return rc;
     scr.n_part = n_part;
-    return launch_expert_ffn(d, d_pool, slot_elems, n_slots_total, scr, d_slot_ids, d_gate_w, n_act, d_x, d_y, d_flags, s);
+    return launch_expert_ffn(d, d_pool, slot_elems, n_slots_total, scr, d_slot_ids, d_gate_w, n_act, d_x, d_y, d_flags, nullptr, 0, s);
+}
+
+namespace {
+// The streaming kernel reads 16-byte pieces: rows and addresses have to allow it, and the registers hold up to 16 chunks
+// of a row (other shapes take ffn_fused_generic_kernel).
+bool ffn_streams(const moei_model_desc& d, const void* d_pool, size_t slot_elems) {
+    const int wb = d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4;
+    static const bool force_generic = env_int("MOEI_FFN_GENERIC", 0) != 0;
+    return (d.H * wb) % 16 == 0 && (uintptr_t)d_pool % 16 == 0 && (slot_elems * wb) % 16 == 0 && !force_generic;
+}
+}  // namespace
+
+bool expert_ffn_takes_match(const moei_model_desc& d, const void* d_pool, size_t slot_elems, const void* d_x) {
+    const int chunk = kWave * 16 / (d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4);
+    return ffn_streams(d, d_pool, slot_elems) && d.H <= 16 * chunk && (uintptr_t)d_x % 16 == 0;
 }
 
 int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_elems, int n_slots_total,
                       const FfnScratch& scr, const int32_t* d_slot_ids, const float* d_gate_w, int n_act,
-                      const void* d_x, float* d_y, int32_t* d_flags, hipStream_t s) {
-    if (n_act == 0) {  // an empty sum: the reduction over zero partial rows writes zeros
+                      const void* d_x, float* d_y, int32_t* d_flags, const StepMatchArgs* match, size_t match_lds,
+                      hipStream_t s) {
+    if (n_act == 0 && !match) {  // an empty sum: the reduction over zero partial rows writes zeros
         launch(K_FFN_REDUCE, ffn_reduce_kernel, dim3((d.H + 31) / 32), dim3(256), 0, s, (const float*)scr.d_part, 0, d.H,
                d_y);
         MOEI_LAUNCH_CHECK();
@@ -1013,13 +1040,11 @@ int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_
     a.I = d.I;
     a.n_act = n_act;
     a.flags = d_flags;
-    const int wb = d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4;
-    const int n = 16 / wb;
-    static const bool force_generic = env_int("MOEI_FFN_GENERIC", 0) != 0;
-    const bool fast = (d.H % n == 0) && ((uintptr_t)d_pool % 16 == 0) && ((slot_elems * wb) % 16 == 0) &&
-                      !force_generic;
-    if (d.wdtype == MOEI_WDTYPE_BF16) return launch_ffn_typed<uint16_t>(a, fast, scr.n_part, d_y, s);
-    return launch_ffn_typed<float>(a, fast, scr.n_part, d_y, s);
+    a.n_wg = scr.n_part;
+    if (match) a.match = *match;
+    const bool fast = ffn_streams(d, d_pool, slot_elems);
+    if (d.wdtype == MOEI_WDTYPE_BF16) return launch_ffn_typed<uint16_t>(a, fast, scr.n_part, match_lds, d_y, s);
+    return launch_ffn_typed<float>(a, fast, scr.n_part, match_lds, d_y, s);
 }
 
 

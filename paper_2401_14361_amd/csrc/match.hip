@@ -11,6 +11,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <type_traits>
 #include <vector>
@@ -18,8 +19,9 @@
 #include <stdio.h>
 
 #include "kernels.hpp"
+#include "match.hpp"
 #include "score.hpp"
-#include "wtypes.hpp"
+#include "step_match.hpp"
 
 namespace moei {
 
@@ -27,7 +29,6 @@ namespace {
 
 constexpr int kDotThreads = 256;
 constexpr int kMaxE = 2048;
-typedef unsigned __int128 u128;
 
 struct DotArgs {
     const void* traces;   // [L][n_cap][E]
@@ -41,67 +42,6 @@ struct DotArgs {
     int rowV;             // vectors per trace row
     int once;             // the scan exceeds the last-level cache: load with the non-temporal hint
     int lane_rows;        // a trace row's vectors sit in rowV consecutive lanes (see the kernel)
-};
-
-template <typename CT, int VEC>
-struct CellVec;
-
-template <>
-struct CellVec<int32_t, 4> {
-    using raw = int4;
-    static __device__ __forceinline__ raw load(const int32_t* p) { return *reinterpret_cast<const int4*>(p); }
-    static __device__ __forceinline__ raw load_once(const int32_t* p) {
-        const uint4 v = load_once_16(p);
-        return make_int4((int)v.x, (int)v.y, (int)v.z, (int)v.w);
-    }
-    static __device__ __forceinline__ u64 dot(raw v, const int32_t* q, u64 acc) {
-        int4 qq = *reinterpret_cast<const int4*>(q);
-        acc += (u64)(uint32_t)v.x * (uint32_t)qq.x;
-        acc += (u64)(uint32_t)v.y * (uint32_t)qq.y;
-        acc += (u64)(uint32_t)v.z * (uint32_t)qq.z;
-        acc += (u64)(uint32_t)v.w * (uint32_t)qq.w;
-        return acc;
-    }
-};
-
-template <>
-struct CellVec<int32_t, 1> {
-    using raw = int32_t;
-    static __device__ __forceinline__ raw load(const int32_t* p) { return *p; }
-    static __device__ __forceinline__ raw load_once(const int32_t* p) { return *p; }
-    static __device__ __forceinline__ u64 dot(raw v, const int32_t* q, u64 acc) {
-        return acc + (u64)(uint32_t)v * (uint32_t)q[0];
-    }
-};
-
-template <>
-struct CellVec<uint16_t, 8> {
-    using raw = uint4;
-    static __device__ __forceinline__ raw load(const uint16_t* p) { return *reinterpret_cast<const uint4*>(p); }
-    static __device__ __forceinline__ raw load_once(const uint16_t* p) { return load_once_16(p); }
-    static __device__ __forceinline__ u64 dot(raw v, const int32_t* q, u64 acc) {
-        int4 q0 = *reinterpret_cast<const int4*>(q);
-        int4 q1 = *reinterpret_cast<const int4*>(q + 4);
-        acc += (u64)(v.x & 0xffffu) * (uint32_t)q0.x;
-        acc += (u64)(v.x >> 16) * (uint32_t)q0.y;
-        acc += (u64)(v.y & 0xffffu) * (uint32_t)q0.z;
-        acc += (u64)(v.y >> 16) * (uint32_t)q0.w;
-        acc += (u64)(v.z & 0xffffu) * (uint32_t)q1.x;
-        acc += (u64)(v.z >> 16) * (uint32_t)q1.y;
-        acc += (u64)(v.w & 0xffffu) * (uint32_t)q1.z;
-        acc += (u64)(v.w >> 16) * (uint32_t)q1.w;
-        return acc;
-    }
-};
-
-template <>
-struct CellVec<uint16_t, 1> {
-    using raw = uint16_t;
-    static __device__ __forceinline__ raw load(const uint16_t* p) { return *p; }
-    static __device__ __forceinline__ raw load_once(const uint16_t* p) { return *p; }
-    static __device__ __forceinline__ u64 dot(raw v, const int32_t* q, u64 acc) {
-        return acc + (u64)v * (uint32_t)q[0];
-    }
 };
 
 // The query rows of a workgroup's layers, for its NB queries, into LDS.  A query's cells of these
@@ -127,25 +67,6 @@ __device__ __forceinline__ void stage_queries(const int32_t* __restrict__ q, int
             for (int r = 0; r < R; ++r)
                 if (c0 + r * kDotThreads < per) qs[b * q_stride + c0 + r * kDotThreads] = b0 + b < B ? v[b][r] : 0;
     }
-}
-
-// Sum of a 64-bit value over each group of `group` consecutive lanes (a power of two up to 64; all 64
-// lanes take part; every lane of a group ends with the group's sum): two-word adds with carry over
-// DPP exchanges inside a row of 16 lanes, shuffles beyond.
-__device__ __forceinline__ u64 add_step_dpp(u64 v, unsigned lo_o, unsigned hi_o) {
-    const unsigned lo = (unsigned)v + lo_o;
-    const unsigned hi = (unsigned)(v >> 32) + hi_o + (lo < lo_o ? 1u : 0u);
-    return ((u64)hi << 32) | lo;
-}
-#define MOEI_GROUP_STEP(v, ctrl) (v) = add_step_dpp((v), MOEI_DPP_U32((unsigned)(v), ctrl), MOEI_DPP_U32((unsigned)((v) >> 32), ctrl))
-__device__ __forceinline__ u64 group_sum_u64(u64 v, int group) {
-    if (group >= 2) MOEI_GROUP_STEP(v, 0xB1);    // quad_perm [1,0,3,2]
-    if (group >= 4) MOEI_GROUP_STEP(v, 0x4E);    // quad_perm [2,3,0,1]
-    if (group >= 8) MOEI_GROUP_STEP(v, 0x141);   // row_half_mirror
-    if (group >= 16) MOEI_GROUP_STEP(v, 0x140);  // row_mirror
-    if (group >= 32) v += ((u64)__shfl_xor((unsigned)(v >> 32), 16, 64) << 32 | __shfl_xor((unsigned)v, 16, 64));
-    if (group >= 64) v += ((u64)__shfl_xor((unsigned)(v >> 32), 32, 64) << 32 | __shfl_xor((unsigned)v, 32, 64));
-    return v;
 }
 
 // The same for NB = 8 or 16 values per lane and groups of 16 lanes, at a quarter of the additions: at
@@ -578,164 +499,6 @@ __global__ void __launch_bounds__(kDotThreads) eamc_dot_mm_kernel(DotMmArgs a) {
     }
 }
 
-struct Best {
-    u64 dot;     // <q, T>
-    u64 nt;      // |T|^2, never 0 here (an all-zero trace enters as dot 0, nt 1)
-    double key;  // dot^2 / nt in fp64: decides all but near ties
-    int idx;     // -1: none
-};
-
-__device__ __forceinline__ Best make_best(u64 dot, u64 nt, int idx) {
-    Best b;
-    b.dot = nt ? dot : 0;
-    b.nt = nt ? nt : 1;
-    b.key = ((double)b.dot * (double)b.dot) / (double)b.nt;
-    b.idx = idx;
-    return b;
-}
-
-// a.dot^2 * b.nt  vs  b.dot^2 * a.nt, exactly, as 192-bit integers.
-__device__ __noinline__ int cmp_sim_exact(u64 adot, u64 ant, u64 bdot, u64 bnt) {
-    u128 a2 = (u128)adot * adot, b2 = (u128)bdot * bdot;
-    u128 al = (u128)(u64)a2 * bnt, ah = (u128)(u64)(a2 >> 64) * bnt + (al >> 64);
-    u128 bl = (u128)(u64)b2 * ant, bh = (u128)(u64)(b2 >> 64) * ant + (bl >> 64);
-    if (ah != bh) return ah > bh ? 1 : -1;
-    u64 all = (u64)al, bll = (u64)bl;
-    if (all != bll) return all > bll ? 1 : -1;
-    return 0;
-}
-
-// The fp64 keys carry a relative error below 2^-50; a gap wider than 2^-48 settles the
-// order, anything closer is decided by the exact integer comparison.
-__device__ __forceinline__ int cmp_sim(Best a, Best b) {
-    const double d = a.key - b.key;
-    const double tol = fmax(a.key, b.key) * 0x1p-48;
-    if (d > tol) return 1;
-    if (d < -tol) return -1;
-    return cmp_sim_exact(a.dot, a.nt, b.dot, b.nt);
-}
-
-// The better of two candidates, field by field (the structs stay in registers).
-__device__ __forceinline__ Best pick(Best a, Best b) {
-    bool take_b;
-    if (b.idx < 0) {
-        take_b = false;
-    } else if (a.idx < 0) {
-        take_b = true;
-    } else {
-        const int c = cmp_sim(a, b);
-        take_b = c < 0 || (c == 0 && b.idx < a.idx);  // equal similarity: lowest trace index
-    }
-    Best r;
-    r.dot = take_b ? b.dot : a.dot;
-    r.nt = take_b ? b.nt : a.nt;
-    r.key = take_b ? b.key : a.key;
-    r.idx = take_b ? b.idx : a.idx;
-    return r;
-}
-
-// A candidate moved across lanes by a DPP pattern / read from one lane through scalar registers.
-template <int CTRL>
-__device__ __forceinline__ Best best_dpp(Best me) {
-    auto mv = [](unsigned v) { return MOEI_DPP_U32(v, CTRL); };
-    auto mv64 = [&](u64 v) { return ((u64)mv((unsigned)(v >> 32)) << 32) | mv((unsigned)v); };
-    Best o;
-    o.dot = mv64(me.dot);
-    o.nt = mv64(me.nt);
-    o.key = __longlong_as_double((long long)mv64((u64)__double_as_longlong(me.key)));
-    o.idx = (int)mv((unsigned)me.idx);
-    return o;
-}
-__device__ __forceinline__ Best best_lane(Best me, int lane) {
-    auto rd = [&](unsigned v) { return (unsigned)__builtin_amdgcn_readlane((int)v, lane); };
-    auto rd64 = [&](u64 v) { return ((u64)rd((unsigned)(v >> 32)) << 32) | rd((unsigned)v); };
-    Best o;
-    o.dot = rd64(me.dot);
-    o.nt = rd64(me.nt);
-    o.key = __longlong_as_double((long long)rd64((u64)__double_as_longlong(me.key)));
-    o.idx = (int)rd((unsigned)me.idx);
-    return o;
-}
-
-// The same search on (key, index) alone: three registers per exchange instead of seven.  It is
-// final only if no comparison on the way was a near tie (keys within 2^-48 of each other and
-// not both zero); `tie` reports that, and the caller then repeats the search with the exact
-// comparison.  Two zero keys are two zero similarities: the lower index wins, exactly.
-struct KeyIdx {
-    double key;
-    int idx;
-};
-__device__ __forceinline__ KeyIdx pick_key(KeyIdx a, KeyIdx b, bool& tie) {
-    if (b.idx < 0) return a;
-    if (a.idx < 0) return b;
-    const double d = a.key - b.key;
-    const double tol = fmax(a.key, b.key) * 0x1p-48;
-    bool take_b;
-    if (d > tol) {
-        take_b = false;
-    } else if (d < -tol) {
-        take_b = true;
-    } else if (a.key == 0.0 && b.key == 0.0) {
-        take_b = b.idx < a.idx;
-    } else {
-        tie = true;
-        take_b = false;
-    }
-    KeyIdx r;
-    r.key = take_b ? b.key : a.key;
-    r.idx = take_b ? b.idx : a.idx;
-    return r;
-}
-template <int CTRL>
-__device__ __forceinline__ KeyIdx keyidx_dpp(KeyIdx me) {
-    const u64 k = (u64)__double_as_longlong(me.key);
-    KeyIdx o;
-    o.key = __longlong_as_double((long long)(((u64)MOEI_DPP_U32((unsigned)(k >> 32), CTRL) << 32) | MOEI_DPP_U32((unsigned)k, CTRL)));
-    o.idx = (int)MOEI_DPP_U32((unsigned)me.idx, CTRL);
-    return o;
-}
-__device__ __forceinline__ KeyIdx keyidx_lane(KeyIdx me, int lane) {
-    const u64 k = (u64)__double_as_longlong(me.key);
-    KeyIdx o;
-    o.key = __longlong_as_double((long long)(((u64)(unsigned)__builtin_amdgcn_readlane((int)(k >> 32), lane) << 32) |
-                                             (unsigned)__builtin_amdgcn_readlane((int)k, lane)));
-    o.idx = __builtin_amdgcn_readlane(me.idx, lane);
-    return o;
-}
-
-__device__ __forceinline__ Best wave_pick_exact(Best me) {
-    me = pick(me, best_dpp<0xB1>(me));   // quad_perm [1,0,3,2]
-    me = pick(me, best_dpp<0x4E>(me));   // quad_perm [2,3,0,1]
-    me = pick(me, best_dpp<0x141>(me));  // row_half_mirror
-    me = pick(me, best_dpp<0x140>(me));  // row_mirror
-    const Best r0 = best_lane(me, 0), r1 = best_lane(me, 16), r2 = best_lane(me, 32), r3 = best_lane(me, 48);
-    return pick(pick(r0, r1), pick(r2, r3));
-}
-
-// The wavefront's best candidate, in every lane: DPP inside each row of 16 lanes (the order is
-// total, so both partners of an exchange keep the same winner), then the four row winners
-// through scalar registers.  All 64 lanes must be active.
-__device__ __forceinline__ Best wave_pick(Best me) {
-    bool tie = false;
-    KeyIdx k{me.key, me.idx};
-    k = pick_key(k, keyidx_dpp<0xB1>(k), tie);
-    k = pick_key(k, keyidx_dpp<0x4E>(k), tie);
-    k = pick_key(k, keyidx_dpp<0x141>(k), tie);
-    k = pick_key(k, keyidx_dpp<0x140>(k), tie);
-    const KeyIdx r0 = keyidx_lane(k, 0), r1 = keyidx_lane(k, 16), r2 = keyidx_lane(k, 32), r3 = keyidx_lane(k, 48);
-    const KeyIdx w = pick_key(pick_key(r0, r1, tie), pick_key(r2, r3, tie), tie);
-    if (__ballot(tie) != 0ull) return wave_pick_exact(me);  // uniform
-    if (w.idx < 0) return make_best(0, 1, -1);
-    // the winner's dot product and norm come from the lane that holds it
-    const int owner = __builtin_amdgcn_readfirstlane(__ffsll((long long)__ballot(me.idx == w.idx)) - 1);
-    return best_lane(me, owner);
-}
-
-__device__ __forceinline__ double cosine(u64 dot, u64 nq, u64 nt) {
-    if (nq == 0 || nt == 0) return 0.0;
-    return (double)dot / (sqrt((double)nq) * sqrt((double)nt));
-}
-
 constexpr int kPickThreads = 1024;
 static_assert(kPickThreads == kScoreThreads, "the finishing workgroup of the match also runs the scoring");
 constexpr int kPickChunk = kPickThreads;  // traces per workgroup: one per thread
@@ -869,7 +632,10 @@ __device__ __forceinline__ void pick_traces(const PickArgs& a) {
             s_best[0] = fin.idx;
         }
     }
-    if constexpr (SCORE != Scoring::none) score_and_heads<SCORE == Scoring::large>(a.sc, s_score, s_sn, s_best);
+    if constexpr (SCORE != Scoring::none) {
+        barrier_lds();  // s_best
+        score_and_heads<SCORE == Scoring::large>(a.sc, s_score, s_sn, s_best);
+    }
 }
 // The scoring kernels run beside the FFN that streams an expert's weights.  At most four of their wavefronts to a SIMD asks
 // for so many registers that they don't share a compute unit with a workgroup of that FFN but run on those it leaves
@@ -1572,6 +1338,31 @@ int launch_match(const moei_eamc* c, const int32_t* d_eam, int B, int layer_hi, 
            dim3(n_blk, B), dim3(kPickThreads), 0, s, pa);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
+}
+
+// How many workgroups match beside the experts' stream, 0: the match stays on the side stream.  One (no arrival count) for up
+// to 64 KB and 256 traces, else one per 64 KB or 128 traces, on the compute units that the experts leave free.
+// What such a workgroup does besides reading its traces takes about 16 us, and it reads 29 KB/us, so traces of more than
+// 110 KB a workgroup (then it ends about when a short FFN does: 26 x 64 cells, 69 MB of experts, a step in a graph over 200 /
+// 400 / 1,000 traces - 55 / 111 / 277 KB a workgroup - 28.4 / 29.1 / 32.4 us, on the side stream 30.3 / 30.2 / 30.6) are read beside
+// experts that take longer only (32 x 8 cells, 1,000 traces beside 295 MB of experts: 62.3 us, on the side stream 64.0).  Issued one
+// by one the same steps take 25 - 33 us, and 34 - 36 on the side stream: the host, with two launches and four event calls less.
+int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_units) {
+    const size_t scan = (size_t)c->N * d.L * d.E * c->cell_bytes;
+    const size_t experts = (size_t)(d.k + d.n_shared) * 3 * d.H * d.I * (d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4);
+    if (d.L * d.E > kKeyLdsCells) return 0;  // the scoring of more cells is a kernel of its own
+    int n = 1;
+    if (c->N > 256 || scan > (64 << 10)) {
+        n = (int)std::min<size_t>(std::min(free_units, kStepMatchMaxBlocks), std::max<size_t>((c->N + 127) / 128, (scan + (64 << 10) - 1) / (64 << 10)));
+        if (n < 1) return 0;
+    }
+    const double ffn_us = 4.0 + (double)experts / 6.5e6;
+    const double room = std::max(110.0 * 1024, (ffn_us - 16.0) * 29e3);
+    return (double)scan / n <= room && (c->N + n - 1) / n <= kStepMatchMaxTraces ? n : 0;
+}
+size_t step_match_lds(const moei_eamc* c, int n_blocks) {
+    const size_t per = (c->N + n_blocks - 1) / n_blocks;
+    return sizeof(StepMatchLds) + per * 16 + (((size_t)c->d.L * c->d.E * 4 + 15) & ~(size_t)15);
 }
 
 int launch_match_topm(const moei_eamc* c, const int32_t* d_eam, int layer_hi, int m, int32_t* d_top, float* d_top_sim,

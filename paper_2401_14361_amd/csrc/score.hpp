@@ -61,14 +61,112 @@ struct KeyLds {
     u64 k[2][kKeyLdsCells];
 };
 
-// Called by all kScoreThreads threads of ONE workgroup: scores for every cell, a 64-bit sort
-// key per cell and list (kNone where the cell is not a candidate) and the two candidate
-// counts.  One wavefront per layer row, the next row's loads out before a row is scored (the trip to the
+// Adds the lanes' candidate counts.  (Every lane of the workgroup adding to the two words itself took 3.9 us.)
+__device__ __forceinline__ void count_candidates(int my_pf, int my_ev, int* s_n) {
+    const unsigned pf = wave_sum_u32_dpp((unsigned)my_pf), ev = wave_sum_u32_dpp((unsigned)my_ev);
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        atomicAdd(&s_n[0], (int)pf);
+        atomicAdd(&s_n[1], (int)ev);
+    }
+}
+
+// One thread: the candidate counts and what the host reads first.
+__device__ __forceinline__ void publish_counts(const ScoreArgs& a, const int* s_n, const int* s_best) {
+    *a.n_pf = s_n[0];
+    *a.n_ev = s_n[1];
+    if (a.host_n) {
+        a.host_n[0] = s_n[0];
+        a.host_n[1] = s_n[1];
+    }
+    if (a.host_best) *a.host_best = s_best[0];
+    if (a.host_seq) {
+        __threadfence_system();  // the matched trace is in host memory before the number that announces it
+        __hip_atomic_store(a.host_seq, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// Models of up to kKeyLdsCells cells: called by all threads (at least 512) of ONE workgroup: scores for every cell, a 64-bit sort
+// key per cell and list (kNone where the cell is not a candidate) and the two candidate counts.  s_n[2] and
+// s_best[kMaxMatchBatch] are LDS; the caller has put the matched trace indices (-1 = none) into s_best, before a barrier; s_cell holds
+// kKeyLdsCells words.
+// The workgroup is alone on its compute unit and goes through this code once, so what counts is the trips to memory and the
+// instructions to fetch: all cells are requested together, whatever rows they belong to, then one short loop runs over the
+// rows, 0.7 us each (26 x 64 cells by 16 wavefronts: 3.1 us, and 6.1 with a wavefront per row, its loads in the loop, and the
+// counts added up by every lane).
+__device__ __forceinline__ void score_cells_small(const ScoreArgs& a, int* s_n, const int* s_best, KeyLds& keys, uint32_t* s_cell) {
+    const int tid = threadIdx.x, T = blockDim.x, lane = tid & (kWave - 1);
+    const int L = a.L, E = a.E, l = a.cur_layer, LE = L * E;
+    constexpr int kRounds = kKeyLdsCells / 512;
+    constexpr uint32_t kResident = 0x80000000u;  // (an aggregate of 16 cells of 24 bits takes 28)
+    uint32_t t[kRounds];
+    size_t at[kRounds];
+    const float inv = 1.0f / (float)E;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int f = min(tid + r * T, LE - 1);
+        const int i = (int)(((float)f + 0.5f) * inv);  // f / E: (f + 0.5) / E is at least 0.5 / E away from an integer, the error of the product less than 2^-11 / E
+        t[r] = a.slot_of[f] >= 0 ? kResident : 0u;
+        at[r] = (size_t)i * (a.n_cap - 1) * E + f;  // the cell of trace 0
+    }
+    const int cur = lane < a.n_cur ? a.cur_idx[lane] : -1;  // lane m holds pick m of the current layer
+#pragma unroll 1
+    for (int b = 0; b < a.B; ++b) {
+        const int n = s_best[b];
+        if (n < 0) continue;  // uniform
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) t[r] += cell_at(a.traces, a.cell_bytes, at[r] + (size_t)n * E);
+    }
+    if (tid < 2) s_n[tid] = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+        if (tid + r * T < LE) s_cell[tid + r * T] = t[r];
+    barrier_lds();
+    int my_ev = 0, my_pf = 0;
+#pragma unroll 1
+    for (int i = tid / kWave; i < L; i += T / kWave) {
+        u64 R = 0;
+#pragma unroll 1
+        for (int j = lane; j - lane < E; j += kWave) {
+            const uint32_t c = j < E ? s_cell[i * E + j] & ~kResident : 0u;
+            R += wave_sum_u32_dpp(c & 0xffffu) + ((u64)wave_sum_u32_dpp(c >> 16) << 16);
+        }
+        const double den = (double)(R ? R : 1ull) * (double)L;
+#pragma unroll 1
+        for (int j = lane; j - lane < E; j += kWave) {
+            bool excluded = false;  // is expert j one of the current picks?
+            if (i == l)
+                for (int m = 0; m < a.n_cur; ++m) excluded |= __builtin_amdgcn_readlane(cur, m) == j;
+            if (j >= E) continue;
+            const int f = i * E + j;
+            const uint32_t c = s_cell[f];
+            const double td = (double)(c & ~kResident);
+            const double v = ((td + a.eps) * (double)(L - i)) / den;
+            double p = 0.0;
+            if (i > l && R > 0) p = (td * (double)(L - i + l)) / den;
+            a.P[f] = (float)p;
+            a.V[f] = (float)v;
+            if (a.host_V) a.host_V[f] = (float)v;
+            // positive doubles order like their bit patterns; ~bits turns descending into ascending
+            const bool is_pf = i > l && p > 0.0 && !(c & kResident);
+            const bool is_ev = (c & kResident) && !excluded;
+            const u64 key_p = is_pf ? ~(u64)__double_as_longlong(p) : kNone;
+            const u64 key_v = is_ev ? (u64)__double_as_longlong(v) : kNone;
+            a.keys[f] = keys.k[0][f] = key_p;
+            a.keys[LE + f] = keys.k[1][f] = key_v;
+            my_pf += is_pf;
+            my_ev += is_ev;
+        }
+    }
+    count_candidates(my_pf, my_ev, s_n);
+    barrier_lds();
+    if (tid == 0) publish_counts(a, s_n, s_best);
+}
+
+// More cells than that: called by all kScoreThreads threads of ONE workgroup.  One wavefront per layer row, the next row's loads out before a row is scored (the trip to the
 // matched cells is what a row costs, and beside the streaming FFN it is a long one).  s_n[2] and
 // s_best[kMaxMatchBatch] are LDS; the caller has put the matched trace indices (-1 = none) into s_best.
-template <bool LARGE>
-__device__ __forceinline__ void score_cells(const ScoreArgs& a, int* s_n, const int* s_best, u64* kp, u64* kv,
-                                            KeyLds* lds_keys) {
+__device__ __forceinline__ void score_cells_large(const ScoreArgs& a, int* s_n, const int* s_best) {
+    u64 *kp = a.keys, *kv = a.keys + a.L * a.E;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wv = tid / kWave;
     const int L = a.L, E = a.E, l = a.cur_layer;
@@ -139,14 +237,8 @@ __device__ __forceinline__ void score_cells(const ScoreArgs& a, int* s_n, const 
             // positive doubles order like their bit patterns; ~bits turns descending into ascending
             const bool is_pf = i > l && p > 0.0 && slot < 0;
             const bool is_ev = slot >= 0 && !excluded;
-            const u64 key_p = is_pf ? ~(u64)__double_as_longlong(p) : kNone;
-            const u64 key_v = is_ev ? (u64)__double_as_longlong(v) : kNone;
-            kp[f] = key_p;
-            kv[f] = key_v;
-            if constexpr (!LARGE) {
-                lds_keys->k[0][f] = key_p;
-                lds_keys->k[1][f] = key_v;
-            }
+            kp[f] = is_pf ? ~(u64)__double_as_longlong(p) : kNone;
+            kv[f] = is_ev ? (u64)__double_as_longlong(v) : kNone;
             my_pf += is_pf;
             my_ev += is_ev;
         };
@@ -166,22 +258,9 @@ __device__ __forceinline__ void score_cells(const ScoreArgs& a, int* s_n, const 
         if (i >= 0) score_row(i, row);
         row = next;
     }
-    if (my_pf) atomicAdd(&s_n[0], my_pf);
-    if (my_ev) atomicAdd(&s_n[1], my_ev);
-    __syncthreads();
-    if (tid == 0) {
-        *a.n_pf = s_n[0];
-        *a.n_ev = s_n[1];
-        if (a.host_n) {
-            a.host_n[0] = s_n[0];
-            a.host_n[1] = s_n[1];
-        }
-        if (a.host_best) *a.host_best = s_best[0];
-        if (a.host_seq) {
-            __threadfence_system();  // the matched trace is in host memory before the number that announces it
-            __hip_atomic_store(a.host_seq, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        }
-    }
+    count_candidates(my_pf, my_ev, s_n);
+    __syncthreads();  // (the keys are read from memory next)
+    if (tid == 0) publish_counts(a, s_n, s_best);
 }
 
 // ---- heads of the two orders
@@ -234,9 +313,14 @@ static_assert(2 * Sel<true>::kThreads <= kScoreThreads, "both lists are searched
 static_assert(Sel<false>::kOwn * Sel<false>::kThreads >= kKeyLdsCells, "a small model's keys fit the registers");
 template <bool LARGE>
 struct ScoreLds {
-    u64 key[2][Sel<LARGE>::kWaves][kHeadMax];
-    int id[2][Sel<LARGE>::kWaves][kHeadMax];
-    std::conditional_t<LARGE, char, KeyLds> cells;
+    union {
+        struct {
+            u64 key[2][Sel<LARGE>::kWaves * kHeadMax];  // candidates of a list: wavefront w's at w * (entries asked for)
+            int id[2][Sel<LARGE>::kWaves * kHeadMax];
+        };
+        uint32_t cell[LARGE ? 1 : kKeyLdsCells];  // before them
+    };
+    std::conditional_t<LARGE, char, KeyLds> keys;
 };
 
 // The h smallest (key, flat id) pairs of the calling wavefront's cells ltid, ltid + STRIDE, ... of one list,
@@ -251,17 +335,21 @@ __device__ __forceinline__ void wave_head(const u64* keys, int LE, int ltid, int
         const int f = ltid + r * STRIDE;
         mine[r] = f < LE ? keys[f] : kNone;
     }
+    // a lane keeps its two best remaining cells: it looks through its cells again only where it has lost both
     bool have_last = false;
     KeyId last{0, -1};
-    KeyId cur{kNone, 0x7fffffff};
-    bool cur_valid = false;  // this lane's best remaining cell is known
+    KeyId cur{kNone, 0x7fffffff}, nxt = cur;
+    int known = 0;
     for (int round = 0; round < want; ++round) {
-        if (!cur_valid) {
-            cur = KeyId{kNone, 0x7fffffff};
+        if (known == 0) {
+            cur = nxt = KeyId{kNone, 0x7fffffff};
             auto consider = [&](u64 k, int f) {
                 if (k == kNone) return;
                 if (have_last && (k < last.k || (k == last.k && f <= last.id))) return;
-                cur = keyid_min(cur, KeyId{k, f});
+                const KeyId c{k, f};
+                const bool first = k < cur.k || (k == cur.k && f < cur.id);
+                nxt = first ? cur : keyid_min(nxt, c);
+                cur = first ? c : cur;
             };
             if constexpr (OWN > 0) {
 #pragma unroll
@@ -269,7 +357,7 @@ __device__ __forceinline__ void wave_head(const u64* keys, int LE, int ltid, int
             } else {
                 for (int f = ltid; f < LE; f += STRIDE) consider(keys[f], f);
             }
-            cur_valid = true;
+            known = 2;
         }
         const KeyId w = wave_keyid_min(cur);
         if (lane == 0) {
@@ -278,11 +366,14 @@ __device__ __forceinline__ void wave_head(const u64* keys, int LE, int ltid, int
         }
         last = w;
         have_last = true;
-        if (cur.id == w.id) cur_valid = false;  // this lane's best has been taken: look for its next one
+        if (cur.id == w.id) {  // this lane's best has been taken: its next one
+            cur = nxt;
+            --known;
+        }
     }
 }
 
-// All kScoreThreads threads of the scoring workgroup call, after score_cells (whose closing barrier
+// All threads of the scoring workgroup (at least 2 * Sel<LARGE>::kThreads) call, after score_cells (whose closing barrier
 // has made the keys visible).  The first kWaves wavefronts search the prefetch list, the next as many the eviction
 // list, others only meet the barrier.  First every wavefront extracts the h smallest pairs of its own cells, then the
 // list's first wavefront the h smallest of those kWaves h candidates the same way.
@@ -306,23 +397,36 @@ __device__ __forceinline__ void select_heads(const ScoreArgs& a, const u64* kp, 
     int32_t* host_out = list == 0 ? a.host_pf_head : a.host_ev_head;
     const int want = list > 1 ? 0 : min(list == 0 ? min(a.h_pf, s_n[0]) : min(a.h_ev, s_n[1]), kHeadMax);
     if (want > 0) {  // uniform over the wavefront
-        u64* okey = hl.key[list][lwave];
-        int* oid = hl.id[list][lwave];
+        u64* okey = hl.key[list] + lwave * want;
+        int* oid = hl.id[list] + lwave * want;
         if (!LARGE || LE <= kOwn * kSelThreads)
             wave_head<kSelThreads, kOwn>(keys, LE, ltid, lane, want, okey, oid);
         else
             wave_head<kSelThreads, 0>(keys, LE, ltid, lane, want, okey, oid);
     }
-    __syncthreads();
-    if (want > 0 && lwave == 0) {
-        // kSelWaves * want candidates, lane-major: candidate c = wave * want + round sits in lane c % 64
+    barrier_lds();
+    const int total = kSelWaves * want;
+    if (want > 0 && lwave == 0 && total <= kWave) {
+        // a candidate per lane: its place is the number of candidates before it (all pairs are different, and the rounds
+        // below are a chain of want arg-mins)
+        const u64* ck = hl.key[list];
+        const int* ci = hl.id[list];
+        const KeyId me = lane < total ? KeyId{ck[lane], ci[lane]} : KeyId{kNone, 0x7fffffff};
+        int before = 0;
+#pragma unroll 8
+        for (int c = 0; c < total; ++c) before += (int)(ck[c] < me.k) | ((int)(ck[c] == me.k) & (int)(ci[c] < me.id));
+        if (me.k != kNone && before < want) {
+            out[before] = me.id;
+            if (host_out) host_out[before] = me.id;
+        }
+    } else if (want > 0 && lwave == 0) {
+        // kSelWaves * want candidates, lane-major: candidate c sits in lane c % 64
         constexpr int kPer = (kSelWaves * kHeadMax + kWave - 1) / kWave;
-        const int total = kSelWaves * want;
         KeyId cand[kPer];
 #pragma unroll
         for (int r = 0; r < kPer; ++r) {
             const int c = lane + r * kWave;
-            cand[r] = c < total ? KeyId{hl.key[list][c / want][c % want], hl.id[list][c / want][c % want]} : KeyId{kNone, 0x7fffffff};
+            cand[r] = c < total ? KeyId{hl.key[list][c], hl.id[list][c]} : KeyId{kNone, 0x7fffffff};
         }
         bool have_last = false;
         KeyId last{0, -1};
@@ -352,11 +456,11 @@ template <bool LARGE>
 __device__ __forceinline__ void score_and_heads(const ScoreArgs& a, ScoreLds<LARGE>& sl, int* s_n, const int* s_best) {
     const u64 *kp = a.keys, *kv = a.keys + a.L * a.E;
     if constexpr (LARGE) {
-        score_cells<LARGE>(a, s_n, s_best, a.keys, a.keys + a.L * a.E, nullptr);
+        score_cells_large(a, s_n, s_best);
     } else {
-        score_cells<LARGE>(a, s_n, s_best, a.keys, a.keys + a.L * a.E, &sl.cells);
-        kp = sl.cells.k[0];
-        kv = sl.cells.k[1];
+        score_cells_small(a, s_n, s_best, sl.keys, sl.cell);
+        kp = sl.keys.k[0];
+        kv = sl.keys.k[1];
     }
     if (a.h_pf > 0 || a.h_ev > 0) select_heads<LARGE>(a, kp, kv, s_n, sl);
 }

@@ -1,0 +1,173 @@
+// The match and the scoring of an asynchronous layer step inside the launch that streams the experts.
+//
+// That launch leaves some compute units free; a few more workgroups in it find the most similar trace of the EAM that
+// routing has just updated (Sec. 4.5 of the paper), score the matched trace and select the heads of both orders, while the
+// others stream weights.  The step is then one chain of three launches on the caller's stream: no kernels of its own for the
+// match, no event calls, no wait between routing and FFN for the fork to the side stream (4 - 6 us).  Four layer steps of the tiny
+// model issued one by one: 221 us on the side stream, 105 like this.
+#pragma once
+
+#include "match.hpp"
+#include "score.hpp"
+
+namespace moei {
+
+constexpr int kStepMatchMaxBlocks = 128;  // never more workgroups than that match
+constexpr int kStepMatchMaxTraces = 1024;  // traces of one of them (their dot products and norms are held in LDS)
+
+struct StepMatchArgs {
+    int n_blocks;            // workgroups that match, behind the ones that stream (0: none)
+    const unsigned long long* norm2;  // [n_cap]
+    const int32_t* q;        // [L*E] the EAM that holds this step's routing
+    unsigned long long* cand;  // [n_blocks][2] winners of the workgroups (dot, norm) ...
+    int32_t* cand_idx;       // [n_blocks] ... and their trace indices
+    unsigned* ticket;        // arrival counter, zero between launches
+    int32_t* best;
+    float* best_sim;
+    ScoreArgs sc;
+};
+// 0: a step over this collection keeps the match on the side stream
+int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_units);
+size_t step_match_lds(const moei_eamc* c, int n_blocks);
+
+#if defined(__HIPCC__)
+
+struct StepMatchLds {
+    ScoreLds<false> score;
+    u64 nq;
+    Best win;
+    int finish;
+    int sn[2];
+    int best[kMaxMatchBatch];
+};
+
+// Dot products of the query (in LDS) with traces t0 .. t0 + nt, added into s_dot (zero before).  Per layer the tile is one run
+// of cells; a thread owns a vector of it and, where the tile is small, every groups-th layer only, and sixteen of
+// its layers are requested together: beside the streaming workgroups a trip to memory takes 2 - 3 us.
+template <typename CT, int VEC>
+__device__ __forceinline__ void step_scan(const ScoreArgs& a, int t0, int nt, const int32_t* qs, u64* s_dot) {
+    using CV = CellVec<CT, VEC>;
+    constexpr int U = 16;
+    const int tid = threadIdx.x, T = blockDim.x, L = a.L, E = a.E;
+    const int rowV = E / VEC, nvec = nt * rowV;
+    const int span = (nvec + kWave - 1) & ~(kWave - 1);
+    const int groups = span >= T || span == 0 ? 1 : min(L, T / span);
+    const int g = groups > 1 ? tid / span : 0;
+    const bool lane_rows = rowV <= kWave && (rowV & (rowV - 1)) == 0;
+    const size_t lstride = (size_t)a.n_cap * E;
+    if (g >= groups) return;
+    for (int p = tid - g * span; p < span; p += T) {  // (uniform over a wavefront)
+        const bool valid = p < nvec;
+        const int pc = valid ? p : 0, row = pc / rowV, col = (pc - row * rowV) * VEC;
+        const CT* src = reinterpret_cast<const CT*>(a.traces) + (size_t)t0 * E + (size_t)pc * VEC;
+        u64 acc = 0;
+        for (int l0 = g; l0 < L; l0 += U * groups) {
+            typename CV::raw v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int l = l0 + u * groups;
+                v[u] = CV::load(src + (size_t)(l < L ? l : l0) * lstride);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int l = l0 + u * groups;
+                if (l < L) acc = CV::dot(v[u], qs + (size_t)l * E + col, acc);
+            }
+        }
+        if (lane_rows) {
+            const u64 t = group_sum_u64(valid ? acc : 0, rowV);  // rows are valid or not as a whole
+            if (valid && (threadIdx.x & (rowV - 1)) == 0) atomicAdd(&s_dot[row], t);
+        } else if (valid && acc != 0) {
+            atomicAdd(&s_dot[row], acc);
+        }
+    }
+}
+
+// Workgroup `blk` of a.n_blocks; the last one to arrive picks among the winners and scores.  Eight to sixteen wavefronts.  All of
+// it is one chain, so what counts is its trips to memory and, since it runs once, the instructions to fetch: the
+// arg-max over a workgroup's traces and the one over the winners are one loop of one wavefront.
+__device__ __forceinline__ void step_match(const StepMatchArgs& a, int blk, unsigned char* smem) {
+    StepMatchLds& s = *reinterpret_cast<StepMatchLds*>(smem);
+    const ScoreArgs& sc = a.sc;
+    const int tid = threadIdx.x, T = blockDim.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int LE = sc.L * sc.E;
+    const int per = (sc.N + a.n_blocks - 1) / a.n_blocks;
+    const int t0 = min(sc.N, blk * per), nt = min(sc.N - t0, per);
+    u64* s_dot = reinterpret_cast<u64*>(smem + sizeof(StepMatchLds));
+    u64* s_norm = s_dot + per;
+    int32_t* qs = reinterpret_cast<int32_t*>(smem + sizeof(StepMatchLds) + ((size_t)per * 16));
+    for (int i = tid; i < nt; i += T) {
+        s_dot[i] = 0;
+        s_norm[i] = a.norm2[t0 + i];
+    }
+    for (int i = tid; i < LE; i += T) qs[i] = a.q[i];
+    barrier_lds();
+    if (sc.cell_bytes == 4) {
+        if (sc.E % 4 == 0) step_scan<int32_t, 4>(sc, t0, nt, qs, s_dot);
+        else step_scan<int32_t, 1>(sc, t0, nt, qs, s_dot);
+    } else {
+        if (sc.E % 8 == 0) step_scan<uint16_t, 8>(sc, t0, nt, qs, s_dot);
+        else step_scan<uint16_t, 1>(sc, t0, nt, qs, s_dot);
+    }
+    barrier_lds();
+    if (wv == 0) {
+        Best me = make_best(0, 1, -1);
+        bool finish = true;
+#pragma unroll 1
+        for (int stage = 0; stage < (a.n_blocks > 1 ? 2 : 1); ++stage) {
+            if (stage == 1) {  // publish this workgroup's winner; the last one to arrive goes on
+                unsigned arrived = 0;
+                if (lane == 0) {
+                    a.cand[2 * blk] = me.dot;
+                    a.cand[2 * blk + 1] = me.nt;
+                    a.cand_idx[blk] = me.idx;
+                    __threadfence();
+                    arrived = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (arrived == (unsigned)a.n_blocks - 1) {
+                        __threadfence();
+                        *a.ticket = 0;  // ready for the next launch on this stream
+                    }
+                }
+                finish = (int)__builtin_amdgcn_readfirstlane((int)arrived) == a.n_blocks - 1;
+                if (!finish) break;
+            }
+            me = make_best(0, 1, -1);
+            for (int i = lane; i < (stage == 0 ? nt : a.n_blocks); i += kWave) {
+                u64 dot, norm;
+                int idx;
+                if (stage == 0) {
+                    dot = s_dot[i];
+                    norm = s_norm[i];
+                    idx = t0 + i;
+                } else {
+                    dot = __hip_atomic_load(&a.cand[2 * i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    norm = __hip_atomic_load(&a.cand[2 * i + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    idx = __hip_atomic_load(&a.cand_idx[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (idx >= 0) me = pick(me, make_best(dot, norm, idx));
+            }
+            me = wave_pick(me);
+        }
+        if (lane == 0) {
+            s.finish = finish;
+            s.win = me;
+            s.best[0] = me.idx;
+        }
+    } else if (wv == 1) {  // meanwhile: the query's norm, for the similarity
+        u64 nq = 0;
+        for (int i = lane; i < LE; i += kWave) nq += (u64)(uint32_t)qs[i] * (uint32_t)qs[i];
+        nq = wave_sum_u64_dpp(nq);
+        if (lane == 0) s.nq = nq;
+    }
+    barrier_lds();
+    if (!s.finish) return;  // uniform
+    if (tid == kWave) {
+        a.best[0] = s.win.idx;
+        a.best_sim[0] = s.win.idx >= 0 ? (float)cosine(s.win.dot, s.nq, s.win.nt) : 0.f;
+    }
+    score_and_heads<false>(sc, s.score, s.sn, s.best);
+}
+
+#endif  // __HIPCC__
+
+}  // namespace moei

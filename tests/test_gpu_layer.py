@@ -508,3 +508,54 @@ def test_heads_of_the_orders_from_several_matches(m, L, E, N, matches):
         assert ev_head.tolist() == rev[:k + depth] and pf_head.tolist() == rpf[:depth]
     cache.close()
     eamc.close()
+
+
+# asynchronous steps whose match runs beside the experts: no trace, one, the most that one workgroup takes and one more, rows
+# of whole vectors (a power of two of them, another number, more than a wavefront's lanes) and of single cells, either width
+# of cells, 2,048 cells; read from other streams than the step's, and after a step that matched on the side stream
+@pytest.mark.parametrize("L,E,N,cell_bytes", [(4, 8, 0, 4), (4, 8, 1, 2), (4, 8, 256, 4), (4, 8, 257, 4), (5, 25, 300, 4),
+                                              (7, 12, 300, 2), (6, 40, 700, 2), (32, 64, 30, 4), (2, 1024, 130, 2), (26, 64, 300, 4)])
+def test_match_beside_the_experts(m, L, E, N, cell_bytes):
+    rng = np.random.default_rng(L * E + N)
+    k, H, I = 3, 64, 8
+    desc = m.ModelDesc(L, E, k, 0, H, I, m.WDTYPE_BF16, 0, EPS)
+    T = (rng.integers(0, 30, size=(N, L, E)) * (rng.random((N, L, E)) < 0.3)).astype(np.int32)
+    T[N // 2:] = T[:N - N // 2]  # equal similarities: the lower index wins
+    eamc = m.Eamc(desc, max(N, 1), cell_bytes)
+    eamc.load(T)
+    cache = m.Cache(desc, L * E, pinned(np.zeros((2, 3 * H * I), dtype=np.uint16)))
+    cache.reset(L * E - k)
+    d_eam = dev(T[N // 3].copy() if N else np.zeros((L, E), dtype=np.int32))
+    y = torch.empty(H, dtype=torch.float32, device="cuda")
+    W, x = dev(np.zeros((E, H), dtype=np.uint16)), dev(np.zeros(H, dtype=np.uint16))
+    torch.cuda.synchronize()
+    streams = [torch.cuda.current_stream(), torch.cuda.Stream(), torch.cuda.Stream()]
+    for step, (layer, sync) in enumerate([(0, False), (L - 2, False), (0, True), (1, False), (L - 2, False)]):
+        bias = rng.standard_normal(E).astype(np.float32)
+        bias[-k:] = -10.0  # the last layer's experts that are not resident are no picks
+        ref_eam = d_eam.cpu().numpy().astype(np.int64)
+        d_bias, s = dev(bias), streams[step % 3]
+        torch.cuda.synchronize()
+        res = cache.get_slots().reshape(L, E) >= 0
+        m.moe_decode_layer(cache, eamc, d_eam, layer, W, d_bias, x, y, sync=sync, stream=s.cuda_stream)
+        if step % 2:
+            cache.join(streams[2 - step % 3].cuda_stream)
+        top, sim = cache.last_matches()
+        last = cache.last_step()
+        picks = np.argsort(-bias, kind="stable")[:k]
+        ref_eam[layer, picks] += 1
+        assert (d_eam.cpu().numpy() == ref_eam).all()
+        best, ref_sim, _ = O.eamc_match(T, ref_eam) if N else (-1, 0.0, None)
+        assert top.tolist() == [best]
+        np.testing.assert_allclose(sim, [ref_sim], rtol=1e-5)
+        P, V, rpf, rev = O.expert_priority(T[best].astype(np.int64) if N else np.zeros((L, E), dtype=np.int64), layer, res, EPS,
+                                           [layer * E + int(j) for j in picks])
+        np.testing.assert_allclose(last["P"], P, rtol=1e-6)
+        np.testing.assert_allclose(last["V"], V, rtol=1e-6)
+        assert last["pf_order"].tolist() == rpf and last["ev_order"].tolist() == rev
+        assert cache.last_heads()[1].tolist() == rev[:k]
+        streams[0].synchronize()
+        s.synchronize()
+    assert cache.error_flags() == 0
+    cache.close()
+    eamc.close()
