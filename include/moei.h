@@ -215,8 +215,8 @@ int expert_ffn_gemv_static(moei_cache* c, const int32_t* d_slot_ids, const float
 /* Step 5 for a decode batch of B independent requests (B <= 16): for every token b,
  *   y[b] = sum_j d_w[b][j] * expert(layer, d_idx[b][j])(x[b]) + sum over the layer's shared experts,
  * with the picks' slots looked up in the device slot table.  Tokens are grouped per activated
- * expert on the device and an expert's weights are streamed once per group of up to 4 of its
- * tokens, so bytes read grow with the number of distinct experts, not with B.
+ * expert on the device and an expert's weights are streamed once per group of its tokens (up to 16 of them
+ * on the matrix cores, else up to 4), so bytes read grow with the number of distinct experts, not with B.
  * d_idx[B][k] int32, d_w[B][k] fp32, d_x[B][H] in desc->wdtype, d_y[B][H] fp32.  A pick that is
  * not resident contributes nothing and raises error flag bit 1; a pick outside [0, E) (a token
  * that got no picks) is passed over.  Needs H to be a multiple of 64 lanes x 16 bytes, E <= 256

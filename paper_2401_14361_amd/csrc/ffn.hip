@@ -529,7 +529,7 @@ struct GroupArgs {
     const float* w;              // [B][k] gate weights
     const int32_t* slot_of_row;  // slot_of + layer*E
     int B, k, E, n_shared, shared_base, tb;
-    GroupItem* items;
+    void* items;  // GroupItem or GmItemOut
     int32_t* n_items;
     int32_t* flags;
 };
@@ -643,7 +643,7 @@ __device__ __forceinline__ int build_items(const GroupArgs& a, GroupItem* s_item
     n += a.n_shared * tiles;
     __syncthreads();
     if (publish) {
-        for (int q = tid; q < n; q += blockDim.x) a.items[q] = s_items[q];
+        for (int q = tid; q < n; q += blockDim.x) reinterpret_cast<GroupItem*>(a.items)[q] = s_items[q];
         if (tid == 0) *a.n_items = n;
     }
     return n;
@@ -678,16 +678,21 @@ struct GroupedShape {
 // requests of 32 experts of 700 units, H = 1,024, 17.3 / 23.1 / 35.6 / 42.7 and 14.9 / 21.0 / 32.0 / 40.0.)
 // Where the items divide the workgroups nobody changes items and every share is the same as it is: there a
 // start counts nothing (one request, 8 items: 34.4 us with it, 33.5 without).
-__device__ __host__ inline long grouped_range_begin(long total, int g, int G) { return total * g / G; }
+// (32 bits hold it: a pool of 16 (k + n_shared) x I < 2^31 units of at least 3 KB is 400 GB.  A 64-bit division is some 150
+// instructions, and a workgroup makes five before its first load.)
+__device__ __forceinline__ int grouped_range_begin(int total, int g, int G) {  // total * g / G
+    const int q = total / G, r = total - q * G;
+    return q * g + r * g / G;
+}
 __host__ inline int grouped_cost(int H, int wb) { return (180 * 1024 + 3 * H * wb - 1) / (3 * H * wb); }
 __device__ __forceinline__ int grouped_start(int n_items, int G, int cost) {
     return n_items > 0 && G % n_items == 0 ? 0 : cost;
 }
 // The next segment of a range: rows r0 .. r1 of `item` (none: r0 == r1); *row moves past it.
-__device__ __forceinline__ void grouped_segment(long* row, long end, int I, int cost, int* item, int* r0, int* r1) {
-    *item = (int)(*row / (I + cost));
-    const int c0 = (int)(*row - (long)*item * (I + cost));
-    const int c1 = (int)min((long)(I + cost), c0 + (end - *row));
+__device__ __forceinline__ void grouped_segment(int* row, int end, int I, int cost, int* item, int* r0, int* r1) {
+    *item = *row / (I + cost);
+    const int c0 = *row - *item * (I + cost);
+    const int c1 = min(I + cost, c0 + (end - *row));
     *row += c1 - c0;
     *r0 = max(0, c0 - cost);
     *r1 = max(0, c1 - cost);
@@ -720,9 +725,9 @@ __global__ void __launch_bounds__((kGroupedWaves * kWave)) ffn_grouped_kernel(Gr
     int* s_pick = reinterpret_cast<int*>(s_items + a.max_items);  // [2][B*k]
     const int n_items = build_items(a.grp, s_items, s_pick, &s_is, blockIdx.x == 0);
     const int cost = grouped_start(n_items, gridDim.x, a.cost);
-    const long total = (long)n_items * (I + cost);
-    const long R0 = grouped_range_begin(total, blockIdx.x, gridDim.x);
-    const long R1 = grouped_range_begin(total, blockIdx.x + 1, gridDim.x);
+    const int total = n_items * (I + cost);
+    const int R0 = grouped_range_begin(total, blockIdx.x, gridDim.x);
+    const int R1 = grouped_range_begin(total, blockIdx.x + 1, gridDim.x);
     auto scalar = [](size_t v) -> size_t {
         uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
         uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
@@ -734,7 +739,7 @@ __global__ void __launch_bounds__((kGroupedWaves * kWave)) ffn_grouped_kernel(Gr
     auto ld = [&](size_t unit, int off) -> Raw { return V::load_once(pool + unit + off + lane_off); };
 
     int seg = 0;
-    for (long row = R0; row < R1 && seg < a.seg_max; ++seg) {  // uniform over the workgroup
+    for (int row = R0; row < R1 && seg < a.seg_max; ++seg) {  // uniform over the workgroup
         int item, r0, r1;
         grouped_segment(&row, R1, I, cost, &item, &r0, &r1);
         if (r0 == r1) continue;
@@ -846,13 +851,449 @@ __global__ void __launch_bounds__((kGroupedWaves * kWave)) ffn_grouped_kernel(Gr
     }
 }
 
+// ---- the same for bf16 weights on the matrix cores: an item is one expert with up to 16 of its picks, so a call streams every
+// activated expert once (the shared ones too), whatever the batch.
+//
+// grid: a workgroup of eight wavefronts per compute unit.  Its range of the items' units is cut into blocks of 16 units, and
+// wavefront w has columns w * HW .. + HW (HW = H / 8) of all three matrices: for gate and up its share of the sum over
+// the columns (D = A B, A = 16 units x 32 columns, B = 32 columns x 16 tokens, bf16 products added in fp32), which eight
+// partial tiles in LDS are added up in wavefront order; for down those columns of y, whose sums stay in its registers
+// from an item's first block to its last.  The activations stay fp32: the down product runs on the fp32 matrix instruction (A =
+// 16 tokens x 4 units, B = 4 units x 16 columns), which lets a lane use the eight columns of one 16-byte piece as the same column of
+// eight tiles, so nothing is transposed; its rate is a quarter of what would hold the stream up.
+// The weights go from global memory straight into a ring of S::kRing stages per wavefront (16 rows of 128 columns: 4 KiB; no
+// barrier, the waits are counted), the token rows of an item through the same ring before its first block.  The ring runs on across
+// blocks and items: a block's down rows come behind the next block's gate and up rows, so that the exchange of the
+// partial tiles (two barriers that wait for LDS only) does not hold it up, and what an item's end costs is the store of its rows.
+// Bound by the stream: sixteen requests of the 64-expert shape 155 us a call, 865 MB at 5.9 TB/s between start and end; with
+// items of four tokens in registers (the kernel above: the shared experts pass four times, and at a segment's end the window
+// drains and eight rows a token are added through LDS) 182.  Loads without the non-temporal hint took 12 % longer, stages of 128
+// columns, four in the ring, 1 %.
+// Rounding: sums run as several short chains (a chain per matrix instruction of a stage, two per block and down tile, a block's sum
+// added to those before it), so that the error against 64 bits is that of the kernel above or less: relative 2-norm 1.6 - 2.0e-7, there
+// 1.6 - 2.1e-7; with one chain for the columns of a wavefront and one for an item's units it was 3.3e-7.
+constexpr int kGmTokens = 16;
+constexpr int kGmUnits = 16;  // of a block
+constexpr int kGmMaxSegs = 16;
+typedef float gm_f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 gm_bf16x8 __attribute__((ext_vector_type(8)));
+
+struct GmItem {   // in LDS
+    int slot, first, ntok;  // its picks are entries first .. + ntok of the sorted list
+};
+struct GmItemOut {  // for the reduction: token j in bits 4 j .. + 4
+    int32_t slot, ntok;
+    unsigned long long toks;
+};
+struct GmSeg {
+    int item, r0, r1;
+};
+
+struct GroupedMmArgs {
+    const uint16_t* pool;
+    size_t slot_elems;
+    GroupArgs grp;  // items / n_items: GmItemOut
+    int max_items, n_list;  // room in LDS: items, entries of the sorted list
+    const uint16_t* x;      // [B][H]
+    float* part;            // [workgroups][seg_max][kGmTokens][H]
+    int H, I, cost, seg_max;
+};
+
+template <int HW>
+struct GmShape {
+    static constexpr int kCols = HW == 512 ? 128 : HW;  // of a stage (256 need registers that rows of 4,096 don't leave)
+    static constexpr int kStages = HW / kCols;          // per matrix and block
+    static constexpr bool kKeepX = HW != 512;           // the tokens of an item stay in registers, else they pass with every block
+    static constexpr int kRing = HW == 512 ? 4 : 2;     // stages
+    static constexpr int kStageBytes = kGmUnits * kCols * 2;
+    static constexpr int kLoads = kStageBytes / 1024;
+};
+constexpr size_t kGmPartBytes = (size_t)kGroupedWaves * 2 * 256 * 4;
+constexpr size_t kGmActBytes = (size_t)2 * 256 * 4;
+
+template <int HW>
+size_t gm_lds(int max_items, int n_list) {
+    return (size_t)kGroupedWaves * GmShape<HW>::kRing * GmShape<HW>::kStageBytes + kGmPartBytes + kGmActBytes +
+           (((size_t)n_list * 8 + (size_t)max_items * sizeof(GmItem) + 15) & ~(size_t)15);
+}
+
+// The item list of a call, as build_items forms it, with the picks sorted by expert (and by token within one) in a list of
+// their own: s_tok / s_w, behind them the tokens 0 .. B - 1 with weight 1 for the shared experts.  `scratch` is free afterwards.
+__device__ __forceinline__ int gm_build_items(const GroupArgs& a, GmItem* s_items, int* s_tok, float* s_w, unsigned char* scratch,
+                                              bool publish) {
+    ItemScratch* sc = reinterpret_cast<ItemScratch*>(scratch);
+    int* s_pick = reinterpret_cast<int*>(scratch + ((sizeof(ItemScratch) + 15) & ~(size_t)15));
+    int* s_first = s_pick + 512;  // [256] the expert's first entry of the list
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int n_pick = a.B * a.k;  // at most 512, one per thread
+    const int row_slot = tid < a.E ? a.slot_of_row[tid] : -1;
+    int my_e = -1;
+    float my_w = 0.f;
+    if (tid < n_pick) {
+        my_e = a.idx[tid];
+        my_w = a.w[tid];
+        if (my_e < 0 || my_e >= a.E) my_e = -1;  // a token without picks (no softmax exists for its logits)
+    }
+    s_pick[tid] = my_e;
+    if (tid < 256) sc->cnt[tid] = 0;
+    __syncthreads();
+    int rank = 0;
+    if (tid < n_pick) {
+        for (int q = 0; q < tid; q += 4) {
+            const int4 v = *reinterpret_cast<const int4*>(s_pick + q);
+            rank += (v.x == my_e) + ((q + 1 < tid) & (v.y == my_e)) + ((q + 2 < tid) & (v.z == my_e)) + ((q + 3 < tid) & (v.w == my_e));
+        }
+        if (my_e >= 0) atomicAdd(&sc->cnt[my_e], 1);
+    }
+    __syncthreads();
+    // items and list entries per expert, both scanned over the experts (at most 512 each: one word)
+    int ntok = tid < a.E ? sc->cnt[tid & 255] : 0;
+    if (ntok > 0 && row_slot < 0) {  // not resident: contributes nothing, flagged
+        if (publish) atomicOr(a.flags, 2);
+        ntok = 0;
+    }
+    const int n_mine = (ntok + kGmTokens - 1) / kGmTokens;
+    const int mine = n_mine << 16 | ntok;
+    int incl = mine;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int up = __shfl_up(incl, off, kWave);
+        if (lane >= off) incl += up;
+    }
+    if (lane == kWave - 1 && wv < 4) sc->wsum[wv] = incl;
+    __syncthreads();
+    const int total = sc->wsum[0] + sc->wsum[1] + sc->wsum[2] + sc->wsum[3];
+    const int n_list = total & 0xffff;
+    int n = total >> 16;
+    if (tid < 256) {
+        int before = incl - mine;
+        for (int w = 0; w < wv; ++w) before += sc->wsum[w];
+        s_first[tid] = before & 0xffff;
+        sc->slot[tid] = ntok > 0 ? row_slot : -1;
+        for (int i = 0; i < n_mine; ++i)
+            s_items[(before >> 16) + i] = GmItem{row_slot, (before & 0xffff) + i * kGmTokens, min(kGmTokens, ntok - i * kGmTokens)};
+    }
+    __syncthreads();
+    if (my_e >= 0 && sc->slot[my_e] >= 0) {
+        const int at = s_first[my_e] + rank;
+        s_tok[at] = tid / a.k;
+        s_w[at] = my_w;
+    }
+    if (tid < a.B) {
+        s_tok[n_list + tid] = tid;
+        s_w[n_list + tid] = 1.0f;
+    }
+    for (int q = tid; q < a.n_shared; q += blockDim.x) s_items[n + q] = GmItem{a.shared_base + q, n_list, a.B};
+    n += a.n_shared;
+    __syncthreads();
+    if (publish) {
+        GmItemOut* out = reinterpret_cast<GmItemOut*>(a.items);
+        for (int q = tid; q < n; q += blockDim.x) {
+            const GmItem it = s_items[q];
+            unsigned long long toks = 0;
+            for (int j = 0; j < it.ntok; ++j) toks |= (unsigned long long)s_tok[it.first + j] << (4 * j);
+            out[q] = GmItemOut{it.slot, it.ntok, toks};
+        }
+        if (tid == 0) *a.n_items = n;
+    }
+    return n;
+}
+
+template <int HW>
+__global__ void __launch_bounds__((kGroupedWaves * kWave), 2) ffn_grouped_mm_kernel(GroupedMmArgs a) {
+    using S = GmShape<HW>;
+    constexpr int H = HW * kGroupedWaves;
+    constexpr int RB = S::kCols * 2;       // bytes of a stage's row
+    constexpr int CH = RB / 16;            // its 16-byte pieces: 8 to 32
+    constexpr int KS = S::kCols / 32;      // matrix instructions per gate or up stage
+    constexpr int CPL = S::kCols >= 128 ? 8 : 4;  // columns per lane of a group of 16 CPL columns
+    constexpr int GR = S::kCols / (16 * CPL);     // such groups in a stage
+    extern __shared__ __align__(16) float smem[];
+    __shared__ GmSeg s_seg[kGmMaxSegs];
+    unsigned char* ring0 = reinterpret_cast<unsigned char*>(smem);
+    float* s_part = reinterpret_cast<float*>(ring0 + (size_t)kGroupedWaves * S::kRing * S::kStageBytes);  // [wavefront][gate, up][256]
+    float* s_act = s_part + kGroupedWaves * 2 * 256;  // [2][unit][token]
+    int* s_tok = reinterpret_cast<int*>(s_act + 2 * 256);
+    float* s_w = reinterpret_cast<float*>(s_tok + a.n_list);
+    GmItem* s_items = reinterpret_cast<GmItem*>(s_w + a.n_list);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int I = a.I;
+    const int n_items = gm_build_items(a.grp, s_items, s_tok, s_w, reinterpret_cast<unsigned char*>(s_part), blockIdx.x == 0);
+    int n_seg = 0, n_blocks = 0;
+    {  // the workgroup's segments (the empty ones keep their number: the reduction counts them too)
+        const int cost = grouped_start(n_items, gridDim.x, a.cost);
+        const int total = n_items * (I + cost);
+        int row = grouped_range_begin(total, blockIdx.x, gridDim.x);
+        const int R1 = grouped_range_begin(total, blockIdx.x + 1, gridDim.x);
+        for (; row < R1 && n_seg < a.seg_max; ++n_seg) {
+            GmSeg sg;
+            grouped_segment(&row, R1, I, cost, &sg.item, &sg.r0, &sg.r1);
+            if (tid == 0) s_seg[n_seg] = sg;
+            n_blocks += (sg.r1 - sg.r0 + kGmUnits - 1) / kGmUnits;
+        }
+    }
+    __syncthreads();
+    if (n_blocks == 0) return;
+
+    // One block of 16 units (the last of a segment may have fewer), as both the loads and the products walk through them.
+    struct Block {
+        const unsigned char* base;  // gate row of its first unit, this wavefront's first column
+        int seg, row, valid, first_tok, ntok;
+        bool first, last;  // of its segment
+    };
+    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    auto block_at = [&](Block& b, int seg, int row) {  // the block at `row` of segment `seg`, or of the next one that has rows
+        int r0 = uniform(s_seg[seg].r0), r1 = uniform(s_seg[seg].r1);
+        if (row < 0) row = r0;
+        while (row >= r1) {  // (the caller knows that there is a block)
+            ++seg;
+            row = r0 = uniform(s_seg[seg].r0);
+            r1 = uniform(s_seg[seg].r1);
+        }
+        const GmItem* it = s_items + uniform(s_seg[seg].item);
+        b.seg = seg;
+        b.row = row;
+        b.first = row == r0;
+        b.last = row + kGmUnits >= r1;
+        b.valid = min(kGmUnits, r1 - row);
+        b.first_tok = uniform(it->first);
+        b.ntok = uniform(it->ntok);
+        b.base = reinterpret_cast<const unsigned char*>(a.pool) + ((size_t)uniform(it->slot) * a.slot_elems + (size_t)row * 3 * H + wv * HW) * 2;
+    };
+
+    // ---- the ring's loads.  Piece p of row r of a stage lies at place p ^ r of the row (no bank conflicts in the reads below).
+    const uint32_t my_ring = lds_address(ring0) + (uint32_t)wv * (S::kRing * S::kStageBytes);
+    constexpr int RPL = 1024 / RB;  // rows per load
+    // byte offset of this lane's piece in load i of a stage whose rows lie `stride` bytes apart, rows past `rows` repeating the last.
+    // (Formed anew at each load: kept across the loop, these offsets push the sums of rows of 4,096 out of the registers.)
+    auto opaque = [](int v) {
+        asm volatile("" : "+v"(v));
+        return v;
+    };
+    auto row_of = [&](int lv, int i, int rows) { return min(i * RPL + lv / CH, rows - 1); };
+    auto piece_of = [&](int lv, int i) { return (uint32_t)(((lv % CH) ^ ((i * RPL + lv / CH) & (CH - 1))) * 16); };
+    Block ib, ip;        // the block whose gate and up rows are loaded now, and the one before it (its down rows follow)
+    bool have_b = true, have_p = false;
+    int left = n_blocks, step = 0, slot_i = 0;
+    block_at(ib, 0, -1);
+    auto issue = [&]() {  // the next stage of the sequence; past its end one piece again and again, so that every stage has as many loads
+        const uint32_t dst = my_ring + (uint32_t)slot_i * S::kStageBytes;
+        slot_i = (slot_i + 1) % S::kRing;
+        const int lv = opaque(lane);
+        auto weights = [&](const unsigned char* base, int rows) {
+#pragma unroll
+            for (int i = 0; i < S::kLoads; ++i)
+                load16_once_to_lds_at(base, (uint32_t)row_of(lv, i, rows) * (3 * H * 2) + piece_of(lv, i), dst + i * 1024);
+        };
+        const bool with_x = have_b && (ib.first || !S::kKeepX);
+        const int per = with_x ? 3 : 2;
+        const int n_gu = have_b ? per * S::kStages : 0;
+        if (have_b && step < n_gu) {
+            const int c = per == 3 ? step / 3 : step / 2;
+            const int kind = step - c * per + (per == 2);  // 0: tokens, 1: gate, 2: up
+            if (kind == 0) {
+                const unsigned char* base = reinterpret_cast<const unsigned char*>(a.x) + (size_t)(wv * HW + c * S::kCols) * 2;
+#pragma unroll
+                for (int i = 0; i < S::kLoads; ++i)
+                    load16_to_lds_at(base, (uint32_t)s_tok[ib.first_tok + row_of(lv, i, ib.ntok)] * (H * 2) + piece_of(lv, i), dst + i * 1024);
+            } else {
+                weights(ib.base + (size_t)((kind - 1) * H + c * S::kCols) * 2, ib.valid);
+            }
+        } else if (have_p) {
+            weights(ip.base + (size_t)(2 * H + (step - n_gu) * S::kCols) * 2, ip.valid);
+        } else {
+#pragma unroll
+            for (int i = 0; i < S::kLoads; ++i) load16_to_lds_at(a.x, 0u, dst + i * 1024);
+        }
+        ++step;
+        if (step >= n_gu + (have_p ? S::kStages : 0) && (have_b || have_p)) {  // on to the next block
+            step = 0;
+            ip = ib;
+            have_p = have_b;
+            if (have_b && --left > 0)
+                block_at(ib, ip.seg, ip.row + kGmUnits);
+            else
+                have_b = false;
+        }
+    };
+#pragma unroll 1
+    for (int i = 0; i < S::kRing; ++i) issue();
+
+    // ---- the products
+    int slot_c = 0;
+    auto next_stage = [&]() {  // the oldest stage has landed; where it lies
+        wait_vm_fence<(S::kRing - 1) * S::kLoads>();
+        const unsigned char* st = ring0 + (size_t)wv * (S::kRing * S::kStageBytes) + (size_t)slot_c * S::kStageBytes;
+        slot_c = (slot_c + 1) % S::kRing;
+        return st;
+    };
+    auto read_rows = [&](const unsigned char* st, gm_bf16x8 (&v)[KS]) {  // lane: row lane % 16, columns 32 s + 8 grp .. + 8 of step s
+        const int lv = opaque(lane), r = lv & 15;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) v[s] = *reinterpret_cast<const gm_bf16x8*>(st + r * RB + (((4 * s + (lv >> 4)) ^ (r & (CH - 1))) * 16));
+    };
+    constexpr bool keep = S::kKeepX;
+    gm_bf16x8 xr[keep ? S::kStages : 1][KS];  // the tokens of the item
+    constexpr int NT = HW == 512 ? 2 : 4;  // down tiles at a time ...
+    constexpr int NC = HW == 512 ? 1 : 2;  // ... and chains of products in each
+    gm_f32x4 y[S::kStages * GR][CPL];
+#pragma unroll
+    for (int c = 0; c < S::kStages * GR; ++c)
+#pragma unroll
+        for (int j = 0; j < CPL; ++j) y[c][j] = gm_f32x4{0.f, 0.f, 0.f, 0.f};
+    Block cb, cp;  // this block, the one before
+    block_at(cb, 0, -1);
+#pragma unroll 1
+    for (int n = 0; n <= n_blocks; ++n) {
+        if (n < n_blocks) {
+            if (n > 0) block_at(cb, cp.seg, cp.row + kGmUnits);
+            gm_f32x4 g[KS], u[KS];
+#pragma unroll
+            for (int q = 0; q < KS; ++q) g[q] = u[q] = gm_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < S::kStages; ++c) {
+                if (!keep || cb.first) {
+                    read_rows(next_stage(), xr[keep ? c : 0]);
+                    wait_lds_fence();
+                    issue();
+                }
+                gm_bf16x8 w[KS];
+                __builtin_amdgcn_sched_barrier(0);  // (a stage's operands are read when they are due: rows of 4,096 have no registers to spare)
+                read_rows(next_stage(), w);
+                wait_lds_fence();
+                issue();
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < KS; ++s) g[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[s], xr[keep ? c : 0][s], g[s], 0, 0, 0);
+                read_rows(next_stage(), w);
+                wait_lds_fence();
+                issue();
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < KS; ++s) u[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[s], xr[keep ? c : 0][s], u[s], 0, 0, 0);
+            }
+#pragma unroll
+            for (int d = KS / 2; d > 0; d /= 2)
+#pragma unroll
+                for (int q = 0; q < d; ++q) {
+                    g[q] += g[q + d];
+                    u[q] += u[q + d];
+                }
+            barrier_lds();  // the partial tiles of the block before have been added up
+            float* part = s_part + wv * 512 + opaque(lane) * 4;  // units 4 (lane / 16) .. + 4 of token lane % 16
+            *reinterpret_cast<gm_f32x4*>(part) = g[0];
+            *reinterpret_cast<gm_f32x4*>(part + 256) = u[0];
+        }
+        barrier_lds();
+        if (n < n_blocks) {  // a lane below 32 adds a gate value up, one above the up value of the same unit and token
+            const int lv = opaque(lane), e = wv * 32 + (lv & 31), unit = 4 * (e >> 6) + (e & 3), tok = (e >> 2) & 15;
+            float p[kGroupedWaves];
+#pragma unroll
+            for (int w = 0; w < kGroupedWaves; ++w) p[w] = s_part[(w * 2 + (lv >> 5)) * 256 + e];
+            const float v = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+            const float up = __shfl_xor(v, 32, kWave);
+            if (lv < 32) {
+                const float gate = tok < cb.ntok ? s_w[cb.first_tok + tok] : 0.f;
+                s_act[(n & 1) * 256 + unit * 16 + tok] = unit < cb.valid && tok < cb.ntok ? silu(v) * up * gate : 0.f;
+            }
+        }
+        if (n > 0) {  // the block before: its activations are complete since the barrier
+            const float* act = s_act + ((n - 1) & 1) * 256;
+            float av[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) av[s] = act[s * 64 + opaque(lane)];  // token lane % 16, unit 4 s + grp
+#pragma unroll
+            for (int c = 0; c < S::kStages; ++c) {
+                __builtin_amdgcn_sched_barrier(0);
+                const unsigned char* st = next_stage();
+#pragma unroll
+                for (int h = 0; h < GR; ++h) {
+                    const int lv = opaque(lane), l16 = lv & 15, grp = lv >> 4;
+                    uint32_t w[4][CPL / 2];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {  // unit 4 s + grp, columns CPL * (lane % 16) .. + CPL
+                        const int r = 4 * s + grp;
+                        if constexpr (CPL == 8) {
+                            const uint4 v = *reinterpret_cast<const uint4*>(st + r * RB + (((h * 16 + l16) ^ (r & (CH - 1))) * 16));
+                            w[s][0] = v.x; w[s][1] = v.y; w[s][2] = v.z; w[s][3] = v.w;
+                        } else {
+                            const uint2 v = *reinterpret_cast<const uint2*>(st + r * RB + (((l16 >> 1) ^ (r & (CH - 1))) * 16) + (l16 & 1) * 8);
+                            w[s][0] = v.x; w[s][1] = v.y;
+                        }
+                    }
+                    if (h == GR - 1) {
+                        wait_lds_fence();
+                        issue();
+                    }
+                    if (cp.valid < kGmUnits) {  // uniform: rows past the block repeat its last one, and zero times infinity is not zero
+#pragma unroll
+                        for (int s = 0; s < 4; ++s)
+#pragma unroll
+                            for (int j = 0; j < CPL / 2; ++j) w[s][j] = 4 * s + grp < cp.valid ? w[s][j] : 0u;
+                    }
+#pragma unroll
+                    for (int j0 = 0; j0 < CPL; j0 += NT) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        gm_f32x4 t[NC][NT];
+#pragma unroll
+                        for (int q = 0; q < NC; ++q)
+#pragma unroll
+                            for (int j = 0; j < NT; ++j) t[q][j] = gm_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int s = 0; s < 4; ++s)
+#pragma unroll
+                            for (int j = 0; j < NT; ++j) {
+                                const uint32_t v = w[s][(j0 + j) / 2];
+                                t[s % NC][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s], j & 1 ? bf16_hi(v) : bf16_lo(v), t[s % NC][j], 0, 0, 0);
+                            }
+#pragma unroll
+                        for (int j = 0; j < NT; ++j)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) y[c * GR + h][j0 + j][i] = (cp.first ? 0.f : y[c * GR + h][j0 + j][i]) + (NC == 1 ? t[0][j][i] : t[0][j][i] + t[NC - 1][j][i]);
+                    }
+                }
+            }
+            if (cp.last) {  // tokens 4 grp .. + 4, columns CPL * (lane % 16) .. + CPL of every stage
+                const int lv = opaque(lane), l16 = lv & 15, grp = lv >> 4;
+                float* out = a.part + ((size_t)blockIdx.x * a.seg_max + cp.seg) * kGmTokens * H + wv * HW + l16 * CPL;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (4 * grp + i < cp.ntok)
+#pragma unroll
+                        for (int c = 0; c < S::kStages * GR; ++c)
+#pragma unroll
+                            for (int j = 0; j < CPL; j += 4)
+                                *reinterpret_cast<float4*>(out + (size_t)(4 * grp + i) * H + c * (16 * CPL) + j) =
+                                    make_float4(y[c][j][i], y[c][j + 1][i], y[c][j + 2][i], y[c][j + 3][i]);
+            }
+        }
+        cp = cb;
+    }
+    wait_vm_fence<0>();  // nothing is on its way into this LDS when it is given back
+}
+
 // y[b][h] = sum of the partial rows of the segments whose item holds token b.  The workgroup
 // first lists those rows in segment order (workgroup-major) in LDS; 32 slices of the list are
 // then added by a thread each, all of a slice's loads in flight together, and the slice sums are
 // added in slice order.  grid (H / 32, B), 256 threads = 32 slices x 8 float4 columns;
 // dynamic LDS: 2 * n_blocks * seg_max ints.
+__device__ __forceinline__ int place_of(const GroupItem& it, int b) {
+    int j = -1;
+    for (int q = 0; q < it.ntok; ++q)
+        if (it.tok[q] == b) j = q;
+    return j;
+}
+__device__ __forceinline__ int place_of(const GmItemOut& it, int b) {
+    const unsigned long long t = it.toks;
+    int j = -1;
+    for (int q = 0; q < it.ntok; ++q)
+        if ((int)(t >> (4 * q) & 15) == b) j = q;
+    return j;
+}
+template <typename Item>
 __global__ void __launch_bounds__(256) ffn_grouped_reduce_kernel(const float* __restrict__ part,
-                                                                 const GroupItem* __restrict__ items,
+                                                                 const Item* __restrict__ items,
                                                                  const int32_t* __restrict__ n_items, int tb, int I,
                                                                  int cost, int H, int n_blocks, int seg_max,
                                                                  float* __restrict__ y) {
@@ -864,17 +1305,17 @@ __global__ void __launch_bounds__(256) ffn_grouped_reduce_kernel(const float* __
     int32_t* s_list = s_rows + n;  // the rows that exist, in segment order
     const int b = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     cost = grouped_start(*n_items, n_blocks, cost);
-    const long total = (long)*n_items * (I + cost);
+    const int total = *n_items * (I + cost);
     for (int g = tid; g < n_blocks; g += 256) {
-        long row = grouped_range_begin(total, g, n_blocks);
-        const long R1 = grouped_range_begin(total, g + 1, n_blocks);
+        int row = grouped_range_begin(total, g, n_blocks);
+        const int R1 = grouped_range_begin(total, g + 1, n_blocks);
         for (int seg = 0; seg < seg_max; ++seg) {
             int entry = -1;
             if (row < R1) {
                 int item, r0, r1;
                 grouped_segment(&row, R1, I, cost, &item, &r0, &r1);
-                for (int j = 0; r0 < r1 && j < items[item].ntok; ++j)
-                    if (items[item].tok[j] == b) entry = (g * seg_max + seg) * tb + j;
+                const int j = r0 < r1 ? place_of(items[item], b) : -1;
+                if (j >= 0) entry = (g * seg_max + seg) * tb + j;
             }
             s_rows[g * seg_max + seg] = entry;
         }
@@ -1048,11 +1489,34 @@ int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_
 }
 
 
+namespace {
+// Which kernel a bf16 call takes.  Both stream an expert once for up to four requests (rows of 4,096: the vector kernel once per
+// request), and the matrix kernel takes 1 - 7 us longer to start and to end, so it has to save something: it does from
+// four requests on where an expert is expected to serve more than 1.25 of them, by as much as there is to stream.  us a call,
+// vector / matrix kernel: 64 experts of 1,408 units + 2 shared, H = 2,048, top 6, 1 / 2 / 3 / 4 / 8 / 16 requests 33.9 / 37.1, 50.2 / 51.7, 66.4 /
+// 65.4, 83.2 / 77.4, 125 / 115, 182 / 155; 8 of 6,000 units, H = 4,096, top 2, 8 / 16 requests 268 / 216, 439 / 226;
+// 100 of 2,000, H = 1,024, top 8, 6 requests (1.2 of them an expert) 85.3 / 86.2; 20 of 300, H = 4,096, top 1, 8 requests (1.2) 22.5 /
+// 26.1; 16 of 400, H = 512, top 4, 4 / 6 / 12 requests (1.5 / 1.8 / 3.1) 14.7 / 15.5, 16.8 / 15.8, 20.0 / 16.6.
+bool grouped_mm(const moei_model_desc& d, int B) {
+    if (d.wdtype != MOEI_WDTYPE_BF16 || B < 4) return false;
+    double none = 1.0;  // share of the experts that nobody picks, picks being even
+    for (int b = 0; b < B; ++b) none *= 1.0 - (double)d.k / d.E;
+    const double streamed = d.E * (1.0 - none) + d.n_shared;
+    return (B * (d.k + d.n_shared) - 1.25 * streamed) * 6.0 * d.H * d.I >= 5e6;
+}
+// items of 16 picks: the sum over the experts of ceil(picks / 16), and the shared experts
+int gm_max_items(const moei_model_desc& d, int B) { return std::min(B * d.k, d.E + (B * d.k + kGmTokens - 1) / kGmTokens) + d.n_shared; }
+int gm_segments(const moei_model_desc& d) { return grouped_seg_max(gm_max_items(d, kMaxBatch), compute_units()); }
+size_t gm_rows(const moei_model_desc& d) { return (size_t)compute_units() * gm_segments(d) * kGmTokens; }
+}  // namespace
+
 int grouped_max_items(const moei_model_desc& d) { return kMaxBatch * d.k + d.n_shared * kMaxBatch; }
-size_t grouped_item_bytes() { return sizeof(GroupItem); }
+size_t grouped_item_bytes() { return std::max(sizeof(GroupItem), sizeof(GmItemOut)); }
 size_t grouped_part_floats(const moei_model_desc& d) {
     const int G = compute_units();
-    return (size_t)G * grouped_seg_max(grouped_max_items(d), G) * kMaxGroup * d.H;
+    const size_t rows = (size_t)G * grouped_seg_max(grouped_max_items(d), G) * kMaxGroup;
+    if (d.wdtype != MOEI_WDTYPE_BF16) return rows * d.H;
+    return std::max(rows, gm_rows(d)) * d.H + (size_t)kMaxBatch * d.H / 2;  // behind the rows: an aligned copy of the tokens
 }
 
 namespace {
@@ -1086,9 +1550,43 @@ int launch_grouped_typed(const moei_model_desc& d, GroupedFfnArgs ga, int B, flo
                       kWave * V::N);
     }
 #undef MOEI_GROUPED_CASE
-    launch(K_FFN_REDUCE, ffn_grouped_reduce_kernel, dim3(d.H / 32, B), dim3(256),
+    launch(K_FFN_REDUCE, ffn_grouped_reduce_kernel<GroupItem>, dim3(d.H / 32, B), dim3(256),
            (size_t)2 * grid * ga.seg_max * sizeof(int32_t), s, (const float*)ga.part, (const GroupItem*)ga.grp.items,
            (const int32_t*)ga.grp.n_items, ga.grp.tb, d.I, ga.cost, d.H, grid, ga.seg_max, d_y);
+    MOEI_LAUNCH_CHECK();
+    return MOEI_OK;
+}
+
+int launch_grouped_mm(const moei_model_desc& d, GroupedMmArgs ga, int B, float* d_y, hipStream_t s) {
+    const int grid = compute_units();
+    int rc;
+    if ((uintptr_t)ga.x % 16 != 0) {  // the ring's loads take 16-byte pieces
+        uint16_t* copy = reinterpret_cast<uint16_t*>(ga.part + gm_rows(d) * d.H);
+        MOEI_HIP(hipMemcpyAsync(copy, ga.x, (size_t)B * d.H * 2, hipMemcpyDeviceToDevice, s));
+        ga.x = copy;
+    }
+    if (ga.seg_max > kGmMaxSegs) MOEI_FAIL(MOEI_ECAPACITY, "expert_ffn_grouped: %d segments a workgroup exceed %d", ga.seg_max, kGmMaxSegs);
+#define MOEI_GM_CASE(HW_)                                                                              \
+    case HW_ * kGroupedWaves: {                                                                        \
+        const size_t smem = gm_lds<HW_>(ga.max_items, ga.n_list);                                      \
+        rc = allow_big_lds(ffn_grouped_mm_kernel<HW_>, smem);                                          \
+        if (rc) return rc;                                                                             \
+        launch(K_FFN_FUSED, ffn_grouped_mm_kernel<HW_>, dim3(grid), dim3(kGroupedWaves * kWave), smem, s, ga); \
+        MOEI_LAUNCH_CHECK();                                                                           \
+        break;                                                                                         \
+    }
+    switch (d.H) {
+        MOEI_GM_CASE(64)
+        MOEI_GM_CASE(128)
+        MOEI_GM_CASE(256)
+        MOEI_GM_CASE(512)
+        default:
+            MOEI_FAIL(d.H == 5120 ? MOEI_ECAPACITY : MOEI_EINVAL, "expert_ffn_grouped: H = %d is not supported (needs H / 512 in {1,2,4,8})", d.H);
+    }
+#undef MOEI_GM_CASE
+    launch(K_FFN_REDUCE, ffn_grouped_reduce_kernel<GmItemOut>, dim3(d.H / 32, B), dim3(256),
+           (size_t)2 * grid * ga.seg_max * sizeof(int32_t), s, (const float*)ga.part, (const GmItemOut*)ga.grp.items,
+           (const int32_t*)ga.grp.n_items, kGmTokens, d.I, ga.cost, d.H, grid, ga.seg_max, d_y);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
 }
@@ -1106,8 +1604,12 @@ int launch_expert_ffn_grouped(const moei_model_desc& d, const void* d_pool, size
     const int n = 16 / wb;
     if (d.H % (kWave * n) != 0 || (uintptr_t)d_pool % 16 != 0 || (slot_elems * wb) % 16 != 0)
         MOEI_FAIL(MOEI_EINVAL, "expert_ffn_grouped: H = %d must be a multiple of %d", d.H, kWave * n);
-    GroupArgs gr{d_idx, d_w, d_slot_of_row, B, d.k, d.E, d.n_shared, shared_base, 0,
-                 reinterpret_cast<GroupItem*>(d_items), d_n_items, d_flags};
+    GroupArgs gr{d_idx, d_w, d_slot_of_row, B, d.k, d.E, d.n_shared, shared_base, 0, d_items, d_n_items, d_flags};
+    if (grouped_mm(d, B)) {
+        GroupedMmArgs ga{reinterpret_cast<const uint16_t*>(d_pool), slot_elems, gr, gm_max_items(d, B), B * (d.k + 1),
+                         reinterpret_cast<const uint16_t*>(d_x), d_part, d.H, d.I, grouped_cost(d.H, 2), gm_segments(d)};
+        return launch_grouped_mm(d, ga, B, d_y, s);
+    }
     GroupedFfnArgs ga{d_pool, slot_elems, gr, grouped_max_items(d), d_x, d_part, d.H, d.I, grouped_cost(d.H, wb), 0};
     if (d.wdtype == MOEI_WDTYPE_BF16) return launch_grouped_typed<uint16_t>(d, ga, B, d_y, s);
     return launch_grouped_typed<float>(d, ga, B, d_y, s);

@@ -176,3 +176,49 @@ def test_batched_ffn_rejects_more_experts_than_the_item_builder_takes(m):
     with pytest.raises(m.MoeiError):
         m.expert_ffn_grouped(cache, 0, idx, w, dev(np.zeros((2, 256), np.float32)))
     cache.close()
+
+
+# items of up to 16 picks (the matrix kernel): every row width, units that are no whole number of blocks, fewer than a block for
+# a workgroup and many blocks, batches of 4 to 16, a full list of picks and experts
+@pytest.mark.parametrize("H,I,E,k,n_shared,B", [(512, 60, 2, 2, 0, 16), (512, 1100, 3, 3, 1, 5), (512, 7, 256, 32, 0, 16),
+                                                (1024, 50, 4, 3, 1, 16), (1024, 4099, 2, 1, 0, 9), (2048, 33, 3, 2, 2, 13),
+                                                (2048, 250, 2, 1, 0, 4), (4096, 17, 6, 5, 1, 7), (4096, 600, 3, 2, 0, 16)])
+def test_batched_ffn_on_the_matrix_cores(m, H, I, E, k, n_shared, B):
+    cfg = mi.get_config("C5").scaled(L=1, E=E, k=k, n_shared=n_shared, H=H, I=I, N=8, prompt=16)
+    rng = np.random.default_rng(H + I)
+    idx = np.stack([rng.choice(E, size=k, replace=False) for _ in range(B)]).astype(np.int32)
+    if B > 8:
+        idx[3] = -1  # a token without picks
+    _ffn_only_case(m, cfg, B, idx, rng.random((B, k)).astype(np.float32))
+
+
+def test_batched_ffn_on_the_matrix_cores_infinite_weights_and_unaligned_inputs(m):
+    # an infinite weight of the down projection reaches the tokens of its expert as an infinity, in the last unit of an expert
+    # of 37 (a block of fewer than 16), and no other token; an expert that is not resident contributes nothing
+    L, E, k, H, I, B = 1, 4, 2, 1024, 37, 12
+    desc = m.ModelDesc(L, E, k, 0, H, I, m.WDTYPE_BF16, 0, EPS)
+    cache = m.Cache(desc, E)
+    cache.reset(E - 1)  # expert 3 has no slot
+    g = torch.Generator(device="cuda").manual_seed(5)
+    bank = (torch.randn((E, I, 3, H), generator=g, device="cuda") * 0.05).bfloat16()
+    bank[1, I - 1, 2, 100] = float("inf")
+    for e in range(E):
+        cache.slot_tensor(e).copy_(bank[e].reshape(-1))
+    room = torch.randn(B * H + 8, generator=g, device="cuda").bfloat16()
+    x = room[1:1 + B * H].view(B, H)  # 2 bytes past a 16-byte boundary
+    idx = torch.tensor([[0, 2] if b % 3 == 0 else ([1, 0] if b % 3 == 1 else [2, 3]) for b in range(B)], dtype=torch.int32, device="cuda")
+    w = torch.rand((B, k), generator=g, device="cuda") + 0.1
+    y = m.expert_ffn_grouped(cache, 0, idx, w, x).double()
+    ref = torch.zeros_like(y)
+    for b in range(B):
+        for j in range(k):
+            e = int(idx[b, j])
+            if e < 3:
+                W = bank[e].double()
+                a = torch.nn.functional.silu(W[:, 0] @ x[b].double()) * (W[:, 1] @ x[b].double()) * w[b, j].double()
+                ref[b] += a @ W[:, 2]
+    inf = torch.isinf(ref)
+    assert inf.sum() == 4 and (y[inf] == ref[inf]).all()
+    assert ((y - ref)[~inf].abs().max() / ref[~inf].abs().max()) <= FFN_TOL_FP32ACC
+    assert cache.error_flags() & 2
+    cache.close()
