@@ -381,8 +381,8 @@ def expert_priority(eamc: Eamc, best: torch.Tensor, cur_layer: int, slot_of, eps
     V = torch.empty((L, E), dtype=torch.float32, device=dev)
     pf = torch.empty(L * E, dtype=torch.int32, device=dev)
     ev = torch.empty(L * E, dtype=torch.int32, device=dev)
-    n_pf = torch.zeros(1, dtype=torch.int32, device=dev)
-    n_ev = torch.zeros(1, dtype=torch.int32, device=dev)
+    n_pf = torch.empty(1, dtype=torch.int32, device=dev)  # (the kernel writes both counts: no launches to clear them)
+    n_ev = torch.empty(1, dtype=torch.int32, device=dev)
     k = 0
     if cur_idx is not None:
         _dev(cur_idx, torch.int32)
