@@ -307,6 +307,8 @@ struct MmArgs {
     int cus;       // compute units of an XCD
     int n_shared, sh_tiles;  // shared experts, and how many items each has
     int dn_split;  // the down kernel takes an item in this many parts of TM tokens (items of the wide tile: 2)
+    int k_per;     // ... and its units in parts of this many slices, a workgroup each
+    size_t part_rows;  // the rows of part q begin at row q * part_rows of yc
 };
 
 // Workgroups are handed to the chip's 8 XCDs in turn, and every XCD has an L2 of its own.  The
@@ -874,7 +876,8 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_gateup_wide_kernel(MmAr
 // 16 columns of W_down.  The slot stores W_down unit-major, so a lane loads eight units x eight
 // columns and transposes them in registers into eight operands of eight units each; the column
 // a lane serves in matrix i is then col0 + 8*lrow + i (which 16 columns a matrix covers is only
-// a labelling).  A wavefront owns 64 tokens x 128 columns.
+// a labelling).  A wavefront owns 64 tokens x 128 columns.  Where that leaves the chip idle the units are cut into parts
+// (see down_parts), whose rows the reduction adds up.
 template <int TM>
 __global__ void __launch_bounds__(TM * 4, 2) prefill_down_kernel(MmArgs a) {  // two wavefronts per SIMD: 256 registers
     constexpr int kMmThreads = TM * 4;
@@ -884,6 +887,7 @@ __global__ void __launch_bounds__(TM * 4, 2) prefill_down_kernel(MmArgs a) {  //
     if (item >= a.meta[0]) return;
     PItem it = a.items[item];
     it.row0 += part * TM;  // this workgroup's TM tokens of the item
+    float* yc = a.yc + (size_t)blockIdx.z * a.part_rows * a.H;
     it.ntok = min(TM, it.ntok - part * TM);
     if (it.ntok <= 0) return;
     const bool once = it.n == 1;  // the expert has no other item: its weights are read once (non-temporal loads)
@@ -899,7 +903,7 @@ __global__ void __launch_bounds__(TM * 4, 2) prefill_down_kernel(MmArgs a) {  //
         if (tid == 0) atomicOr(a.flags, 1);
         const int c_end = min(H, (int)(blockIdx.x + 1) * kDnCols);
         for (int r = 0; r < it.ntok; ++r)
-            for (int c = blockIdx.x * kDnCols + tid; c < c_end; c += kMmThreads) a.yc[(size_t)(it.row0 + r) * H + c] = 0.f;
+            for (int c = blockIdx.x * kDnCols + tid; c < c_end; c += kMmThreads) yc[(size_t)(it.row0 + r) * H + c] = 0.f;
         return;
     }
     const uint16_t* wd = a.pool + (size_t)it.slot * a.slot_elems + 2 * H + (col0 < H ? col0 : 0) + lrow * 8;
@@ -910,7 +914,8 @@ __global__ void __launch_bounds__(TM * 4, 2) prefill_down_kernel(MmArgs a) {  //
     constexpr int RPJ = kMmThreads / VPR;
     const int srow = tid / VPR, schunk = tid % VPR;
     const uint16_t* abase = a.act + (size_t)(it.row0 + srow) * I + schunk * 8;
-    const int n_slices = (I + kDnKS - 1) / kDnKS;
+    const int all_slices = (I + kDnKS - 1) / kDnKS;
+    const int s_begin = blockIdx.z * a.k_per, n_slices = min(all_slices, s_begin + a.k_per);
     uint4 stage[NV];
     auto fetch = [&](int s) {
         const bool in_k = s * kDnKS + schunk * 8 < I;
@@ -943,12 +948,12 @@ __global__ void __launch_bounds__(TM * 4, 2) prefill_down_kernel(MmArgs a) {  //
 #pragma unroll
         for (int i = 0; i < 8; ++i) Y[tb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    fetch(0);
-    put(0);
+    fetch(s_begin);
+    put(s_begin & 1);
     __syncthreads();
     uint4 cur[8], nxt[8];
-    if (active) load_w(0, cur);
-    for (int s = 0; s < n_slices; ++s) {
+    if (active) load_w(s_begin * kDnKS, cur);
+    for (int s = s_begin; s < n_slices; ++s) {
         if (s + 1 < n_slices) fetch(s + 1);
         const uint16_t* ab = As + ((size_t)(s & 1) * TM + 64 * tq + lrow) * kTileK;
         const int k0 = s * kDnKS;
@@ -993,7 +998,7 @@ __global__ void __launch_bounds__(TM * 4, 2) prefill_down_kernel(MmArgs a) {  //
         for (int v = 0; v < 4; ++v) {
             const int tok = tq * 64 + tb * 16 + lgrp * 4 + v;
             if (tok < it.ntok) {
-                float* dst = a.yc + (size_t)(it.row0 + tok) * H + col0 + lrow * 8;
+                float* dst = yc + (size_t)(it.row0 + tok) * H + col0 + lrow * 8;
                 *reinterpret_cast<float4*>(dst) = make_float4(Y[tb][0][v], Y[tb][1][v], Y[tb][2][v], Y[tb][3][v]);
                 *reinterpret_cast<float4*>(dst + 4) = make_float4(Y[tb][4][v], Y[tb][5][v], Y[tb][6][v], Y[tb][7][v]);
             }
@@ -1190,28 +1195,42 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_down_wide_kernel(MmArgs
 }
 
 // ------------------------------------------------------------------ 4. y[t] = sum of the token's rows, in pick order
-// grid n, one workgroup per token: the k picks' rows, then the shared experts' rows.
+// grid (n, groups of 1,024 columns): the k picks' rows, then the shared experts' rows, each in its parts.  Bound by memory for long
+// prompts (2,048 tokens of the 26-layer shape 27 us, 5 TB/s) and by its trips there for short ones, so eight rows are requested
+// together (77 / 512 tokens 7.6 / 10.7 us with one after the other, 5.0 / 7.8).
+constexpr int kRedAhead = 8;
 __global__ void __launch_bounds__(256) prefill_reduce_kernel(const float* __restrict__ yc,
                                                              const int32_t* __restrict__ where, int n, int k,
-                                                             int n_shared, int H, float* __restrict__ y) {
+                                                             int n_shared, int H, int parts, size_t part_rows,
+                                                             float* __restrict__ y) {
     __shared__ int s_rows[kWave + kWave];
     const int t = blockIdx.x;
     const int nc = k + n_shared;
     if ((int)threadIdx.x < nc)
         s_rows[threadIdx.x] = (int)threadIdx.x < k ? where[(size_t)t * k + threadIdx.x] : n * k + ((int)threadIdx.x - k) * n + t;
     __syncthreads();
-    for (int c = threadIdx.x; c < H / 4; c += 256) {
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int j = 0; j < nc; ++j) {
-            if (s_rows[j] < 0) continue;  // a pick that was never placed (token without picks)
-            const float4 v = *reinterpret_cast<const float4*>(yc + (size_t)s_rows[j] * H + c * 4);
-            acc.x += v.x;
-            acc.y += v.y;
-            acc.z += v.z;
-            acc.w += v.w;
+    const int c = blockIdx.y * 256 + threadIdx.x;
+    if (c >= H / 4) return;
+    const int total = nc * parts;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j0 = 0; j0 < total; j0 += kRedAhead) {
+        float4 v[kRedAhead];
+#pragma unroll
+        for (int u = 0; u < kRedAhead; ++u) {
+            v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            const int j = j0 + u < total ? (j0 + u) / parts : 0, part = j0 + u - j * parts;
+            const int row = j0 + u < total ? s_rows[j] : -1;  // -1: a pick that was never placed (token without picks)
+            if (row >= 0) v[u] = *reinterpret_cast<const float4*>(yc + ((size_t)part * part_rows + row) * H + c * 4);
         }
-        *reinterpret_cast<float4*>(y + (size_t)t * H + c * 4) = acc;
+#pragma unroll
+        for (int u = 0; u < kRedAhead; ++u) {
+            acc.x += v[u].x;
+            acc.y += v[u].y;
+            acc.z += v[u].z;
+            acc.w += v[u].w;
+        }
     }
+    *reinterpret_cast<float4*>(y + (size_t)t * H + c * 4) = acc;
 }
 
 // 1, long prompts.  The routing kernel of short prompts spends its time on the multiply-adds of the
@@ -1438,10 +1457,26 @@ int tile_tokens(const moei_model_desc& d, int n) {
     return (long)n * d.k >= (long)48 * d.E ? kTileTokWide : kTileTok;
 }
 
+// In how many parts the down kernel of the 64-token items takes an expert's units: a workgroup has 512 columns of an item, so a
+// few experts of few tokens leave most of the chip idle while each workgroup works through thousands of units by itself.  As many
+// as bring two workgroups to a compute unit, none shorter than two slices, and no more than the rows of 512 tokens hold (what
+// the scratch has at least).  us a layer without / with, prompts of 8 - 90 tokens: 4 experts of 2,432 units, H = 1,536 134 / 60; 5 of 2,216 + 1,
+// H = 640 122 / 56; 10 of 2,024 + 2, H = 1,408 128 / 65; 31 of 3,840 + 2, H = 1,408 257 / 146; 100 prompts of 5 - 1,500 tokens of
+// perf/cases.py's ranges 0.885 of the time in the mean, none slower.  64 experts of 1,408 units, H = 2,048, 77 tokens fill the chip as
+// they are (in two parts the product gained 4 us and the reduction lost them).
+int down_parts(const moei_model_desc& d, int n) {
+    double none = 1.0;  // share of the experts that nobody picks, picks being even
+    for (int t = 0; t < n && none > 1e-3; ++t) none *= 1.0 - (double)d.k / d.E;
+    const double items = d.E * (1.0 - none) + d.n_shared * ((n + kTileTok - 1) / kTileTok);
+    const int slices = (d.I + kDnKS - 1) / kDnKS;
+    const int fill = (int)(2 * compute_units() / (items * ((d.H + kDnCols - 1) / kDnCols)));
+    return std::max(1, std::min({fill, slices / 2, 512 / n}));
+}
+
 int cus_per_xcd() { return std::max(1, compute_units() / kXcds); }
 
 template <int TM>
-int launch_mm(const moei_model_desc& d, MmArgs a, int max_items, hipStream_t s) {
+int launch_mm(const moei_model_desc& d, MmArgs a, int max_items, int parts, hipStream_t s) {
     const size_t dn_smem = (size_t)2 * TM * kTileK * 2;
     int rc = pf_allow_lds(prefill_down_kernel<TM>, dn_smem);
     if (rc) return rc;
@@ -1470,7 +1505,7 @@ int launch_mm(const moei_model_desc& d, MmArgs a, int max_items, hipStream_t s) 
         MOEI_LAUNCH_CHECK();
         return MOEI_OK;
     }
-    launch(K_PF_DOWN, prefill_down_kernel<TM>, dim3((d.H + kDnCols - 1) / kDnCols, max_items * a.dn_split), dim3(TM * 4), dn_smem, s, a);
+    launch(K_PF_DOWN, prefill_down_kernel<TM>, dim3((d.H + kDnCols - 1) / kDnCols, max_items * a.dn_split, parts), dim3(TM * 4), dn_smem, s, a);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
 }
@@ -1532,11 +1567,18 @@ int launch_prefill(const moei_model_desc& d, const PrefillScratch& ps, const voi
     MmArgs a{reinterpret_cast<const uint16_t*>(d_pool), slot_elems, n_slots_total,
              reinterpret_cast<const PItem*>(ps.d_items), ps.d_meta, reinterpret_cast<const uint16_t*>(d_X), ps.d_perm,
              ps.d_pgate, ps.d_act, ps.d_yc, d.H, d.I, d_flags, 0, (d.H + kDnCols - 1) / kDnCols,
-             cus_per_xcd(), d.n_shared, (n + tm - 1) / tm, tm == kTileTokWide ? 2 : 1};
-    rc = tm == kTileTok ? launch_mm<kTileTok>(d, a, max_items, s) : launch_mm<kTileTokBig>(d, a, max_items, s);
+             cus_per_xcd(), d.n_shared, (n + tm - 1) / tm, tm == kTileTokWide ? 2 : 1, 0, prefill_rows(d, n)};
+    const int slices = (d.I + kDnKS - 1) / kDnKS;
+    a.k_per = slices;
+    int parts = tm == kTileTok ? down_parts(d, n) : 1;
+    if (parts > 1) {
+        a.k_per = (slices + parts - 1) / parts;
+        parts = (slices + a.k_per - 1) / a.k_per;  // (none is empty)
+    }
+    rc = tm == kTileTok ? launch_mm<kTileTok>(d, a, max_items, parts, s) : launch_mm<kTileTokBig>(d, a, max_items, parts, s);
     if (rc) return rc;
-    launch(K_PF_REDUCE, prefill_reduce_kernel, dim3(n), dim3(256), 0, s, (const float*)ps.d_yc,
-           (const int32_t*)ps.d_where, n, d.k, d.n_shared, d.H, d_Y);
+    launch(K_PF_REDUCE, prefill_reduce_kernel, dim3(n, (d.H / 4 + 255) / 256), dim3(256), 0, s, (const float*)ps.d_yc,
+           (const int32_t*)ps.d_where, n, d.k, d.n_shared, d.H, parts, a.part_rows, d_Y);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
 }

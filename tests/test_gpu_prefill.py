@@ -164,6 +164,20 @@ def test_prefill_long_prompt_with_experts_that_are_not_resident(m, n_shared, H, 
         assert not o["rY"][t].any() and not o["Y"][t].any() or rel_max_err(o["Y"][t], o["rY"][t]) <= FFN_TOL, t
 
 
+# few experts of few tokens: the down kernel takes an expert's units in parts (a last one that is shorter, units that are no whole
+# slice, an item more than one expert has), with experts that are not resident too
+@pytest.mark.parametrize("E,k,n_shared,H,I,n,resident", [(4, 2, 0, 512, 1032, 5, None), (3, 2, 1, 640, 2056, 60, None), (2, 1, 0, 1024, 520, 90, None),
+                                                         (5, 3, 2, 384, 1600, 23, 3), (1, 1, 0, 4096, 264, 1, None), (8, 4, 0, 128, 3000, 90, None)])
+def test_prefill_short_prompts_in_parts_of_an_experts_units(m, E, k, n_shared, H, I, n, resident):
+    cfg = mi.get_config("C2").scaled(L=1, E=E, k=k, n_shared=n_shared, H=H, I=I, N=4, prompt=16)
+    o = _prefill_case(m, cfg, n, layer=0, resident=resident)
+    if resident is None:
+        _check(o)
+        return
+    assert o["flags"] & 2 and (o["idx"] == o["ridx"]).all() and (o["eam"] == o["ream"]).all()
+    assert rel_max_err(o["Y"], o["rY"]) <= FFN_TOL_BF16_ACT
+
+
 def test_prefill_long_prompts_with_256_token_items(m):
     # n k > 128 E: the items hold up to 256 tokens and the gate/up products run in the kernel that
     # fills its LDS ring straight from global memory.  Mixtral structure, I = 72 (less than one
