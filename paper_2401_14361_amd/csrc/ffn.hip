@@ -861,8 +861,8 @@ __global__ void __launch_bounds__((kGroupedWaves * kWave)) ffn_grouped_kernel(Gr
 // from an item's first block to its last.  The activations stay fp32: the down product runs on the fp32 matrix instruction (A =
 // 16 tokens x 4 units, B = 4 units x 16 columns), which lets a lane use the eight columns of one 16-byte piece as the same column of
 // eight tiles, so nothing is transposed; its rate is a quarter of what would hold the stream up.
-// The weights go from global memory straight into a ring of S::kRing stages per wavefront (16 rows of 128 columns: 4 KiB; no
-// barrier, the waits are counted), the token rows of an item through the same ring before its first block.  The ring runs on across
+// The weights go from global memory straight into a ring of two stages per wavefront (16 rows of the wavefront's columns; four of 128
+// columns for rows of 4,096; no barrier, the waits are counted), the token rows of an item through the same ring before its first block.  The ring runs on across
 // blocks and items: a block's down rows come behind the next block's gate and up rows, so that the exchange of the
 // partial tiles (two barriers that wait for LDS only) does not hold it up, and what an item's end costs is the store of its rows.
 // Bound by the stream: sixteen requests of the 64-expert shape 155 us a call, 865 MB at 5.9 TB/s between start and end; with

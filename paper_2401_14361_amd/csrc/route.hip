@@ -120,8 +120,11 @@ __global__ void eam_update_kernel(int32_t* __restrict__ eam, int B, int L, int E
 // forms logit = <W_r[e], x> + b_e; the last workgroup to finish (arrival counter) then takes
 // the top-k, updates the EAM row and writes the slot ids / gate weights the FFN reads.
 constexpr int kRouteWaves = 4;  // expert rows per workgroup: fewer workgroups, fewer device-scope fences
-template <typename WT>
-__global__ void __launch_bounds__(kRouteWaves * kWave) route_fused_kernel(RouteFusedArgs a) {
+// NW wavefronts a workgroup, of which kRouteWaves form a logit: the others share the ranking, E^2 comparisons by the last workgroup
+// alone.  us a launch with 4 / 8 / 16: 8 experts 5.1 / 5.4 / 5.7, 64 5.6 / 5.5 / 5.8, 100 7.6 / 7.0 / 7.3, 160 9.7 / 8.7 / 8.4 (H = 5,120 10.3 / 9.3 /
+// 9.4), 256 14.0 / 11.0 / 10.2, 512 37.5 / 24.6 / 19.6: four up to 64 experts, eight up to 192, then sixteen while their counts fit 64 KiB.
+template <typename WT, int NW>
+__global__ void __launch_bounds__(NW * kWave) route_fused_kernel(RouteFusedArgs a) {
     using V = WVec<WT>;
     extern __shared__ float z[];  // E logits, then E slot ids, the E counts of this layer's EAM row, 4 x E partial ranks
     __shared__ unsigned s_ticket;
@@ -131,8 +134,8 @@ __global__ void __launch_bounds__(kRouteWaves * kWave) route_fused_kernel(RouteF
     int* s_eam = s_slot + a.E;
     int* s_prank = s_eam + a.E;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    constexpr int NT = kRouteWaves * kWave;
-    const int e = blockIdx.x * kRouteWaves + wv;
+    constexpr int NT = NW * kWave;
+    const int e = wv < kRouteWaves ? blockIdx.x * kRouteWaves + wv : a.E;  // a.E: none
     int32_t* eam_row = a.eam + (size_t)a.layer * a.E;
     // Everything this workgroup reads before the arrival counter is requested at once, the router row
     // and the token first (a wavefront's loads complete in issue order, and the logit is what the
@@ -142,7 +145,7 @@ __global__ void __launch_bounds__(kRouteWaves * kWave) route_fused_kernel(RouteF
     const WT* x = reinterpret_cast<const WT*>(a.x);
     const bool one_round = a.vec_ok && a.H <= 4 * CW;  // the whole row in four chunk loads per lane
     typename V::raw wr[4], xv[4];
-    if (one_round) {
+    if (one_round && wv < kRouteWaves) {
         const int c0 = lane * V::N;
         const int cin = c0 < a.H ? c0 : 0;  // rows shorter than 64 vectors: the lanes past the end read the start
 #pragma unroll
@@ -224,11 +227,11 @@ __global__ void __launch_bounds__(kRouteWaves * kWave) route_fused_kernel(RouteF
     for (int j = tid; j < a.E; j += NT)
         z[j] = __hip_atomic_load(&a.logits[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    // every expert's rank is a count over all experts: each of the four wavefronts counts over a quarter
-    // of them (at 160 experts the loop of one wavefront alone took as long as the rest of the kernel)
+    // every expert's rank is a count over all experts: each wavefront counts over its share of them (at 160 experts the loop of one
+    // wavefront alone took as long as the rest of the kernel)
     const bool by_rank = a.E <= kRankMaxE;
     if (by_rank) {
-        const int q = (a.E + kRouteWaves - 1) / kRouteWaves;
+        const int q = (a.E + NW - 1) / NW;
         rank_part(z, a.E, lane, min(a.E, wv * q), min(a.E, (wv + 1) * q), s_prank + wv * a.E);
         __syncthreads();
     }
@@ -243,7 +246,7 @@ __global__ void __launch_bounds__(kRouteWaves * kWave) route_fused_kernel(RouteF
         my_w = 0.f;
         if (lane == 0 && a.flags) atomicOr(a.flags, 4);
     } else if (by_rank) {
-        const float sel = wave_topk_rank(z, a.E, a.k, a.renorm, lane, s_pick, s_pw, false, s_prank, kRouteWaves);
+        const float sel = wave_topk_rank(z, a.E, a.k, a.renorm, lane, s_pick, s_pw, false, s_prank, NW);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         my_idx = lane < a.k ? s_pick[lane] : -1;
@@ -295,12 +298,17 @@ int launch_route_fused(RouteFusedArgs a, int wdtype, hipStream_t s) {
         MOEI_FAIL(MOEI_EINVAL, "fused routing needs E <= %d and k + n_shared <= %d", kMaxE, kWave);
     const int n = wdtype == MOEI_WDTYPE_BF16 ? 8 : 4;
     a.vec_ok = (a.H % n == 0) && ((uintptr_t)a.W % 16 == 0) && ((uintptr_t)a.x % 16 == 0);
-    if (wdtype == MOEI_WDTYPE_BF16)
-        launch(K_ROUTE_TOPK, route_fused_kernel<uint16_t>, dim3((a.E + kRouteWaves - 1) / kRouteWaves), dim3(kRouteWaves * kWave),
-               (3 + (a.E <= kRankMaxE ? kRouteWaves : 0)) * a.E * sizeof(float), s, a);
+    const bool bf16 = wdtype == MOEI_WDTYPE_BF16;
+    auto go = [&](auto kernel, int waves) {
+        launch(K_ROUTE_TOPK, kernel, dim3((a.E + kRouteWaves - 1) / kRouteWaves), dim3(waves * kWave),
+               (3 + (a.E <= kRankMaxE ? waves : 0)) * a.E * sizeof(float), s, a);
+    };
+    if (a.E <= 64)
+        bf16 ? go(route_fused_kernel<uint16_t, 4>, 4) : go(route_fused_kernel<float, 4>, 4);
+    else if (a.E <= 192 || a.E > 768)
+        bf16 ? go(route_fused_kernel<uint16_t, 8>, 8) : go(route_fused_kernel<float, 8>, 8);
     else
-        launch(K_ROUTE_TOPK, route_fused_kernel<float>, dim3((a.E + kRouteWaves - 1) / kRouteWaves), dim3(kRouteWaves * kWave),
-               (3 + (a.E <= kRankMaxE ? kRouteWaves : 0)) * a.E * sizeof(float), s, a);
+        bf16 ? go(route_fused_kernel<uint16_t, 16>, 16) : go(route_fused_kernel<float, 16>, 16);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
 }
