@@ -1195,10 +1195,11 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_down_wide_kernel(MmArgs
 }
 
 // ------------------------------------------------------------------ 4. y[t] = sum of the token's rows, in pick order
-// grid (n, groups of 1,024 columns): the k picks' rows, then the shared experts' rows, each in its parts.  Bound by memory for long
+// grid (n, groups of 1,024 columns, or one workgroup for all of them): the k picks' rows, then the shared experts' rows, each in its parts.  Bound by memory for long
 // prompts (2,048 tokens of the 26-layer shape 27 us, 5 TB/s) and by its trips there for short ones, so eight rows are requested
 // together (77 / 512 tokens 7.6 / 10.7 us with one after the other, 5.0 / 7.8).
 constexpr int kRedAhead = 8;
+template <bool PARTS>
 __global__ void __launch_bounds__(256) prefill_reduce_kernel(const float* __restrict__ yc,
                                                              const int32_t* __restrict__ where, int n, int k,
                                                              int n_shared, int H, int parts, size_t part_rows,
@@ -1209,28 +1210,31 @@ __global__ void __launch_bounds__(256) prefill_reduce_kernel(const float* __rest
     if ((int)threadIdx.x < nc)
         s_rows[threadIdx.x] = (int)threadIdx.x < k ? where[(size_t)t * k + threadIdx.x] : n * k + ((int)threadIdx.x - k) * n + t;
     __syncthreads();
-    const int c = blockIdx.y * 256 + threadIdx.x;
-    if (c >= H / 4) return;
-    const int total = nc * parts;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int j0 = 0; j0 < total; j0 += kRedAhead) {
-        float4 v[kRedAhead];
+    const int total = PARTS ? nc * parts : nc;
+    for (int c = blockIdx.y * 256 + threadIdx.x; c < H / 4; c += gridDim.y * 256) {
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int j0 = 0; j0 < total; j0 += kRedAhead) {
+            float4 v[kRedAhead];
 #pragma unroll
-        for (int u = 0; u < kRedAhead; ++u) {
-            v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            const int j = j0 + u < total ? (j0 + u) / parts : 0, part = j0 + u - j * parts;
-            const int row = j0 + u < total ? s_rows[j] : -1;  // -1: a pick that was never placed (token without picks)
-            if (row >= 0) v[u] = *reinterpret_cast<const float4*>(yc + ((size_t)part * part_rows + row) * H + c * 4);
-        }
+            for (int u = 0; u < kRedAhead; ++u) {
+                v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (j0 + u < total) {  // uniform
+                    const int j = PARTS ? (j0 + u) / parts : j0 + u;
+                    const size_t part = PARTS ? (size_t)(j0 + u - j * parts) * part_rows : 0;
+                    const int row = s_rows[j];  // -1: a pick that was never placed (token without picks)
+                    if (row >= 0) v[u] = *reinterpret_cast<const float4*>(yc + (part + row) * H + c * 4);
+                }
+            }
 #pragma unroll
-        for (int u = 0; u < kRedAhead; ++u) {
-            acc.x += v[u].x;
-            acc.y += v[u].y;
-            acc.z += v[u].z;
-            acc.w += v[u].w;
+            for (int u = 0; u < kRedAhead; ++u) {
+                acc.x += v[u].x;
+                acc.y += v[u].y;
+                acc.z += v[u].z;
+                acc.w += v[u].w;
+            }
         }
+        *reinterpret_cast<float4*>(y + (size_t)t * H + c * 4) = acc;
     }
-    *reinterpret_cast<float4*>(y + (size_t)t * H + c * 4) = acc;
 }
 
 // 1, long prompts.  The routing kernel of short prompts spends its time on the multiply-adds of the
@@ -1577,8 +1581,10 @@ int launch_prefill(const moei_model_desc& d, const PrefillScratch& ps, const voi
     }
     rc = tm == kTileTok ? launch_mm<kTileTok>(d, a, max_items, parts, s) : launch_mm<kTileTokBig>(d, a, max_items, parts, s);
     if (rc) return rc;
-    launch(K_PF_REDUCE, prefill_reduce_kernel, dim3(n, (d.H / 4 + 255) / 256), dim3(256), 0, s, (const float*)ps.d_yc,
-           (const int32_t*)ps.d_where, n, d.k, d.n_shared, d.H, parts, a.part_rows, d_Y);
+    // long prompts have workgroups enough with one per token
+    launch(K_PF_REDUCE, parts > 1 ? prefill_reduce_kernel<true> : prefill_reduce_kernel<false>,
+           dim3(n, n < 1024 ? (d.H / 4 + 255) / 256 : 1), dim3(256), 0, s, (const float*)ps.d_yc, (const int32_t*)ps.d_where, n, d.k,
+           d.n_shared, d.H, parts, a.part_rows, d_Y);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
 }
