@@ -1065,6 +1065,7 @@ extern "C" int moei_cache_join(moei_cache* c, void* stream) {
         if (e == hipSuccess) {
             MOEI_HIP(hipStreamWaitEvent(as_stream(stream), c->ev_routed, 0));
         } else {
+            (void)hipGetLastError();  // the stream is gone: it has drained
             int rc = wait_for_match(c, as_stream(stream));
             if (rc) return rc;
         }
