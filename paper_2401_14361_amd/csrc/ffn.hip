@@ -1496,13 +1496,18 @@ namespace {
 // vector / matrix kernel: 64 experts of 1,408 units + 2 shared, H = 2,048, top 6, 1 / 2 / 3 / 4 / 8 / 16 requests 33.9 / 37.1, 50.2 / 51.7, 66.4 /
 // 65.4, 83.2 / 77.4, 125 / 115, 182 / 155; 8 of 6,000 units, H = 4,096, top 2, 8 / 16 requests 268 / 216, 439 / 226;
 // 100 of 2,000, H = 1,024, top 8, 6 requests (1.2 of them an expert) 85.3 / 86.2; 20 of 300, H = 4,096, top 1, 8 requests (1.2) 22.5 /
-// 26.1; 16 of 400, H = 512, top 4, 4 / 6 / 12 requests (1.5 / 1.8 / 3.1) 14.7 / 15.5, 16.8 / 15.8, 20.0 / 16.6.
+// 26.1; 16 of 400, H = 512, top 4, 4 / 6 / 12 requests (1.5 / 1.8 / 3.1) 14.7 / 15.5, 16.8 / 15.8, 20.0 / 16.6.  Rows of 4,096, which start
+// and end longest, have to save 100 MB (17 of 325 units, top 2, 13 requests, 71 MB: 46.9 / 49.6), and the partial rows - one per workgroup and
+// token of its item - must not outweigh the weights (4 of 225 units, H = 1,024, 12 requests of all four: 12.6 MB of rows, 5.5 MB of
+// weights, 19.7 / 23.6).  Over 60 calls of 3 - 16 requests drawn from the ranges of perf/cases.py 0.70 of the vector kernel's time.
 bool grouped_mm(const moei_model_desc& d, int B) {
     if (d.wdtype != MOEI_WDTYPE_BF16 || B < 4) return false;
     double none = 1.0;  // share of the experts that nobody picks, picks being even
     for (int b = 0; b < B; ++b) none *= 1.0 - (double)d.k / d.E;
-    const double streamed = d.E * (1.0 - none) + d.n_shared;
-    return (B * (d.k + d.n_shared) - 1.25 * streamed) * 6.0 * d.H * d.I >= 5e6;
+    const double streamed = d.E * (1.0 - none) + d.n_shared, expert = 6.0 * d.H * d.I;
+    const double served = (double)B * (d.k + d.n_shared);
+    if (compute_units() * (served / streamed) * 4.0 * d.H > 1.5 * streamed * expert) return false;
+    return (served - 1.25 * streamed) * expert >= (d.H > 2048 ? 100e6 : 5e6);
 }
 // items of 16 picks: the sum over the experts of ceil(picks / 16), and the shared experts
 int gm_max_items(const moei_model_desc& d, int B) { return std::min(B * d.k, d.E + (B * d.k + kGmTokens - 1) / kGmTokens) + d.n_shared; }

@@ -180,9 +180,9 @@ def test_batched_ffn_rejects_more_experts_than_the_item_builder_takes(m):
 
 # items of up to 16 picks (the matrix kernel): every row width, units that are no whole number of blocks, fewer than a block for
 # a workgroup and many blocks, batches of 4 to 16, a full list of picks and experts
-@pytest.mark.parametrize("H,I,E,k,n_shared,B", [(512, 60, 2, 2, 0, 16), (512, 1100, 3, 3, 1, 5), (512, 7, 256, 32, 0, 16),
-                                                (1024, 50, 4, 3, 1, 16), (1024, 4099, 2, 1, 0, 9), (2048, 33, 3, 2, 2, 13),
-                                                (2048, 250, 2, 1, 0, 4), (4096, 17, 6, 5, 1, 7), (4096, 600, 3, 2, 0, 16)])
+@pytest.mark.parametrize("H,I,E,k,n_shared,B", [(512, 923, 2, 2, 0, 16), (512, 1100, 3, 3, 1, 5), (512, 7, 256, 32, 0, 16),
+                                                (1024, 307, 4, 3, 1, 16), (1024, 4099, 2, 1, 0, 9), (2048, 250, 3, 2, 2, 13),
+                                                (2048, 250, 2, 1, 0, 4), (4096, 133, 6, 5, 1, 7), (4096, 600, 3, 2, 0, 16)])
 def test_batched_ffn_on_the_matrix_cores(m, H, I, E, k, n_shared, B):
     cfg = mi.get_config("C5").scaled(L=1, E=E, k=k, n_shared=n_shared, H=H, I=I, N=8, prompt=16)
     rng = np.random.default_rng(H + I)
@@ -194,8 +194,8 @@ def test_batched_ffn_on_the_matrix_cores(m, H, I, E, k, n_shared, B):
 
 def test_batched_ffn_on_the_matrix_cores_infinite_weights_and_unaligned_inputs(m):
     # an infinite weight of the down projection reaches the tokens of its expert as an infinity, in the last unit of an expert
-    # of 37 (a block of fewer than 16), and no other token; an expert that is not resident contributes nothing
-    L, E, k, H, I, B = 1, 4, 2, 1024, 37, 12
+    # of 181 (a block of fewer than 16), and no other token; an expert that is not resident contributes nothing
+    L, E, k, H, I, B = 1, 4, 2, 1024, 181, 12
     desc = m.ModelDesc(L, E, k, 0, H, I, m.WDTYPE_BF16, 0, EPS)
     cache = m.Cache(desc, E)
     cache.reset(E - 1)  # expert 3 has no slot
