@@ -1274,22 +1274,24 @@ __global__ void __launch_bounds__((kGroupedWaves * kWave), 2) ffn_grouped_mm_ker
 }
 
 // y[b][h] = sum of the partial rows of the segments whose item holds token b.  The workgroup
-// first lists those rows in segment order (workgroup-major) in LDS; 32 slices of the list are
+// first lists those segments in order (workgroup-major) in LDS; 32 slices of the list are
 // then added by a thread each, all of a slice's loads in flight together, and the slice sums are
 // added in slice order.  grid (H / 32, B), 256 threads = 32 slices x 8 float4 columns;
 // dynamic LDS: 2 * n_blocks * seg_max ints.
-__device__ __forceinline__ int place_of(const GroupItem& it, int b) {
-    int j = -1;
+// The places of the item at which token b stands, a bit each (at most 16): more than one where the token lists the expert
+// more than once.
+__device__ __forceinline__ unsigned places_of(const GroupItem& it, int b) {
+    unsigned m = 0;
     for (int q = 0; q < it.ntok; ++q)
-        if (it.tok[q] == b) j = q;
-    return j;
+        if (it.tok[q] == b) m |= 1u << q;
+    return m;
 }
-__device__ __forceinline__ int place_of(const GmItemOut& it, int b) {
+__device__ __forceinline__ unsigned places_of(const GmItemOut& it, int b) {
     const unsigned long long t = it.toks;
-    int j = -1;
+    unsigned m = 0;
     for (int q = 0; q < it.ntok; ++q)
-        if ((int)(t >> (4 * q) & 15) == b) j = q;
-    return j;
+        if ((int)(t >> (4 * q) & 15) == b) m |= 1u << q;
+    return m;
 }
 template <typename Item>
 __global__ void __launch_bounds__(256) ffn_grouped_reduce_kernel(const float* __restrict__ part,
@@ -1297,12 +1299,12 @@ __global__ void __launch_bounds__(256) ffn_grouped_reduce_kernel(const float* __
                                                                  const int32_t* __restrict__ n_items, int tb, int I,
                                                                  int cost, int H, int n_blocks, int seg_max,
                                                                  float* __restrict__ y) {
-    extern __shared__ __align__(16) int32_t s_rows[];  // partial row of each segment for this token, or -1
+    extern __shared__ __align__(16) int32_t s_rows[];  // per segment: its number << 16 | the token's places in its item; -1: none
     __shared__ float s_sum[32][32];
     __shared__ int s_wbase[4];
     __shared__ int s_nv;
-    const int n = n_blocks * seg_max;
-    int32_t* s_list = s_rows + n;  // the rows that exist, in segment order
+    const int n = n_blocks * seg_max;  // (below 2^15: a few segments for each compute unit)
+    int32_t* s_list = s_rows + n;  // the segments that hold the token, in order
     const int b = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     cost = grouped_start(*n_items, n_blocks, cost);
     const int total = *n_items * (I + cost);
@@ -1314,8 +1316,8 @@ __global__ void __launch_bounds__(256) ffn_grouped_reduce_kernel(const float* __
             if (row < R1) {
                 int item, r0, r1;
                 grouped_segment(&row, R1, I, cost, &item, &r0, &r1);
-                const int j = r0 < r1 ? place_of(items[item], b) : -1;
-                if (j >= 0) entry = (g * seg_max + seg) * tb + j;
+                const unsigned at = r0 < r1 ? places_of(items[item], b) : 0;
+                if (at != 0) entry = (g * seg_max + seg) << 16 | (int)at;
             }
             s_rows[g * seg_max + seg] = entry;
         }
@@ -1343,19 +1345,34 @@ __global__ void __launch_bounds__(256) ffn_grouped_reduce_kernel(const float* __
     const int per = (nv + 31) / 32;
     const int p0 = sl * per, p1 = min(nv, p0 + per);
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto add = [&](const float4& v) {
+        acc.x += v.x;
+        acc.y += v.y;
+        acc.z += v.z;
+        acc.w += v.w;
+    };
+    auto row = [&](int entry, unsigned places) {  // the row of the first of `places`
+        return *reinterpret_cast<const float4*>(part + ((size_t)(entry >> 16) * tb + (__ffs((int)places) - 1)) * H + h);
+    };
     for (int p = p0; p < p1; p += 8) {
         float4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            v[u] = p + u < p1 ? *reinterpret_cast<const float4*>(part + (size_t)s_list[p + u] * H + h)
-                              : make_float4(0.f, 0.f, 0.f, 0.f);
+        unsigned more = 0;
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            acc.x += v[u].x;
-            acc.y += v[u].y;
-            acc.z += v[u].z;
-            acc.w += v[u].w;
+            v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (p + u < p1) {
+                const int entry = s_list[p + u];
+                const unsigned places = (unsigned)entry & 0xffffu;
+                v[u] = row(entry, places);
+                more |= places & (places - 1);
+            }
         }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) add(v[u]);
+        if (more != 0)  // an expert that the token lists more than once
+            for (int q = p; q < min(p + 8, p1); ++q)
+                for (unsigned places = (unsigned)s_list[q] & 0xffffu & ((unsigned)s_list[q] - 1); places != 0; places &= places - 1)
+                    add(row(s_list[q], places));
     }
     s_sum[sl][cq * 4 + 0] = acc.x;
     s_sum[sl][cq * 4 + 1] = acc.y;

@@ -222,3 +222,16 @@ def test_batched_ffn_on_the_matrix_cores_infinite_weights_and_unaligned_inputs(m
     assert ((y - ref)[~inf].abs().max() / ref[~inf].abs().max()) <= FFN_TOL_FP32ACC
     assert cache.error_flags() & 2
     cache.close()
+
+
+# a token that lists an expert twice (or more often) gets its output with each of the weights: in one item, in several, and beside
+# tokens that list it once; on both kernels (3 requests and fp32 weights: the vector kernel)
+@pytest.mark.parametrize("wdtype,H,I,B", [("bf16", 4096, 600, 8), ("bf16", 1024, 400, 16), ("bf16", 4096, 40, 3), ("bf16", 512, 60, 3), ("fp32", 256, 50, 16)])
+def test_batched_ffn_with_an_expert_listed_twice(m, wdtype, H, I, B):
+    cfg = mi.get_config("C5").scaled(L=1, E=4, k=4, n_shared=1, H=H, I=I, N=8, prompt=16, wdtype=wdtype)
+    rng = np.random.default_rng(H + B)
+    idx = np.stack([rng.permutation(4) for _ in range(B)])
+    idx[0] = [2, 1, 2, 0]
+    idx[1] = 3
+    idx[B - 1] = [1, 1, 0, 0]
+    _ffn_only_case(m, cfg, B, idx, rng.random((B, 4)) + 0.1)
