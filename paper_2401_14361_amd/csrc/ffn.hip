@@ -20,6 +20,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "ffn_plan.hpp"
 #include "kernels.hpp"
 #include "step_match.hpp"
 #include "wtypes.hpp"
@@ -387,30 +388,9 @@ int env_int(const char* name, int dflt) {
 
 constexpr size_t kLdsBudget = 150 * 1024;  // of the 160 KiB per compute unit
 
-// Wavefronts per workgroup: the count in [min_waves, max_waves] that wastes the fewest unit slots when
-// n_units are dealt out to blocks * waves wavefronts (ties go to more wavefronts).
-int plan_waves(int n_units, int blocks, int max_waves, int min_waves) {
+int forced_waves() {
     static const int forced = env_int("MOEI_FFN_WAVES", 0);  // the environment is read once per process
-    if (forced >= min_waves && forced <= max_waves) return forced;
-    // a layer step repeats the same shape call after call: the last plan is kept
-    static int memo_key[4] = {-1, -1, -1, -1}, memo_val = 0;
-    if (memo_key[0] == n_units && memo_key[1] == blocks && memo_key[2] == max_waves && memo_key[3] == min_waves) return memo_val;
-    int best = max_waves;
-    double best_eff = -1.0;
-    for (int m = max_waves; m >= min_waves; --m) {
-        long per = ((long)n_units + (long)blocks * m - 1) / ((long)blocks * m);
-        double eff = (double)n_units / ((double)per * blocks * m);
-        if (eff > best_eff + 1e-9) {
-            best_eff = eff;
-            best = m;
-        }
-    }
-    memo_key[0] = n_units;
-    memo_key[1] = blocks;
-    memo_key[2] = max_waves;
-    memo_key[3] = min_waves;
-    memo_val = best;
-    return best;
+    return forced;
 }
 
 // Raises a kernel's dynamic-LDS limit above 64 KiB, once per kernel and size (the call
@@ -442,7 +422,9 @@ int launch_ffn_typed(FfnArgs a, bool fast, int grid, size_t match_lds, float* d_
     if (fast) {
 #define MOEI_FFN_CASE(N_, TAIL_)                                                                        \
     case N_: {                                                                                         \
-        a.waves = plan_waves(a.n_act * a.I, grid, StreamShape<N_>::kMaxWaves, a.match.n_blocks > 0 ? 8 : 4); \
+        a.waves = plan_waves(a.n_act * a.I, grid, StreamShape<N_>::kMaxWaves, a.match.n_blocks > 0 ? kMatchWaves : 4, \
+                             forced_waves());                                                          \
+        static_assert(StreamShape<N_>::kMaxWaves >= kMatchWaves, "the match finds its wavefronts");    \
         const size_t padded = (size_t)N_ * kWave * V::N * sizeof(float);                               \
         int yg = (int)((kLdsBudget - padded) / padded);                                                \
         a.ygroup = yg < 1 ? 1 : (yg > a.waves ? a.waves : yg);                                         \
