@@ -1455,7 +1455,7 @@ bool ffn_streams(const moei_model_desc& d, const void* d_pool, size_t slot_elems
 
 bool expert_ffn_takes_match(const moei_model_desc& d, const void* d_pool, size_t slot_elems, const void* d_x) {
     const int chunk = kWave * 16 / (d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4);
-    return ffn_streams(d, d_pool, slot_elems) && d.H <= 16 * chunk && (uintptr_t)d_x % 16 == 0;
+    return ffn_streams(d, d_pool, slot_elems) && d.H <= 16 * chunk && (uintptr_t)d_x % 16 == 0 && forced_takes_match(forced_waves());
 }
 
 int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_elems, int n_slots_total,

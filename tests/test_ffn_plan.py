@@ -7,7 +7,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-MAIN = r"""
+RULE = r"""
 #include "ffn_plan.hpp"
 #include <cstdio>
 #include <thread>
@@ -71,4 +71,33 @@ def _run(tmp_path, main):
 
 
 def test_plan_is_the_rule_in_every_thread(tmp_path):
-    _run(tmp_path, MAIN)
+    _run(tmp_path, RULE)
+
+
+FORCED = r"""
+#include "ffn_plan.hpp"
+#include <cstdio>
+#include <initializer_list>
+
+int main() {
+    int bad = 0;
+    for (int max : {8, 12, 16})
+        for (int forced = 1; forced <= max; ++forced) {
+            if (moei::plan_waves(11264, 232, max, 4, forced) != forced) {
+                std::printf("%d of at most %d wavefronts asked for, %d planned\n", forced, max, moei::plan_waves(11264, 232, max, 4, forced));
+                ++bad;
+            }
+            // a launch that also matches takes the count where its workgroups are large enough, else the match is not put there
+            const bool takes = moei::forced_takes_match(forced);
+            bad += takes != (forced >= 8);
+            bad += takes && moei::plan_waves(11264, 232, max, 8, forced) != forced;
+        }
+    for (int none : {-1, 0}) bad += !moei::forced_takes_match(none) || moei::plan_waves(11264, 232, 16, 8, none) < 8;
+    bad += moei::plan_waves(11264, 232, 8, 4, 9) > 8;  // more than the kernel takes: as if nothing was asked for
+    return bad != 0;
+}
+"""
+
+
+def test_a_forced_count_is_taken(tmp_path):
+    _run(tmp_path, FORCED)
