@@ -32,7 +32,7 @@ size_t step_match_lds(const moei_eamc* c, int n_blocks);
 
 #if defined(__HIPCC__)
 
-struct StepMatchLds {
+struct alignas(16) StepMatchLds {
     ScoreLds<false> score;
     u64 nq;
     Best win;
@@ -40,6 +40,8 @@ struct StepMatchLds {
     int sn[2];
     int best[kMaxMatchBatch];
 };
+// behind it lie 16 bytes per trace and the query's cells, which are read as 16-byte vectors
+static_assert(sizeof(StepMatchLds) % 16 == 0, "the query's cells in LDS begin at a 16-byte boundary");
 
 // Dot products of the query (in LDS) with traces t0 .. t0 + nt, added into s_dot (zero before).  Per layer the tile is one run
 // of cells; a thread owns a vector of it and, where the tile is small, every groups-th layer only, and sixteen of
