@@ -20,8 +20,9 @@
  *     counters, sort keys, partial rows) that their calls reuse: calls that name
  *     the same object must be ordered by the caller (one stream, or events
  *     between streams); calls on different objects are independent.  A cache's
- *     layer step uses the EAMC it is handed on the cache's own side stream:
- *     moei_cache_join / moei_cache_sync order that work before other uses of it.
+ *     layer step uses the EAMC it is handed on the cache's own side stream, or beside
+ *     the experts on the caller's: moei_cache_join / moei_cache_sync order that work
+ *     before other uses of it.
  *   - Matrices are row-major and dense.  Layer indices are 0-based.
  *   - Notation (Sec. 4.3 of the paper): L MoE layers, E routed experts per
  *     layer, k experts per token, EAM = L x E matrix of token counts; H hidden
@@ -316,14 +317,16 @@ int moe_prefill_layer(moei_cache* c, int32_t* d_eam, int32_t layer,
                       const void* d_router_w, const float* d_router_bias,
                       const void* d_X, int32_t n, float* d_Y,
                       int32_t* d_idx_out, float* d_w_out, void* stream);
-/* Makes `stream` wait for the match/priority work that the last moe_decode_layer put on
- * the cache's side stream (the next moe_decode_layer does this by itself) and for every
+/* Makes `stream` wait for the match/priority work of the last moe_decode_layer (the next
+ * moe_decode_layer does this by itself) - for an asynchronous step that matched beside its experts
+ * the call itself waits, on the host, until that launch has matched; the step's own stream is not
+ * touched and may have been destroyed or be under capture by then - and for every
  * prefetch copy that no stream has waited for yet; carries out the prefetch plan of an
  * asynchronous step first (then it waits for that step's side stream on the host).  Call it
  * before ending a stream capture that contains asynchronous layer steps, so that the
  * side stream has joined `stream` again. */
 int moei_cache_join(moei_cache* c, void* stream);
-/* Waits on the host for the cache's own streams (match/priority work, miss fills) and
+/* Waits on the host for the cache's own streams and the last step's match (match/priority work, miss fills) and
  * forgets any pending cross-stream dependency.  Call it before beginning and after
  * ending a stream capture, so that no wait inside the capture refers to work outside
  * it and vice versa. */

@@ -6,6 +6,7 @@
 
 #include <atomic>
 #include <chrono>
+#include <thread>
 #include <new>
 #include <vector>
 
@@ -50,6 +51,7 @@ struct Pinned {
     int32_t flags;
     int32_t matches[2 * kMaxMatchBatch];  // d_best and d_best_sim, for moei_cache_last_matches
     int32_t best_seq;  // number of the step whose `best` is in place (written by the scoring workgroup after it)
+    StepMatched matched;  // of the last step that matched beside its experts
 };
 
 }  // namespace
@@ -114,15 +116,16 @@ struct moei_cache {
     u64* d_step_cand = nullptr;
     int32_t* d_step_idx = nullptr;
     unsigned* d_step_ticket = nullptr;
-    hipStream_t match_stream = nullptr;  // the stream that holds the last step's match (match_on_stream), its caller's
-    bool match_on_stream = false;
+    bool match_on_stream = false;  // the last step matched beside its experts, on its caller's stream ...
+    bool match_captured = false;   // ... which was being captured
+    bool ever_captured = false;    // a graph may hold steps of this cache: what its replays match is in device memory only
     hipEvent_t ev_copy = nullptr, ev_routed = nullptr, ev_side = nullptr, ev_main = nullptr;
     hipEvent_t ev_match[kRing] = {};             // end of the side chain of the last step with this parity;
                                                   // ev_side aliases the most recent of the two
     bool match_pending[kRing] = {};
     bool side_pending = false;
     bool poll = true;      // the synchronous step polls pinned memory before it falls back to events (MOEI_SYNC_POLL=0: events only)
-    int32_t step_seq = 0;  // number of the last step whose scoring writes into pinned memory
+    int32_t step_seq = 0;  // number of the last step whose kernels write into pinned memory
     int parity = 0;  // which buffer set the current step writes
     FfnScratch ffn;
     void* d_items = nullptr;        // batched FFN: token groups, allocated at the first batched call
@@ -744,6 +747,15 @@ extern "C" int moei_cache_error_flags(moei_cache* c, int32_t* h_flags, void* str
 }
 
 namespace {
+bool is_capturing(hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {  // the default stream while another one is captured
+        (void)hipGetLastError();
+        return false;
+    }
+    return cap != hipStreamCaptureStatusNone;
+}
+
 // Carries out the prefetch plan an asynchronous layer step has left behind: waits for that step's
 // side chain, then runs the same admission as the synchronous step on the heads and scores it
 // wrote to pinned memory.  The cache is in the state that step left it in, so the result is the one
@@ -786,6 +798,8 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
     }
     rc = flush_prefetch_plan(c, s);
     if (rc) return rc;
+    const bool captured = !sync_mode && is_capturing(s);
+    c->ever_captured |= captured;
 
     // Routing hands the side stream a snapshot of the updated EAM and its picks in one of
     // kRing buffer sets used in turn, so the main stream never waits for the match and scoring
@@ -859,9 +873,10 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
     c->last_h_ev = sc.h_ev;
     c->match_on_stream = match_blocks > 0;
     if (match_blocks > 0) {
+        c->match_captured = captured;  // (what a capture records runs with the graph: no call outside it waits for that)
         const StepMatchArgs ma{match_blocks, eamc->d_norm2, d_snap, c->d_step_cand, c->d_step_idx, c->d_step_ticket, c->d_best,
-                               c->d_best_sim, sc};
-        c->match_stream = s;
+                               c->d_best_sim, c->match_captured ? nullptr : &c->pin_dev->matched,
+                               c->match_captured ? 0 : ++c->step_seq, sc};
         return launch_expert_ffn(d, c->d_pool, c->slot_elems, c->n_total, c->ffn, c->d_slot_ids, c->d_gate, k + d.n_shared, d_x, d_y,
                                  c->d_flags, &ma, step_match_lds(eamc, match_blocks), s);
     }
@@ -987,24 +1002,39 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
 }
 
 namespace {
-// The host waits for the last step's match, except for what the caller's own wait for `s` covers.  The match of a step that
-// holds it on its caller's stream is as far as that stream; a stream that has been destroyed since has drained.
-int wait_for_match(moei_cache* c, hipStream_t s) {
-    if (c->side_pending) MOEI_HIP(hipStreamSynchronize(c->side_stream));
-    if (c->match_on_stream && c->match_stream != s && hipStreamSynchronize(c->match_stream) != hipSuccess) {
-        (void)hipGetLastError();
-        MOEI_HIP(hipDeviceSynchronize());
+// The host waits until the last step has matched, where that is on its caller's stream: by the number that the kernel stores
+// behind its results.  Nothing of the caller's is needed for it - the stream may have been destroyed since, or be captured - and
+// nothing is put on the stream: an event behind each step, the other way, takes 3 - 4 us of the chain every time (four layer steps
+// of large experts 501 -> 515 us).
+int wait_for_step(moei_cache* c) {
+    if (!c->match_on_stream || c->match_captured) return MOEI_OK;
+    volatile int32_t* p = &c->pin->matched.seq;
+    const int32_t want = c->step_seq;
+    auto there = [&] { return *p == want; };
+    if (poll_pinned(there, 20e3)) return MOEI_OK;
+    for (int i = 0; i < 100000; ++i) {  // a long queue before the step
+        if (poll_pinned(there, 1.0)) return MOEI_OK;
+        std::this_thread::sleep_for(std::chrono::microseconds(100));
     }
+    MOEI_HIP(hipDeviceSynchronize());
+    if (!there()) MOEI_FAIL(MOEI_ESTATE, "the last layer step has not matched");
     return MOEI_OK;
+}
+
+// The host waits for `s` and for the last step's match.  (In this order: mostly `s` is the step's stream, and then nothing is left
+// to wait for; behind the other wait the one for the stream would begin with a packet of its own.)
+int drain_step(moei_cache* c, hipStream_t s) {
+    MOEI_HIP(hipStreamSynchronize(s));
+    if (c->side_pending) MOEI_HIP(hipStreamSynchronize(c->side_stream));
+    return wait_for_step(c);
 }
 }  // namespace
 
 extern "C" int moei_cache_last_heads(moei_cache* c, int32_t* h_pf_head, int32_t cap_pf, int32_t* h_n_pf_head,
                                      int32_t* h_ev_head, int32_t cap_ev, int32_t* h_n_ev_head, void* stream) {
     MOEI_REQUIRE(c && h_n_pf_head && h_n_ev_head, "moei_cache_last_heads: null pointer");
-    int rc = wait_for_match(c, as_stream(stream));
+    int rc = drain_step(c, as_stream(stream));
     if (rc) return rc;
-    MOEI_HIP(hipStreamSynchronize(as_stream(stream)));
     int32_t n_pf = 0, n_ev = 0;
     MOEI_HIP(hipMemcpy(&n_pf, c->d_n_pf, 4, hipMemcpyDeviceToHost));
     MOEI_HIP(hipMemcpy(&n_ev, c->d_n_ev, 4, hipMemcpyDeviceToHost));
@@ -1043,7 +1073,17 @@ extern "C" int moei_cache_last_matches(moei_cache* c, int32_t* h_top, float* h_t
     // one copy behind what the caller's stream holds, and one wait for both: a program that reads the
     // matches once a token pays for each trip to the device (two blocking copies behind two waits before)
     hipStream_t s = as_stream(stream);
-    int rc = wait_for_match(c, s);
+    int rc;
+    if (c->match_on_stream && !c->ever_captured && c->match_m == 1) {  // the step has brought its match here itself
+        rc = drain_step(c, s);
+        if (rc) return rc;
+        if (h_top) *h_top = c->pin->matched.best;
+        if (h_top_sim) *h_top_sim = c->pin->matched.best_sim;
+        *h_m = 1;
+        return MOEI_OK;
+    }
+    if (c->side_pending) MOEI_HIP(hipStreamSynchronize(c->side_stream));
+    rc = wait_for_step(c);
     if (rc) return rc;
     MOEI_HIP(hipMemcpyAsync(c->pin->matches, c->d_best, sizeof(c->pin->matches), hipMemcpyDeviceToHost, s));
     MOEI_HIP(hipStreamSynchronize(s));
@@ -1060,19 +1100,11 @@ extern "C" int moei_cache_join(moei_cache* c, void* stream) {
         if (rc) return rc;
     }
     if (c->side_pending) MOEI_HIP(hipStreamWaitEvent(as_stream(stream), c->ev_side, 0));
-    if (c->match_on_stream && c->match_stream != as_stream(stream)) {
-        hipError_t e = hipEventRecord(c->ev_routed, c->match_stream);
-        if (e == hipSuccess) {
-            MOEI_HIP(hipStreamWaitEvent(as_stream(stream), c->ev_routed, 0));
-        } else {
-            (void)hipGetLastError();  // the stream is gone: it has drained
-            int rc = wait_for_match(c, as_stream(stream));
-            if (rc) return rc;
-        }
-    }
+    int rc = wait_for_step(c);
+    if (rc) return rc;
     if (c->n_pending > 0) {  // prefetch copies that no stream has waited for yet
         for (int t = 0; t < c->S; ++t) {
-            int rc = settle_pending(c, t, as_stream(stream));
+            rc = settle_pending(c, t, as_stream(stream));
             if (rc) return rc;
         }
     }
@@ -1084,10 +1116,8 @@ extern "C" int moei_cache_sync(moei_cache* c) {
     MOEI_HIP(hipStreamSynchronize(c->side_stream));
     MOEI_HIP(hipStreamSynchronize(c->copy_stream));
     MOEI_HIP(hipStreamSynchronize(c->pf_stream));
-    if (c->match_on_stream) {
-        int rc = wait_for_match(c, c->side_stream);  // (never the stream that holds it)
-        if (rc) return rc;
-    }
+    int rc = wait_for_step(c);
+    if (rc) return rc;
     std::fill(c->slot_pending.begin(), c->slot_pending.end(), 0);
     c->n_pending = 0;
     c->side_pending = false;
@@ -1100,9 +1130,8 @@ extern "C" int moei_cache_last_step(moei_cache* c, float* h_gate_w, float* h_bes
                                     float* h_evict, int32_t* h_pf_order, int32_t* h_n_pf, int32_t* h_ev_order,
                                     int32_t* h_n_ev, void* stream) {
     MOEI_REQUIRE(c, "moei_cache_last_step: null pointer");
-    int rc = wait_for_match(c, as_stream(stream));
+    int rc = drain_step(c, as_stream(stream));
     if (rc) return rc;
-    MOEI_HIP(hipStreamSynchronize(as_stream(stream)));
     if (h_pf_order || h_ev_order) {  // the step selected the heads only: the complete orders are ranked from its keys now
         rc = launch_priority_rank(c->d, c->d_keys, c->d_n_pf, c->d_n_ev, c->d_pf_order, c->d_ev_order, c->side_stream);
         if (rc) return rc;

@@ -15,6 +15,13 @@ namespace moei {
 constexpr int kStepMatchMaxBlocks = 128;  // never more workgroups than that match
 constexpr int kStepMatchMaxTraces = 1024;  // traces of one of them (their dot products and norms are held in LDS)
 
+// What such a step tells the host, in pinned memory
+struct StepMatched {
+    int32_t best;
+    float best_sim;
+    int32_t seq;  // number of the step, stored when all of its results are in place
+};
+
 struct StepMatchArgs {
     int n_blocks;            // workgroups that match, behind the ones that stream (0: none)
     const unsigned long long* norm2;  // [n_cap]
@@ -24,6 +31,8 @@ struct StepMatchArgs {
     unsigned* ticket;        // arrival counter, zero between launches
     int32_t* best;
     float* best_sim;
+    StepMatched* host;       // null: a captured step
+    int32_t seq;             // for host->seq
     ScoreArgs sc;
 };
 // 0: a step over this collection keeps the match on the side stream
@@ -164,10 +173,26 @@ __device__ __forceinline__ void step_match(const StepMatchArgs& a, int blk, unsi
     barrier_lds();
     if (!s.finish) return;  // uniform
     if (tid == kWave) {
+        const float sim = s.win.idx >= 0 ? (float)cosine(s.win.dot, s.nq, s.win.nt) : 0.f;
         a.best[0] = s.win.idx;
-        a.best_sim[0] = s.win.idx >= 0 ? (float)cosine(s.win.dot, s.nq, s.win.nt) : 0.f;
+        a.best_sim[0] = sim;
+        if (a.host) {
+            a.host->best = s.win.idx;
+            a.host->best_sim = sim;
+        }
     }
     score_and_heads<false>(sc, s.score, s.sn, s.best);
+    // The host waits for the step by this word, whatever has become of its stream.  Its way over the host link is hidden by the
+    // experts (four steps of large ones 502 -> 503 us, of the tiny model 113 -> 113); stored by the reduction kernel it held every step
+    // up by 5 us.
+    if (a.host) {
+        wait_vm_fence<0>();
+        barrier_lds();
+        if (tid == 0) {
+            __threadfence_system();
+            __hip_atomic_store(&a.host->seq, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
 }
 
 #endif  // __HIPCC__

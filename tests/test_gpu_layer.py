@@ -4,6 +4,8 @@ sequence must agree exactly at every layer step; FFN outputs within tolerance.
 Layer inputs are teacher-forced (each (token, layer) has its own pre-drawn x), so a
 rounding difference in one FFN output cannot change a later routing decision.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -557,5 +559,96 @@ def test_match_beside_the_experts(m, L, E, N, cell_bytes):
         streams[0].synchronize()
         s.synchronize()
     assert cache.error_flags() == 0
+    cache.close()
+    eamc.close()
+
+
+def _step_beside_the_experts(m):
+    """A cache whose asynchronous steps match beside the experts: (cache, eamc, step(stream), start(n): the next step's EAM is trace n
+    and what it will match)."""
+    L, E, k, H, I, N = 4, 8, 2, 64, 8, 60
+    rng = np.random.default_rng(11)
+    desc = m.ModelDesc(L, E, k, 0, H, I, m.WDTYPE_BF16, 0, EPS)
+    T = (rng.integers(0, 30, size=(N, L, E)) * (rng.random((N, L, E)) < 0.5)).astype(np.int32)
+    eamc = m.Eamc(desc, N)
+    eamc.load(T)
+    cache = m.Cache(desc, L * E, pinned(np.zeros((1, 3 * H * I), dtype=np.uint16)))
+    cache.reset(L * E)
+    d_eam = dev(T[17].copy())
+    W, x, bias = dev(np.zeros((E, H), dtype=np.uint16)), dev(np.zeros(H, dtype=np.uint16)), dev(np.arange(E, dtype=np.float32))
+    y = torch.empty(H, dtype=torch.float32, device="cuda")
+
+    def start(n):
+        ref = T[n].astype(np.int64)
+        ref[0, [E - 1, E - 2]] += 1
+        d_eam.copy_(dev(T[n].copy()))
+        torch.cuda.synchronize()
+        return O.eamc_match(T, ref)[0]
+
+    return cache, eamc, lambda s: m.moe_decode_layer(cache, eamc, d_eam, 0, W, bias, x, y, sync=False, stream=s), start
+
+
+def test_a_steps_stream_may_be_captured_afterwards(m):
+    # after an asynchronous step its stream is the caller's again: waiting for the match on another stream neither touches nor joins
+    # a capture that the caller has begun there
+    cache, eamc, step, start = _step_beside_the_experts(m)
+    best = start(17)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    v = torch.ones(64, device="cuda")
+    step(a.cuda_stream)
+    a.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=a, capture_error_mode="relaxed"):
+        v.mul_(2)
+        cache.join(b.cuda_stream)
+        assert cache.last_matches(b.cuda_stream)[0].tolist() == [best]
+        cache.sync()
+    for _ in range(3):
+        graph.replay()
+    torch.cuda.synchronize()
+    assert (v == 8).all()
+    cache.close()
+    eamc.close()
+
+
+def test_a_steps_stream_may_be_destroyed_afterwards(m):
+    # the match of the last step is still waited for, and read, through a stream that exists
+    cache, eamc, step, start = _step_beside_the_experts(m)
+    best = start(17)
+    b = torch.cuda.Stream()
+    handle = ctypes.c_void_p(0)
+    assert int(torch.cuda.cudart().cudaStreamCreate(ctypes.addressof(handle))) == 0
+    step(handle.value)
+    assert int(torch.cuda.cudart().cudaStreamDestroy(handle.value)) == 0
+    cache.join(b.cuda_stream)
+    assert cache.last_matches(b.cuda_stream)[0].tolist() == [best]
+    assert cache.last_heads(b.cuda_stream)[1].size == 2
+    assert cache.last_step(b.cuda_stream)["ev_order"].size == 30
+    cache.sync()
+    cache.close()
+    eamc.close()
+
+
+def test_last_matches_follows_a_graphs_replay(m):
+    # a graph holds a step; the last step may be an eager one or the graph's
+    cache, eamc, step, start = _step_beside_the_experts(m)
+    a = torch.cuda.Stream()
+    best = start(3)
+    step(a.cuda_stream)
+    assert cache.last_matches(a.cuda_stream)[0].tolist() == [best]
+    cache.sync()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=a):
+        step(a.cuda_stream)
+        cache.join(a.cuda_stream)
+    cache.sync()
+    for first, second in ((17, 30), (8, 41), (52, 1)):
+        best = start(first)
+        step(a.cuda_stream)
+        assert cache.last_matches(a.cuda_stream)[0].tolist() == [best]
+        best = start(second)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert cache.last_matches(a.cuda_stream)[0].tolist() == [best]
     cache.close()
     eamc.close()
