@@ -335,21 +335,27 @@ __device__ __forceinline__ void wave_head(const u64* keys, int LE, int ltid, int
         const int f = ltid + r * STRIDE;
         mine[r] = f < LE ? keys[f] : kNone;
     }
-    // a lane keeps its two best remaining cells: it looks through its cells again only where it has lost both
+    // a lane keeps its two best remaining cells: it looks through its cells again only where it has lost both.  (Key and
+    // id each by themselves: a choice between two structs is one between their addresses, and both lie in private memory then, a trip
+    // there for every comparison.)
     bool have_last = false;
     KeyId last{0, -1};
-    KeyId cur{kNone, 0x7fffffff}, nxt = cur;
+    u64 cur_k = kNone, nxt_k = kNone;
+    int cur_id = 0x7fffffff, nxt_id = 0x7fffffff;
     int known = 0;
     for (int round = 0; round < want; ++round) {
         if (known == 0) {
-            cur = nxt = KeyId{kNone, 0x7fffffff};
+            cur_k = nxt_k = kNone;
+            cur_id = nxt_id = 0x7fffffff;
             auto consider = [&](u64 k, int f) {
                 if (k == kNone) return;
                 if (have_last && (k < last.k || (k == last.k && f <= last.id))) return;
-                const KeyId c{k, f};
-                const bool first = k < cur.k || (k == cur.k && f < cur.id);
-                nxt = first ? cur : keyid_min(nxt, c);
-                cur = first ? c : cur;
+                const bool first = k < cur_k || (k == cur_k && f < cur_id);
+                const bool second = k < nxt_k || (k == nxt_k && f < nxt_id);
+                nxt_k = first ? cur_k : (second ? k : nxt_k);
+                nxt_id = first ? cur_id : (second ? f : nxt_id);
+                cur_k = first ? k : cur_k;
+                cur_id = first ? f : cur_id;
             };
             if constexpr (OWN > 0) {
 #pragma unroll
@@ -359,15 +365,16 @@ __device__ __forceinline__ void wave_head(const u64* keys, int LE, int ltid, int
             }
             known = 2;
         }
-        const KeyId w = wave_keyid_min(cur);
+        const KeyId w = wave_keyid_min(KeyId{cur_k, cur_id});
         if (lane == 0) {
             okey[round] = w.k;
             oid[round] = w.id;
         }
         last = w;
         have_last = true;
-        if (cur.id == w.id) {  // this lane's best has been taken: its next one
-            cur = nxt;
+        if (cur_id == w.id) {  // this lane's best has been taken: its next one
+            cur_k = nxt_k;
+            cur_id = nxt_id;
             --known;
         }
     }
