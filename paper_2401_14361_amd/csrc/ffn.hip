@@ -86,7 +86,9 @@ struct StreamShape {
     static constexpr int kMaxWaves = NCH <= 4 ? 16 : (NCH <= 10 ? 12 : 8);
 };
 
-template <typename WT, int NCH, bool TAIL>
+// MATCH: the launch has workgroups that match and score beside the ones that stream.  An instance of its own: they take 124 registers,
+// and the ones that stream far fewer (35 - 99 for up to four chunks), so that a scan on the side stream finds room beside them.
+template <typename WT, int NCH, bool TAIL, bool MATCH>
 __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fused_kernel(FfnArgs a) {
     using V = WVec<WT>;
     using Raw = typename V::raw;
@@ -96,9 +98,11 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
     constexpr int PF = StreamShape<NCH>::kWindow;
     static_assert(STEPS % PF == 0, "the window must divide the steps of a unit");
     extern __shared__ __align__(16) float smem[];
-    if ((int)blockIdx.x >= a.n_wg) {  // a workgroup that matches and scores beside the ones that stream
-        step_match(a.match, blockIdx.x - a.n_wg, reinterpret_cast<unsigned char*>(smem));
-        return;
+    if constexpr (MATCH) {
+        if ((int)blockIdx.x >= a.n_wg) {
+            step_match(a.match, blockIdx.x - a.n_wg, reinterpret_cast<unsigned char*>(smem));
+            return;
+        }
     }
     float* xs = smem;
     float* yp = smem + NCH * CW;
@@ -397,15 +401,16 @@ int forced_waves() {
 // is not a stream operation, so it stays out of the per-launch path and of captures).
 template <typename K>
 int allow_big_lds(K kernel, size_t bytes) {
-    static const void* seen_fn[64];
-    static size_t seen_bytes[64];
+    constexpr int kSeen = 128;  // kernels of one argument type: 104 streaming FFNs are the most
+    static const void* seen_fn[kSeen];
+    static size_t seen_bytes[kSeen];
     static int n_seen = 0;
     if (bytes <= 64 * 1024) return MOEI_OK;
     const void* fn = reinterpret_cast<const void*>(kernel);
     for (int i = 0; i < n_seen; ++i)
         if (seen_fn[i] == fn && seen_bytes[i] >= bytes) return MOEI_OK;
     MOEI_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-    if (n_seen < 64) {
+    if (n_seen < kSeen) {
         seen_fn[n_seen] = fn;
         seen_bytes[n_seen++] = bytes;
     }
@@ -429,9 +434,10 @@ int launch_ffn_typed(FfnArgs a, bool fast, int grid, size_t match_lds, float* d_
         int yg = (int)((kLdsBudget - padded) / padded);                                                \
         a.ygroup = yg < 1 ? 1 : (yg > a.waves ? a.waves : yg);                                         \
         const size_t smem = std::max(padded * (1 + a.ygroup), match_lds);                              \
-        rc = allow_big_lds(ffn_fused_kernel<WT, N_, TAIL_>, smem);                                     \
+        auto kernel = a.match.n_blocks > 0 ? ffn_fused_kernel<WT, N_, TAIL_, true> : ffn_fused_kernel<WT, N_, TAIL_, false>; \
+        rc = allow_big_lds(kernel, smem);                                                              \
         if (rc) return rc;                                                                             \
-        launch(K_FFN_FUSED, ffn_fused_kernel<WT, N_, TAIL_>, dim3(grid + a.match.n_blocks), dim3(a.waves * kWave), smem, s, a); \
+        launch(K_FFN_FUSED, kernel, dim3(grid + a.match.n_blocks), dim3(a.waves * kWave), smem, s, a); \
         break;                                                                                         \
     }
         // whole chunks, for the counts of chunks that configurations have; any other row through TAIL

@@ -55,3 +55,17 @@ def _named(kernels, *starts):
 def test_no_private_memory(kernels, name):
     for n, k in _named(kernels, name).items():
         assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, (n, k[".private_segment_fixed_size"])
+
+
+def test_a_scan_fits_beside_the_streaming_ffn(kernels):
+    # a compute unit holds a workgroup of the FFN that streams (4, 3 or 2 wavefronts a SIMD, by the chunks of its rows) and one of a
+    # scan of 48 registers; the code that steps with a match beside their experts need is in instances of their own
+    checked = 0
+    for n, k in _named(kernels, "ffn_fused_kernel<").items():
+        _, chunks, _, match = n[len("ffn_fused_kernel<"):n.index(">")].split(", ")
+        if match == "true":
+            continue
+        waves = 4 if int(chunks) <= 4 else 3 if int(chunks) <= 10 else 2
+        assert waves * (k[".vgpr_count"] + 7 & ~7) + 48 <= 512, (n, k[".vgpr_count"])
+        checked += 1
+    assert checked == 52
