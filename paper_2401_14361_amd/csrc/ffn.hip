@@ -1174,14 +1174,15 @@ __global__ void __launch_bounds__((kGroupedWaves * kWave), 2) ffn_grouped_mm_ker
             *reinterpret_cast<gm_f32x4*>(part + 256) = u[0];
         }
         barrier_lds();
-        if (n < n_blocks) {  // a lane below 32 adds a gate value up, one above the up value of the same unit and token
+        if (n < n_blocks) {  // a lane from 32 on adds a gate value up, one below the up value of the same unit and token
             const int lv = opaque(lane), e = wv * 32 + (lv & 31), unit = 4 * (e >> 6) + (e & 3), tok = (e >> 2) & 15;
             float p[kGroupedWaves];
 #pragma unroll
-            for (int w = 0; w < kGroupedWaves; ++w) p[w] = s_part[(w * 2 + (lv >> 5)) * 256 + e];
+            for (int w = 0; w < kGroupedWaves; ++w) p[w] = s_part[(w * 2 + (lv < 32)) * 256 + e];
             const float v = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-            const float up = __shfl_xor(v, 32, kWave);
-            if (lv < 32) {
+            const int b = __builtin_bit_cast(int, v);
+            const float up = __builtin_bit_cast(float, __builtin_amdgcn_permlane32_swap(b, b, false, false)[0]);  // lanes 32..63 take lanes 0..31
+            if (lv >= 32) {
                 const float gate = tok < cb.ntok ? s_w[cb.first_tok + tok] : 0.f;
                 s_act[(n & 1) * 256 + unit * 16 + tok] = unit < cb.valid && tok < cb.ntok ? silu(v) * up * gate : 0.f;
             }
@@ -1239,6 +1240,10 @@ __global__ void __launch_bounds__((kGroupedWaves * kWave), 2) ffn_grouped_mm_ker
                         for (int j = 0; j < NT; ++j)
 #pragma unroll
                             for (int i = 0; i < 4; ++i) y[c * GR + h][j0 + j][i] = (cp.first ? 0.f : y[c * GR + h][j0 + j][i]) + (NC == 1 ? t[0][j][i] : t[0][j][i] + t[NC - 1][j][i]);
+                        // added here and not where the sums are needed: the tiles would stay in registers until then, and those of
+                        // rows of 4,096 were spilled (256 and scratch, now 205), each reload a wait for the whole ring
+#pragma unroll
+                        for (int j = 0; j < NT; ++j) asm volatile("" : "+v"(y[c * GR + h][j0 + j]));
                     }
                 }
             }

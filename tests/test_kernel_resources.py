@@ -51,7 +51,7 @@ def _named(kernels, *starts):
     return got
 
 
-@pytest.mark.parametrize("name", ["ffn_fused_kernel<", "eamc_pick_kernel", "eamc_pick_score_kernel<", "eamc_topm_kernel", "eamc_topm_score_kernel<"])
+@pytest.mark.parametrize("name", ["ffn_fused_kernel<", "ffn_grouped_mm_kernel<", "ffn_grouped_kernel<", "eamc_pick_kernel", "eamc_pick_score_kernel<", "eamc_topm_kernel", "eamc_topm_score_kernel<"])
 def test_no_private_memory(kernels, name):
     for n, k in _named(kernels, name).items():
         assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, (n, k[".private_segment_fixed_size"])
