@@ -1295,10 +1295,11 @@ __global__ void __launch_bounds__(256) ffn_grouped_reduce_kernel(const float* __
     extern __shared__ __align__(16) int32_t s_rows[];  // per segment: its number << 16 | the token's places in its item; -1: none
     __shared__ float s_sum[32][32];
     __shared__ int s_wbase[4];
-    __shared__ int s_nv;
+    __shared__ int s_nv, s_more;  // s_more: the token has a second place somewhere
     const int n = n_blocks * seg_max;  // (below 2^15: a few segments for each compute unit)
-    int32_t* s_list = s_rows + n;  // the segments that hold the token, in order
+    int32_t* s_list = s_rows + n;  // rows of the token: of its first place in every segment that holds it, in order
     const int b = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    if (tid == 0) s_more = 0;
     cost = grouped_start(*n_items, n_blocks, cost);
     const int total = *n_items * (I + cost);
     for (int g = tid; g < n_blocks; g += 256) {
@@ -1326,7 +1327,10 @@ __global__ void __launch_bounds__(256) ffn_grouped_reduce_kernel(const float* __
         __syncthreads();
         int before = base;
         for (int w = 0; w < wv; ++w) before += s_wbase[w];
-        if (r >= 0) s_list[before + __popcll(mask & ((1ull << lane) - 1ull))] = r;
+        if (r >= 0) {
+            s_list[before + __popcll(mask & ((1ull << lane) - 1ull))] = (r >> 16) * tb + __ffs(r) - 1;
+            if ((r & 0xffff & (r - 1)) != 0) s_more = 1;
+        }
         base += s_wbase[0] + s_wbase[1] + s_wbase[2] + s_wbase[3];
         __syncthreads();
     }
@@ -1344,29 +1348,19 @@ __global__ void __launch_bounds__(256) ffn_grouped_reduce_kernel(const float* __
         acc.z += v.z;
         acc.w += v.w;
     };
-    auto row = [&](int entry, unsigned places) {  // the row of the first of `places`
-        return *reinterpret_cast<const float4*>(part + ((size_t)(entry >> 16) * tb + (__ffs((int)places) - 1)) * H + h);
-    };
+    auto row = [&](int at) { return *reinterpret_cast<const float4*>(part + (size_t)at * H + h); };
     for (int p = p0; p < p1; p += 8) {
         float4 v[8];
-        unsigned more = 0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (p + u < p1) {
-                const int entry = s_list[p + u];
-                const unsigned places = (unsigned)entry & 0xffffu;
-                v[u] = row(entry, places);
-                more |= places & (places - 1);
-            }
-        }
+        for (int u = 0; u < 8; ++u) v[u] = p + u < p1 ? row(s_list[p + u]) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int u = 0; u < 8; ++u) add(v[u]);
-        if (more != 0)  // an expert that the token lists more than once
-            for (int q = p; q < min(p + 8, p1); ++q)
-                for (unsigned places = (unsigned)s_list[q] & 0xffffu & ((unsigned)s_list[q] - 1); places != 0; places &= places - 1)
-                    add(row(s_list[q], places));
     }
+    if (s_more != 0)  // an expert that the token lists more than once
+        for (int e = sl; e < n; e += 32)
+            if (s_rows[e] >= 0)
+                for (int places = s_rows[e] & 0xffff & (s_rows[e] - 1); places != 0; places &= places - 1)
+                    add(row((s_rows[e] >> 16) * tb + __ffs(places) - 1));
     s_sum[sl][cq * 4 + 0] = acc.x;
     s_sum[sl][cq * 4 + 1] = acc.y;
     s_sum[sl][cq * 4 + 2] = acc.z;
