@@ -221,7 +221,9 @@ int expert_ffn_gemv_static(moei_cache* c, const int32_t* d_slot_ids, const float
  * d_idx[B][k] int32, d_w[B][k] fp32, d_x[B][H] in desc->wdtype, d_y[B][H] fp32.  A pick that is
  * not resident contributes nothing and raises error flag bit 1; a pick outside [0, E) (a token
  * that got no picks) is passed over.  Needs H to be a multiple of 64 lanes x 16 bytes, E <= 256
- * and B * k <= 512 (MOEI_EINVAL otherwise).  Results are bit-reproducible run to run. */
+ * and B * k <= 512 (MOEI_EINVAL otherwise).  Results are bit-reproducible run to run.  The first call allocates
+ * the cache's scratch for all batches: partial rows of 4 tokens for every compute unit and expert it may
+ * work on, of 16 where the model has batches for the matrix cores (256 units, H = 2048: 17 and 67 MB). */
 int expert_ffn_grouped(moei_cache* c, int32_t layer, const int32_t* d_idx, const float* d_w, int32_t B,
                        const void* d_x, float* d_y, void* stream);
 /* Device-side error flags raised by kernels since the last call (bit 0: bad slot id,

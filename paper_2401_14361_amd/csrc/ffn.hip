@@ -1513,6 +1513,13 @@ bool grouped_mm(const moei_model_desc& d, int B) {
     if (compute_units() * (served / streamed) * 4.0 * d.H > 1.5 * streamed * expert) return false;
     return (served - 1.25 * streamed) * expert >= (d.H > 2048 ? 100e6 : 5e6);
 }
+// Whether any batch of the model takes it: its rows are up to four times those of the vector kernel (67 MB, 17 without, for the
+// 64-expert shape).
+bool grouped_mm_any(const moei_model_desc& d) {
+    for (int B = 1; B <= kMaxBatch; ++B)
+        if (grouped_mm(d, B)) return d.H == 512 || d.H == 1024 || d.H == 2048 || d.H == 4096;
+    return false;
+}
 // items of 16 picks: the sum over the experts of ceil(picks / 16), and the shared experts
 int gm_max_items(const moei_model_desc& d, int B) { return std::min(B * d.k, d.E + (B * d.k + kGmTokens - 1) / kGmTokens) + d.n_shared; }
 int gm_segments(const moei_model_desc& d) { return grouped_seg_max(gm_max_items(d, kMaxBatch), compute_units()); }
@@ -1524,7 +1531,7 @@ size_t grouped_item_bytes() { return std::max(sizeof(GroupItem), sizeof(GmItemOu
 size_t grouped_part_floats(const moei_model_desc& d) {
     const int G = compute_units();
     const size_t rows = (size_t)G * grouped_seg_max(grouped_max_items(d), G) * kMaxGroup;
-    if (d.wdtype != MOEI_WDTYPE_BF16) return rows * d.H;
+    if (!grouped_mm_any(d)) return rows * d.H;
     return std::max(rows, gm_rows(d)) * d.H + (size_t)kMaxBatch * d.H / 2;  // behind the rows: an aligned copy of the tokens
 }
 

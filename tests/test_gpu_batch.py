@@ -235,3 +235,28 @@ def test_batched_ffn_with_an_expert_listed_twice(m, wdtype, H, I, B):
     idx[1] = 3
     idx[B - 1] = [1, 1, 0, 0]
     _ffn_only_case(m, cfg, B, idx, rng.random((B, 4)) + 0.1)
+
+
+# scratch of the first call: rows of 16 tokens only where a batch of the model can take the matrix kernel (not where none saves
+# enough, and not for rows that the call refuses)
+@pytest.mark.parametrize("H,I,taken", [(4096, 16, True), (5120, 600, False)])
+def test_batched_ffn_scratch_is_what_its_calls_take(m, H, I, taken):
+    E, k, B = 64, 2, 16
+    desc = m.ModelDesc(1, E, k, 0, H, I, m.WDTYPE_BF16, 0, EPS)
+    caches = [m.Cache(desc, E) for _ in range(2)]
+    idx, w = dev(np.tile(np.arange(k, dtype=np.int32), (B, 1))), dev(np.ones((B, k), np.float32))
+    x = dev(np.zeros((B, H), dtype=np.uint16))
+    free = []
+    for cache in caches:  # the first one's call loads the code
+        cache.reset(E)
+        if taken:
+            m.expert_ffn_grouped(cache, 0, idx, w, x)
+        else:
+            with pytest.raises(m.MoeiError):
+                m.expert_ffn_grouped(cache, 0, idx, w, x)
+        torch.cuda.synchronize()
+        free.append(torch.cuda.mem_get_info()[0])
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    assert free[0] - free[1] <= units * 2 * 4 * H * 4 + (4 << 20), (free[0] - free[1]) / 2**20
+    for cache in caches:
+        cache.close()
