@@ -58,6 +58,7 @@ enum KernelId {
     K_PF_GATEUP,
     K_PF_DOWN,
     K_PF_REDUCE,
+    K_FFN_GROUPED_MM,
     K_COUNT
 };
 extern bool g_prof_on;

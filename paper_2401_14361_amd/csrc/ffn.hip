@@ -1587,7 +1587,7 @@ int launch_grouped_mm(const moei_model_desc& d, GroupedMmArgs ga, int B, float* 
         const size_t smem = gm_lds<HW_>(ga.max_items, ga.n_list);                                      \
         rc = allow_big_lds(ffn_grouped_mm_kernel<HW_>, smem);                                          \
         if (rc) return rc;                                                                             \
-        launch(K_FFN_FUSED, ffn_grouped_mm_kernel<HW_>, dim3(grid), dim3(kGroupedWaves * kWave), smem, s, ga); \
+        launch(K_FFN_GROUPED_MM, ffn_grouped_mm_kernel<HW_>, dim3(grid), dim3(kGroupedWaves * kWave), smem, s, ga); \
         MOEI_LAUNCH_CHECK();                                                                           \
         break;                                                                                         \
     }

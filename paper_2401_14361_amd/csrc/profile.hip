@@ -20,6 +20,7 @@ const char* const kNames[K_COUNT] = {
     "route_topk_kernel", "eamc_dot_kernel",   "eamc_pick_kernel", "priority_order_kernel",
     "priority_rank_kernel", "ffn_fused_kernel", "ffn_reduce_kernel", "prefill_group_kernels",
     "prefill_route_kernel", "prefill_gateup_kernel", "prefill_down_kernel", "prefill_reduce_kernel",
+    "ffn_grouped_mm_kernel",
 };
 
 void drop_pool() {

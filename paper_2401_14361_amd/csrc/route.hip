@@ -126,7 +126,7 @@ constexpr int kRouteWaves = 4;  // expert rows per workgroup: fewer workgroups, 
 template <typename WT, int NW>
 __global__ void __launch_bounds__(NW * kWave) route_fused_kernel(RouteFusedArgs a) {
     using V = WVec<WT>;
-    extern __shared__ float z[];  // E logits, then E slot ids, the E counts of this layer's EAM row, 4 x E partial ranks
+    extern __shared__ float z[];  // E logits, then E slot ids, the E counts of this layer's EAM row, NW x E partial ranks
     __shared__ unsigned s_ticket;
     __shared__ int s_pick[kWave];
     __shared__ float s_pw[kWave];

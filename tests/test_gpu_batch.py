@@ -96,8 +96,18 @@ def test_batched_ffn_other_shapes(m, wdtype, H, I):
     _batch_case(m, cfg, 32, [3, 16])
 
 
-def _ffn_only_case(m, cfg, B, idx, w, seed=3):
-    """expert_ffn_grouped on given picks (all experts resident) against the oracle, token by token."""
+def _kernels_of(m, call):
+    """(what `call` returns, launches of the vector kernel, launches of the matrix kernel)"""
+    m.profile_enable(8)
+    out = call()
+    prof = m.profile_read()
+    m.profile_disable()
+    return out, prof["ffn_fused_kernel"][0], prof["ffn_grouped_mm_kernel"][0]
+
+
+def _ffn_only_case(m, cfg, B, idx, w, seed=3, matrix=None, resident=None):
+    """expert_ffn_grouped on given picks against the oracle, token by token.  All experts are resident, or the first `resident`;
+    `matrix`: whether the call is expected on the matrix cores."""
     L, E = cfg.L, cfg.E
     rng = np.random.default_rng(seed)
     n_unique = min(E, 40)
@@ -114,22 +124,24 @@ def _ffn_only_case(m, cfg, B, idx, w, seed=3):
     for s in range(L * cfg.n_shared):
         t = cache.slot_tensor(S + s)
         t.copy_(dev(sh_packed[s]).view(t.dtype))
-    cache.reset(S)
+    cache.reset(S if resident is None else resident)
     x = (rng.standard_normal((B, cfg.H)) * 0.5).astype(np.float32)
     xr = mi.f32_to_bf16_bits(x) if cfg.wdtype == "bf16" else x  # stored form: the oracle decodes it exactly
     xq = dev(xr)
     layer = L - 1
-    y = m.expert_ffn_grouped(cache, layer, dev(idx.astype(np.int32)), dev(w.astype(np.float32)), xq).cpu().numpy()
+    y, n_vector, n_matrix = _kernels_of(m, lambda: m.expert_ffn_grouped(cache, layer, dev(idx.astype(np.int32)), dev(w.astype(np.float32)), xq))
+    assert n_vector + n_matrix == 1 and (matrix is None or n_matrix == matrix)
+    y = y.cpu().numpy()
     for b in range(B):
         ex, ws = [], []
         for j, wj in zip(idx[b], w[b]):
-            if j >= 0:
+            if j >= 0 and (resident is None or layer * E + j < resident):
                 ex.append(split_expert(cfg, bank[(layer * E + int(j)) % n_unique]))
                 ws.append(float(wj))
         ex += [split_expert(cfg, shared[layer * cfg.n_shared + s]) for s in range(cfg.n_shared)]
         ref = O.expert_ffn(xr[b], ex, ws + [1.0] * cfg.n_shared)
         assert rel_max_err(y[b], ref) <= FFN_TOL_FP32ACC, b
-    assert cache.error_flags() == 0
+    assert cache.error_flags() == (0 if resident is None else 2)
     cache.close()
 
 
@@ -180,7 +192,7 @@ def test_batched_ffn_rejects_more_experts_than_the_item_builder_takes(m):
 
 # items of up to 16 picks (the matrix kernel): every row width, units that are no whole number of blocks, fewer than a block for
 # a workgroup and many blocks, batches of 4 to 16, a full list of picks and experts
-@pytest.mark.parametrize("H,I,E,k,n_shared,B", [(512, 923, 2, 2, 0, 16), (512, 1100, 3, 3, 1, 5), (512, 7, 256, 32, 0, 16),
+@pytest.mark.parametrize("H,I,E,k,n_shared,B", [(512, 923, 2, 2, 0, 16), (512, 1100, 3, 3, 1, 5), (512, 8, 256, 32, 0, 16),
                                                 (1024, 307, 4, 3, 1, 16), (1024, 4099, 2, 1, 0, 9), (2048, 250, 3, 2, 2, 13),
                                                 (2048, 250, 2, 1, 0, 4), (4096, 133, 6, 5, 1, 7), (4096, 600, 3, 2, 0, 16)])
 def test_batched_ffn_on_the_matrix_cores(m, H, I, E, k, n_shared, B):
@@ -189,7 +201,18 @@ def test_batched_ffn_on_the_matrix_cores(m, H, I, E, k, n_shared, B):
     idx = np.stack([rng.choice(E, size=k, replace=False) for _ in range(B)]).astype(np.int32)
     if B > 8:
         idx[3] = -1  # a token without picks
-    _ffn_only_case(m, cfg, B, idx, rng.random((B, k)).astype(np.float32))
+    _ffn_only_case(m, cfg, B, idx, rng.random((B, k)).astype(np.float32), matrix=True)
+
+
+# experts beyond the item builder's first wavefront of 64, in each of its four, the last of them not resident
+@pytest.mark.parametrize("H,I,E,k,n_shared,B,resident", [(1024, 64, 200, 16, 2, 16, 150), (512, 40, 256, 32, 0, 16, 100), (2048, 24, 65, 9, 1, 13, 64),
+                                                         (512, 130, 129, 20, 0, 7, 128)])
+def test_batched_ffn_on_the_matrix_cores_many_experts(m, H, I, E, k, n_shared, B, resident):
+    cfg = mi.get_config("C5").scaled(L=1, E=E, k=k, n_shared=n_shared, H=H, I=I, N=8, prompt=16)
+    rng = np.random.default_rng(E + k)
+    idx = np.stack([rng.choice(E, size=k, replace=False) for _ in range(B)]).astype(np.int32)
+    idx[0, 0] = E - 1
+    _ffn_only_case(m, cfg, B, idx, rng.random((B, k)).astype(np.float32), matrix=True, resident=resident)
 
 
 def test_batched_ffn_on_the_matrix_cores_infinite_weights_and_unaligned_inputs(m):
@@ -208,7 +231,9 @@ def test_batched_ffn_on_the_matrix_cores_infinite_weights_and_unaligned_inputs(m
     x = room[1:1 + B * H].view(B, H)  # 2 bytes past a 16-byte boundary
     idx = torch.tensor([[0, 2] if b % 3 == 0 else ([1, 0] if b % 3 == 1 else [2, 3]) for b in range(B)], dtype=torch.int32, device="cuda")
     w = torch.rand((B, k), generator=g, device="cuda") + 0.1
-    y = m.expert_ffn_grouped(cache, 0, idx, w, x).double()
+    y, _, n_matrix = _kernels_of(m, lambda: m.expert_ffn_grouped(cache, 0, idx, w, x))
+    assert n_matrix == 1
+    y = y.double()
     ref = torch.zeros_like(y)
     for b in range(B):
         for j in range(k):
@@ -226,15 +251,16 @@ def test_batched_ffn_on_the_matrix_cores_infinite_weights_and_unaligned_inputs(m
 
 # a token that lists an expert twice (or more often) gets its output with each of the weights: in one item, in several, and beside
 # tokens that list it once; on both kernels (3 requests and fp32 weights: the vector kernel)
-@pytest.mark.parametrize("wdtype,H,I,B", [("bf16", 4096, 600, 8), ("bf16", 1024, 400, 16), ("bf16", 4096, 40, 3), ("bf16", 512, 60, 3), ("fp32", 256, 50, 16)])
-def test_batched_ffn_with_an_expert_listed_twice(m, wdtype, H, I, B):
+@pytest.mark.parametrize("wdtype,H,I,B,matrix", [("bf16", 4096, 600, 8, True), ("bf16", 1024, 400, 16, True), ("bf16", 4096, 40, 3, False),
+                                                 ("bf16", 512, 60, 3, False), ("fp32", 256, 50, 16, False)])
+def test_batched_ffn_with_an_expert_listed_twice(m, wdtype, H, I, B, matrix):
     cfg = mi.get_config("C5").scaled(L=1, E=4, k=4, n_shared=1, H=H, I=I, N=8, prompt=16, wdtype=wdtype)
     rng = np.random.default_rng(H + B)
     idx = np.stack([rng.permutation(4) for _ in range(B)])
     idx[0] = [2, 1, 2, 0]
     idx[1] = 3
     idx[B - 1] = [1, 1, 0, 0]
-    _ffn_only_case(m, cfg, B, idx, rng.random((B, 4)) + 0.1)
+    _ffn_only_case(m, cfg, B, idx, rng.random((B, 4)) + 0.1, matrix=matrix)
 
 
 # scratch of the first call: rows of 16 tokens only where a batch of the model can take the matrix kernel (not where none saves

@@ -520,16 +520,19 @@ def test_heads_of_the_orders_from_several_matches(m, L, E, N, matches):
 def test_match_beside_the_experts(m, L, E, N, cell_bytes):
     rng = np.random.default_rng(L * E + N)
     k, H, I = 3, 64, 8
-    desc = m.ModelDesc(L, E, k, 0, H, I, m.WDTYPE_BF16, 0, EPS)
+    cfg = mi.get_config("C2").scaled(L=L, E=E, k=k, n_shared=0, H=H, I=I)
+    desc = m.ModelDesc.from_config(cfg)
+    bank = mi.expert_bank(cfg, 3, threads=2)
     T = (rng.integers(0, 30, size=(N, L, E)) * (rng.random((N, L, E)) < 0.3)).astype(np.int32)
     T[N // 2:] = T[:N - N // 2]  # equal similarities: the lower index wins
     eamc = m.Eamc(desc, max(N, 1), cell_bytes)
     eamc.load(T)
-    cache = m.Cache(desc, L * E, pinned(np.zeros((2, 3 * H * I), dtype=np.uint16)))
+    cache = m.Cache(desc, L * E, pinned(pack_bank(m, cfg, bank)))
     cache.reset(L * E - k)
     d_eam = dev(T[N // 3].copy() if N else np.zeros((L, E), dtype=np.int32))
     y = torch.empty(H, dtype=torch.float32, device="cuda")
-    W, x = dev(np.zeros((E, H), dtype=np.uint16)), dev(np.zeros(H, dtype=np.uint16))
+    xq = mi.f32_to_bf16_bits((rng.standard_normal(H) * 0.5).astype(np.float32))
+    W, x = dev(np.zeros((E, H), dtype=np.uint16)), dev(xq)  # the bias alone decides the picks
     torch.cuda.synchronize()
     streams = [torch.cuda.current_stream(), torch.cuda.Stream(), torch.cuda.Stream()]
     for step, (layer, sync) in enumerate([(0, False), (L - 2, False), (0, True), (1, False), (L - 2, False)]):
@@ -539,14 +542,24 @@ def test_match_beside_the_experts(m, L, E, N, cell_bytes):
         d_bias, s = dev(bias), streams[step % 3]
         torch.cuda.synchronize()
         res = cache.get_slots().reshape(L, E) >= 0
+        y.fill_(float("nan"))
+        m.profile_enable(16)
+        torch.cuda.synchronize()
         m.moe_decode_layer(cache, eamc, d_eam, layer, W, d_bias, x, y, sync=sync, stream=s.cuda_stream)
         if step % 2:
             cache.join(streams[2 - step % 3].cuda_stream)
         top, sim = cache.last_matches()
+        s.synchronize()
+        assert m.profile_read()["eamc_pick_kernel"][0] == (1 if sync else 0)  # beside the experts: no kernel of its own
+        m.profile_disable()
         last = cache.last_step()
         picks = np.argsort(-bias, kind="stable")[:k]
         ref_eam[layer, picks] += 1
         assert (d_eam.cpu().numpy() == ref_eam).all()
+        ridx, rw = O.route_topk(bias[None], k, bool(cfg.renorm))
+        assert ridx[0].tolist() == picks.tolist()
+        ref_y = O.expert_ffn(xq, [split_expert(cfg, bank[(layer * E + int(j)) % 3]) for j in picks], list(rw[0]))
+        assert rel_max_err(y.cpu().numpy(), ref_y) <= FFN_TOL_FP32ACC
         best, ref_sim, _ = O.eamc_match(T, ref_eam) if N else (-1, 0.0, None)
         assert top.tolist() == [best]
         np.testing.assert_allclose(sim, [ref_sim], rtol=1e-5)
