@@ -853,9 +853,10 @@ __global__ void __launch_bounds__((kGroupedWaves * kWave)) ffn_grouped_kernel(Gr
 // columns for rows of 4,096; no barrier, the waits are counted), the token rows of an item through the same ring before its first block.  The ring runs on across
 // blocks and items: a block's down rows come behind the next block's gate and up rows, so that the exchange of the
 // partial tiles (two barriers that wait for LDS only) does not hold it up, and what an item's end costs is the store of its rows.
-// Bound by the stream: sixteen requests of the 64-expert shape 155 us a call, 865 MB at 5.9 TB/s between start and end; with
+// Bound by the stream: sixteen requests of the 64-expert shape 162 us a call, 865 MB at 5.7 TB/s between start and end; with
 // items of four tokens in registers (the kernel above: the shared experts pass four times, and at a segment's end the window
-// drains and eight rows a token are added through LDS) 182.  Loads without the non-temporal hint took 12 % longer, stages of 128
+// drains and eight rows a token are added through LDS) 190.  Nothing on the way waits for the whole ring: with sums in private memory
+// and the exchange's lane address there too, 8 experts of 6,000 units, H = 4,096, 8 / 16 requests took 207 / 234 us, now 190 / 217.  Loads without the non-temporal hint took 12 % longer, stages of 128
 // columns, four in the ring, 1 %.
 // Rounding: sums run as several short chains (a chain per matrix instruction of a stage, two per block and down tile, a block's sum
 // added to those before it), so that the error against 64 bits is that of the kernel above or less: relative 2-norm 1.6 - 2.0e-7, there
@@ -1497,13 +1498,17 @@ namespace {
 // Which kernel a bf16 call takes.  Both stream an expert once for up to four requests (rows of 4,096: the vector kernel once per
 // request), and the matrix kernel takes 1 - 7 us longer to start and to end, so it has to save something: it does from
 // four requests on where an expert is expected to serve more than 1.25 of them, by as much as there is to stream.  us a call,
-// vector / matrix kernel: 64 experts of 1,408 units + 2 shared, H = 2,048, top 6, 1 / 2 / 3 / 4 / 8 / 16 requests 33.9 / 37.1, 50.2 / 51.7, 66.4 /
-// 65.4, 83.2 / 77.4, 125 / 115, 182 / 155; 8 of 6,000 units, H = 4,096, top 2, 8 / 16 requests 268 / 216, 439 / 226;
-// 100 of 2,000, H = 1,024, top 8, 6 requests (1.2 of them an expert) 85.3 / 86.2; 20 of 300, H = 4,096, top 1, 8 requests (1.2) 22.5 /
-// 26.1; 16 of 400, H = 512, top 4, 4 / 6 / 12 requests (1.5 / 1.8 / 3.1) 14.7 / 15.5, 16.8 / 15.8, 20.0 / 16.6.  Rows of 4,096, which start
-// and end longest, have to save 100 MB (17 of 325 units, top 2, 13 requests, 71 MB: 46.9 / 49.6), and the partial rows - one per workgroup and
+// vector / matrix kernel: 64 experts of 1,408 units + 2 shared, H = 2,048, top 6, 1 / 2 / 3 / 4 / 8 / 16 requests 30.8 / 35.7, 47.1 / 50.9, 65.5 /
+// 66.1, 83.2 / 81.0, 129 / 119, 190 / 162; 8 of 6,000 units, H = 4,096, top 2, 3 / 8 / 16 requests 143 / 145, 269 / 190, 472 / 217.  Three
+// requests of other models are slower too or the same (8 of 1,400 + 2, H = 2,048 33.9 / 37.5; 16 of 400, H = 512 13.0 / 15.2; 32 of 700 + 1, H = 1,024
+// 19.9 / 19.3).
+// 100 of 2,000, H = 1,024, top 8, 6 requests (1.2 of them an expert) 84.0 / 84.4; 20 of 300, H = 4,096, top 1, 8 requests (1.2) 20.9 /
+// 26.7; 16 of 400, H = 512, top 4, 4 / 6 / 12 requests (1.5 / 1.8 / 3.1) 13.1 / 15.5, 15.3 / 15.9, 19.2 / 16.8.  Rows of 4,096, which start
+// and end longest, have to save 100 MB (17 of 325 units, top 2, 13 requests, 71 MB: 44.9 / 47.5), and the partial rows - one per workgroup and
 // token of its item - must not outweigh the weights (4 of 225 units, H = 1,024, 12 requests of all four: 12.6 MB of rows, 5.5 MB of
-// weights, 19.7 / 23.6).  Over 60 calls of 3 - 16 requests drawn from the ranges of perf/cases.py 0.70 of the vector kernel's time.
+// weights, 18.7 / 22.8).  Over 606 calls of 4 - 16 requests that the rule gives to it (2 - 160 experts of 60 - 6,000 units) 0.78 of the vector
+// kernel's time; 36 of them take 3 % longer or more (29 of 1,727, H = 512, top 2, 13 requests 27.8 / 34.6 is the worst), which neither the bytes it
+// is expected to save nor the requests an expert set apart from those that gain.
 bool grouped_mm(const moei_model_desc& d, int B) {
     if (d.wdtype != MOEI_WDTYPE_BF16 || B < 4) return false;
     double none = 1.0;  // share of the experts that nobody picks, picks being even

@@ -1463,8 +1463,8 @@ int tile_tokens(const moei_model_desc& d, int n) {
 
 // In how many parts the down kernel of the 64-token items takes an expert's units: a workgroup has 512 columns of an item, so a
 // few experts of few tokens leave most of the chip idle while each workgroup works through thousands of units by itself.  As many
-// as bring two workgroups to a compute unit, none shorter than two slices, and no more than the rows of 512 tokens hold (what
-// the scratch has at least).  us a layer without / with, prompts of 8 - 90 tokens: 4 experts of 2,432 units, H = 1,536 134 / 60; 5 of 2,216 + 1,
+// as bring two workgroups to a compute unit, of two slices or more (the last may be left with one: seven slices in three parts
+// are 3 + 3 + 1), and no more than the rows of 512 tokens hold (what the scratch has at least).  us a layer without / with, prompts of 8 - 90 tokens: 4 experts of 2,432 units, H = 1,536 134 / 60; 5 of 2,216 + 1,
 // H = 640 122 / 56; 10 of 2,024 + 2, H = 1,408 128 / 65; 31 of 3,840 + 2, H = 1,408 257 / 146; 100 prompts of 5 - 1,500 tokens of
 // perf/cases.py's ranges 0.885 of the time in the mean, none slower.  64 experts of 1,408 units, H = 2,048, 77 tokens fill the chip as
 // they are (in two parts the product gained 4 us and the reduction lost them).

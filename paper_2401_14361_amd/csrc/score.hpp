@@ -388,9 +388,10 @@ __device__ __forceinline__ void wave_head(const u64* keys, int LE, int ltid, int
 // A chain of dependent steps, so what counts is their number: with four wavefronts a list and eight keys in
 // registers, every round over 9,440 cells was one more trip to memory per 256 of them, and the finishing workgroup of the
 // match took 60.8 us (59 x 160 cells, heads of 6 and 0 entries), 260 with a prefetch depth of 32; with eight and 20 keys 34.0
-// and 90.1.  Few cells are searched by four: with eight a list has twice the candidates to merge (26 x 64 cells, depth 32: 55.0
-// us, with four 47.0), and both forms in one kernel are more than twice the instructions to fetch (4 x 8 cells 9.0 us, in a
-// kernel of their own 8.4; 32 x 8 cells 16.0 and 15.2).
+// and 90.1, and with a lane's two best cells kept as well 31.4 and 74.  Few cells are searched by four: with eight a list has
+// twice the candidates to merge (26 x 64 cells, depth 32: 55.0
+// us, with four 47.0, now 36.9), and both forms in one kernel are more than twice the instructions to fetch (4 x 8 cells 9.0 us, in a
+// kernel of their own 8.4; 32 x 8 cells 16.0 and 15.2, now 13.9).
 template <bool LARGE>
 __device__ __forceinline__ void select_heads(const ScoreArgs& a, const u64* kp, const u64* kv, const int* s_n, ScoreLds<LARGE>& hl) {
     constexpr int kSelWaves = Sel<LARGE>::kWaves, kSelThreads = Sel<LARGE>::kThreads, kOwn = Sel<LARGE>::kOwn;
