@@ -22,6 +22,7 @@
 
 #include "ffn_plan.hpp"
 #include "kernels.hpp"
+#include "lds_limit.hpp"
 #include "step_match.hpp"
 #include "wtypes.hpp"
 
@@ -401,20 +402,13 @@ int forced_waves() {
 // is not a stream operation, so it stays out of the per-launch path and of captures).
 template <typename K>
 int allow_big_lds(K kernel, size_t bytes) {
-    constexpr int kSeen = 128;  // kernels of one argument type: 104 streaming FFNs are the most
-    static const void* seen_fn[kSeen];
-    static size_t seen_bytes[kSeen];
-    static int n_seen = 0;
+    static LdsLimits<128> limits;  // kernels of one argument type: 104 streaming FFNs are the most
     if (bytes <= 64 * 1024) return MOEI_OK;
     const void* fn = reinterpret_cast<const void*>(kernel);
-    for (int i = 0; i < n_seen; ++i)
-        if (seen_fn[i] == fn && seen_bytes[i] >= bytes) return MOEI_OK;
-    MOEI_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-    if (n_seen < kSeen) {
-        seen_fn[n_seen] = fn;
-        seen_bytes[n_seen++] = bytes;
-    }
-    return MOEI_OK;
+    return limits.at_least(fn, bytes, [&]() -> int {
+        MOEI_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+        return MOEI_OK;
+    });
 }
 
 template <typename WT>

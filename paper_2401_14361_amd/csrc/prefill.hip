@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "lds_limit.hpp"
 #include "topk.hpp"
 #include "wtypes.hpp"
 
@@ -1413,19 +1414,13 @@ __global__ void __launch_bounds__(kRtThreads) prefill_route_wide_kernel(const ui
 
 template <typename K>
 int pf_allow_lds(K kernel, size_t bytes) {
-    static const void* seen_fn[8];
-    static size_t seen_bytes[8];
-    static int n_seen = 0;
+    static LdsLimits<8> limits;
     if (bytes <= 64 * 1024) return MOEI_OK;
     const void* fn = reinterpret_cast<const void*>(kernel);
-    for (int i = 0; i < n_seen; ++i)
-        if (seen_fn[i] == fn && seen_bytes[i] >= bytes) return MOEI_OK;
-    MOEI_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-    if (n_seen < 8) {
-        seen_fn[n_seen] = fn;
-        seen_bytes[n_seen++] = bytes;
-    }
-    return MOEI_OK;
+    return limits.at_least(fn, bytes, [&]() -> int {
+        MOEI_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+        return MOEI_OK;
+    });
 }
 
 }  // namespace
