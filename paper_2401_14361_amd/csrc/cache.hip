@@ -877,8 +877,10 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
         const StepMatchArgs ma{match_blocks, eamc->d_norm2, d_snap, c->d_step_cand, c->d_step_idx, c->d_step_ticket, c->d_best,
                                c->d_best_sim, c->match_captured ? nullptr : &c->pin_dev->matched,
                                c->match_captured ? 0 : ++c->step_seq, sc};
-        return launch_expert_ffn(d, c->d_pool, c->slot_elems, c->n_total, c->ffn, c->d_slot_ids, c->d_gate, k + d.n_shared, d_x, d_y,
-                                 c->d_flags, &ma, step_match_lds(eamc, match_blocks), s);
+        rc = launch_expert_ffn(d, c->d_pool, c->slot_elems, c->n_total, c->ffn, c->d_slot_ids, c->d_gate, k + d.n_shared, d_x, d_y,
+                               c->d_flags, &ma, step_match_lds(eamc, match_blocks), s);
+        if (rc) c->match_on_stream = false;  // nobody will store the step's number
+        return rc;
     }
     MOEI_HIP(hipEventRecord(c->ev_routed, s));
     // Asynchronous step: the expert FFNs go onto the main stream right behind the routing,
