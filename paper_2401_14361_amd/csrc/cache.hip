@@ -112,7 +112,9 @@ struct moei_cache {
     int32_t* d_flags = nullptr;
     unsigned* d_ticket = nullptr;
     hipStream_t copy_stream = nullptr, side_stream = nullptr;
-    // scratch of the steps that match beside the experts (step_match.hpp)
+    // scratch of the steps in one launch (step_match.hpp, step_route.hpp)
+    u64* d_step_words = nullptr;
+    int step_spin = 0;             // polls after which a workgroup of such a step routes by itself (MOEI_STEP_SPIN)
     u64* d_step_cand = nullptr;
     int32_t* d_step_idx = nullptr;
     unsigned* d_step_ticket = nullptr;
@@ -204,6 +206,7 @@ extern "C" int moei_cache_destroy(moei_cache* c) {
     (void)hipFree(c->d_step_cand);
     (void)hipFree(c->d_step_idx);
     (void)hipFree(c->d_step_ticket);
+    (void)hipFree(c->d_step_words);
     ffn_scratch_free(&c->ffn);
     (void)hipFree(c->d_items);
     (void)hipFree(c->d_n_items);
@@ -247,6 +250,8 @@ extern "C" int moei_cache_destroy(moei_cache* c) {
 
 namespace {
 
+size_t step_words_bytes(const moei_model_desc& d) { return kStepCopies * step_copy_words(d.E) * sizeof(u64); }
+
 int upload_slot_table(moei_cache* c) {
     MOEI_HIP(hipMemcpy(c->d_slot_of, c->slot_of.data(), c->slot_of.size() * 4, hipMemcpyHostToDevice));
     return MOEI_OK;
@@ -270,6 +275,7 @@ int cache_alloc(moei_cache* c) {
     MOEI_DMALLOC(c->d_step_cand, (size_t)kStepMatchMaxBlocks * 2 * sizeof(u64));
     MOEI_DMALLOC(c->d_step_idx, (size_t)kStepMatchMaxBlocks * 4);
     MOEI_DMALLOC(c->d_step_ticket, 4);
+    MOEI_DMALLOC(c->d_step_words, step_words_bytes(d));
     MOEI_DMALLOC(c->d_logits, (size_t)d.E * 4);
     for (int r = 0; r < kRing; ++r) {
         MOEI_DMALLOC(c->d_idx2[r], (size_t)kMaxAct * 4);
@@ -294,6 +300,7 @@ int cache_alloc(moei_cache* c) {
     MOEI_HIP(hipMemset(c->d_flags, 0, 4));
     MOEI_HIP(hipMemset(c->d_ticket, 0, 4));
     MOEI_HIP(hipMemset(c->d_step_ticket, 0, 4));
+    MOEI_HIP(hipMemset(c->d_step_words, 0, step_words_bytes(c->d)));
     MOEI_HIP(hipMemset(c->d_n_pf, 0, 4));
     MOEI_HIP(hipMemset(c->d_n_ev, 0, 4));
     MOEI_HIP(hipMemset(c->d_best, 0xff, kMaxMatchBatch * 4));
@@ -302,6 +309,9 @@ int cache_alloc(moei_cache* c) {
     {
         const char* v = getenv("MOEI_SYNC_POLL");  // read when a cache is created
         c->poll = !(v && *v == '0');
+        // a poll takes 0.5 - 3 us
+        v = getenv("MOEI_STEP_SPIN");
+        c->step_spin = v && *v ? atoi(v) : 400;
     }
     // mapped, coherent host memory: the routing and scoring kernels of a synchronous step store what the
     // host reads next (picks, matched trace, heads, scores) straight into it
@@ -310,9 +320,11 @@ int cache_alloc(moei_cache* c) {
     MOEI_HIP(hipHostMalloc((void**)&c->pin_V, LE * sizeof(float), hipHostMallocMapped | hipHostMallocCoherent));
     MOEI_HIP(hipHostGetDevicePointer((void**)&c->pin_dev, c->pin, 0));
     MOEI_HIP(hipHostGetDevicePointer((void**)&c->pin_V_dev, c->pin_V, 0));
-    MOEI_HIP(hipStreamCreateWithFlags(&c->pf_stream, hipStreamNonBlocking));
-    MOEI_HIP(hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking));
     MOEI_HIP(hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking));
+    if (c->h_experts) {  // the others carry copies from the host
+        MOEI_HIP(hipStreamCreateWithFlags(&c->pf_stream, hipStreamNonBlocking));
+        MOEI_HIP(hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking));
+    }
     MOEI_HIP(hipEventCreateWithFlags(&c->ev_copy, hipEventDisableTiming));
     MOEI_HIP(hipEventCreateWithFlags(&c->ev_routed, hipEventDisableTiming));
     for (int r = 0; r < kRing; ++r) MOEI_HIP(hipEventCreateWithFlags(&c->ev_match[r], hipEventDisableTiming));
@@ -403,6 +415,7 @@ extern "C" int moei_cache_reset(moei_cache* c, int32_t n_resident) {
     MOEI_HIP(hipMemset(c->d_flags, 0, 4));
     MOEI_HIP(hipMemset(c->d_ticket, 0, 4));
     MOEI_HIP(hipMemset(c->d_step_ticket, 0, 4));
+    MOEI_HIP(hipMemset(c->d_step_words, 0, step_words_bytes(c->d)));
     return upload_slot_table(c);
 }
 
@@ -656,7 +669,7 @@ extern "C" int expert_ffn_gemv(moei_cache* c, const int32_t* d_slot_ids, const f
                  n_act, c->ffn.n_act_max);
     MOEI_REQUIRE(n_act == 0 || (d_slot_ids && d_gate_w), "expert_ffn_gemv: null slot ids or gate weights");
     return launch_expert_ffn(c->d, c->d_pool, c->slot_elems, c->n_total, c->ffn, d_slot_ids, d_gate_w, n_act, d_x, d_y,
-                             c->d_flags, nullptr, 0, as_stream(stream));
+                             c->d_flags, nullptr, as_stream(stream));
 }
 
 extern "C" int expert_ffn_gemv_static(moei_cache* c, const int32_t* d_slot_ids, const float* d_gate_w, int32_t n_act,
@@ -827,37 +840,6 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
             if (rc) return rc;
         }
     c->d_idx = c->d_idx2[c->parity];
-    int32_t* d_snap = c->d_snap[c->parity];
-
-    RouteFusedArgs ra{};
-    ra.W = d_router_w;
-    ra.bias = d_router_bias;
-    ra.x = d_x;
-    ra.H = d.H;
-    ra.logits = c->d_logits;
-    ra.ticket = c->d_ticket;
-    ra.E = E;
-    ra.k = k;
-    ra.renorm = d.renorm_topk != 0;
-    ra.idx = c->d_idx;
-    ra.w = c->d_w;
-    ra.eam = d_eam;
-    ra.snap = d_snap;
-    ra.LE = d.L * E;
-    ra.layer = layer;
-    ra.slot_of_row = c->d_slot_of + (size_t)layer * E;
-    ra.n_shared = d.n_shared;
-    ra.shared_base = c->S + layer * d.n_shared;
-    ra.slot_ids = c->d_slot_ids;
-    ra.gate = c->d_gate;
-    ra.flags = sync_mode ? nullptr : c->d_flags;
-    ra.host_idx = sync_mode ? c->pin_dev->idx : nullptr;
-    if (sync_mode && c->poll) {  // only synchronous steps write these words, and each waits for its own
-        volatile int32_t* pi = c->pin->idx;
-        for (int j = 0; j < k; ++j) pi[j] = kNotWritten;
-    }
-    rc = launch_route_fused(ra, d.wdtype, s);
-    if (rc) return rc;
     // match and scoring (the workgroup that finishes the match scores the matched trace), then the heads of the two orders:
     // Alg. 1 takes the victims from the head of the eviction order (one per miss at most) and prefetching
     // looks at `depth` candidates; the complete orders are ranked from the step's keys when
@@ -874,21 +856,80 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
     c->match_on_stream = match_blocks > 0;
     if (match_blocks > 0) {
         c->match_captured = captured;  // (what a capture records runs with the graph: no call outside it waits for that)
-        const StepMatchArgs ma{match_blocks, eamc->d_norm2, d_snap, c->d_step_cand, c->d_step_idx, c->d_step_ticket, c->d_best,
-                               c->d_best_sim, c->match_captured ? nullptr : &c->pin_dev->matched,
-                               c->match_captured ? 0 : ++c->step_seq, sc};
-        rc = launch_expert_ffn(d, c->d_pool, c->slot_elems, c->n_total, c->ffn, c->d_slot_ids, c->d_gate, k + d.n_shared, d_x, d_y,
-                               c->d_flags, &ma, step_match_lds(eamc, match_blocks), s);
-        if (rc) c->match_on_stream = false;  // nobody will store the step's number
+        StepArgs sa{};
+        StepMatchArgs& ma = sa.match;
+        ma.n_blocks = match_blocks;
+        ma.norm2 = eamc->d_norm2;
+        ma.q = d_eam;
+        ma.cand = c->d_step_cand;
+        ma.cand_idx = c->d_step_idx;
+        ma.ticket = c->d_step_ticket;
+        ma.best = c->d_best;
+        ma.best_sim = c->d_best_sim;
+        ma.host = captured ? nullptr : &c->pin_dev->matched;
+        ma.seq = captured ? 0 : ++c->step_seq;
+        ma.sc = sc;
+        sa.match_lds = step_match_lds(eamc, match_blocks);
+        sa.shared_base = c->S + layer * d.n_shared;
+        sa.eam_row = d_eam + (size_t)layer * E;
+        StepRouteArgs& ro = sa.route;
+        ro.W = d_router_w;
+        ro.bias = d_router_bias;
+        ro.x = d_x;
+        ro.H = d.H;
+        ro.E = E;
+        ro.k = k;
+        ro.renorm = d.renorm_topk != 0;
+        ro.words = c->d_step_words;
+        ro.idx = c->d_idx;
+        ro.w = c->d_w;
+        ro.slot_of_row = c->d_slot_of + (size_t)layer * E;
+        ro.flags = c->d_flags;
+        ro.spin = c->step_spin;
+        rc = launch_expert_ffn(d, c->d_pool, c->slot_elems, c->n_total, c->ffn, nullptr, nullptr, k + d.n_shared, d_x, d_y,
+                               c->d_flags, &sa, s);
+        if (rc) {
+            c->match_on_stream = false;  // nobody will store the step's number
+            if (!captured) (void)hipMemsetAsync(c->d_step_words, 0, step_words_bytes(d), s);  // the reduction, which clears them, may be what has failed
+        }
         return rc;
     }
+    RouteFusedArgs ra{};
+    ra.W = d_router_w;
+    ra.bias = d_router_bias;
+    ra.x = d_x;
+    ra.H = d.H;
+    ra.logits = c->d_logits;
+    ra.ticket = c->d_ticket;
+    ra.E = E;
+    ra.k = k;
+    ra.renorm = d.renorm_topk != 0;
+    ra.idx = c->d_idx;
+    ra.w = c->d_w;
+    ra.eam = d_eam;
+    ra.snap = c->d_snap[c->parity];
+    ra.LE = d.L * E;
+    ra.layer = layer;
+    ra.slot_of_row = c->d_slot_of + (size_t)layer * E;
+    ra.n_shared = d.n_shared;
+    ra.shared_base = c->S + layer * d.n_shared;
+    ra.slot_ids = c->d_slot_ids;
+    ra.gate = c->d_gate;
+    ra.flags = sync_mode ? nullptr : c->d_flags;
+    ra.host_idx = sync_mode ? c->pin_dev->idx : nullptr;
+    if (sync_mode && c->poll) {  // only synchronous steps write these words, and each waits for its own
+        volatile int32_t* pi = c->pin->idx;
+        for (int j = 0; j < k; ++j) pi[j] = kNotWritten;
+    }
+    rc = launch_route_fused(ra, d.wdtype, s);
+    if (rc) return rc;
     MOEI_HIP(hipEventRecord(c->ev_routed, s));
     // Asynchronous step: the expert FFNs go onto the main stream right behind the routing,
     // before any side-stream work is enqueued, so that neither the host-side enqueue time of
     // the match nor a captured graph's branch placement comes between routing and FFN.
     if (!sync_mode) {
         rc = launch_expert_ffn(d, c->d_pool, c->slot_elems, c->n_total, c->ffn, c->d_slot_ids, c->d_gate,
-                               k + d.n_shared, d_x, d_y, c->d_flags, nullptr, 0, s);
+                               k + d.n_shared, d_x, d_y, c->d_flags, nullptr, s);
         if (rc) return rc;
     }
 
@@ -905,9 +946,9 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
         sc.seq = ++c->step_seq;
     }
     if (c->match_m == 1)
-        rc = launch_match(eamc, d_snap, 1, d.L - 1, c->d_best, c->d_best_sim, nullptr, &sc, side);
+        rc = launch_match(eamc, c->d_snap[c->parity], 1, d.L - 1, c->d_best, c->d_best_sim, nullptr, &sc, side);
     else
-        rc = launch_match_topm(eamc, d_snap, d.L - 1, c->match_m, c->d_best, c->d_best_sim, nullptr, &sc, side);
+        rc = launch_match_topm(eamc, c->d_snap[c->parity], d.L - 1, c->match_m, c->d_best, c->d_best_sim, nullptr, &sc, side);
     if (rc) return rc;
     const bool do_prefetch = sync_mode && c->pf_depth > 0 && c->policy == kPolicyEam;
     const int LE = d.L * E;
@@ -973,7 +1014,7 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
         // slots they take - but not for this layer's experts, whose slots they never touch)
         if (do_prefetch) MOEI_HIP(hipEventRecord(c->ev_main, s));
         rc = launch_expert_ffn(d, c->d_pool, c->slot_elems, c->n_total, c->ffn, c->d_slot_ids, c->d_gate, k + d.n_shared,
-                               d_x, d_y, c->d_flags, nullptr, 0, s);
+                               d_x, d_y, c->d_flags, nullptr, s);
         if (rc) return rc;
         if (do_prefetch) {
             if (!side_done) MOEI_HIP(hipEventSynchronize(c->ev_side));
@@ -1116,8 +1157,8 @@ extern "C" int moei_cache_join(moei_cache* c, void* stream) {
 extern "C" int moei_cache_sync(moei_cache* c) {
     MOEI_REQUIRE(c, "moei_cache_sync: null pointer");
     MOEI_HIP(hipStreamSynchronize(c->side_stream));
-    MOEI_HIP(hipStreamSynchronize(c->copy_stream));
-    MOEI_HIP(hipStreamSynchronize(c->pf_stream));
+    if (c->copy_stream) MOEI_HIP(hipStreamSynchronize(c->copy_stream));
+    if (c->pf_stream) MOEI_HIP(hipStreamSynchronize(c->pf_stream));
     int rc = wait_for_step(c);
     if (rc) return rc;
     std::fill(c->slot_pending.begin(), c->slot_pending.end(), 0);

@@ -143,6 +143,15 @@ __device__ __forceinline__ unsigned wave_sum_u32_dpp(unsigned v) {
     return (unsigned)__builtin_amdgcn_readlane((int)v, 0) + (unsigned)__builtin_amdgcn_readlane((int)v, 16) +
            (unsigned)__builtin_amdgcn_readlane((int)v, 32) + (unsigned)__builtin_amdgcn_readlane((int)v, 48);
 }
+__device__ __forceinline__ unsigned wave_min_u32_dpp(unsigned v) {
+    v = min(v, MOEI_DPP_U32(v, 0xB1));   // quad_perm [1,0,3,2]
+    v = min(v, MOEI_DPP_U32(v, 0x4E));   // quad_perm [2,3,0,1]
+    v = min(v, MOEI_DPP_U32(v, 0x141));  // row_half_mirror
+    v = min(v, MOEI_DPP_U32(v, 0x140));  // row_mirror
+    const unsigned a = (unsigned)__builtin_amdgcn_readlane((int)v, 0), b = (unsigned)__builtin_amdgcn_readlane((int)v, 16);
+    const unsigned c = (unsigned)__builtin_amdgcn_readlane((int)v, 32), d = (unsigned)__builtin_amdgcn_readlane((int)v, 48);
+    return min(min(a, b), min(c, d));
+}
 // Exact 64-bit sum over the wavefront: four 16-bit digits are summed separately (each digit
 // sum stays below 2^22) and recombined.
 __device__ __forceinline__ unsigned long long wave_sum_u64_dpp(unsigned long long v) {
@@ -190,6 +199,12 @@ __device__ __forceinline__ void wait_lds_fence() { asm volatile("s_waitcnt lgkmc
 // A barrier for what the workgroup exchanges through LDS alone: unlike __syncthreads it does not wait until the stores to
 // global memory before it have arrived (1 - 2 us each time while other workgroups stream).
 __device__ __forceinline__ void barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Orders the LDS accesses of one wavefront: what its lanes have written is there for all of its lanes.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 #endif  // __HIPCC__
 

@@ -38,12 +38,16 @@ struct FfnArgs {
     const float* gate_w;
     const void* x;
     float* part;  // [n_wg][H] workgroup partial sums
-    int n_wg;     // workgroups that stream; the launch's others match and score (StepMatchArgs)
+    int n_wg;     // workgroups that stream; the launch's others, before them, match and score (StepMatchArgs)
     int H, I, n_act;
-    int waves;    // wavefronts per workgroup
+    int waves;    // wavefronts per workgroup that stream
     int ygroup;   // wavefronts whose y rows fit in LDS together
     int32_t* flags;
+    // a layer step in one launch: slots and gate weights of the n_shared first experts are known, the picks' come from `route`
+    int n_shared, shared_base;
+    size_t idle;  // elements from the pool to a unit of zeros
     StepMatchArgs match;
+    StepRouteArgs route;
 };
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + expf(-g)); }
@@ -103,11 +107,12 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
     static_assert(STEPS % PF == 0, "the window must divide the steps of a unit");
     extern __shared__ __align__(16) float smem[];
     if constexpr (MATCH) {
-        if ((int)blockIdx.x >= a.n_wg) {
-            step_match(a.match, blockIdx.x - a.n_wg, reinterpret_cast<unsigned char*>(smem));
+        if ((int)blockIdx.x < a.match.n_blocks) {
+            step_match<WT>(a.match, a.route, blockIdx.x, a.n_wg, reinterpret_cast<unsigned char*>(smem));
             return;
         }
     }
+    const int blk = MATCH ? (int)blockIdx.x - a.match.n_blocks : (int)blockIdx.x;
     float* xs = smem;
     float* yp = smem + NCH * CW;
     constexpr bool kPacked = std::is_same<WT, uint16_t>::value;  // bf16: x stays bf16 in LDS, products by v_dot2c_f32_bf16
@@ -122,6 +127,33 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
     const unsigned lane_off = (unsigned)lane * N;  // this lane's elements inside a chunk
     int* s_slot = reinterpret_cast<int*>(yp);      // slot ids and gate weights of the call, staged
     float* s_gate = yp + 64;                       // in LDS (the y rows are not in use before the end)
+    volatile int* s_known = reinterpret_cast<int*>(yp + 128);  // MATCH: 1 once the picks' are there
+    const int nthr = a.waves * kWave;              // threads that stream
+    float* out = a.part + (size_t)blk * H;
+    if constexpr (MATCH) {
+        if (wv == a.waves) {  // the wavefront that routes
+            if (lane < a.n_shared) {
+                s_slot[lane] = a.shared_base + lane;
+                s_gate[lane] = 1.0f;
+            }
+            if (lane == 0) *s_known = 0;
+            float* z = yp + 192;
+            const int before = a.match.n_blocks * a.waves;  // wavefronts that have rows first
+            step_route_rows<WT>(a.route, before + blk, before + a.n_wg, lane);
+            barrier_lds();
+            const StepPick p = step_picks<WT, true>(a.route, z, lane);
+            if (lane < a.route.k) {
+                s_slot[a.n_shared + lane] = p.slot;
+                s_gate[a.n_shared + lane] = p.w;
+            }
+            wait_lds_fence();
+            if (lane == 0) *s_known = 1;
+            if (blk == 0) step_publish(a.route, p, lane);
+            __syncthreads();
+            block_sum_rows(yp, H, NCH * CW, a.waves, a.ygroup, wv, out, [](float*, bool) {});
+            return;
+        }
+    }
 
     auto scalar = [](size_t v) -> size_t {
         uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
@@ -152,7 +184,7 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
     // unit t -> wavefront t mod W, numbered wavefront-major (w = wv * workgroups + workgroup): when
     // the units do not fill the last round, every compute unit keeps most of its wavefronts busy
     // instead of whole workgroups running out of work
-    int t = wv * a.n_wg + blockIdx.x;
+    int t = wv * a.n_wg + blk;
     float gate = 0.f, gate_n = 0.f;
     bool ok = false, ok_n = false;
     size_t p = 0;
@@ -167,29 +199,46 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
     if constexpr (kPacked) {
         // a piece past the row is read as the row's last one (and not stored)
         const int n_pieces = TAIL ? H / N : NCH * kWave;
-        auto piece = [&](int u) { return reinterpret_cast<const uint4*>(a.x)[min(tid + u * (int)blockDim.x, n_pieces - 1)]; };
+        auto piece = [&](int u) { return reinterpret_cast<const uint4*>(a.x)[min(tid + u * nthr, n_pieces - 1)]; };
         xv0 = piece(0);
         if constexpr (kXRounds > 1) xv1 = piece(1);
         if constexpr (kXRounds > 2) xv2 = piece(2);
         if constexpr (kXRounds > 3) xv3 = piece(3);
     }
-    const int act = min(tid, a.n_act - 1);
-    const int my_slot = a.slot_ids[act];
-    const float my_gate = a.gate_w[act];
+    const int NS = a.n_shared * I;  // MATCH: units whose slots are known from the start
+    bool known = false;
+    int my_slot = 0;
+    float my_gate = 0.f;
+    if constexpr (!MATCH) {
+        const int act = min(tid, a.n_act - 1);
+        my_slot = a.slot_ids[act];
+        my_gate = a.gate_w[act];
+    }
     {  // the first window is on its way while x is staged; a wavefront without units reads the pool's
        // first unit instead, so that there is one path and the wait counts stay exact
-        const bool any = t < NT;
-        const int e = any ? t / I : 0;
-        const int slot0 = a.slot_ids[e];
-        gate = a.gate_w[e];
-        if (any) p = unit_off(slot0, t - e * I, ok);
+        if constexpr (MATCH) {
+            const int e = t / I;
+            if (t < NS) {
+                gate = 1.0f;
+                p = unit_off(a.shared_base + e, t - e * I, ok);
+            } else {
+                p = a.idle;
+                t -= W;  // the unit itself comes next
+            }
+        } else {
+            const bool any = t < NT;
+            const int e = any ? t / I : 0;
+            const int slot0 = a.slot_ids[e];
+            gate = a.gate_w[e];
+            if (any) p = unit_off(slot0, t - e * I, ok);
+        }
 #pragma unroll
         for (int s = 0; s < PF; ++s) win[s] = ld(p, s);
     }
     if constexpr (kPacked) {
         uint4* dst = reinterpret_cast<uint4*>(xs);
         auto put = [&](int u, uint4 v) {
-            const int c = tid + u * (int)blockDim.x;
+            const int c = tid + u * nthr;
             if (c < NCH * kWave) dst[c] = !TAIL || c * N < H ? v : make_uint4(0u, 0u, 0u, 0u);
         };
         put(0, xv0);
@@ -197,21 +246,32 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
         if constexpr (kXRounds > 2) put(2, xv2);
         if constexpr (kXRounds > 3) put(3, xv3);
     } else {
-        stage_as_f32(reinterpret_cast<const WT*>(a.x), xs, H);
+        for (int c = tid; c < H; c += nthr) xs[c] = V::one(reinterpret_cast<const WT*>(a.x) + c);
         if constexpr (TAIL)
-            for (int c = H + tid; c < NCH * CW; c += blockDim.x) xs[c] = 0.f;
+            for (int c = H + tid; c < NCH * CW; c += nthr) xs[c] = 0.f;
     }
-    if (tid < a.n_act) {
-        s_slot[tid] = my_slot;
-        s_gate[tid] = my_gate;
+    if constexpr (!MATCH) {
+        if (tid < a.n_act) {
+            s_slot[tid] = my_slot;
+            s_gate[tid] = my_gate;
+        }
+        __syncthreads();
+    } else {
+        barrier_lds();
     }
-    __syncthreads();
 
     while (t < NT) {
         const int tn = t + W;
         const bool more = tn < NT;
         size_t pn = p;
         if (more) {
+            if constexpr (MATCH) {
+                if (!known && tn >= NS) {  // (uniform; what has been requested arrives meanwhile)
+                    while (__builtin_amdgcn_readfirstlane(*s_known) == 0) __builtin_amdgcn_s_sleep(1);
+                    wait_lds_fence();
+                    known = true;
+                }
+            }
             const int e = tn / I;
             pn = unit_off(s_slot[e], tn - e * I, ok_n);
             gate_n = s_gate[e];
@@ -278,7 +338,6 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
         ok = ok_n;
     }
     __syncthreads();  // the LDS behind the y rows held the slot ids until here
-    float* out = a.part + (size_t)blockIdx.x * H;
     block_sum_rows(yp, H, NCH * CW, a.waves, a.ygroup, wv, out, [&](float* row, bool add) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
@@ -341,9 +400,10 @@ __global__ void __launch_bounds__(1024) ffn_fused_generic_kernel(FfnArgs a) {
 // y[h] = sum of the n_part workgroup partials.  A workgroup owns 32 columns; its 256
 // threads are 8 column quads x 32 slices of the partial list; every thread adds its
 // slice in index order, then the 32 slice sums are added in slice order.
-__global__ void __launch_bounds__(256) ffn_reduce_kernel(const float* __restrict__ part, int n_part, int H,
-                                                         float* __restrict__ y) {
+__global__ void __launch_bounds__(kStepTailThreads) ffn_reduce_kernel(const float* __restrict__ part, int n_part, int H,
+                                                         float* __restrict__ y, StepTail tail) {
     __shared__ float s_sum[32][32];
+    if (tail.k > 0) step_tail(tail);
     const int cq = threadIdx.x & 7, sl = threadIdx.x >> 3;
     const int h = blockIdx.x * 32 + cq * 4;
     const int per = (n_part + 31) / 32;
@@ -421,7 +481,7 @@ int allow_big_lds(K kernel, size_t bytes) {
 }
 
 template <typename WT>
-int launch_ffn_typed(FfnArgs a, bool fast, int grid, size_t match_lds, float* d_y, hipStream_t s) {
+int launch_ffn_typed(FfnArgs a, bool fast, int grid, size_t match_lds, const StepTail& tail, float* d_y, hipStream_t s) {
     using V = WVec<WT>;
     const int H = a.H;
     int rc = MOEI_OK;
@@ -430,17 +490,19 @@ int launch_ffn_typed(FfnArgs a, bool fast, int grid, size_t match_lds, float* d_
     if (fast) {
 #define MOEI_FFN_CASE(N_, TAIL_)                                                                        \
     case N_: {                                                                                         \
-        a.waves = plan_waves(a.n_act * a.I, grid, StreamShape<N_>::kMaxWaves, a.match.n_blocks > 0 ? kMatchWaves : 4, \
-                             forced_waves());                                                          \
+        const bool step = a.match.n_blocks > 0; /* one wavefront more than stream */                   \
+        const int most = StreamShape<N_>::kMaxWaves - step;                                            \
+        a.waves = plan_waves(a.n_act * a.I, grid, most, step ? kMatchWaves - 1 : 4, std::min(forced_waves(), step ? most : 64)); \
         static_assert(StreamShape<N_>::kMaxWaves >= kMatchWaves, "the match finds its wavefronts");    \
         const size_t padded = (size_t)N_ * kWave * V::N * sizeof(float);                               \
         int yg = (int)((kLdsBudget - padded) / padded);                                                \
         a.ygroup = yg < 1 ? 1 : (yg > a.waves ? a.waves : yg);                                         \
-        const size_t smem = std::max(padded * (1 + a.ygroup), match_lds);                              \
-        auto kernel = a.match.n_blocks > 0 ? ffn_fused_kernel<WT, N_, TAIL_, true> : ffn_fused_kernel<WT, N_, TAIL_, false>; \
+        const size_t smem = std::max({padded * (1 + a.ygroup), match_lds, step ? padded + 192 * 4 + step_route_lds(a.route.E) : 0}); \
+        if (step) step_scan_plan(&a.match, a.waves);                                                   \
+        auto kernel = step ? ffn_fused_kernel<WT, N_, TAIL_, true> : ffn_fused_kernel<WT, N_, TAIL_, false>; \
         rc = allow_big_lds(kernel, smem);                                                              \
         if (rc) return rc;                                                                             \
-        launch(K_FFN_FUSED, kernel, dim3(grid + a.match.n_blocks), dim3(a.waves * kWave), smem, s, a); \
+        launch(K_FFN_FUSED, kernel, dim3(grid + a.match.n_blocks), dim3((a.waves + step) * kWave), smem, s, a); \
         break;                                                                                         \
     }
         // whole chunks, for the counts of chunks that configurations have; any other row through TAIL
@@ -493,7 +555,7 @@ int launch_ffn_typed(FfnArgs a, bool fast, int grid, size_t match_lds, float* d_
         launch(K_FFN_FUSED, ffn_fused_generic_kernel<WT>, dim3(grid), dim3(m * kWave), smem, s, a);
     }
     MOEI_LAUNCH_CHECK();
-    launch(K_FFN_REDUCE, ffn_reduce_kernel, dim3((H + 31) / 32), dim3(256), 0, s, (const float*)a.part, grid, H, d_y);
+    launch(K_FFN_REDUCE, ffn_reduce_kernel, dim3((H + 31) / 32), dim3(256), 0, s, (const float*)a.part, grid, H, d_y, tail);
     MOEI_LAUNCH_CHECK();
     return MOEI_OK;
 }
@@ -1398,12 +1460,21 @@ int ffn_scratch_alloc(const moei_model_desc& d, int n_act_max, FfnScratch* out) 
         out->d_part = nullptr;
         MOEI_FAIL(MOEI_ENOMEM, "FFN scratch allocation failed: %s", hipGetErrorString(e));
     }
+    const size_t unit = (size_t)3 * d.H * (d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4);
+    e = hipMalloc(&out->d_idle, unit);
+    if (e == hipSuccess) e = hipMemset(out->d_idle, 0, unit);
+    if (e != hipSuccess) {
+        ffn_scratch_free(out);
+        MOEI_FAIL(MOEI_ENOMEM, "FFN scratch allocation failed: %s", hipGetErrorString(e));
+    }
     return MOEI_OK;
 }
 
 void ffn_scratch_free(FfnScratch* s) {
     (void)hipFree(s->d_part);
+    (void)hipFree(s->d_idle);
     s->d_part = nullptr;
+    s->d_idle = nullptr;
 }
 
 // ------------------------------------------------------------------ scratch that is never allocated
@@ -1449,7 +1520,7 @@ int launch_expert_ffn_static(const moei_model_desc& d, const void* d_pool, size_
     int rc = static_part_ptr(&scr.d_part);
     if (rc) return rc;
     scr.n_part = n_part;
-    return launch_expert_ffn(d, d_pool, slot_elems, n_slots_total, scr, d_slot_ids, d_gate_w, n_act, d_x, d_y, d_flags, nullptr, 0, s);
+    return launch_expert_ffn(d, d_pool, slot_elems, n_slots_total, scr, d_slot_ids, d_gate_w, n_act, d_x, d_y, d_flags, nullptr, s);
 }
 
 namespace {
@@ -1469,11 +1540,10 @@ bool expert_ffn_takes_match(const moei_model_desc& d, const void* d_pool, size_t
 
 int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_elems, int n_slots_total,
                       const FfnScratch& scr, const int32_t* d_slot_ids, const float* d_gate_w, int n_act,
-                      const void* d_x, float* d_y, int32_t* d_flags, const StepMatchArgs* match, size_t match_lds,
-                      hipStream_t s) {
-    if (n_act == 0 && !match) {  // an empty sum: the reduction over zero partial rows writes zeros
+                      const void* d_x, float* d_y, int32_t* d_flags, const StepArgs* step, hipStream_t s) {
+    if (n_act == 0) {  // an empty sum: the reduction over zero partial rows writes zeros
         launch(K_FFN_REDUCE, ffn_reduce_kernel, dim3((d.H + 31) / 32), dim3(256), 0, s, (const float*)scr.d_part, 0, d.H,
-               d_y);
+               d_y, StepTail{});
         MOEI_LAUNCH_CHECK();
         return MOEI_OK;
     }
@@ -1490,10 +1560,22 @@ int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_
     a.n_act = n_act;
     a.flags = d_flags;
     a.n_wg = scr.n_part;
-    if (match) a.match = *match;
+    StepTail tail{};
+    size_t match_lds = 0;
+    if (step) {
+        const bool bf16 = d.wdtype == MOEI_WDTYPE_BF16;
+        a.match = step->match;
+        a.route = step->route;
+        a.route.vec_ok = ((uintptr_t)a.route.W | (uintptr_t)a.route.x) % 16 == 0 && d.H % (bf16 ? 8 : 4) == 0;
+        a.n_shared = d.n_shared;
+        a.shared_base = step->shared_base;
+        a.idle = ((uintptr_t)scr.d_idle - (uintptr_t)d_pool) / (bf16 ? 2 : 4);
+        match_lds = step->match_lds;
+        tail = StepTail{a.route.k, a.route.E, a.route.idx, step->eam_row, a.route.words};
+    }
     const bool fast = ffn_streams(d, d_pool, slot_elems);
-    if (d.wdtype == MOEI_WDTYPE_BF16) return launch_ffn_typed<uint16_t>(a, fast, scr.n_part, match_lds, d_y, s);
-    return launch_ffn_typed<float>(a, fast, scr.n_part, match_lds, d_y, s);
+    if (d.wdtype == MOEI_WDTYPE_BF16) return launch_ffn_typed<uint16_t>(a, fast, scr.n_part, match_lds, tail, d_y, s);
+    return launch_ffn_typed<float>(a, fast, scr.n_part, match_lds, tail, d_y, s);
 }
 
 

@@ -36,20 +36,20 @@ int launch_gather_slots(const int32_t* d_idx, int k, const int32_t* d_slot_of_ro
 int compute_units();  // of the device the library was first used on
 struct FfnScratch {
     float* d_part = nullptr;  // [n_part][H] workgroup partial sums of y
+    void* d_idle = nullptr;   // [3][H] zeros in the weight dtype: the unit of a wavefront that has none yet
     int n_part = 0;           // = workgroups of the fused kernel (one per compute unit)
     int n_free = 0;           // compute units that kernel leaves free
     int n_act_max = 0;
 };
 int ffn_scratch_alloc(const moei_model_desc& d, int n_act_max, FfnScratch* out);
 void ffn_scratch_free(FfnScratch* s);
-// `match` (or null): the launch also finds and scores the most similar trace (step_match.hpp), which
-// expert_ffn_takes_match must have allowed
-struct StepMatchArgs;
+// `step` (or null): the launch also routes the token, finds and scores the most similar trace (step_route.hpp, step_match.hpp), which
+// expert_ffn_takes_match must have allowed; it takes no slot ids and gate weights
+struct StepArgs;
 bool expert_ffn_takes_match(const moei_model_desc& d, const void* d_pool, size_t slot_elems, const void* d_x);
 int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_elems, int n_slots_total,
                       const FfnScratch& scr, const int32_t* d_slot_ids, const float* d_gate_w, int n_act,
-                      const void* d_x, float* d_y, int32_t* d_flags, const StepMatchArgs* match, size_t match_lds,
-                      hipStream_t s);
+                      const void* d_x, float* d_y, int32_t* d_flags, const StepArgs* step, hipStream_t s);
 
 // the same with the partial rows in a static device array (no allocation anywhere on the path)
 constexpr size_t kStaticPartFloats = (size_t)256 * 5120;  // 5 MiB: 256 workgroups x H = 5120

@@ -1370,11 +1370,14 @@ int launch_match(const moei_eamc* c, const int32_t* d_eam, int B, int layer_hi, 
 
 // How many workgroups match beside the experts' stream, 0: the match stays on the side stream.  One (no arrival count) for up
 // to 64 KB and 256 traces, else one per 64 KB or 128 traces, on the compute units that the experts leave free.
-// What such a workgroup does besides reading its traces takes about 16 us, and it reads 29 KB/us, so traces of more than
-// 110 KB a workgroup (then it ends about when a short FFN does: 26 x 64 cells, 69 MB of experts, a step in a graph over 200 /
-// 400 / 1,000 traces - 55 / 111 / 277 KB a workgroup - 28.4 / 29.1 / 32.4 us, on the side stream 30.3 / 30.2 / 30.6) are read beside
-// experts that take longer only (32 x 8 cells, 1,000 traces beside 295 MB of experts: 62.3 us, on the side stream 64.0).  Issued one
-// by one the same steps take 25 - 33 us, and 34 - 36 on the side stream: the host, with two launches and four event calls less.
+// Such a workgroup is done 17 us after it has read its traces, at a rate that the form of its loads decides (16 bytes of 4-byte or 2-byte
+// cells, single cells where a row is no multiple of 16 bytes).  A step in one launch saves the routing's launch and the fork to the side
+// stream, and the chain there takes 35 us whatever the experts do, so the match may end 10 us after the experts or up to then.
+// us a layer, steps in a graph, side stream / one launch: 26 x 64 cells, 1,000 traces (277 KB a workgroup) beside 138 MB 38.2 / 31.8; 4-byte
+// cells: 20 x 64, 356 KB, 37.5 / 28.1, 8 x 100, 507 KB, 38.6 / 39.2, 32 x 64, 865 KB, 38.1 / 38.7, 29 x 60, 978 KB beside 84 MB 43.1 / 46.3; 2-byte cells: 14
+// x 32, 219 KB, 34.3 / 27.6, 8 x 128, 500 KB, 37.2 / 41.5; single 4-byte cells: 40 x 23, 158 KB, 36.2 / 28.5, 31 x 55, 268 KB, 36.0 / 38.0; single 2-byte
+// cells: 27 x 37, 92 KB, 38.7 / 34.6, 16 x 23, 180 KB, 38.1 / 43.9, 3 x 150, 220 KB, 44 / 136.  (Of 110 such shapes this rule gives 71 to the one
+// launch, 0.80 of the time in the mean, the worst 1.02, and leaves 24 out that it would serve better.)
 int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_units) {
     const size_t scan = (size_t)c->N * d.L * d.E * c->cell_bytes;
     const size_t experts = (size_t)(d.k + d.n_shared) * 3 * d.H * d.I * (d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4);
@@ -1384,13 +1387,32 @@ int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_uni
         n = (int)std::min<size_t>(std::min(free_units, kStepMatchMaxBlocks), std::max<size_t>((c->N + 127) / 128, (scan + (64 << 10) - 1) / (64 << 10)));
         if (n < 1) return 0;
     }
+    const bool whole = d.E % (16 / c->cell_bytes) == 0;
+    const double rate = 1024.0 * (c->cell_bytes == 4 ? (whole ? 28 : 10) : (whole ? 22 : 5));  // bytes a us
     const double ffn_us = 4.0 + (double)experts / 6.5e6;
-    const double room = std::max(110.0 * 1024, (ffn_us - 16.0) * 29e3);
+    const double room = std::max(18.0, ffn_us - 7.0) * rate;
     return (double)scan / n <= room && (c->N + n - 1) / n <= kStepMatchMaxTraces ? n : 0;
+}
+void step_scan_plan(StepMatchArgs* a, int waves) {
+    const int whole = 16 / a->sc.cell_bytes;
+    a->per = (a->sc.N + a->n_blocks - 1) / a->n_blocks;
+    a->vec = a->sc.E % whole == 0 ? whole : 1;
+    // whole wavefronts, as many to a pass as make the fewest trips to memory
+    const int T = waves * kWave, nvec = a->per * (a->sc.E / a->vec);
+    int trips = 0x7fffffff;
+    for (int span = kWave; span <= T; span += kWave) {
+        const int groups = std::min(a->sc.L, T / span), layers = (a->sc.L + groups - 1) / groups;
+        const int n = ((nvec + span - 1) / span) * ((layers + kStepScanLayers - 1) / kStepScanLayers);
+        if (n < trips) {
+            trips = n;
+            a->span = span;
+            a->groups = groups;
+        }
+    }
 }
 size_t step_match_lds(const moei_eamc* c, int n_blocks) {
     const size_t per = (c->N + n_blocks - 1) / n_blocks;
-    return sizeof(StepMatchLds) + per * 16 + (((size_t)c->d.L * c->d.E * 4 + 15) & ~(size_t)15);
+    return sizeof(StepMatchLds) + per * 16 + (((size_t)c->d.L * c->d.E * 4 + 15) & ~(size_t)15) + step_route_lds(c->d.E);
 }
 
 int launch_match_topm(const moei_eamc* c, const int32_t* d_eam, int layer_hi, int m, int32_t* d_top, float* d_top_sim,

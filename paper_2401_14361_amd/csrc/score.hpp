@@ -280,15 +280,6 @@ __device__ __forceinline__ KeyId keyid_min(KeyId a, KeyId b) {
     r.id = take_b ? b.id : a.id;
     return r;
 }
-__device__ __forceinline__ unsigned wave_min_u32_dpp(unsigned v) {
-    v = min(v, MOEI_DPP_U32(v, 0xB1));   // quad_perm [1,0,3,2]
-    v = min(v, MOEI_DPP_U32(v, 0x4E));   // quad_perm [2,3,0,1]
-    v = min(v, MOEI_DPP_U32(v, 0x141));  // row_half_mirror
-    v = min(v, MOEI_DPP_U32(v, 0x140));  // row_mirror
-    const unsigned a = (unsigned)__builtin_amdgcn_readlane((int)v, 0), b = (unsigned)__builtin_amdgcn_readlane((int)v, 16);
-    const unsigned c = (unsigned)__builtin_amdgcn_readlane((int)v, 32), d = (unsigned)__builtin_amdgcn_readlane((int)v, 48);
-    return min(min(a, b), min(c, d));
-}
 // smallest (key, id) of the wavefront, in every lane (all 64 lanes active): three one-word minima -
 // the key's high word, the low word among the lanes that hold that high word, the id among the
 // lanes that hold that key

@@ -1,18 +1,21 @@
-// The match and the scoring of an asynchronous layer step inside the launch that streams the experts.
+// The match and the scoring of an asynchronous layer step inside the launch that routes it and streams its experts.
 //
-// That launch leaves some compute units free; a few more workgroups in it find the most similar trace of the EAM that
-// routing has just updated (Sec. 4.5 of the paper), score the matched trace and select the heads of both orders, while the
-// others stream weights.  The step is then one chain of three launches on the caller's stream: no kernels of its own for the
-// match, no event calls, no wait between routing and FFN for the fork to the side stream (4 - 6 us).  Four layer steps of the tiny
-// model issued one by one: 221 us on the side stream, 105 like this.
+// That launch leaves some compute units free; a few more workgroups in it find the most similar trace of the EAM that holds the
+// step's routing (Sec. 4.5 of the paper), score the matched trace and select the heads of both orders, while the
+// others stream weights.  They do not wait for the picks to begin: the scan, the longest part, runs over the EAM as it
+// was before the step, and the picks' k cells of every trace are added when they are known.
+// The step is then one chain of two launches on the caller's stream: no kernels of its own for the
+// match, no event calls, no fork to the side stream.
 #pragma once
 
 #include "match.hpp"
 #include "score.hpp"
+#include "step_route.hpp"
 
 namespace moei {
 
 constexpr int kStepMatchMaxBlocks = 128;  // never more workgroups than that match
+constexpr int kStepScanLayers = 16;        // loads of the scan that one thread has under way
 constexpr int kStepMatchMaxTraces = 1024;  // traces of one of them (their dot products and norms are held in LDS)
 
 // What such a step tells the host, in pinned memory
@@ -23,9 +26,12 @@ struct StepMatched {
 };
 
 struct StepMatchArgs {
-    int n_blocks;            // workgroups that match, behind the ones that stream (0: none)
+    int n_blocks;            // workgroups that match, before the ones that stream (0: none)
+    int per;                 // traces of each of them
+    int vec;                 // cells of a load
+    int span, groups;        // threads per pass over them, and how many such groups share the layers (step_scan_plan)
     const unsigned long long* norm2;  // [n_cap]
-    const int32_t* q;        // [L*E] the EAM that holds this step's routing
+    const int32_t* q;        // [L*E] the EAM without this step's picks (the reduction adds them)
     unsigned long long* cand;  // [n_blocks][2] winners of the workgroups (dot, norm) ...
     int32_t* cand_idx;       // [n_blocks] ... and their trace indices
     unsigned* ticket;        // arrival counter, zero between launches
@@ -35,6 +41,16 @@ struct StepMatchArgs {
     int32_t seq;             // for host->seq
     ScoreArgs sc;
 };
+// A layer step in one launch and the reduction behind it.
+struct StepArgs {
+    StepMatchArgs match;
+    size_t match_lds;
+    StepRouteArgs route;
+    int shared_base;   // slots of the layer's shared experts: shared_base + s
+    int32_t* eam_row;  // row of the EAM that the reduction adds the picks to
+};
+// Fills in how a.n_blocks workgroups with `waves` wavefronts that scan go about it.
+void step_scan_plan(StepMatchArgs* a, int waves);
 // 0: a step over this collection keeps the match on the side stream
 int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_units);
 size_t step_match_lds(const moei_eamc* c, int n_blocks);
@@ -48,26 +64,24 @@ struct alignas(16) StepMatchLds {
     int finish;
     int sn[2];
     int best[kMaxMatchBatch];
+    int pick[kStepPicks];
 };
-// behind it lie 16 bytes per trace and the query's cells, which are read as 16-byte vectors
+// behind it lie 16 bytes per trace, the query's cells, which are read as 16-byte vectors, and step_route_lds
 static_assert(sizeof(StepMatchLds) % 16 == 0, "the query's cells in LDS begin at a 16-byte boundary");
 
-// Dot products of the query (in LDS) with traces t0 .. t0 + nt, added into s_dot (zero before).  Per layer the tile is one run
+// Dot products of the query (in LDS) with traces t0 .. t0 + nt, added into s_dot (zero before), by the first groups * span threads.  Per layer the tile is one run
 // of cells; a thread owns a vector of it and, where the tile is small, every groups-th layer only, and sixteen of
 // its layers are requested together: beside the streaming workgroups a trip to memory takes 2 - 3 us.
 template <typename CT, int VEC>
-__device__ __forceinline__ void step_scan(const ScoreArgs& a, int t0, int nt, const int32_t* qs, u64* s_dot) {
+__device__ __forceinline__ void step_scan(const ScoreArgs& a, int span, int groups, int t0, int nt, const int32_t* qs, u64* s_dot) {
     using CV = CellVec<CT, VEC>;
-    constexpr int U = 16;
-    const int tid = threadIdx.x, T = blockDim.x, L = a.L, E = a.E;
-    const int rowV = E / VEC, nvec = nt * rowV;
-    const int span = (nvec + kWave - 1) & ~(kWave - 1);
-    const int groups = span >= T || span == 0 ? 1 : min(L, T / span);
-    const int g = groups > 1 ? tid / span : 0;
+    constexpr int U = kStepScanLayers;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), L = a.L, E = a.E;
+    const int rowV = E / VEC, nvec = nt * rowV, g = tid / span;
     const bool lane_rows = rowV <= kWave && (rowV & (rowV - 1)) == 0;
     const size_t lstride = (size_t)a.n_cap * E;
     if (g >= groups) return;
-    for (int p = tid - g * span; p < span; p += T) {  // (uniform over a wavefront)
+    for (int p = tid - g * span; p - lane < nvec; p += span) {  // (uniform over a wavefront)
         const bool valid = p < nvec;
         const int pc = valid ? p : 0, row = pc / rowV, col = (pc - row * rowV) * VEC;
         const CT* src = reinterpret_cast<const CT*>(a.traces) + (size_t)t0 * E + (size_t)pc * VEC;
@@ -94,16 +108,18 @@ __device__ __forceinline__ void step_scan(const ScoreArgs& a, int t0, int nt, co
     }
 }
 
-// Workgroup `blk` of a.n_blocks; the last one to arrive picks among the winners and scores.  Eight to sixteen wavefronts.  All of
+// Workgroup `blk` of a.n_blocks; the last one to arrive picks among the winners and scores.  Eight to sixteen wavefronts, the last of
+// which waits for the picks while the others scan (n_wg: workgroups that stream, each with a wavefront for routing too).  All of
 // it is one chain, so what counts is its trips to memory and, since it runs once, the instructions to fetch: the
 // arg-max over a workgroup's traces and the one over the winners are one loop of one wavefront.
-__device__ __forceinline__ void step_match(const StepMatchArgs& a, int blk, unsigned char* smem) {
+template <typename WT>
+__device__ __forceinline__ void step_match(const StepMatchArgs& a, const StepRouteArgs& ra, int blk, int n_wg, unsigned char* smem) {
     StepMatchLds& s = *reinterpret_cast<StepMatchLds*>(smem);
-    const ScoreArgs& sc = a.sc;
+    ScoreArgs sc = a.sc;
+    sc.cur_idx = s.pick;
     const int tid = threadIdx.x, T = blockDim.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int LE = sc.L * sc.E;
-    const int per = (sc.N + a.n_blocks - 1) / a.n_blocks;
-    const int t0 = min(sc.N, blk * per), nt = min(sc.N - t0, per);
+    const int per = a.per, t0 = min(sc.N, blk * per), nt = min(sc.N - t0, per);
     u64* s_dot = reinterpret_cast<u64*>(smem + sizeof(StepMatchLds));
     u64* s_norm = s_dot + per;
     int32_t* qs = reinterpret_cast<int32_t*>(smem + sizeof(StepMatchLds) + ((size_t)per * 16));
@@ -113,13 +129,32 @@ __device__ __forceinline__ void step_match(const StepMatchArgs& a, int blk, unsi
     }
     for (int i = tid; i < LE; i += T) qs[i] = a.q[i];
     barrier_lds();
-    if (sc.cell_bytes == 4) {
-        if (sc.E % 4 == 0) step_scan<int32_t, 4>(sc, t0, nt, qs, s_dot);
-        else step_scan<int32_t, 1>(sc, t0, nt, qs, s_dot);
+    const int Ts = T - kWave, scan_waves = Ts / kWave;
+    if (tid < Ts) step_route_rows<WT>(ra, wv * a.n_blocks + blk, a.n_blocks * scan_waves + n_wg, lane);
+    if (tid >= Ts) {
+        const StepPick p = step_picks<WT, false>(ra, reinterpret_cast<float*>(qs + ((LE + 3) & ~3)), lane);
+        if (lane < ra.k) s.pick[lane] = p.e;
+    } else if (sc.cell_bytes == 4) {
+        if (a.vec > 1) step_scan<int32_t, 4>(sc, a.span, a.groups, t0, nt, qs, s_dot);
+        else step_scan<int32_t, 1>(sc, a.span, a.groups, t0, nt, qs, s_dot);
     } else {
-        if (sc.E % 8 == 0) step_scan<uint16_t, 8>(sc, t0, nt, qs, s_dot);
-        else step_scan<uint16_t, 1>(sc, t0, nt, qs, s_dot);
+        if (a.vec > 1) step_scan<uint16_t, 8>(sc, a.span, a.groups, t0, nt, qs, s_dot);
+        else step_scan<uint16_t, 1>(sc, a.span, a.groups, t0, nt, qs, s_dot);
     }
+    barrier_lds();
+    // each pick adds one to its cell of the query
+    const size_t row = ((size_t)sc.cur_layer * sc.n_cap + t0) * sc.E;
+    for (int i = tid; i < nt; i += T) {
+        u64 sum = 0;
+#pragma unroll 8
+        for (int j = 0; j < ra.k; ++j) {
+            const int e = s.pick[j];
+            const uint32_t v = cell_at(sc.traces, sc.cell_bytes, row + (size_t)i * sc.E + max(e, 0));
+            sum += e >= 0 ? v : 0u;
+        }
+        s_dot[i] += sum;
+    }
+    if (tid < ra.k && s.pick[tid] >= 0) qs[sc.cur_layer * sc.E + s.pick[tid]] += 1;
     barrier_lds();
     if (wv == 0) {
         Best me = make_best(0, 1, -1);
@@ -129,15 +164,13 @@ __device__ __forceinline__ void step_match(const StepMatchArgs& a, int blk, unsi
             if (stage == 1) {  // publish this workgroup's winner; the last one to arrive goes on
                 unsigned arrived = 0;
                 if (lane == 0) {
-                    a.cand[2 * blk] = me.dot;
-                    a.cand[2 * blk + 1] = me.nt;
-                    a.cand_idx[blk] = me.idx;
-                    __threadfence();
+                    // (stored past the caches and acknowledged before the count: no write-back of the L2 by a fence)
+                    __hip_atomic_store(&a.cand[2 * blk], me.dot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(&a.cand[2 * blk + 1], me.nt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(&a.cand_idx[blk], me.idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    wait_vm_fence<0>();
                     arrived = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (arrived == (unsigned)a.n_blocks - 1) {
-                        __threadfence();
-                        *a.ticket = 0;  // ready for the next launch on this stream
-                    }
+                    if (arrived == (unsigned)a.n_blocks - 1) *a.ticket = 0;  // ready for the next launch on this stream
                 }
                 finish = (int)__builtin_amdgcn_readfirstlane((int)arrived) == a.n_blocks - 1;
                 if (!finish) break;

@@ -113,6 +113,63 @@ __device__ __forceinline__ float wave_topk_rank(const float* z, int E, int k, in
     return sel;
 }
 
+// The same picks and bits for E <= 64 * NR logits in registers (lane l holds l, l + 64, ...), by k rounds of an arg-max: one
+// wavefront, no LDS and no loop whose length depends on E.  `other` (an int per logit, held the same way) travels with the picks.
+// Lane j < k returns pick j, its weight, its `other`; the weights are not divided, their sum is returned in every lane.
+template <int NR>
+__device__ __forceinline__ float wave_topk_regs(const float (&z)[NR], const int (&other)[NR], int E, int k, int lane, int& pick,
+                                                float& weight, int& pick_other) {
+    float m = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+        if (lane + r * kWave < E) m = fmaxf(m, z[r]);
+    m = wave_max_dpp(m);
+    float p[NR], s = 0.f;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        p[r] = 0.f;
+        if (r * kWave < E) {  // uniform
+            p[r] = lane + r * kWave < E ? expf(z[r] - m) : 0.f;
+            s += p[r];
+        }
+    }
+    s = wave_sum_dpp(s);
+    unsigned left = 0u;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) left |= lane + r * kWave < E ? 1u << r : 0u;
+    const unsigned all = left;
+    pick = -1;
+    pick_other = 0;
+    for (int j = 0; j < k; ++j) {
+        float v = -INFINITY;
+        unsigned c = 0x7fffffffu;  // the lane's largest remaining logit, the lowest index that holds it
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const bool take = ((left >> r) & 1u) && (c == 0x7fffffffu || z[r] > v);
+            v = take ? z[r] : v;
+            c = take ? (unsigned)(lane + r * kWave) : c;
+        }
+        const float top = wave_max_dpp(v);
+        const int win = (int)wave_min_u32_dpp(v == top ? c : 0x7fffffffu);
+        int o = 0;
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+            if (win / kWave == r) o = __builtin_amdgcn_readlane(other[r], win & (kWave - 1));
+        if ((win & (kWave - 1)) == lane) left &= ~(1u << (win / kWave));
+        if (lane == j) {
+            pick = win;
+            pick_other = o;
+            weight = top;
+        }
+    }
+    weight = lane < k ? expf(weight - m) / s : 0.f;
+    float sel = 0.f;
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+        if ((all & ~left) >> r & 1u) sel += p[r] / s;
+    return wave_sum_dpp(sel);
+}
+
 // The same by k rounds of a 64-lane butterfly arg-max (any E up to 4096).
 // Lane j < k returns pick j in (idx, w); other lanes return idx = -1.
 __device__ __forceinline__ void wave_topk(const float* z, int E, int k, int renorm, int lane, int& idx_out,
