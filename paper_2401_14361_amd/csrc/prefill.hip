@@ -306,7 +306,6 @@ struct MmArgs {
     int n_ub;  // gate/up: blocks of 64 (wide kernel: 128) units;  down: blocks of 512 columns
     int n_cb;
     int cus;       // compute units of an XCD
-    int n_shared, sh_tiles;  // shared experts, and how many items each has
     int dn_split;  // the down kernel takes an item in this many parts of TM tokens (items of the wide tile: 2)
     int k_per;     // ... and its units in parts of this many slices, a workgroup each
     size_t part_rows;  // the rows of part q begin at row q * part_rows of yc
@@ -353,16 +352,6 @@ __device__ __forceinline__ int tile_of_xcd(int total, int full, int xcd, int me,
     }
     const int t = b + cus - 1 - me;
     return t < e ? total - left + t : total;
-}
-// The wide down kernel runs an item whole on one XCD, position p of its order on XCD p % 8.  Item `tile` of
-// shared expert s is at position s + 8 * tile there: the items of a shared expert run on one XCD, several
-// at a time, and its weights pass through that L2 once for them; the routed items fill the other
-// positions in the list's order.  (Needs at most 8 shared experts and enough routed items to leave no gap.)
-__device__ __forceinline__ int item_at(const MmArgs& a, int p, int n_routed) {
-    const int free8 = kXcds - a.n_shared;  // routed positions per block of 8 among the first 8 * tiles
-    if (a.n_shared == 0 || free8 < 0 || n_routed < a.sh_tiles * free8 || p >= kXcds * a.sh_tiles) return p;
-    const int s = p % kXcds;
-    return s < a.n_shared ? s * a.sh_tiles + p / kXcds : a.n_shared * a.sh_tiles + p / kXcds * free8 + s - a.n_shared;
 }
 // Read-only tables are read through the constant address space: uniform loads that count on lgkmcnt, so
 // that waiting for them does not wait for a ring's loads.
@@ -1007,192 +996,219 @@ __global__ void __launch_bounds__(TM * 4, 2) prefill_down_kernel(MmArgs a) {  //
 }
 
 // 3b, long prompts: the down product for items of up to 256 tokens, built like the wide gate/up
-// kernel.  A workgroup forms 256 tokens x 256 columns; its stream of W_down (64 units x 256 columns
-// = 64 rows of 512 bytes per stage, ring of three) and the item's activations (256 rows of 128 bytes
-// per stage, ring of two) go from global memory straight into LDS, loaded by wavefronts 0..3 and
-// 4..7; all column blocks of an item run on one XCD.  (The kernel above loads W_down into registers,
-// every token quarter again: at 256 tokens that path, ~16 bytes per clock and CU, is what bounds
-// it.)  A wavefront owns four 16-token blocks (blocks q, q + 4, ... of the item for quarter q) x 128
-// columns: 32 accumulator tiles, which leave registers for one set of W_down pieces (eight units x
-// eight columns per lane, transposed in registers as above) and two of activations.  So the
-// activations of a half stage are read one half step ahead and the W_down pieces at its start, and
-// each ring has a barrier of its own: before the first half of a stage the wavefronts that load
-// W_down have seen that stage land (after the barrier the stage before it has been read by all and
-// its slot is loaded again), before the second half the same for the activations of the next stage.
-// Needs I % 64 == 0 and H % 256 == 0; other shapes take the kernel above, an item in two parts.
+// kernel: persistent workgroups of 256 columns x 256 tokens, tiles - items times column blocks - dealt out by tile_of_xcd, and
+// both operands brought straight into LDS by all wavefronts, an item's activations (256 rows of 128 bytes a stage, ring of two) ahead of
+// the W_down rows that are needed a stage later (64 units x 256 columns = 64 rows of 512 bytes, ring of three); one barrier a stage.
+// The slot stores W_down unit-major, so sixteen columns x 32 units of it are a matrix operand only after a transposition:
+// ds_read_b64_tr_b16 does it on the way from LDS (lane l of sixteen gets column l of four rows, of which lanes 4r .. 4r + 3 name
+// row r's sixteen columns).  Its rows are 32 bytes, eight of them read at a time, and all rows of a stage begin at the same bank: the
+// 32-byte piece c of row r sits at piece c ^ dw_key(r), which differs for those eight.  (In registers the transposition was 32 byte
+// permutes a half stage, and the pieces it works on left no room to read the next half stage's ahead.)
+// A wavefront owns 128 columns x four 16-token blocks (blocks q, q + 4, ... of the item for quarter q), 32 accumulator tiles.
+// Bound by how fast a compute unit takes its operands in, as gate/up (2,048 tokens of the 26-layer shape: 750 MB).
+// Needs I % 64 == 0, I >= 192 (the rings look up to three stages ahead) and H % 256 == 0; other shapes take the kernel
+// above, an item in two parts.
 constexpr int kDwCols = 256;
 constexpr int kDwKS = 64;
+constexpr int kDwMinSlices = 3;
 constexpr int kDwStagesW = 3;
 constexpr int kDwStagesA = 2;
 constexpr int kDwStageElemsW = kDwKS * kDwCols;       // 64 rows of 256 columns: 32 KiB
 constexpr int kDwStageElemsA = kTileTokWide * kDwKS;  // 256 rows of 64 units: 32 KiB
-// waits until at most `n` of this wavefront's vector memory operations are outstanding (n <= 32)
-__device__ __forceinline__ void wait_vm(int n) {
-    // s_waitcnt: vmcnt in bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima
-#define MOEI_WAIT_CASE(v) case v: __builtin_amdgcn_s_waitcnt(0x0f70 | ((v) & 15) | (((v) >> 4) << 14)); break;
-    switch (n) {
-        MOEI_WAIT_CASE(0) MOEI_WAIT_CASE(1) MOEI_WAIT_CASE(2) MOEI_WAIT_CASE(3) MOEI_WAIT_CASE(4) MOEI_WAIT_CASE(5)
-        MOEI_WAIT_CASE(6) MOEI_WAIT_CASE(7) MOEI_WAIT_CASE(8) MOEI_WAIT_CASE(9) MOEI_WAIT_CASE(10) MOEI_WAIT_CASE(11)
-        MOEI_WAIT_CASE(12) MOEI_WAIT_CASE(13) MOEI_WAIT_CASE(14) MOEI_WAIT_CASE(15) MOEI_WAIT_CASE(16) MOEI_WAIT_CASE(17)
-        MOEI_WAIT_CASE(18) MOEI_WAIT_CASE(19) MOEI_WAIT_CASE(20) MOEI_WAIT_CASE(21) MOEI_WAIT_CASE(22) MOEI_WAIT_CASE(23)
-        MOEI_WAIT_CASE(24) MOEI_WAIT_CASE(25) MOEI_WAIT_CASE(26) MOEI_WAIT_CASE(27) MOEI_WAIT_CASE(28) MOEI_WAIT_CASE(29)
-        MOEI_WAIT_CASE(30) MOEI_WAIT_CASE(31)
-        default: __builtin_amdgcn_s_waitcnt(0x8f70); break;  // 32
-    }
-#undef MOEI_WAIT_CASE
+__device__ __forceinline__ int dw_key(int row) { return (row & 3) | ((row >> 3) & 1) << 2; }
+// four 16-bit values of a column; see above
+__device__ __forceinline__ uint2 ld_lds_tr(uint32_t addr) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)addr));
 }
 
 __global__ void __launch_bounds__(kWdThreads, 2) prefill_down_wide_kernel(MmArgs a) {
+    constexpr int NTB = kTileTokWide / 64;  // 16-token blocks per wavefront: 4
+    static_assert(kDwCols == 256 && kDwKS == 64 && kTileTokWide == 256 && kWdThreads == 8 * kWave, "eight wavefronts load 64 rows of 512 bytes and 256 of 128");
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    uint16_t* ring_w = reinterpret_cast<uint16_t*>(smem_raw);         // [kDwStagesW][64][256]
-    uint16_t* ring_a = ring_w + (size_t)kDwStagesW * kDwStageElemsW;  // [kDwStagesA][256][64], chunks swizzled
-    // all column blocks of an item on one XCD, all items of a shared expert on one XCD too
-    const int pos = blockIdx.x % kXcds + kXcds * (blockIdx.x / kXcds / a.n_cb), cb = blockIdx.x / kXcds % a.n_cb;
-    if (pos >= a.meta[0]) return;
-    const PItem it = a.items[item_at(a, pos, a.meta[1])];
+    uint16_t* ring_w = reinterpret_cast<uint16_t*>(smem_raw);         // [kDwStagesW][64][256], 32-byte pieces swizzled
+    uint16_t* ring_a = ring_w + (size_t)kDwStagesW * kDwStageElemsW;  // [kDwStagesA][256][64], 16-byte pieces swizzled (wd_pos)
     const int H = a.H, I = a.I;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lrow = lane & 15, lgrp = lane >> 4;
     const int cg = wv & 1, tq = wv >> 1;  // column group (128 columns), token quarter
-    const int col_wg = cb * kDwCols;
-    if (it.slot < 0 || it.slot >= a.n_slots_total) {  // not resident: the rows are zero, the flag says so
-        if (tid == 0) atomicOr(a.flags, 1);
-        for (int r = 0; r < it.ntok; ++r)
-            for (int c = tid; c < kDwCols; c += kWdThreads) a.yc[(size_t)(it.row0 + r) * H + col_wg + c] = 0.f;
-        return;
-    }
-    // 16-token blocks of this wavefront that hold tokens of the item (blocks tq, tq + 4, ...)
-    const int n_live = max(0, ((it.ntok + 15) / 16 - tq + 3) / 4);
-    const bool loads_w = wv < 4;  // else the activations
-    const uint16_t* wd = a.pool + (size_t)it.slot * a.slot_elems + 2 * H + col_wg;
-
-    // Weights: load j (of 8) of wavefront w fills rows 2 * (4 * j + w) .. + 2 of a stage (a row = 256
-    // columns = 32 pieces); this lane brings piece lane % 32 of row .. + lane / 32.  Activations: load
-    // j (of at most 8) fills rows 8 * (4 * j + w) .. + 8 (a row = 64 units = 8 pieces), chunk position
-    // lane % 8 of row .. + lane / 8; rows past the item's tokens are not loaded (what the ring holds
-    // there is multiplied at most within a token block that also holds tokens, never stored).  One
-    // source address per lane; the loads of a stage lie a fixed number of rows apart.
-    const uint16_t* src0;
-    const int arow = 8 * (wv & 3) + (lane >> 3);  // this lane's row of an activation load, before 32 * j
-    if (loads_w) {
-        const int r = 2 * (wv & 3) + (lane >> 5);
-        src0 = wd + (size_t)r * 3 * H + (lane & 31) * 8;
-    } else {
-        const int c = (lane & 7) ^ ((arow >> 1) & 7);  // rows 32 apart share the swizzle key
-        src0 = a.act + (size_t)it.row0 * I + c * 8;
-    }
-    const int nld = loads_w ? 8 : min(8, max(0, (it.ntok - 8 * (wv & 3) + 31) / 32));  // loads per stage of this wavefront
-    const uint32_t my_ring = lds_address(loads_w ? ring_w : ring_a) + (uint32_t)(wv & 3) * 1024;
-    auto issue = [&](int s) {  // the calling wavefront's share of stage s of its ring
-        if (loads_w) {
-            const uint32_t st = my_ring + (uint32_t)(s % kDwStagesW) * (kDwStageElemsW * 2);
-            const uint16_t* p = src0 + (size_t)s * kDwKS * 3 * H;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) load16_to_lds(p + (size_t)j * 8 * 3 * H, st + (uint32_t)j * 4096);
-        } else {
-            const uint32_t st = my_ring + (uint32_t)(s % kDwStagesA) * (kDwStageElemsA * 2);
-            const uint16_t* p = src0 + s * kDwKS;
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (j < nld) load16_to_lds(p + (uint32_t)min(arow + 32 * j, it.ntok - 1) * (uint32_t)I, st + (uint32_t)j * 4096);
+    const int n_items = ((const_ints)(uintptr_t)a.meta)[0];
+    const int n_slices = I / kDwKS;
+    const int total = n_items * a.n_cb, full = total / (kXcds * a.cus);
+    int round = 0;
+    auto next_tile = [&]() { return tile_at(a, total, a.n_cb, tile_of_xcd(total, full, blockIdx.x % kXcds, blockIdx.x / kXcds, round++, a.cus)); };
+    // an expert that is not resident: the rows are zero, the flag says so
+    auto resident = [&](Tile& t) {
+        while (t.ok && (t.slot < 0 || t.slot >= a.n_slots_total)) {
+            if (tid == 0) atomicOr(a.flags, 1);
+            for (int r = tid / kDwCols; r < t.ntok; r += kWdThreads / kDwCols)
+                a.yc[(size_t)(t.row0 + r) * H + t.block * kDwCols + tid % kDwCols] = 0.f;
+            t = next_tile();
         }
     };
+    Tile cur = next_tile();
+    resident(cur);
+    if (!cur.ok) return;
 
-    f32x4 Y[4][8];
+    // ---- loads: stage after stage of one tile, then on into the next tile
+    // Load j (of four) of a wavefront fills rows 16 * j + 2 * wv .. + 2 of a stage of weights (this lane brings the 16 bytes that
+    // belong at piece lane % 32 of row .. + lane / 32) and rows 8 * (8 * j + wv) .. + 8 of a stage of activations (chunk position lane % 8 of
+    // row .. + lane / 8).  Activation rows past the item's tokens are not loaded by whole groups of eight, and repeat its last
+    // row inside one: what they yield is never stored.
+    const int w_row = 2 * wv + (lane >> 5), a_row = 8 * wv + (lane >> 3);
+    const uint32_t off_w = (uint32_t)w_row * (uint32_t)(6 * H) + (uint32_t)(((lane & 31) ^ (dw_key(w_row) << 1)) * 16);
+    const uint32_t off_a = (uint32_t)a_row * (uint32_t)(2 * I), my_chunk = (uint32_t)((lane & 7) ^ ((a_row >> 1) & 7)) * 16;
+    const uint32_t my_w = lds_address(ring_w) + (uint32_t)wv * 1024, my_a = lds_address(ring_a) + (uint32_t)wv * 1024;
+    const unsigned char *base_w = nullptr, *base_a = nullptr;  // of the stage to be loaded next (uniform)
+    int slice_w = 0, put_w = 0, n_a = 0, slice_a = 0, put_a = 0;
+    uint32_t end_a = 0;  // the item's last row
+    auto aim_w = [&](const Tile& t) {
+        slice_w = 0;
+        base_w = scalar_ptr(a.pool + (size_t)t.slot * a.slot_elems + 2 * H + t.block * kDwCols);
+    };
+    auto aim_a = [&](const Tile& t) {
+        slice_a = 0;
+        base_a = scalar_ptr(a.act + (size_t)t.row0 * I);
+        n_a = min(4, max(0, (t.ntok - 8 * wv + 63) / 64));
+        end_a = (uint32_t)(t.ntok - 1) * (uint32_t)(2 * I);
+    };
+    auto issue_w = [&]() {
+        const uint32_t st = my_w + (uint32_t)put_w * (kDwStageElemsW * 2);
 #pragma unroll
-    for (int tb = 0; tb < 4; ++tb)
+        for (int j = 0; j < 4; ++j) load16_to_lds_at(base_w + (size_t)j * 16 * 6 * H, off_w, st + (uint32_t)j * 8192);
+        base_w += (size_t)kDwKS * 6 * H;
+        if (++put_w == kDwStagesW) put_w = 0;
+        ++slice_w;
+    };
+    auto load_a = [&](uint32_t st, int j) {
+        load16_to_lds_at(base_a, min(off_a + (uint32_t)j * (uint32_t)(64 * 2 * I), end_a) + my_chunk, st + (uint32_t)j * 8192);
+    };
+    auto issue_a = [&]() {
+        const uint32_t st = my_a + (uint32_t)put_a * (kDwStageElemsA * 2);
+        if (n_a == 4) {  // no branch between the loads
 #pragma unroll
-        for (int i = 0; i < 8; ++i) Y[tb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < 4; ++j) load_a(st, j);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (j < n_a) load_a(st, j);
+        }
+        base_a += kDwKS * 2;
+        if (++put_a == kDwStagesA) put_a = 0;
+        ++slice_a;
+    };
+    static_assert(kDwStagesA == 2 && kDwStagesW == 3, "one stage of activations and two of weights are on their way");
+    aim_w(cur);
+    issue_w();
+    aim_a(cur);
+    issue_a();
+    issue_w();
+    Tile nxt = next_tile();
+    bool more_w = true;  // the weights of the stage after the one entered next are on their way
+    // Enters the next stage, as in the gate/up kernel
+    auto enter = [&]() {
+        if (more_w)
+            wait_vm_c<4>();
+        else
+            wait_vm_c<0>();
+        __syncthreads();
+        if (slice_a == n_slices && nxt.ok) aim_a(nxt);
+        if (slice_a < n_slices) issue_a();
+        if (slice_w == n_slices && nxt.ok) aim_w(nxt);
+        more_w = slice_w < n_slices;
+        if (more_w) issue_w();
+    };
 
-    struct Acts {
-        bf16x8 av[4];  // the token blocks' activations of a half stage
+    struct Ops {
+        bf16x8 w[8], b[NTB];  // columns 16 * i .. + 16 of the wavefront's; token blocks
     };
-    auto read_acts = [&](int t, Acts& o, auto nt_tag) {  // half step t: stage t / 2, units 32 * (t % 2) .. + 32
-        constexpr int NT = decltype(nt_tag)::value;
-        const uint16_t* sa = ring_a + (size_t)((t >> 1) % kDwStagesA) * kDwStageElemsA;
-#pragma unroll
-        for (int tb = 0; tb < NT; ++tb) o.av[tb] = ld_bf16x8(sa + wd_pos((4 * tb + tq) * 16 + lrow, 4 * (t & 1) + lgrp));
+    int slot_w = 0, slot_a = 0;  // ring slots of the stage entered last
+    auto step_slots = [&]() {
+        if (++slot_w == kDwStagesW) slot_w = 0;
+        if (++slot_a == kDwStagesA) slot_a = 0;
     };
-    auto multiply = [&](int t, const Acts& o, auto nt_tag) {
+    // LDS addresses, slot 0, half 0: this lane's eight bytes of row 8 * lgrp + lrow / 4, columns 0 .. 15 of the wavefront's; of the first token block
+    const uint32_t pos_w = lds_address(ring_w) + (uint32_t)(8 * lgrp + (lrow >> 2)) * 512 + (uint32_t)cg * 256 + (uint32_t)dw_key(8 * lgrp + (lrow >> 2)) * 32 + (lrow & 3) * 8;
+    const uint32_t pos_a = lds_address(ring_a + wd_pos(16 * tq + lrow, lgrp));
+    auto read_ops = [&](int half, Ops& o, auto nt_tag) {  // half 0 or 1 of the stage entered last: units 32 * half .. + 32
         constexpr int NT = decltype(nt_tag)::value;
-        const uint16_t* sw = ring_w + (size_t)((t >> 1) % kDwStagesW) * kDwStageElemsW;
-        uint4 w[8];  // units 8 * lgrp + j of the half stage, columns 8 * lrow .. + 8 of the wavefront's 128
+        const uint32_t sw = pos_w + (uint32_t)slot_w * (kDwStageElemsW * 2) + (uint32_t)half * (32 * 512);
+        const uint32_t sa = (pos_a + (uint32_t)slot_a * (kDwStageElemsA * 2)) ^ (uint32_t)(64 * half);
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            w[j] = *reinterpret_cast<const uint4*>(sw + (size_t)(32 * (t & 1) + 8 * lgrp + j) * kDwCols + cg * 128 + lrow * 8);
+        for (int tb = 0; tb < NT; ++tb) o.b[tb] = *(const __attribute__((address_space(3))) bf16x8*)(uintptr_t)(sa + (uint32_t)tb * 8192);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            uint32_t dw[4];
-#pragma unroll
-            for (int p2 = 0; p2 < 4; ++p2) {
-                const uint32_t lo = reinterpret_cast<const uint32_t*>(&w[2 * p2])[i >> 1];
-                const uint32_t hi = reinterpret_cast<const uint32_t*>(&w[2 * p2 + 1])[i >> 1];
-                dw[p2] = (i & 1) ? __builtin_amdgcn_perm(hi, lo, 0x07060302u) : __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-            }
-            bf16x8 wt;
-            memcpy(&wt, dw, 16);
-#pragma unroll
-            for (int tb = 0; tb < NT; ++tb) Y[tb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o.av[tb], wt, Y[tb][i], 0, 0, 0);
+            const uint32_t at = sw ^ (uint32_t)(32 * i);
+            const uint2 lo = ld_lds_tr(at), hi = ld_lds_tr(at + 4 * 512);  // units 8 * lgrp .. + 4, .. + 8
+            o.w[i] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
         }
     };
-    const int n_slices = I / kDwKS;  // I is a multiple of 64 here
-    // both rings start full; stage 0 of both has landed for all after the first barrier
-    if (loads_w) {
-        for (int s = 0; s < kDwStagesW; ++s)
-            if (s < n_slices) issue(s);
-        wait_vm((min(n_slices, kDwStagesW) - 1) * 8);
-    } else {
-        for (int s = 0; s < kDwStagesA; ++s)
-            if (s < n_slices) issue(s);
-        wait_vm((min(n_slices, kDwStagesA) - 1) * nld);
-    }
-    __syncthreads();
+    auto multiply = [&](const Ops& o, f32x4 (&Y)[NTB][8], auto nt_tag) {
+        constexpr int NT = decltype(nt_tag)::value;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int tb = 0; tb < NT; ++tb) Y[tb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o.w[i], o.b[tb], Y[tb][i], 0, 0, 0);
+    };
+    // A whole tile, whose first stage has been entered; written once for each count of token blocks a wavefront may have.
     auto run = [&](auto nt_tag) {
         constexpr int NT = decltype(nt_tag)::value;
-        Acts actA, actB;
-        if constexpr (NT > 0) read_acts(0, actA, nt_tag);
-        for (int s = 0; s < n_slices; ++s) {
-            // first half of stage s: its W_down rows have landed (stages 0 .. s + 1 have been issued);
-            // stage s - 1 has been read by all, its slot takes stage s + 2
-            if (s >= 1) {
-                if (loads_w) wait_vm(min(n_slices - 1 - s, 1) * 8);
-                __syncthreads();
-                if (loads_w && s + 2 < n_slices) issue(s + 2);
-            }
+        f32x4 Y[NTB][8];
+#pragma unroll
+        for (int tb = 0; tb < NT; ++tb)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) Y[tb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        Ops opA, opB;
+        if constexpr (NT > 0) read_ops(0, opA, nt_tag);
+        for (int s = 1; s < n_slices; ++s) {
             if constexpr (NT > 0) {
-                read_acts(2 * s + 1, actB, nt_tag);
-                multiply(2 * s, actA, nt_tag);
+                read_ops(1, opB, nt_tag);
+                multiply(opA, Y, nt_tag);
             }
-            // second half: the activations of stage s + 1 (read during this half step) have landed; those of
-            // stage s have been read by all, their slot takes stage s + 2
-            if (s + 1 < n_slices) {
-                if (!loads_w) wait_vm(0);
-                __syncthreads();
-                if (!loads_w && s + 2 < n_slices) issue(s + 2);
-                if constexpr (NT > 0) read_acts(2 * s + 2, actA, nt_tag);
+            if (s == 1) resident(nxt);  // (first needed when the last stage but one is entered; there are at least three)
+            enter();
+            step_slots();
+            if constexpr (NT > 0) {
+                read_ops(0, opA, nt_tag);
+                multiply(opB, Y, nt_tag);
             }
-            if constexpr (NT > 0) multiply(2 * s + 1, actB, nt_tag);
+        }
+        if constexpr (NT > 0) {
+            read_ops(1, opB, nt_tag);
+            multiply(opA, Y, nt_tag);
+        }
+        if (nxt.ok) {  // the next tile's first stage, while this one's last products are formed and stored
+            enter();
+            step_slots();
+        }
+        if constexpr (NT > 0) {
+            multiply(opB, Y, nt_tag);
+            // D[column 4 * lgrp + v][token lrow] of matrix i
+#pragma unroll
+            for (int tb = 0; tb < NT; ++tb) {
+                const int tok = (4 * tb + tq) * 16 + lrow;
+                if (tok >= cur.ntok) continue;
+                float* dst = a.yc + (size_t)(cur.row0 + tok) * H + cur.block * kDwCols + cg * 128 + lgrp * 4;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) *reinterpret_cast<f32x4*>(dst + 16 * i) = Y[tb][i];
+            }
         }
     };
-    switch ((n_live + 1) / 2) {  // uniform over the wavefront
-        case 0: run(std::integral_constant<int, 0>{}); break;
-        case 1: run(std::integral_constant<int, 2>{}); break;
-        default: run(std::integral_constant<int, 4>{}); break;
-    }
-    // D[token 4*lgrp + v][column lrow] of matrix i is column col0 + 8*lrow + i
-    const int col0 = col_wg + cg * 128;
-#pragma unroll
-    for (int tb = 0; tb < 4; ++tb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int tok = (4 * tb + tq) * 16 + lgrp * 4 + v;
-            if (tok < it.ntok) {
-                float* dst = a.yc + (size_t)(it.row0 + tok) * H + col0 + lrow * 8;
-                *reinterpret_cast<float4*>(dst) = make_float4(Y[tb][0][v], Y[tb][1][v], Y[tb][2][v], Y[tb][3][v]);
-                *reinterpret_cast<float4*>(dst + 4) = make_float4(Y[tb][4][v], Y[tb][5][v], Y[tb][6][v], Y[tb][7][v]);
-            }
+    enter();
+    for (;;) {
+        // 16-token blocks of this wavefront that hold tokens of the item (blocks tq, tq + 4, ...)
+        switch (max(0, ((cur.ntok + 15) / 16 - tq + 3) / 4)) {  // uniform over the wavefront
+            case 0: run(std::integral_constant<int, 0>{}); break;
+            case 1: run(std::integral_constant<int, 1>{}); break;
+            case 2: run(std::integral_constant<int, 2>{}); break;
+            case 3: run(std::integral_constant<int, 3>{}); break;
+            default: run(std::integral_constant<int, 4>{}); break;
         }
+        if (!nxt.ok) break;
+        cur = nxt;
+        nxt = next_tile();
+    }
 }
 
 // ------------------------------------------------------------------ 4. y[t] = sum of the token's rows, in pick order
@@ -1494,13 +1510,12 @@ int launch_mm(const moei_model_desc& d, MmArgs a, int max_items, int parts, hipS
         launch(K_PF_GATEUP, prefill_gateup_wide_kernel, dim3(kXcds * a.cus), dim3(kWdThreads), gu_smem, s, a);
     }
     MOEI_LAUNCH_CHECK();
-    if (a.dn_split == 2 && d.I % kDwKS == 0 && d.H % kDwCols == 0) {
+    if (a.dn_split == 2 && d.I % kDwKS == 0 && d.I >= kDwMinSlices * kDwKS && d.H % kDwCols == 0) {
         const size_t dw_smem = (size_t)(kDwStagesW * kDwStageElemsW + kDwStagesA * kDwStageElemsA) * 2;
         rc = pf_allow_lds(prefill_down_wide_kernel, dw_smem);
         if (rc) return rc;
         a.n_cb = d.H / kDwCols;
-        const int item_rounds = (max_items + kXcds - 1) / kXcds;
-        launch(K_PF_DOWN, prefill_down_wide_kernel, dim3(kXcds * a.n_cb * item_rounds), dim3(kWdThreads), dw_smem, s, a);
+        launch(K_PF_DOWN, prefill_down_wide_kernel, dim3(kXcds * a.cus), dim3(kWdThreads), dw_smem, s, a);
         MOEI_LAUNCH_CHECK();
         return MOEI_OK;
     }
@@ -1566,7 +1581,7 @@ int launch_prefill(const moei_model_desc& d, const PrefillScratch& ps, const voi
     MmArgs a{reinterpret_cast<const uint16_t*>(d_pool), slot_elems, n_slots_total,
              reinterpret_cast<const PItem*>(ps.d_items), ps.d_meta, reinterpret_cast<const uint16_t*>(d_X), ps.d_perm,
              ps.d_pgate, ps.d_act, ps.d_yc, d.H, d.I, d_flags, 0, (d.H + kDnCols - 1) / kDnCols,
-             cus_per_xcd(), d.n_shared, (n + tm - 1) / tm, tm == kTileTokWide ? 2 : 1, 0, prefill_rows(d, n)};
+             cus_per_xcd(), tm == kTileTokWide ? 2 : 1, 0, prefill_rows(d, n)};
     const int slices = (d.I + kDnKS - 1) / kDnKS;
     a.k_per = slices;
     int parts = tm == kTileTok ? down_parts(d, n) : 1;
