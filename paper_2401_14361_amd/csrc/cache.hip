@@ -320,11 +320,9 @@ int cache_alloc(moei_cache* c) {
     MOEI_HIP(hipHostMalloc((void**)&c->pin_V, LE * sizeof(float), hipHostMallocMapped | hipHostMallocCoherent));
     MOEI_HIP(hipHostGetDevicePointer((void**)&c->pin_dev, c->pin, 0));
     MOEI_HIP(hipHostGetDevicePointer((void**)&c->pin_V_dev, c->pin_V, 0));
+    MOEI_HIP(hipStreamCreateWithFlags(&c->pf_stream, hipStreamNonBlocking));
+    MOEI_HIP(hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking));
     MOEI_HIP(hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking));
-    if (c->h_experts) {  // the others carry copies from the host
-        MOEI_HIP(hipStreamCreateWithFlags(&c->pf_stream, hipStreamNonBlocking));
-        MOEI_HIP(hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking));
-    }
     MOEI_HIP(hipEventCreateWithFlags(&c->ev_copy, hipEventDisableTiming));
     MOEI_HIP(hipEventCreateWithFlags(&c->ev_routed, hipEventDisableTiming));
     for (int r = 0; r < kRing; ++r) MOEI_HIP(hipEventCreateWithFlags(&c->ev_match[r], hipEventDisableTiming));
@@ -1157,8 +1155,8 @@ extern "C" int moei_cache_join(moei_cache* c, void* stream) {
 extern "C" int moei_cache_sync(moei_cache* c) {
     MOEI_REQUIRE(c, "moei_cache_sync: null pointer");
     MOEI_HIP(hipStreamSynchronize(c->side_stream));
-    if (c->copy_stream) MOEI_HIP(hipStreamSynchronize(c->copy_stream));
-    if (c->pf_stream) MOEI_HIP(hipStreamSynchronize(c->pf_stream));
+    MOEI_HIP(hipStreamSynchronize(c->copy_stream));
+    MOEI_HIP(hipStreamSynchronize(c->pf_stream));
     int rc = wait_for_step(c);
     if (rc) return rc;
     std::fill(c->slot_pending.begin(), c->slot_pending.end(), 0);

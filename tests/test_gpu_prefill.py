@@ -164,6 +164,21 @@ def test_prefill_long_prompt_with_experts_that_are_not_resident(m, n_shared, H, 
         assert not o["rY"][t].any() and not o["Y"][t].any() or rel_max_err(o["Y"][t], o["rY"][t]) <= FFN_TOL, t
 
 
+# the down product of 256-token items: the fewest units it takes (192) and one stage less, which goes to the kernel of 128-token items;
+# one and several tiles a workgroup; items of every count of 16-token blocks; absent experts, whose tiles are passed over while the rings run on
+@pytest.mark.parametrize("E,k,n_shared,H,I,n,resident", [(1, 1, 1, 256, 128, 270, None), (1, 1, 1, 256, 192, 270, None), (3, 1, 0, 512, 256, 50, None),
+                                                         (40, 3, 1, 4096, 192, 700, None), (40, 3, 1, 4096, 192, 700, 20), (24, 3, 0, 3840, 320, 1300, 12)])
+def test_prefill_down_product_of_few_units(m, E, k, n_shared, H, I, n, resident, monkeypatch):
+    monkeypatch.setenv("MOEI_PREFILL_TILE", "256")
+    cfg = mi.get_config("C2").scaled(L=1, E=E, k=k, n_shared=n_shared, H=H, I=I, N=4, prompt=16)
+    o = _prefill_case(m, cfg, n, layer=0, resident=resident, sample=24)
+    if resident is None:
+        _check(o)
+        return
+    assert o["flags"] & 2 and o["finite"] and (o["idx"] == o["ridx"]).all() and (o["eam"] == o["ream"]).all()
+    assert rel_max_err(o["Y"], o["rY"]) <= FFN_TOL_BF16_ACT
+
+
 # few experts of few tokens: the down kernel takes an expert's units in parts (a last one that is shorter, units that are no whole
 # slice, an item more than one expert has), with experts that are not resident too
 @pytest.mark.parametrize("E,k,n_shared,H,I,n,resident", [(4, 2, 0, 512, 1032, 5, None), (3, 2, 1, 640, 2056, 60, None), (2, 1, 0, 1024, 520, 90, None),
