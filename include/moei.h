@@ -238,8 +238,9 @@ int moei_cache_error_flags(moei_cache* c, int32_t* h_flags, void* stream);
  * One MoE layer of one decode iteration for one request:
  *   logits = W_r x + b -> top-k -> EAM row update -> (EAMC match -> priorities) on a
  *   side stream, while Alg. 1 retrieval and the expert FFNs run on `stream`.
- * An asynchronous step over a short collection has the match and the priorities on `stream` too, beside
- * the FFNs in one launch; the calls below that wait for them take either kind into account.
+ * An asynchronous step over a short collection has the routing, the match and the priorities on `stream` too, beside
+ * the FFNs in one launch; the calls below that wait for them take either kind into account.  In both kinds the
+ * picks, their weights, the EAM row and error flag bits 1 and 2 are final when the match is.
  * d_router_w[E][H] in wdtype, d_router_bias[E] fp32 or NULL, d_eam[L][E] int32.
  * The eviction order used for this layer's misses is the one computed from the EAM
  * that already contains this layer's routing.
@@ -322,7 +323,7 @@ int moe_prefill_layer(moei_cache* c, int32_t* d_eam, int32_t layer,
 /* Makes `stream` wait for the match/priority work of the last moe_decode_layer (the next
  * moe_decode_layer does this by itself) - for an asynchronous step that matched beside its experts
  * the call itself waits, on the host, until that launch has matched; the step's own stream is not
- * touched and may have been destroyed or be under capture by then - and for every
+ * touched and may have been destroyed or be under capture by then (d_y is ordered by that stream alone) - and for every
  * prefetch copy that no stream has waited for yet; carries out the prefetch plan of an
  * asynchronous step first (then it waits for that step's side stream on the host).  Call it
  * before ending a stream capture that contains asynchronous layer steps, so that the

@@ -866,10 +866,12 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
         ma.best_sim = c->d_best_sim;
         ma.host = captured ? nullptr : &c->pin_dev->matched;
         ma.seq = captured ? 0 : ++c->step_seq;
+        ma.idx = c->d_idx;
+        ma.w = c->d_w;
+        ma.flags = c->d_flags;
         ma.sc = sc;
         sa.match_lds = step_match_lds(eamc, match_blocks);
         sa.shared_base = c->S + layer * d.n_shared;
-        sa.eam_row = d_eam + (size_t)layer * E;
         StepRouteArgs& ro = sa.route;
         ro.W = d_router_w;
         ro.bias = d_router_bias;
@@ -879,10 +881,7 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
         ro.k = k;
         ro.renorm = d.renorm_topk != 0;
         ro.words = c->d_step_words;
-        ro.idx = c->d_idx;
-        ro.w = c->d_w;
         ro.slot_of_row = c->d_slot_of + (size_t)layer * E;
-        ro.flags = c->d_flags;
         ro.spin = c->step_spin;
         rc = launch_expert_ffn(d, c->d_pool, c->slot_elems, c->n_total, c->ffn, nullptr, nullptr, k + d.n_shared, d_x, d_y,
                                c->d_flags, &sa, s);

@@ -148,7 +148,6 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
             }
             wait_lds_fence();
             if (lane == 0) *s_known = 1;
-            if (blk == 0) step_publish(a.route, p, lane);
             __syncthreads();
             block_sum_rows(yp, H, NCH * CW, a.waves, a.ygroup, wv, out, [](float*, bool) {});
             return;
@@ -403,7 +402,7 @@ __global__ void __launch_bounds__(1024) ffn_fused_generic_kernel(FfnArgs a) {
 __global__ void __launch_bounds__(kStepTailThreads) ffn_reduce_kernel(const float* __restrict__ part, int n_part, int H,
                                                          float* __restrict__ y, StepTail tail) {
     __shared__ float s_sum[32][32];
-    if (tail.k > 0) step_tail(tail);
+    if (tail.words) step_tail(tail);
     const int cq = threadIdx.x & 7, sl = threadIdx.x >> 3;
     const int h = blockIdx.x * 32 + cq * 4;
     const int per = (n_part + 31) / 32;
@@ -1571,7 +1570,7 @@ int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_
         a.shared_base = step->shared_base;
         a.idle = ((uintptr_t)scr.d_idle - (uintptr_t)d_pool) / (bf16 ? 2 : 4);
         match_lds = step->match_lds;
-        tail = StepTail{a.route.k, a.route.E, a.route.idx, step->eam_row, a.route.words};
+        tail = StepTail{a.route.E, a.route.words};
     }
     const bool fast = ffn_streams(d, d_pool, slot_elems);
     if (d.wdtype == MOEI_WDTYPE_BF16) return launch_ffn_typed<uint16_t>(a, fast, scr.n_part, match_lds, tail, d_y, s);

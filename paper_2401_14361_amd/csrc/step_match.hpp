@@ -3,7 +3,8 @@
 // That launch leaves some compute units free; a few more workgroups in it find the most similar trace of the EAM that holds the
 // step's routing (Sec. 4.5 of the paper), score the matched trace and select the heads of both orders, while the
 // others stream weights.  They do not wait for the picks to begin: the scan, the longest part, runs over the EAM as it
-// was before the step, and the picks' k cells of every trace are added when they are known.
+// was before the step, and the picks' k cells of every trace are added when they are known.  The workgroup that scores also stores
+// what the routing has decided (picks, weights, the EAM's row, flags): calls that wait for the step wait for this workgroup.
 // The step is then one chain of two launches on the caller's stream: no kernels of its own for the
 // match, no event calls, no fork to the side stream.
 #pragma once
@@ -31,7 +32,7 @@ struct StepMatchArgs {
     int vec;                 // cells of a load
     int span, groups;        // threads per pass over them, and how many such groups share the layers (step_scan_plan)
     const unsigned long long* norm2;  // [n_cap]
-    const int32_t* q;        // [L*E] the EAM without this step's picks (the reduction adds them)
+    int32_t* q;              // [L*E] the EAM; the workgroup that scores adds this step's picks
     unsigned long long* cand;  // [n_blocks][2] winners of the workgroups (dot, norm) ...
     int32_t* cand_idx;       // [n_blocks] ... and their trace indices
     unsigned* ticket;        // arrival counter, zero between launches
@@ -39,6 +40,9 @@ struct StepMatchArgs {
     float* best_sim;
     StepMatched* host;       // null: a captured step
     int32_t seq;             // for host->seq
+    int32_t* idx;            // [k] the picks
+    float* w;                // [k] their weights
+    int32_t* flags;          // error flags (bit 1: pick not resident, bit 2: no softmax)
     ScoreArgs sc;
 };
 // A layer step in one launch and the reduction behind it.
@@ -46,8 +50,7 @@ struct StepArgs {
     StepMatchArgs match;
     size_t match_lds;
     StepRouteArgs route;
-    int shared_base;   // slots of the layer's shared experts: shared_base + s
-    int32_t* eam_row;  // row of the EAM that the reduction adds the picks to
+    int shared_base;  // slots of the layer's shared experts: shared_base + s
 };
 // Fills in how a.n_blocks workgroups with `waves` wavefronts that scan go about it.
 void step_scan_plan(StepMatchArgs* a, int waves);
@@ -65,6 +68,7 @@ struct alignas(16) StepMatchLds {
     int sn[2];
     int best[kMaxMatchBatch];
     int pick[kStepPicks];
+    float pick_w[kStepPicks];
 };
 // behind it lie 16 bytes per trace, the query's cells, which are read as 16-byte vectors, and step_route_lds
 static_assert(sizeof(StepMatchLds) % 16 == 0, "the query's cells in LDS begin at a 16-byte boundary");
@@ -133,7 +137,10 @@ __device__ __forceinline__ void step_match(const StepMatchArgs& a, const StepRou
     if (tid < Ts) step_route_rows<WT>(ra, wv * a.n_blocks + blk, a.n_blocks * scan_waves + n_wg, lane);
     if (tid >= Ts) {
         const StepPick p = step_picks<WT, false>(ra, reinterpret_cast<float*>(qs + ((LE + 3) & ~3)), lane);
-        if (lane < ra.k) s.pick[lane] = p.e;
+        if (lane < ra.k) {
+            s.pick[lane] = p.e;
+            s.pick_w[lane] = p.w;
+        }
     } else if (sc.cell_bytes == 4) {
         if (a.vec > 1) step_scan<int32_t, 4>(sc, a.span, a.groups, t0, nt, qs, s_dot);
         else step_scan<int32_t, 1>(sc, a.span, a.groups, t0, nt, qs, s_dot);
@@ -156,6 +163,7 @@ __device__ __forceinline__ void step_match(const StepMatchArgs& a, const StepRou
     }
     if (tid < ra.k && s.pick[tid] >= 0) qs[sc.cur_layer * sc.E + s.pick[tid]] += 1;
     barrier_lds();
+    int slot = 0;  // of the pick, in the last wavefront, which has least to do behind the match
     if (wv == 0) {
         Best me = make_best(0, 1, -1);
         bool finish = true;
@@ -202,6 +210,8 @@ __device__ __forceinline__ void step_match(const StepMatchArgs& a, const StepRou
         for (int i = lane; i < LE; i += kWave) nq += (u64)(uint32_t)qs[i] * (uint32_t)qs[i];
         nq = wave_sum_u64_dpp(nq);
         if (lane == 0) s.nq = nq;
+    } else if (wv == scan_waves && lane < ra.k) {
+        slot = ra.slot_of_row[max(s.pick[lane], 0)];
     }
     barrier_lds();
     if (!s.finish) return;  // uniform
@@ -213,6 +223,16 @@ __device__ __forceinline__ void step_match(const StepMatchArgs& a, const StepRou
             a.host->best = s.win.idx;
             a.host->best_sim = sim;
         }
+    }
+    // What the step leaves for later calls besides.  Here, and not in the workgroups that stream, since the number below says that
+    // all of it is there; the EAM too: the other workgroups that match took their copies of it before they arrived.
+    if (wv == scan_waves && lane < ra.k) {
+        const int e = s.pick[lane];
+        a.idx[lane] = e;
+        a.w[lane] = s.pick_w[lane];
+        if (e >= 0) a.q[sc.cur_layer * sc.E + e] = qs[sc.cur_layer * sc.E + e];  // one more (Sec. 4.3); a token's picks are distinct
+        if (e < 0 && lane == 0) atomicOr(a.flags, 4);
+        if (e >= 0 && slot < 0) atomicOr(a.flags, 2);
     }
     score_and_heads<false>(sc, s.score, s.sn, s.best);
     // The host waits for the step by this word, whatever has become of its stream.  Its way over the host link is hidden by the

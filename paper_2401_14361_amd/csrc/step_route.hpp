@@ -32,20 +32,14 @@ struct StepRouteArgs {
     // kStepCopies times [E] (step_copy_words apart): a logit in the lower half, 1 in the upper one: each word says by itself that it is
     // there.  Zero between steps.
     unsigned long long* words;
-    int32_t* idx;                // [k] out
-    float* w;                    // [k] out
     const int32_t* slot_of_row;  // slot_of + layer*E
-    int32_t* flags;              // error flags (bit 1: pick not resident, bit 2: no softmax)
     int spin;
 };
 
-// What the reduction behind the experts does for the step besides: nobody reads the EAM then, nor waits for the words.
+// What the reduction behind the experts does for the step besides: nobody waits for the words then.
 struct StepTail {
-    int k;  // 0: nothing
     int E;
-    const int32_t* idx;
-    int32_t* eam_row;
-    unsigned long long* words;
+    unsigned long long* words;  // null: nothing
 };
 
 #if defined(__HIPCC__)
@@ -174,23 +168,8 @@ __device__ __forceinline__ StepPick step_picks(const StepRouteArgs& a, float* z,
     return p;
 }
 
-// What the step leaves for later calls, by one wavefront of the launch.
-__device__ __forceinline__ void step_publish(const StepRouteArgs& a, const StepPick& p, int lane) {
-    if (p.bad && lane == 0) atomicOr(a.flags, 4);
-    if (lane < a.k) {
-        a.idx[lane] = p.e;
-        a.w[lane] = p.w;
-        if (p.e >= 0 && p.slot < 0) atomicOr(a.flags, 2);
-    }
-}
-
-// By the first workgroups of the reduction, kStepTailThreads threads each: one added to the EAM per pick (Sec. 4.3), the words cleared for
-// the next step.
+// By the first workgroups of the reduction, kStepTailThreads threads each: the words cleared for the next step.
 __device__ __forceinline__ void step_tail(const StepTail& t) {
-    if (blockIdx.x == 0 && (int)threadIdx.x < t.k) {
-        const int e = t.idx[threadIdx.x];
-        if (e >= 0) t.eam_row[e] += 1;  // a token's picks are distinct
-    }
     for (unsigned c = blockIdx.x; c < kStepCopies; c += gridDim.x)
         for (int e = threadIdx.x; e < t.E; e += kStepTailThreads) t.words[c * step_copy_words(t.E) + e] = 0ull;
 }

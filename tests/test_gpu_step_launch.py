@@ -1,5 +1,7 @@
 """The asynchronous layer step in one launch (routing, match and experts) against the synchronous one, whose routing and match are kernels
 of their own: the same picks, gate weights, matches, scores and orders, bit for bit; the output up to the order of its sums."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -93,4 +95,70 @@ def test_one_launch_is_the_synchronous_step(m, shape, monkeypatch):
         assert np.abs(got[l]["y"] - want[l]["y"]).max() <= 2.0 ** -24 * 4 * np.sqrt((k + ns) * I + H) * scale, l
         for key in ("eam", "w", "sim", "top", "P", "V", "pf_order", "ev_order", "y"):
             assert np.array_equal(alone[l][key], got[l][key]), (l, key)
+    eamc.close()
+
+
+def _step_of_long_experts(m, resident):
+    """One-layer model whose two picks take about 300 us: (cache, eamc, eam, step(n, stream), bias).  Step n routes by the bias alone: picks
+    n % 5 and the next."""
+    E, k, H, I = 5, 2, 4096, 40960
+    desc = m.ModelDesc(1, E, k, 0, H, I, m.WDTYPE_BF16, 0, EPS)
+    cache = m.Cache(desc, E)
+    cache.reset(resident)
+    for s in range(E):
+        cache.slot_tensor(s).zero_()
+    eamc = m.Eamc(desc, 4)
+    eamc.load(np.random.default_rng(2).integers(0, 50, (4, 1, E)).astype(np.int32))
+    eam = torch.zeros((1, E), dtype=torch.int32, device="cuda")
+    W = torch.zeros((E, H), dtype=torch.bfloat16, device="cuda")
+    x, y = torch.zeros(H, dtype=torch.bfloat16, device="cuda"), torch.empty(H, device="cuda")
+    bias = torch.zeros((E, E), device="cuda")
+    for n in range(E):
+        bias[n, n], bias[n, (n + 1) % E] = 3.0 + 0.25 * n, 2.0
+    torch.cuda.synchronize()
+    return cache, eamc, eam, lambda n, s: m.moe_decode_layer(cache, eamc, eam, 0, W, bias[n % E], x, y, sync=False, stream=s), bias.cpu().double()
+
+
+def test_what_a_step_has_routed_is_there_when_it_has_matched(m):
+    # gate weights and the EAM of the last step, through another stream than the step's, while its experts still stream
+    cache, eamc, eam, step, bias = _step_of_long_experts(m, 5)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    seen = torch.zeros((12, 5), dtype=torch.int32, device="cuda")
+    m.profile_enable(4)
+    step(0, a)
+    torch.cuda.synchronize()
+    assert len(m.profile_samples("route_topk_kernel")) == 0  # one launch
+    m.profile_disable()
+    w = np.zeros((12, 2), dtype=np.float32)
+    for n in range(1, 12):
+        step(n, a)
+        cache.join(b)
+        with torch.cuda.stream(b):
+            seen[n].copy_(eam[0])
+        rc = m.lib().moei_cache_last_step(cache.h, C.c_void_p(w[n].ctypes.data), *[None] * 7, C.c_void_p(b.cuda_stream))
+        streams = not a.query()
+        assert rc == 0 and streams, n  # (else nothing is shown)
+        torch.cuda.synchronize()
+    want = np.zeros(5, dtype=np.int32)
+    for n in range(12):
+        want[[n % 5, (n + 1) % 5]] += 1
+        p = torch.softmax(bias[n % 5], 0)
+        if n:
+            assert np.allclose(w[n], [p[n % 5], p[(n + 1) % 5]], rtol=1e-6, atol=0), n
+            assert seen[n].tolist() == want.tolist(), n
+    assert cache.error_flags() == 0
+    cache.close()
+    eamc.close()
+
+
+def test_flags_of_a_step_are_there_when_it_has_matched(m):
+    cache, eamc, eam, step, _ = _step_of_long_experts(m, 3)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    for n, want in ((0, 0), (2, 2), (3, 2), (1, 0)):  # picks n and n + 1: experts 3 and 4 have no slot
+        step(n, a)
+        cache.join(b)
+        assert cache.error_flags(b) & 2 == want, n
+    torch.cuda.synchronize()
+    cache.error_flags()
+    cache.close()
     eamc.close()
