@@ -13,6 +13,7 @@
 #include "kernels.hpp"
 #include "score.hpp"
 #include "step_match.hpp"
+#include "stream_sets.hpp"
 
 namespace moei {
 
@@ -111,6 +112,7 @@ struct moei_cache {
     int32_t* d_slot_of = nullptr;
     int32_t* d_flags = nullptr;
     unsigned* d_ticket = nullptr;
+    StreamSet<hipStream_t> streams;  // ... of which the three below are
     hipStream_t copy_stream = nullptr, side_stream = nullptr;
     // scratch of the steps in one launch (step_match.hpp, step_route.hpp)
     u64* d_step_words = nullptr;
@@ -178,6 +180,38 @@ struct moei_cache {
 };
 
 namespace {
+StreamSets<hipStream_t, 8>& stream_sets() {
+    static auto* sets = new StreamSets<hipStream_t, 8>;  // (never destroyed: a cache may be, after it)
+    return *sets;
+}
+
+void destroy_streams(const StreamSet<hipStream_t>& s) {
+    for (hipStream_t t : {s.copy, s.side, s.prefetch})
+        if (t) (void)hipStreamDestroy(t);
+}
+
+int cache_streams(moei_cache* c) {
+    auto usable = [](const StreamSet<hipStream_t>& s) {
+        for (hipStream_t t : {s.prefetch, s.copy, s.side})
+            if (hipStreamQuery(t) != hipSuccess) {
+                (void)hipGetLastError();
+                return false;
+            }
+        return true;
+    };
+    auto make = [](StreamSet<hipStream_t>* s) -> int {
+        for (hipStream_t* t : {&s->prefetch, &s->copy, &s->side}) MOEI_HIP(hipStreamCreateWithFlags(t, hipStreamNonBlocking));
+        return MOEI_OK;
+    };
+    int device = 0;
+    MOEI_HIP(hipGetDevice(&device));
+    const int rc = stream_sets().take(device, &c->streams, usable, make, destroy_streams);
+    c->pf_stream = c->streams.prefetch;
+    c->copy_stream = c->streams.copy;
+    c->side_stream = c->streams.side;
+    return rc;
+}
+
 void prefill_scratch_free(PrefillScratch* p) {
     (void)hipFree(p->d_idx);
     (void)hipFree(p->d_w);
@@ -197,8 +231,8 @@ extern "C" const char* moei_version(void) { return "moei 0.1 (gfx950)"; }
 
 extern "C" int moei_cache_destroy(moei_cache* c) {
     if (!c) return MOEI_OK;
-    if (c->copy_stream) (void)hipStreamSynchronize(c->copy_stream);
-    if (c->side_stream) (void)hipStreamSynchronize(c->side_stream);
+    bool idle = true;  // (a stream under capture is not)
+    for (hipStream_t t : {c->copy_stream, c->side_stream, c->pf_stream}) idle &= t && hipStreamSynchronize(t) == hipSuccess;
     (void)hipFree(c->d_pool);
     (void)hipFree(c->d_slot_of);
     (void)hipFree(c->d_flags);
@@ -233,17 +267,12 @@ extern "C" int moei_cache_destroy(moei_cache* c) {
     prefill_scratch_free(&c->prefill);
     if (c->pin) (void)hipHostFree(c->pin);
     if (c->pin_V) (void)hipHostFree(c->pin_V);
-    if (c->pf_stream) {
-        (void)hipStreamSynchronize(c->pf_stream);
-        (void)hipStreamDestroy(c->pf_stream);
-    }
     for (hipEvent_t e : c->slot_ev)
         if (e) (void)hipEventDestroy(e);
     if (c->ev_copy) (void)hipEventDestroy(c->ev_copy);
     if (c->ev_routed) (void)hipEventDestroy(c->ev_routed);
     if (c->ev_main) (void)hipEventDestroy(c->ev_main);
-    if (c->copy_stream) (void)hipStreamDestroy(c->copy_stream);
-    if (c->side_stream) (void)hipStreamDestroy(c->side_stream);
+    if (!idle || !stream_sets().keep(c->streams)) destroy_streams(c->streams);
     delete c;
     return MOEI_OK;
 }
@@ -320,9 +349,8 @@ int cache_alloc(moei_cache* c) {
     MOEI_HIP(hipHostMalloc((void**)&c->pin_V, LE * sizeof(float), hipHostMallocMapped | hipHostMallocCoherent));
     MOEI_HIP(hipHostGetDevicePointer((void**)&c->pin_dev, c->pin, 0));
     MOEI_HIP(hipHostGetDevicePointer((void**)&c->pin_V_dev, c->pin_V, 0));
-    MOEI_HIP(hipStreamCreateWithFlags(&c->pf_stream, hipStreamNonBlocking));
-    MOEI_HIP(hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking));
-    MOEI_HIP(hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking));
+    rc = cache_streams(c);
+    if (rc) return rc;
     MOEI_HIP(hipEventCreateWithFlags(&c->ev_copy, hipEventDisableTiming));
     MOEI_HIP(hipEventCreateWithFlags(&c->ev_routed, hipEventDisableTiming));
     for (int r = 0; r < kRing; ++r) MOEI_HIP(hipEventCreateWithFlags(&c->ev_match[r], hipEventDisableTiming));

@@ -5,6 +5,10 @@ prefetch / eviction orders; 1e-5 relative for similarities and gate weights;
 max|y - y_ref| / max|y_ref| <= 2e-2 for FFN outputs (and a much tighter bound that
 fp32 accumulation actually meets, asserted alongside).
 """
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -511,3 +515,47 @@ def test_eamc_match_and_priority_at_deepseek_v2_size(m):
         np.testing.assert_allclose(P, rP, rtol=1e-6)
         np.testing.assert_allclose(V, rV, rtol=1e-6)
         eamc.close()
+
+
+CACHES_AND_STREAMS = r"""
+import time
+
+import numpy as np
+import torch
+import paper_2401_14361_amd as m
+
+desc = m.ModelDesc(1, 2, 2, 0, 4096, 65536, m.WDTYPE_BF16, 0, 2.0 ** -20)  # both experts a step: 3.2 GB, about 500 us
+eamc = m.Eamc(desc, 4)
+eamc.load(np.arange(8, dtype=np.int32).reshape(4, 1, 2))
+W, x, y = torch.zeros((2, 4096), dtype=torch.bfloat16, device="cuda"), torch.zeros(4096, dtype=torch.bfloat16, device="cuda"), torch.empty(4096, device="cuda")
+eam = torch.zeros((1, 2), dtype=torch.int32, device="cuda")
+alive, streams, beside = [], [], []
+for n in range(9):
+    cache = m.Cache(desc, 2)
+    cache.reset(2)
+    cache.set_match_count(2)  # the match of such a step is on the cache's own stream
+    streams.append(torch.cuda.Stream())
+    torch.ones(4, device="cuda")
+    with torch.cuda.stream(streams[-1]):
+        torch.ones(4, device="cuda")
+    alive = [cache] + alive[:2]
+    def seen(c):
+        torch.cuda.synchronize()
+        m.moe_decode_layer(c, eamc, eam, 0, W, None, x, y, sync=False)
+        t = [time.perf_counter()]
+        for wait in (c.sync, torch.cuda.synchronize):  # for the cache's own streams; for the experts too
+            wait()
+            t.append(time.perf_counter())
+        return t[1] - t[0] < 0.5 * (t[2] - t[0])  # 20 of 470 us; behind the experts 490 of 520
+    beside.append([any([seen(c) for _ in range(4)]) for c in alive])
+torch.cuda.synchronize()
+print("beside:", beside, flush=True)
+assert all(all(b) for b in beside)
+"""
+
+
+def test_the_match_runs_beside_the_experts_whatever_came_before():
+    # caches that come and go, the caller's streams made in between; in a process of its own, where nothing else has made any
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", CACHES_AND_STREAMS], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, (r.stdout[-500:], r.stderr[-1500:])
