@@ -297,7 +297,8 @@ int cache_alloc(moei_cache* c) {
             MOEI_FAIL(MOEI_ENOMEM, "moei_cache_create: device allocation of %zu bytes failed: %s",        \
                       (size_t)(bytes), hipGetErrorString(e__));                                            \
     } while (0)
-    MOEI_DMALLOC(c->d_pool, (size_t)c->n_total * c->slot_bytes);
+    const size_t unit_bytes = (size_t)3 * d.H * c->wb;  // zeros behind the last slot (launch_expert_ffn)
+    MOEI_DMALLOC(c->d_pool, (size_t)c->n_total * c->slot_bytes + unit_bytes);
     MOEI_DMALLOC(c->d_slot_of, LE * 4);
     MOEI_DMALLOC(c->d_flags, 4);
     MOEI_DMALLOC(c->d_ticket, 4);
@@ -326,6 +327,7 @@ int cache_alloc(moei_cache* c) {
     MOEI_DMALLOC(c->d_n_pf, 4);
     MOEI_DMALLOC(c->d_n_ev, 4);
 #undef MOEI_DMALLOC
+    MOEI_HIP(hipMemset(c->d_pool + (size_t)c->n_total * c->slot_bytes, 0, unit_bytes));
     MOEI_HIP(hipMemset(c->d_flags, 0, 4));
     MOEI_HIP(hipMemset(c->d_ticket, 0, 4));
     MOEI_HIP(hipMemset(c->d_step_ticket, 0, 4));

@@ -45,7 +45,6 @@ struct FfnArgs {
     int32_t* flags;
     // a layer step in one launch: slots and gate weights of the n_shared first experts are known, the picks' come from `route`
     int n_shared, shared_base;
-    size_t idle;  // elements from the pool to a unit of zeros
     StepMatchArgs match;
     StepRouteArgs route;
 };
@@ -213,15 +212,16 @@ __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fus
         my_slot = a.slot_ids[act];
         my_gate = a.gate_w[act];
     }
-    {  // the first window is on its way while x is staged; a wavefront without units reads the pool's
-       // first unit instead, so that there is one path and the wait counts stay exact
+    {  // the first window is on its way while x is staged.  There is one path and the wait counts stay exact: a wavefront without units reads
+       // the pool's first unit instead, and in a step in one launch one whose first unit is a pick's, whose slot is not known yet, goes
+       // through the zeros behind the last slot first
         if constexpr (MATCH) {
             const int e = t / I;
             if (t < NS) {
                 gate = 1.0f;
                 p = unit_off(a.shared_base + e, t - e * I, ok);
             } else {
-                p = a.idle;
+                p = (size_t)a.n_slots_total * a.slot_elems;
                 t -= W;  // the unit itself comes next
             }
         } else {
@@ -1459,21 +1459,12 @@ int ffn_scratch_alloc(const moei_model_desc& d, int n_act_max, FfnScratch* out) 
         out->d_part = nullptr;
         MOEI_FAIL(MOEI_ENOMEM, "FFN scratch allocation failed: %s", hipGetErrorString(e));
     }
-    const size_t unit = (size_t)3 * d.H * (d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4);
-    e = hipMalloc(&out->d_idle, unit);
-    if (e == hipSuccess) e = hipMemset(out->d_idle, 0, unit);
-    if (e != hipSuccess) {
-        ffn_scratch_free(out);
-        MOEI_FAIL(MOEI_ENOMEM, "FFN scratch allocation failed: %s", hipGetErrorString(e));
-    }
     return MOEI_OK;
 }
 
 void ffn_scratch_free(FfnScratch* s) {
     (void)hipFree(s->d_part);
-    (void)hipFree(s->d_idle);
     s->d_part = nullptr;
-    s->d_idle = nullptr;
 }
 
 // ------------------------------------------------------------------ scratch that is never allocated
@@ -1568,7 +1559,6 @@ int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_
         a.route.vec_ok = ((uintptr_t)a.route.W | (uintptr_t)a.route.x) % 16 == 0 && d.H % (bf16 ? 8 : 4) == 0;
         a.n_shared = d.n_shared;
         a.shared_base = step->shared_base;
-        a.idle = ((uintptr_t)scr.d_idle - (uintptr_t)d_pool) / (bf16 ? 2 : 4);
         match_lds = step->match_lds;
         tail = StepTail{a.route.E, a.route.words};
     }

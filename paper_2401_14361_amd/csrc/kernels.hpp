@@ -36,7 +36,6 @@ int launch_gather_slots(const int32_t* d_idx, int k, const int32_t* d_slot_of_ro
 int compute_units();  // of the device the library was first used on
 struct FfnScratch {
     float* d_part = nullptr;  // [n_part][H] workgroup partial sums of y
-    void* d_idle = nullptr;   // [3][H] zeros in the weight dtype: the unit of a wavefront that has none yet
     int n_part = 0;           // = workgroups of the fused kernel (one per compute unit)
     int n_free = 0;           // compute units that kernel leaves free
     int n_act_max = 0;
@@ -44,7 +43,7 @@ struct FfnScratch {
 int ffn_scratch_alloc(const moei_model_desc& d, int n_act_max, FfnScratch* out);
 void ffn_scratch_free(FfnScratch* s);
 // `step` (or null): the launch also routes the token, finds and scores the most similar trace (step_route.hpp, step_match.hpp), which
-// expert_ffn_takes_match must have allowed; it takes no slot ids and gate weights
+// expert_ffn_takes_match must have allowed; it takes no slot ids and gate weights, and a unit of zeros lies behind the pool's last slot
 struct StepArgs;
 bool expert_ffn_takes_match(const moei_model_desc& d, const void* d_pool, size_t slot_elems, const void* d_x);
 int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_elems, int n_slots_total,
