@@ -85,8 +85,11 @@ def test_one_launch_is_the_synchronous_step(m, shape, monkeypatch):
     assert n >= L
     got, n = _steps(m, desc, eamc, inputs, False)
     assert n == 0  # no launch of its own for the routing
-    monkeypatch.setenv("MOEI_STEP_SPIN", "0")  # every workgroup forms the logits itself
-    alone, _ = _steps(m, desc, eamc, inputs, False)
+    # every workgroup forms the logits itself; some do, others find them in memory, which of them differs from run to run
+    alone = []
+    for spin in ("0", "1", "3"):
+        monkeypatch.setenv("MOEI_STEP_SPIN", spin)
+        alone.append(_steps(m, desc, eamc, inputs, False)[0])
     for l in range(L):
         for key in ("eam", "w", "sim", "top", "sim1", "P", "V", "pf_order", "ev_order"):
             assert np.array_equal(got[l][key], want[l][key]), (l, key)
@@ -94,7 +97,44 @@ def test_one_launch_is_the_synchronous_step(m, shape, monkeypatch):
         scale = np.abs(want[l]["y"]).max()
         assert np.abs(got[l]["y"] - want[l]["y"]).max() <= 2.0 ** -24 * 4 * np.sqrt((k + ns) * I + H) * scale, l
         for key in ("eam", "w", "sim", "top", "P", "V", "pf_order", "ev_order", "y"):
-            assert np.array_equal(alone[l][key], got[l][key]), (l, key)
+            for spin, steps in zip((0, 1, 3), alone):
+                assert np.array_equal(steps[l][key], got[l][key]), (l, key, spin)
+    eamc.close()
+
+
+# E, k: logits that a wavefront holds in two to four registers a lane, the last one whole and in part; as many picks as lanes
+@pytest.mark.parametrize("E,k", [(65, 6), (128, 8), (150, 40), (192, 64), (200, 8), (255, 64), (256, 6)])
+@pytest.mark.parametrize("renorm", [0, 1])
+@pytest.mark.parametrize("logits", ["random", "equal", "few finite"])
+def test_ranking_in_registers(m, E, k, renorm, logits):
+    # the router is zero, so the bias is the logits: drawn at random, from three values (equal ones in every lane and in several registers of
+    # a lane), or mostly -inf, of which some are picked
+    L, H = 2, 256
+    desc = m.ModelDesc(L, E, k, 0, H, 8, m.WDTYPE_BF16, renorm, EPS)
+    rng = np.random.default_rng(E + k)
+    bias = rng.standard_normal((L, E)).astype(np.float32)
+    if logits == "equal":
+        bias = rng.choice(np.float32([-1.5, 0.25, 2.0]), (L, E))
+    elif logits == "few finite":
+        bias = np.where(rng.permuted(np.tile(np.arange(E), (L, 1)), axis=1) < k // 2, bias, -np.inf).astype(np.float32)
+    routers = torch.zeros((L, E, H), dtype=torch.bfloat16, device="cuda")
+    x = torch.randn((L, H), generator=torch.Generator(device="cuda").manual_seed(E), device="cuda").to(torch.bfloat16)
+    eamc = m.Eamc(desc, 20)
+    eamc.load(rng.integers(0, 200, (20, L, E)).astype(np.int32))
+    inputs = (routers, dev(bias), x, torch.zeros((L, E), dtype=torch.int32, device="cuda"))
+    want, n = _steps(m, desc, eamc, inputs, True)
+    assert n >= L
+    got, n = _steps(m, desc, eamc, inputs, False)
+    assert n == 0
+    for l in range(L):
+        picks = np.argsort(-bias[l], kind="stable")[:k]  # equal logits: the lower index first
+        assert np.array_equal(got[l]["eam"][l], np.bincount(picks, minlength=E)), l
+        p = np.exp(bias[l].astype(np.float64) - bias[l].max())
+        p = p[picks] / (p[picks].sum() if renorm else p.sum())
+        # the exponential, a sum of E of them and a quotient in 32 bits, all terms of one sign
+        assert np.allclose(got[l]["w"], p, rtol=2.0 ** -24 * (4 + E), atol=0), l
+        for key in ("eam", "w", "sim", "top", "sim1", "P", "V", "pf_order", "ev_order"):
+            assert np.array_equal(got[l][key], want[l][key]), (l, key)
     eamc.close()
 
 
