@@ -1006,12 +1006,14 @@ __global__ void __launch_bounds__(TM * 4, 2) prefill_down_kernel(MmArgs a) {  //
 // permutes a half stage, and the pieces it works on left no room to read the next half stage's ahead.)
 // A wavefront owns 128 columns x four 16-token blocks (blocks q, q + 4, ... of the item for quarter q), 32 accumulator tiles.
 // Bound by how fast a compute unit takes its operands in, as gate/up (2,048 tokens of the 26-layer shape: 750 MB): 182 us with the
-// transposition in registers, two barriers a stage and a workgroup per tile, 155 like this; 512 tokens 97 us either way.
-// Needs I % 64 == 0, I >= 192 (the rings look up to three stages ahead) and H % 256 == 0; other shapes take the kernel
-// above, an item in two parts.
+// transposition in registers, two barriers a stage and a workgroup per tile, 151 like this; 512 tokens 97 - 99 us either way.
+// The rings look up to three stages ahead.  FEW: tiles of one or two stages, all of which the rings hold: a tile is loaded whole, and the next
+// one while this one's results are stored (2,048 tokens, 64 experts + 2 of 64 / 128 units, H = 2,048: 157 / 165 us a layer with the kernel
+// above, 137 / 148 like this; 8 experts, H = 1,024: 71.4 / 70.7 and 70.0 / 68.9).
+// Needs I % 64 == 0 and H % 256 == 0; other shapes take the kernel above, an item in two parts.
 constexpr int kDwCols = 256;
 constexpr int kDwKS = 64;
-constexpr int kDwMinSlices = 3;
+constexpr int kDwMinSlices = 3;  // of the instance whose rings run on from tile to tile
 constexpr int kDwStagesW = 3;
 constexpr int kDwStagesA = 2;
 constexpr int kDwStageElemsW = kDwKS * kDwCols;       // 64 rows of 256 columns: 32 KiB
@@ -1023,6 +1025,7 @@ __device__ __forceinline__ uint2 ld_lds_tr(uint32_t addr) {
     return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)addr));
 }
 
+template <bool FEW>
 __global__ void __launch_bounds__(kWdThreads, 2) prefill_down_wide_kernel(MmArgs a) {
     constexpr int NTB = kTileTokWide / 64;  // 16-token blocks per wavefront: 4
     static_assert(kDwCols == 256 && kDwKS == 64 && kTileTokWide == 256 && kWdThreads == 8 * kWave, "eight wavefronts load 64 rows of 512 bytes and 256 of 128");
@@ -1100,12 +1103,26 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_down_wide_kernel(MmArgs
         ++slice_a;
     };
     static_assert(kDwStagesA == 2 && kDwStagesW == 3, "one stage of activations and two of weights are on their way");
-    aim_w(cur);
-    issue_w();
-    aim_a(cur);
-    issue_a();
-    issue_w();
-    Tile nxt = next_tile();
+    auto load_tile = [&](const Tile& t) {  // FEW
+        aim_w(t);
+        aim_a(t);
+        put_w = put_a = 0;
+        for (int s = 0; s < n_slices; ++s) {
+            issue_a();
+            issue_w();
+        }
+    };
+    Tile nxt{};
+    if constexpr (FEW) {
+        load_tile(cur);
+    } else {
+        aim_w(cur);
+        issue_w();
+        aim_a(cur);
+        issue_a();
+        issue_w();
+        nxt = next_tile();
+    }
     bool more_w = true;  // the weights of the stage after the one entered next are on their way
     // Enters the next stage, as in the gate/up kernel
     auto enter = [&]() {
@@ -1161,30 +1178,45 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_down_wide_kernel(MmArgs
 #pragma unroll
             for (int i = 0; i < 8; ++i) Y[tb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
         Ops opA, opB;
-        if constexpr (NT > 0) read_ops(0, opA, nt_tag);
-        for (int s = 1; s < n_slices; ++s) {
+        if constexpr (FEW) {
+            for (slot_w = slot_a = 0; slot_w < n_slices; slot_a = ++slot_w) {
+                if constexpr (NT > 0) {
+                    read_ops(0, opA, nt_tag);
+                    read_ops(1, opB, nt_tag);
+                    multiply(opA, Y, nt_tag);
+                    multiply(opB, Y, nt_tag);
+                }
+            }
+            __syncthreads();  // this tile has been read by all
+            nxt = next_tile();
+            resident(nxt);
+            if (nxt.ok) load_tile(nxt);
+        } else {
+            if constexpr (NT > 0) read_ops(0, opA, nt_tag);
+            for (int s = 1; s < n_slices; ++s) {
+                if constexpr (NT > 0) {
+                    read_ops(1, opB, nt_tag);
+                    multiply(opA, Y, nt_tag);
+                }
+                if (s == 1) resident(nxt);  // (first needed when the last stage but one is entered; there are at least three)
+                enter();
+                step_slots();
+                if constexpr (NT > 0) {
+                    read_ops(0, opA, nt_tag);
+                    multiply(opB, Y, nt_tag);
+                }
+            }
             if constexpr (NT > 0) {
                 read_ops(1, opB, nt_tag);
                 multiply(opA, Y, nt_tag);
             }
-            if (s == 1) resident(nxt);  // (first needed when the last stage but one is entered; there are at least three)
-            enter();
-            step_slots();
-            if constexpr (NT > 0) {
-                read_ops(0, opA, nt_tag);
-                multiply(opB, Y, nt_tag);
+            if (nxt.ok) {  // the next tile's first stage, while this one's last products are formed and stored
+                enter();
+                step_slots();
             }
         }
         if constexpr (NT > 0) {
-            read_ops(1, opB, nt_tag);
-            multiply(opA, Y, nt_tag);
-        }
-        if (nxt.ok) {  // the next tile's first stage, while this one's last products are formed and stored
-            enter();
-            step_slots();
-        }
-        if constexpr (NT > 0) {
-            multiply(opB, Y, nt_tag);
+            if constexpr (!FEW) multiply(opB, Y, nt_tag);
             // D[token 4 * lgrp + v][column lrow] of matrix i: sixteen lanes store 64 bytes of a row.  (The other way round a lane has four
             // columns of a token and stores them at once, but its neighbours are in other rows: a last tile, whose stores nothing hides, took 3 - 5 us
             // longer.  A layer of 1,000 tokens, 16 experts of 1,024 units + 1, H = 512: 78.6 us, 74.8 like this; 2,048 tokens of the 26-layer
@@ -1201,8 +1233,12 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_down_wide_kernel(MmArgs
                 }
         }
     };
-    enter();
+    if constexpr (!FEW) enter();
     for (;;) {
+        if constexpr (FEW) {
+            wait_vm_c<0>();
+            __syncthreads();
+        }
         // 16-token blocks of this wavefront that hold tokens of the item (blocks tq, tq + 4, ...)
         switch (max(0, ((cur.ntok + 15) / 16 - tq + 3) / 4)) {  // uniform over the wavefront
             case 0: run(std::integral_constant<int, 0>{}); break;
@@ -1213,7 +1249,7 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_down_wide_kernel(MmArgs
         }
         if (!nxt.ok) break;
         cur = nxt;
-        nxt = next_tile();
+        if constexpr (!FEW) nxt = next_tile();
     }
 }
 
@@ -1516,12 +1552,13 @@ int launch_mm(const moei_model_desc& d, MmArgs a, int max_items, int parts, hipS
         launch(K_PF_GATEUP, prefill_gateup_wide_kernel, dim3(kXcds * a.cus), dim3(kWdThreads), gu_smem, s, a);
     }
     MOEI_LAUNCH_CHECK();
-    if (a.dn_split == 2 && d.I % kDwKS == 0 && d.I >= kDwMinSlices * kDwKS && d.H % kDwCols == 0) {
+    if (a.dn_split == 2 && d.I % kDwKS == 0 && d.H % kDwCols == 0) {
         const size_t dw_smem = (size_t)(kDwStagesW * kDwStageElemsW + kDwStagesA * kDwStageElemsA) * 2;
-        rc = pf_allow_lds(prefill_down_wide_kernel, dw_smem);
+        auto kernel = d.I < kDwMinSlices * kDwKS ? prefill_down_wide_kernel<true> : prefill_down_wide_kernel<false>;
+        rc = pf_allow_lds(kernel, dw_smem);
         if (rc) return rc;
         a.n_cb = d.H / kDwCols;
-        launch(K_PF_DOWN, prefill_down_wide_kernel, dim3(kXcds * a.cus), dim3(kWdThreads), dw_smem, s, a);
+        launch(K_PF_DOWN, kernel, dim3(kXcds * a.cus), dim3(kWdThreads), dw_smem, s, a);
         MOEI_LAUNCH_CHECK();
         return MOEI_OK;
     }

@@ -164,9 +164,11 @@ def test_prefill_long_prompt_with_experts_that_are_not_resident(m, n_shared, H, 
         assert not o["rY"][t].any() and not o["Y"][t].any() or rel_max_err(o["Y"][t], o["rY"][t]) <= FFN_TOL, t
 
 
-# the down product of 256-token items: the fewest units it takes (192) and one stage less, which goes to the kernel of 128-token items;
-# one and several tiles a workgroup; items of every count of 16-token blocks; absent experts, whose tiles are passed over while the rings run on
-@pytest.mark.parametrize("E,k,n_shared,H,I,n,resident", [(1, 1, 1, 256, 128, 270, None), (1, 1, 1, 256, 192, 270, None), (3, 1, 0, 512, 256, 50, None),
+# the down product of 256-token items: the fewest units over which the rings run on (192), and tiles of one and two stages, which are loaded
+# whole; one and several tiles a workgroup; items of every count of 16-token blocks; absent experts, whose tiles are passed over meanwhile
+@pytest.mark.parametrize("E,k,n_shared,H,I,n,resident", [(1, 1, 1, 256, 128, 270, None), (1, 1, 1, 256, 64, 270, None), (40, 3, 1, 4096, 64, 700, None),
+                                                         (40, 3, 1, 4096, 64, 700, 20), (40, 3, 1, 4096, 128, 700, None), (24, 3, 0, 3840, 128, 1300, 12),
+                                                         (1, 1, 1, 256, 192, 270, None), (3, 1, 0, 512, 256, 50, None),
                                                          (40, 3, 1, 4096, 192, 700, None), (40, 3, 1, 4096, 192, 700, 20), (24, 3, 0, 3840, 320, 1300, 12)])
 def test_prefill_down_product_of_few_units(m, E, k, n_shared, H, I, n, resident, monkeypatch):
     monkeypatch.setenv("MOEI_PREFILL_TILE", "256")
