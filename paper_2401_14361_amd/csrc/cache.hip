@@ -850,9 +850,9 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
     // An asynchronous step over a collection that a few workgroups read while the experts stream matches and scores
     // inside that launch: nothing goes to the side stream.  (A plan that the host carries out needs the side
     // stream's event, an aggregate of several traces its kernels.)
-    const int match_blocks = sync_mode || plan_prefetch || c->match_m != 1 || !expert_ffn_takes_match(d, c->d_pool, c->slot_elems, d_x)
-                                 ? 0
-                                 : step_match_blocks(eamc, d, c->ffn.n_free);
+    const int scan_waves =
+        sync_mode || plan_prefetch || c->match_m != 1 ? 0 : expert_ffn_scan_waves(d, c->d_pool, c->slot_elems, c->ffn, d_x);
+    const int match_blocks = scan_waves > 0 ? step_match_blocks(eamc, d, c->ffn.n_free, scan_waves) : 0;
     if (match_blocks > 0 && c->side_pending) {  // an earlier step's match on the side stream writes the same results: it goes first
         MOEI_HIP(hipStreamWaitEvent(s, c->ev_side, 0));
         c->side_pending = false;

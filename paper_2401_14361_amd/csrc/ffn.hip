@@ -83,6 +83,7 @@ __device__ __forceinline__ void block_sum_rows(float* yp, int H, int row, int wa
 // read its first piece (the same for all of them) and add nothing, so a row costs what its chunks cost.
 // (The kernel for any H below reads two or four bytes a lane and keeps its sums in LDS: a call of four experts of
 // 910 units, H = 1,792, takes 59.6 us with it and 17.4 with this one; eight of 301, H = 2,880, 90.7 and 16.4.)
+constexpr int stream_max_waves(int nch) { return nch <= 4 ? 16 : (nch <= 10 ? 12 : 8); }
 template <int NCH>
 struct StreamShape {
     static constexpr int kSteps = 3 * NCH;
@@ -90,7 +91,7 @@ struct StreamShape {
     // (15 loads in flight for rows of 10 chunks left no registers: 3 spills), else a third
     static constexpr int kWindow = kSteps <= 16 ? kSteps : (kSteps / 2 <= 12 && kSteps % 2 == 0 ? kSteps / 2 : kSteps / 3);
     // register budget: window + y accumulators decide how many wavefronts fit a SIMD
-    static constexpr int kMaxWaves = NCH <= 4 ? 16 : (NCH <= 10 ? 12 : 8);
+    static constexpr int kMaxWaves = stream_max_waves(NCH);
 };
 
 // MATCH: the launch has workgroups that match and score beside the ones that stream.  An instance of its own: they take 124 registers,
@@ -466,6 +467,12 @@ int forced_waves() {
     return forced;
 }
 
+// Wavefronts per workgroup that stream, and of those that match that scan, in a step in one launch with rows of `nch` chunks.
+int step_waves(int n_units, int blocks, int nch) {
+    const int most = stream_max_waves(nch) - 1;
+    return plan_waves(n_units, blocks, most, kMatchWaves - 1, std::min(forced_waves(), most));
+}
+
 // Raises a kernel's dynamic-LDS limit above 64 KiB, once per kernel and size (the call
 // is not a stream operation, so it stays out of the per-launch path and of captures).
 template <typename K>
@@ -490,8 +497,8 @@ int launch_ffn_typed(FfnArgs a, bool fast, int grid, size_t match_lds, const Ste
 #define MOEI_FFN_CASE(N_, TAIL_)                                                                        \
     case N_: {                                                                                         \
         const bool step = a.match.n_blocks > 0; /* one wavefront more than stream */                   \
-        const int most = StreamShape<N_>::kMaxWaves - step;                                            \
-        a.waves = plan_waves(a.n_act * a.I, grid, most, step ? kMatchWaves - 1 : 4, std::min(forced_waves(), step ? most : 64)); \
+        a.waves = step ? step_waves(a.n_act * a.I, grid, N_)                                           \
+                       : plan_waves(a.n_act * a.I, grid, StreamShape<N_>::kMaxWaves, 4, forced_waves()); \
         static_assert(StreamShape<N_>::kMaxWaves >= kMatchWaves, "the match finds its wavefronts");    \
         const size_t padded = (size_t)N_ * kWave * V::N * sizeof(float);                               \
         int yg = (int)((kLdsBudget - padded) / padded);                                                \
@@ -1523,9 +1530,10 @@ bool ffn_streams(const moei_model_desc& d, const void* d_pool, size_t slot_elems
 }
 }  // namespace
 
-bool expert_ffn_takes_match(const moei_model_desc& d, const void* d_pool, size_t slot_elems, const void* d_x) {
-    const int chunk = kWave * 16 / (d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4);
-    return ffn_streams(d, d_pool, slot_elems) && d.H <= 16 * chunk && (uintptr_t)d_x % 16 == 0 && forced_takes_match(forced_waves());
+int expert_ffn_scan_waves(const moei_model_desc& d, const void* d_pool, size_t slot_elems, const FfnScratch& scr, const void* d_x) {
+    const int chunk = kWave * 16 / (d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4), nch = (d.H + chunk - 1) / chunk;
+    const bool takes = ffn_streams(d, d_pool, slot_elems) && nch <= 16 && (uintptr_t)d_x % 16 == 0 && forced_takes_match(forced_waves());
+    return takes ? step_waves((d.k + d.n_shared) * d.I, scr.n_part, nch) : 0;
 }
 
 int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_elems, int n_slots_total,

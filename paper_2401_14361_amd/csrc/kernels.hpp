@@ -43,9 +43,10 @@ struct FfnScratch {
 int ffn_scratch_alloc(const moei_model_desc& d, int n_act_max, FfnScratch* out);
 void ffn_scratch_free(FfnScratch* s);
 // `step` (or null): the launch also routes the token, finds and scores the most similar trace (step_route.hpp, step_match.hpp), which
-// expert_ffn_takes_match must have allowed; it takes no slot ids and gate weights, and a unit of zeros lies behind the pool's last slot
+// expert_ffn_scan_waves must have allowed; it takes no slot ids and gate weights, and a unit of zeros lies behind the pool's last slot
 struct StepArgs;
-bool expert_ffn_takes_match(const moei_model_desc& d, const void* d_pool, size_t slot_elems, const void* d_x);
+// wavefronts of a workgroup of such a launch that scan traces, 0: the shape takes no match beside it
+int expert_ffn_scan_waves(const moei_model_desc& d, const void* d_pool, size_t slot_elems, const FfnScratch& scr, const void* d_x);
 int launch_expert_ffn(const moei_model_desc& d, const void* d_pool, size_t slot_elems, int n_slots_total,
                       const FfnScratch& scr, const int32_t* d_slot_ids, const float* d_gate_w, int n_act,
                       const void* d_x, float* d_y, int32_t* d_flags, const StepArgs* step, hipStream_t s);

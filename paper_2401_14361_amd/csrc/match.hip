@@ -1368,32 +1368,7 @@ int launch_match(const moei_eamc* c, const int32_t* d_eam, int B, int layer_hi, 
     return MOEI_OK;
 }
 
-// How many workgroups match beside the experts' stream, 0: the match stays on the side stream.  One (no arrival count) for up
-// to 64 KB and 256 traces, else one per 64 KB or 128 traces, on the compute units that the experts leave free.
-// Such a workgroup is done 17 us after it has read its traces, at a rate that the form of its loads decides (16 bytes of 4-byte or 2-byte
-// cells, single cells where a row is no multiple of 16 bytes).  A step in one launch saves the routing's launch and the fork to the side
-// stream, and the chain there takes 35 us whatever the experts do, so the match may end 10 us after the experts or up to then.
-// us a layer, steps in a graph, side stream / one launch: 26 x 64 cells, 1,000 traces (277 KB a workgroup) beside 138 MB 38.2 / 31.8; 4-byte
-// cells: 20 x 64, 356 KB, 37.5 / 28.1, 8 x 100, 507 KB, 38.6 / 39.2, 32 x 64, 865 KB, 38.1 / 38.7, 29 x 60, 978 KB beside 84 MB 43.1 / 46.3; 2-byte cells: 14
-// x 32, 219 KB, 34.3 / 27.6, 8 x 128, 500 KB, 37.2 / 41.5; single 4-byte cells: 40 x 23, 158 KB, 36.2 / 28.5, 31 x 55, 268 KB, 36.0 / 38.0; single 2-byte
-// cells: 27 x 37, 92 KB, 38.7 / 34.6, 16 x 23, 180 KB, 38.1 / 43.9, 3 x 150, 220 KB, 44 / 136.  (Of 110 such shapes this rule gives 71 to the one
-// launch, 0.80 of the time in the mean, the worst 1.02, and leaves 24 out that it would serve better.)
-int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_units) {
-    const size_t scan = (size_t)c->N * d.L * d.E * c->cell_bytes;
-    const size_t experts = (size_t)(d.k + d.n_shared) * 3 * d.H * d.I * (d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4);
-    if (d.L * d.E > kKeyLdsCells) return 0;  // the scoring of more cells is a kernel of its own
-    int n = 1;
-    if (c->N > 256 || scan > (64 << 10)) {
-        n = (int)std::min<size_t>(std::min(free_units, kStepMatchMaxBlocks), std::max<size_t>((c->N + 127) / 128, (scan + (64 << 10) - 1) / (64 << 10)));
-        if (n < 1) return 0;
-    }
-    const bool whole = d.E % (16 / c->cell_bytes) == 0;
-    const double rate = 1024.0 * (c->cell_bytes == 4 ? (whole ? 28 : 10) : (whole ? 22 : 5));  // bytes a us
-    const double ffn_us = 4.0 + (double)experts / 6.5e6;
-    const double room = std::max(18.0, ffn_us - 7.0) * rate;
-    return (double)scan / n <= room && (c->N + n - 1) / n <= kStepMatchMaxTraces ? n : 0;
-}
-void step_scan_plan(StepMatchArgs* a, int waves) {
+int step_scan_plan(StepMatchArgs* a, int waves) {
     const int whole = 16 / a->sc.cell_bytes;
     a->per = (a->sc.N + a->n_blocks - 1) / a->n_blocks;
     a->vec = a->sc.E % whole == 0 ? whole : 1;
@@ -1409,6 +1384,39 @@ void step_scan_plan(StepMatchArgs* a, int waves) {
             a->groups = groups;
         }
     }
+    return trips;
+}
+
+// How many workgroups match beside the experts' stream, 0: the match stays on the side stream.  One (no arrival count) for up
+// to 64 KB and 256 traces, else one per 64 KB or 128 traces, on the compute units that the experts leave free.
+// Such a workgroup is done 17 us after it has read its traces.  With 16 bytes a load (28 KB/us of 4-byte, 22 of 2-byte cells) the bytes decide how
+// long that takes; with single cells, where a row is no multiple of 16 bytes, the trips to memory do, 1.6 us each however few layers
+// there are to request together.  A step in one launch saves the routing's launch and the fork to the side
+// stream, and the chain there takes 35 us whatever the experts do, so the match may end 10 us after the experts or up to then.
+// us a layer, steps in a graph, side stream / one launch: 26 x 64 cells, 1,000 traces (277 KB a workgroup) beside 138 MB 38.2 / 31.8; 4-byte
+// cells: 20 x 64, 356 KB, 37.5 / 28.1, 8 x 100, 507 KB, 38.6 / 39.2, 32 x 64, 865 KB, 38.1 / 38.7, 29 x 60, 978 KB beside 84 MB 43.1 / 46.3; 2-byte cells: 14
+// x 32, 219 KB, 34.3 / 27.6, 8 x 128, 500 KB, 37.2 / 41.5; single cells, layers x experts and trips: 14 x 45, 9, 44.1 / 40.1, 4 x 55, 10, 38.4 / 38.5, 6 x 55,
+// 11, 40.4 / 40.2, 4 x 77, 14, 37.7 / 42.1, 4 x 61, 17, 36.1 / 47.5, 20 x 78, 40, 48.0 / 81.0; 18 beside 220 MB, 26 x 65, 68.7 / 57.9.  (Of 560 shapes,
+// 300 of them with rows of single cells, this rule gives 0.794 of the side stream's time in the mean and 0.792 is the best there is; two lose more than 2 %, the
+// worst 1.025.  By bytes alone, as 16-byte loads, 0.798 and 18, the worst 1.47.)
+int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_units, int waves) {
+    const size_t scan = (size_t)c->N * d.L * d.E * c->cell_bytes;
+    const size_t experts = (size_t)(d.k + d.n_shared) * 3 * d.H * d.I * (d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4);
+    if (d.L * d.E > kKeyLdsCells) return 0;  // the scoring of more cells is a kernel of its own
+    StepMatchArgs a{};
+    a.n_blocks = 1;
+    if (c->N > 256 || scan > (64 << 10)) {
+        a.n_blocks = (int)std::min<size_t>(std::min(free_units, kStepMatchMaxBlocks), std::max<size_t>((c->N + 127) / 128, (scan + (64 << 10) - 1) / (64 << 10)));
+        if (a.n_blocks < 1) return 0;
+    }
+    a.sc.N = c->N;
+    a.sc.L = d.L;
+    a.sc.E = d.E;
+    a.sc.cell_bytes = c->cell_bytes;
+    const int trips = step_scan_plan(&a, waves);
+    const double scan_us = a.vec == 1 ? 1.6 * trips : (double)scan / a.n_blocks / (1024.0 * (c->cell_bytes == 4 ? 28 : 22));
+    const double ffn_us = 4.0 + (double)experts / 6.5e6;
+    return scan_us <= std::max(18.0, ffn_us - 7.0) && a.per <= kStepMatchMaxTraces ? a.n_blocks : 0;
 }
 size_t step_match_lds(const moei_eamc* c, int n_blocks) {
     const size_t per = (c->N + n_blocks - 1) / n_blocks;

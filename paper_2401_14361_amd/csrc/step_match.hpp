@@ -52,10 +52,10 @@ struct StepArgs {
     StepRouteArgs route;
     int shared_base;  // slots of the layer's shared experts: shared_base + s
 };
-// Fills in how a.n_blocks workgroups with `waves` wavefronts that scan go about it.
-void step_scan_plan(StepMatchArgs* a, int waves);
+// Fills in how a.n_blocks workgroups with `waves` wavefronts that scan go about it; returns the trips to memory this takes a thread.
+int step_scan_plan(StepMatchArgs* a, int waves);
 // 0: a step over this collection keeps the match on the side stream
-int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_units);
+int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_units, int waves);
 size_t step_match_lds(const moei_eamc* c, int n_blocks);
 
 #if defined(__HIPCC__)

@@ -119,8 +119,8 @@ def test_ranking_in_registers(m, E, k, renorm, logits):
         bias = np.where(rng.permuted(np.tile(np.arange(E), (L, 1)), axis=1) < k // 2, bias, -np.inf).astype(np.float32)
     routers = torch.zeros((L, E, H), dtype=torch.bfloat16, device="cuda")
     x = torch.randn((L, H), generator=torch.Generator(device="cuda").manual_seed(E), device="cuda").to(torch.bfloat16)
-    eamc = m.Eamc(desc, 20)
-    eamc.load(rng.integers(0, 200, (20, L, E)).astype(np.int32))
+    eamc = m.Eamc(desc, 12)
+    eamc.load(rng.integers(0, 200, (12, L, E)).astype(np.int32))
     inputs = (routers, dev(bias), x, torch.zeros((L, E), dtype=torch.int32, device="cuda"))
     want, n = _steps(m, desc, eamc, inputs, True)
     assert n >= L
@@ -201,4 +201,24 @@ def test_flags_of_a_step_are_there_when_it_has_matched(m):
     torch.cuda.synchronize()
     cache.error_flags()
     cache.close()
+    eamc.close()
+
+
+# L, E, N, cell bytes: rows of single cells over few layers take a trip to memory for every few cells, and many of them end long after the experts
+@pytest.mark.parametrize("L,E,N,cell,one_launch", [(4, 158, 1741, 4, False), (4, 111, 731, 2, False), (4, 61, 493, 2, False), (20, 78, 2711, 2, False),
+                                                   (14, 45, 2073, 2, True), (26, 64, 1000, 4, True), (4, 160, 1741, 4, True)])
+def test_a_scan_of_many_trips_stays_on_the_side_stream(m, L, E, N, cell, one_launch):
+    desc = m.ModelDesc(L, E, 3, 0, 768, 104, m.WDTYPE_BF16, 1, EPS)
+    rng = np.random.default_rng(E)
+    eamc = m.Eamc(desc, N, cell)
+    eamc.load(rng.integers(0, 200, (N, L, E)).astype(np.int32))
+    routers = torch.zeros((L, E, 768), dtype=torch.bfloat16, device="cuda")
+    inputs = (routers, dev(rng.standard_normal((L, E)).astype(np.float32)), torch.ones((L, 768), dtype=torch.bfloat16, device="cuda"),
+              torch.zeros((L, E), dtype=torch.int32, device="cuda"))
+    want, _ = _steps(m, desc, eamc, inputs, True)
+    got, n = _steps(m, desc, eamc, inputs, False)
+    assert (n == 0) == one_launch
+    for l in range(L):
+        for key in ("eam", "w", "sim", "top", "sim1", "P", "V", "pf_order", "ev_order"):
+            assert np.array_equal(got[l][key], want[l][key]), (l, key)
     eamc.close()
