@@ -113,8 +113,9 @@ __device__ __forceinline__ float wave_topk_rank(const float* z, int E, int k, in
     return sel;
 }
 
-// The same picks and bits for E <= 64 * NR logits in registers (lane l holds l, l + 64, ...), by k rounds of an arg-max: one
-// wavefront, no LDS and no loop whose length depends on E.  `other` (an int per logit, held the same way) travels with the picks.
+// The same picks and bits for E <= 64 * NR logits in registers (lane l holds l, l + 64, ...), by k rounds of a maximum and a ballot: one
+// wavefront, no LDS and no loop whose length depends on E, about 0.14 us a round beside wavefronts that stream.  `other` (an int per logit, held the
+// same way) travels with the picks.
 // Lane j < k returns pick j, its weight, its `other`; the weights are not divided, their sum is returned in every lane.
 template <int NR>
 __device__ __forceinline__ float wave_topk_regs(const float (&z)[NR], const int (&other)[NR], int E, int k, int lane, int& pick,
@@ -134,28 +135,29 @@ __device__ __forceinline__ float wave_topk_regs(const float (&z)[NR], const int 
         }
     }
     s = wave_sum_dpp(s);
-    unsigned left = 0u;
+    float left[NR];  // a logit that has been picked is a NaN here: no maximum, equal to none
 #pragma unroll
-    for (int r = 0; r < NR; ++r) left |= lane + r * kWave < E ? 1u << r : 0u;
-    const unsigned all = left;
+    for (int r = 0; r < NR; ++r) left[r] = lane + r * kWave < E ? z[r] : __builtin_nanf("");
     pick = -1;
     pick_other = 0;
     for (int j = 0; j < k; ++j) {
-        float v = -INFINITY;
-        unsigned c = 0x7fffffffu;  // the lane's largest remaining logit, the lowest index that holds it
+        float v = left[0];
+#pragma unroll
+        for (int r = 1; r < NR; ++r) v = fmaxf(v, left[r]);
+        const float top = wave_max_dpp(v);
+        // the lowest index that holds it: the first register, the first lane
+        int win = -1, o = 0;
+#pragma unroll
+        for (int r = NR - 1; r >= 0; --r) {
+            const unsigned long long holds = __ballot(left[r] == top);
+            if (holds) win = r * kWave + __builtin_ctzll(holds);
+        }
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-            const bool take = ((left >> r) & 1u) && (c == 0x7fffffffu || z[r] > v);
-            v = take ? z[r] : v;
-            c = take ? (unsigned)(lane + r * kWave) : c;
+            const int u = __builtin_amdgcn_readlane(other[r], win & (kWave - 1));
+            o = win / kWave == r ? u : o;
+            left[r] = win == lane + r * kWave ? __builtin_nanf("") : left[r];
         }
-        const float top = wave_max_dpp(v);
-        const int win = (int)wave_min_u32_dpp(v == top ? c : 0x7fffffffu);
-        int o = 0;
-#pragma unroll
-        for (int r = 0; r < NR; ++r)
-            if (win / kWave == r) o = __builtin_amdgcn_readlane(other[r], win & (kWave - 1));
-        if ((win & (kWave - 1)) == lane) left &= ~(1u << (win / kWave));
         if (lane == j) {
             pick = win;
             pick_other = o;
@@ -166,7 +168,7 @@ __device__ __forceinline__ float wave_topk_regs(const float (&z)[NR], const int 
     float sel = 0.f;
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-        if ((all & ~left) >> r & 1u) sel += p[r] / s;
+        if (lane + r * kWave < E && left[r] != left[r]) sel += p[r] / s;
     return wave_sum_dpp(sel);
 }
 

@@ -102,11 +102,12 @@ def test_one_launch_is_the_synchronous_step(m, shape, monkeypatch):
     eamc.close()
 
 
-# E, k: logits that a wavefront holds in two to four registers a lane, the last one whole and in part; as many picks as lanes
-@pytest.mark.parametrize("E,k", [(65, 6), (128, 8), (150, 40), (192, 64), (200, 8), (255, 64), (256, 6)])
+# E, k: logits that a wavefront holds in two to four registers a lane, the last one whole and in part; up to 64, ranked where the picks are a
+# quarter of them or more; as many picks as lanes
+@pytest.mark.parametrize("E,k", [(9, 8), (33, 8), (33, 9), (64, 15), (64, 16), (64, 64), (65, 6), (128, 8), (150, 40), (192, 64), (200, 8), (255, 64), (256, 6)])
 @pytest.mark.parametrize("renorm", [0, 1])
 @pytest.mark.parametrize("logits", ["random", "equal", "few finite"])
-def test_ranking_in_registers(m, E, k, renorm, logits):
+def test_ranking_of_logits(m, E, k, renorm, logits):
     # the router is zero, so the bias is the logits: drawn at random, from three values (equal ones in every lane and in several registers of
     # a lane), or mostly -inf, of which some are picked
     L, H = 2, 256
@@ -119,8 +120,9 @@ def test_ranking_in_registers(m, E, k, renorm, logits):
         bias = np.where(rng.permuted(np.tile(np.arange(E), (L, 1)), axis=1) < k // 2, bias, -np.inf).astype(np.float32)
     routers = torch.zeros((L, E, H), dtype=torch.bfloat16, device="cuda")
     x = torch.randn((L, H), generator=torch.Generator(device="cuda").manual_seed(E), device="cuda").to(torch.bfloat16)
-    eamc = m.Eamc(desc, 12)
-    eamc.load(rng.integers(0, 200, (12, L, E)).astype(np.int32))
+    N = 12 if E % 4 or E > 64 else 200  # 200: more groups of eight picks of a trace than threads
+    eamc = m.Eamc(desc, N)
+    eamc.load(rng.integers(0, 200, (N, L, E)).astype(np.int32))
     inputs = (routers, dev(bias), x, torch.zeros((L, E), dtype=torch.int32, device="cuda"))
     want, n = _steps(m, desc, eamc, inputs, True)
     assert n >= L
