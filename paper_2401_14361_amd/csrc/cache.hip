@@ -852,7 +852,7 @@ extern "C" int moe_decode_layer(moei_cache* c, const moei_eamc* eamc, int32_t* d
     // stream's event, an aggregate of several traces its kernels.)
     const int scan_waves =
         sync_mode || plan_prefetch || c->match_m != 1 ? 0 : expert_ffn_scan_waves(d, c->d_pool, c->slot_elems, c->ffn, d_x);
-    const int match_blocks = scan_waves > 0 ? step_match_blocks(eamc, d, c->ffn.n_free, scan_waves) : 0;
+    const int match_blocks = scan_waves > 0 ? step_match_blocks(eamc, d, c->ffn.n_free, scan_waves, captured) : 0;
     if (match_blocks > 0 && c->side_pending) {  // an earlier step's match on the side stream writes the same results: it goes first
         MOEI_HIP(hipStreamWaitEvent(s, c->ev_side, 0));
         c->side_pending = false;

@@ -55,7 +55,7 @@ struct StepArgs {
 // Fills in how a.n_blocks workgroups with `waves` wavefronts that scan go about it; returns the trips to memory this takes a thread.
 int step_scan_plan(StepMatchArgs* a, int waves);
 // 0: a step over this collection keeps the match on the side stream
-int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_units, int waves);
+int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_units, int waves, bool captured);
 size_t step_match_lds(const moei_eamc* c, int n_blocks);
 
 #if defined(__HIPCC__)

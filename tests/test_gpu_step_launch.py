@@ -224,3 +224,49 @@ def test_a_scan_of_many_trips_stays_on_the_side_stream(m, L, E, N, cell, one_lau
         for key in ("eam", "w", "sim", "top", "sim1", "P", "V", "pf_order", "ev_order"):
             assert np.array_equal(got[l][key], want[l][key]), (l, key)
     eamc.close()
+
+
+# L, E, N, cell bytes: scans of 8, 19 and 42 us: in one launch always, where a step is issued and not captured, never
+@pytest.mark.parametrize("L,E,N,cell,issued,captured", [(12, 19, 300, 2, True, True), (6, 22, 239, 2, True, False), (4, 158, 1741, 4, False, False)])
+def test_a_step_issued_by_itself_may_scan_for_longer(m, L, E, N, cell, issued, captured):
+    desc = m.ModelDesc(L, E, 3, 0, 768, 104, m.WDTYPE_BF16, 1, EPS)
+    rng = np.random.default_rng(E)
+    eamc = m.Eamc(desc, N, cell)
+    eamc.load(rng.integers(0, 200, (N, L, E)).astype(np.int32))
+    routers = torch.zeros((L, E, 768), dtype=torch.bfloat16, device="cuda")
+    bias = dev(rng.standard_normal((L, E)).astype(np.float32))
+    x, eam0 = torch.ones((L, 768), dtype=torch.bfloat16, device="cuda"), torch.zeros((L, E), dtype=torch.int32, device="cuda")
+    want, n = _steps(m, desc, eamc, (routers, bias, x, eam0), False)
+    assert (n == 0) == issued
+    cache = _cache(m, desc, 5)
+    eam, y = eam0.clone(), torch.empty((L, 768), device="cuda")
+
+    def steps():
+        for l in range(L):
+            m.moe_decode_layer(cache, eamc, eam, l, routers[l], bias[l], x[l], y[l], sync=False)
+        cache.join()
+
+    steps()
+    torch.cuda.synchronize()
+    cache.sync()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        steps()
+    cache.sync()
+    nodes = C.c_size_t(0)
+    assert m.lib().hipGraphGetNodes(C.c_void_p(graph.raw_cuda_graph()), None, C.byref(nodes)) == 0
+    assert (nodes.value == 2 * L) == captured, nodes.value  # the launch and the reduction
+    graph.instantiate()
+    for _ in range(3):
+        eam.copy_(eam0)
+        y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        top, sim = cache.last_matches()
+        assert np.array_equal(eam.cpu().numpy(), want[-1]["eam"]) and np.array_equal(top, want[-1]["top"]) and np.array_equal(sim, want[-1]["sim1"])
+        for l in range(L):  # the sums in another order
+            ref = want[l]["y"]
+            assert np.abs(y[l].cpu().numpy() - ref).max() <= 2.0 ** -24 * 4 * np.sqrt(3 * 104 + 768) * np.abs(ref).max(), l
+    assert cache.error_flags() == 0
+    cache.close()
+    eamc.close()
