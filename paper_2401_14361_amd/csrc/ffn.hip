@@ -94,8 +94,9 @@ struct StreamShape {
     static constexpr int kMaxWaves = stream_max_waves(NCH);
 };
 
-// MATCH: the launch has workgroups that match and score beside the ones that stream.  An instance of its own: they take 124 registers,
-// and the ones that stream far fewer (35 - 99 for up to four chunks), so that a scan on the side stream finds room beside them.
+// MATCH: the launch has workgroups that match and score beside the ones that stream.  An instance of its own: the code for those
+// takes 126 registers (224 at most, for rows of sixteen chunks) and spills 90 - 105 scalar ones into lanes of vector registers; launches that
+// only stream take 42 - 101 for up to four chunks and spill none, so that a scan on the side stream finds room beside them.
 template <typename WT, int NCH, bool TAIL, bool MATCH>
 __global__ void __launch_bounds__((StreamShape<NCH>::kMaxWaves * kWave)) ffn_fused_kernel(FfnArgs a) {
     using V = WVec<WT>;

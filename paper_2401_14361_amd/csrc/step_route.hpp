@@ -7,7 +7,7 @@
 // paper) for itself and hands the picks to its workgroup through LDS.  Meanwhile the others stream the shared experts, which need no picks.
 // (One wavefront that takes the picks and publishes them is three trips to memory more: 3 us beside the stream.)
 //
-// Nobody waits for long: a wavefront that has polled `spin` times forms all the logits itself, the same sums in the same
+// Every wait ends: a wavefront that has polled `spin` times (400: 0.2 - 1.2 ms) forms all the logits itself, a trip to memory or more a row, the same sums in the same
 // order, so that workgroups which hold every compute unit (of two steps on two streams, say) never wait for one that has not
 // been scheduled.
 #pragma once
