@@ -101,7 +101,7 @@ struct StepPick {
     float w;
     bool bad;  // no softmax exists: no picks
 };
-constexpr int kRegsE = 256;  // logits that one wavefront holds in registers
+constexpr int kRegsE = 256;  // logits that one wavefront holds in registers beside their slots
 
 // Lane j < k of one wavefront: pick j.  z: step_route_lds.  SLOTS: the picks' slots too.
 template <typename WT, bool SLOTS>
@@ -144,17 +144,9 @@ __device__ __forceinline__ StepPick step_picks(const StepRouteArgs& a, float* z,
     wave_lds_fence();
     StepPick p{-1, -1, 0.f, wave_logits_bad(z, a.E, lane)};
     if (p.bad) return p;  // uniform
-    // Up to 64 experts are ranked where the picks are a quarter of them or more: the ranking takes 0.3 - 2 us by the experts, a round of the other 0.14.
+    // Ranked are few experts for their picks: that takes 0.3 - 2 us for up to 64 experts, twice as long for up to 128, a round of the other 0.14.
     // us a layer, rounds / ranking, 9 experts, 8 picks 40.0 / 38.5; 64, 64 90 / 81; 64, 16 36.7 / 36.1; 64, 8 30.1 / 30.8; 32, 4 28.7 / 29.0; 16, 4 40.8 / 40.4.
-    if (a.E <= kRegsE && (a.E > kWave || 4 * a.k < a.E)) {
-        float zr[NR];
-#pragma unroll
-        for (int r = 0; r < NR; ++r) zr[r] = z[min(lane + r * kWave, a.E - 1)];
-        const float sel = wave_topk_regs<NR>(zr, slot, a.E, a.k, lane, p.e, p.w, p.slot);
-        if (a.renorm) p.w /= sel;
-        return p;
-    }
-    if (a.E <= kRankMaxE) {
+    if (4 * a.k >= (a.E + kWave - 1) / kWave * a.E) {
         int* s_idx = reinterpret_cast<int*>(z + a.E);
         float* s_w = z + a.E + kStepPicks;
         const float sel = wave_topk_rank(z, a.E, a.k, a.renorm, lane, s_idx, s_w, false);
@@ -163,12 +155,28 @@ __device__ __forceinline__ StepPick step_picks(const StepRouteArgs& a, float* z,
             p.e = s_idx[lane];
             p.w = a.renorm ? s_w[lane] / sel : s_w[lane];
         }
+    } else if (a.E <= kRegsE) {
+        float zr[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) zr[r] = z[min(lane + r * kWave, a.E - 1)];
+        const float sel = wave_topk_regs<NR>(zr, a.E, a.k, lane, p.e, p.w);
+        if (a.renorm) p.w /= sel;
+    } else if (a.E <= kRankMaxE) {
+        constexpr int MR = kRankMaxE / kWave;
+        float zr[MR];
+#pragma unroll
+        for (int r = 0; r < MR; ++r) zr[r] = z[min(lane + r * kWave, a.E - 1)];
+        const float sel = wave_topk_regs<MR>(zr, a.E, a.k, lane, p.e, p.w);
+        if (a.renorm) p.w /= sel;
     } else {
         wave_topk(z, a.E, a.k, a.renorm, lane, p.e, p.w);
     }
-    if (SLOTS && a.E <= kWave) {
-        const int held = __shfl(slot[0], max(p.e, 0));
-        if (p.e >= 0) p.slot = held;
+    if (SLOTS && a.E <= kRegsE) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int held = __shfl(slot[r], p.e & (kWave - 1));
+            if (p.e >= 0 && p.e / kWave == r) p.slot = held;
+        }
     } else if (SLOTS && p.e >= 0) {
         p.slot = a.slot_of_row[p.e];
     }

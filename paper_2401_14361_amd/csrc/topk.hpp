@@ -114,12 +114,10 @@ __device__ __forceinline__ float wave_topk_rank(const float* z, int E, int k, in
 }
 
 // The same picks and bits for E <= 64 * NR logits in registers (lane l holds l, l + 64, ...), by k rounds of a maximum and a ballot: one
-// wavefront, no LDS and no loop whose length depends on E, about 0.14 us a round beside wavefronts that stream.  `other` (an int per logit, held the
-// same way) travels with the picks.
-// Lane j < k returns pick j, its weight, its `other`; the weights are not divided, their sum is returned in every lane.
+// wavefront, no LDS and no loop whose length depends on E, about 0.14 us a round of up to 256 beside wavefronts that stream.
+// Lane j < k returns pick j and its weight; the weights are not divided, their sum is returned in every lane.
 template <int NR>
-__device__ __forceinline__ float wave_topk_regs(const float (&z)[NR], const int (&other)[NR], int E, int k, int lane, int& pick,
-                                                float& weight, int& pick_other) {
+__device__ __forceinline__ float wave_topk_regs(const float (&z)[NR], int E, int k, int lane, int& pick, float& weight) {
     float m = -INFINITY;
 #pragma unroll
     for (int r = 0; r < NR; ++r)
@@ -139,28 +137,22 @@ __device__ __forceinline__ float wave_topk_regs(const float (&z)[NR], const int 
 #pragma unroll
     for (int r = 0; r < NR; ++r) left[r] = lane + r * kWave < E ? z[r] : __builtin_nanf("");
     pick = -1;
-    pick_other = 0;
     for (int j = 0; j < k; ++j) {
         float v = left[0];
 #pragma unroll
         for (int r = 1; r < NR; ++r) v = fmaxf(v, left[r]);
         const float top = wave_max_dpp(v);
         // the lowest index that holds it: the first register, the first lane
-        int win = -1, o = 0;
+        int win = -1;
 #pragma unroll
         for (int r = NR - 1; r >= 0; --r) {
             const unsigned long long holds = __ballot(left[r] == top);
             if (holds) win = r * kWave + __builtin_ctzll(holds);
         }
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int u = __builtin_amdgcn_readlane(other[r], win & (kWave - 1));
-            o = win / kWave == r ? u : o;
-            left[r] = win == lane + r * kWave ? __builtin_nanf("") : left[r];
-        }
+        for (int r = 0; r < NR; ++r) left[r] = win == lane + r * kWave ? __builtin_nanf("") : left[r];
         if (lane == j) {
             pick = win;
-            pick_other = o;
             weight = top;
         }
     }

@@ -102,9 +102,10 @@ def test_one_launch_is_the_synchronous_step(m, shape, monkeypatch):
     eamc.close()
 
 
-# E, k: logits that a wavefront holds in two to four registers a lane, the last one whole and in part; up to 64, ranked where the picks are a
-# quarter of them or more; as many picks as lanes
-@pytest.mark.parametrize("E,k", [(9, 8), (33, 8), (33, 9), (64, 15), (64, 16), (64, 64), (65, 6), (128, 8), (150, 40), (192, 64), (200, 8), (255, 64), (256, 6)])
+# E, k: logits that a wavefront holds in two to four and in sixteen registers a lane, the last one whole and in part; up to 64, ranked where the picks are
+# a quarter of them or more, up to 128 half of them; as many picks as lanes
+@pytest.mark.parametrize("E,k", [(9, 8), (33, 8), (33, 9), (64, 15), (64, 16), (64, 64), (65, 6), (65, 32), (65, 33), (128, 8), (128, 64), (150, 40), (192, 64), (200, 8),
+                                 (255, 64), (256, 6), (257, 8), (300, 64), (640, 3), (1023, 16), (1024, 64)])
 @pytest.mark.parametrize("renorm", [0, 1])
 @pytest.mark.parametrize("logits", ["random", "equal", "few finite"])
 def test_ranking_of_logits(m, E, k, renorm, logits):
