@@ -1399,11 +1399,11 @@ int step_scan_plan(StepMatchArgs* a, int waves) {
 // 11, 40.4 / 40.2, 4 x 77, 14, 37.7 / 42.1, 4 x 61, 17, 36.1 / 47.5, 20 x 78, 40, 48.0 / 81.0; 18 beside 220 MB, 26 x 65, 68.7 / 57.9.  (Of 560 shapes,
 // 300 of them with rows of single cells, this rule gives 0.794 of the side stream's time in the mean and 0.792 is the best there is; two lose more than 2 %, the
 // worst 1.025.  By bytes alone, as 16-byte loads, 0.798 and 18, the worst 1.47.)  Steps issued one by one (`captured` false) take the host's
-// time with a side stream, 32 - 50 us for its launches and event calls, so the scan may take 26 us there.  us a step, side stream / one launch, layers x
+// time with a side stream, 32 - 50 us for its launches and event calls, so the scan may take 30 us there.  us a step, side stream / one launch, layers x
 // experts and trips: 5 x 87, 13, 63.9 / 46.5; 6 x 22, 12, 61.1 / 39.6; 11 x 38, 16, 62.3 / 50.1 (issued without a pause 48.4 / 43.4, in a graph 43.1 / 49.0);
-// 16-byte loads: 18 x 56, 25.7 us, 61.1 / 46.0 (47.3 / 39.1; 45.3 / 44.9); beyond: 6 x 134, 21 trips, 62.1 / 55.5 (49.0 / 48.0; 43.0 / 53.3), 36 x 28, 32.7
-// us, 49.3 / 48.6 (35.7 / 42.8).  (Of 64 shapes issued without a pause this line gives 0.774 of the side stream's time in the mean, the worst
-// 1.02, a line at 18 us 0.832; at 33 us 0.768 and 1.54.)
+// 16-byte loads: 18 x 56, 25.7 us, 61.1 / 46.0 (47.3 / 39.1; 45.3 / 44.9); 4 x 107, 19 trips, 55.9 / 47.1; beyond: 6 x 134, 21 trips, 62.1 / 55.5 (49.0 / 48.0; 43.0 / 53.3), 36 x 28, 32.7
+// us, 49.3 / 48.6 (35.7 / 42.8).  (Of 64 shapes issued without a pause this line gives 0.769 of the side stream's time in the mean, the worst
+// 1.02, a line at 18 us 0.832, at 26 us 0.774; at 33 us 0.768 and 1.54.)
 int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_units, int waves, bool captured) {
     const size_t scan = (size_t)c->N * d.L * d.E * c->cell_bytes;
     const size_t experts = (size_t)(d.k + d.n_shared) * 3 * d.H * d.I * (d.wdtype == MOEI_WDTYPE_BF16 ? 2 : 4);
@@ -1421,7 +1421,7 @@ int step_match_blocks(const moei_eamc* c, const moei_model_desc& d, int free_uni
     const int trips = step_scan_plan(&a, waves);
     const double scan_us = a.vec == 1 ? 1.6 * trips : (double)scan / a.n_blocks / (1024.0 * (c->cell_bytes == 4 ? 28 : 22));
     const double ffn_us = 4.0 + (double)experts / 6.5e6;
-    return scan_us <= std::max(captured ? 18.0 : 26.0, ffn_us - 7.0) && a.per <= kStepMatchMaxTraces ? a.n_blocks : 0;
+    return scan_us <= std::max(captured ? 18.0 : 30.0, ffn_us - 7.0) && a.per <= kStepMatchMaxTraces ? a.n_blocks : 0;
 }
 size_t step_match_lds(const moei_eamc* c, int n_blocks) {
     const size_t per = (c->N + n_blocks - 1) / n_blocks;

@@ -208,7 +208,7 @@ def test_flags_of_a_step_are_there_when_it_has_matched(m):
 
 
 # L, E, N, cell bytes: rows of single cells over few layers take a trip to memory for every few cells, and many of them end long after the experts
-@pytest.mark.parametrize("L,E,N,cell,one_launch", [(4, 158, 1741, 4, False), (4, 111, 731, 2, False), (4, 61, 493, 2, False), (20, 78, 2711, 2, False),
+@pytest.mark.parametrize("L,E,N,cell,one_launch", [(4, 158, 1741, 4, False), (4, 111, 731, 2, False), (4, 77, 530, 2, False), (4, 61, 493, 2, True), (20, 78, 2711, 2, False),
                                                    (14, 45, 2073, 2, True), (26, 64, 1000, 4, True), (4, 160, 1741, 4, True)])
 def test_a_scan_of_many_trips_stays_on_the_side_stream(m, L, E, N, cell, one_launch):
     desc = m.ModelDesc(L, E, 3, 0, 768, 104, m.WDTYPE_BF16, 1, EPS)
