@@ -1253,6 +1253,187 @@ __global__ void __launch_bounds__(kWdThreads, 2) prefill_down_wide_kernel(MmArgs
     }
 }
 
+// 3c, long prompts, long experts and at most a tile for every compute unit: a workgroup per tile of the same size.  The wide kernel's gain lies between
+// tiles and in its stores; where a workgroup has one tile of 40 stages or more, its stages take 3 - 10 % longer than this one's, whichever
+// way its reads and loads are ordered.  Its stream of W_down and the item's activations go straight into LDS, loaded by wavefronts 0 .. 3 and
+// 4 .. 7, the pieces unswizzled; a lane transposes eight units x eight columns in registers.  That leaves room for one set of W_down pieces and two of
+// activations: those of a half stage are read one half step ahead, the W_down pieces at its start, and each ring has a barrier of its own:
+// before the first half of a stage the wavefronts that load W_down have seen it land (after the barrier the stage before it has been
+// read by all and its slot is loaded again), before the second half the same for the activations of the next stage.
+// us a layer, wide / this: the 8-expert shape, 1,531 tokens 1,450 / 1,363; 1 expert + 2 shared of 5,120 units, H = 1,536, 486 tokens 182 / 172; 50 of
+// 2,944, H = 1,024, 1,613 tokens 261 / 255; 7 of 3,520, H = 768, 926 tokens 160 / 156; few tokens to an item the other way: 6 + 1 of 3,840, H = 2,304, 155
+// tokens 142 / 149, 1 of 2,496, H = 3,072, 129 tokens 110 / 118.  Of 14 prompts with 40 stages or more it takes longer for one; with fewer (60 prompts)
+// the wide kernel takes 0.98 of its time in the mean, with more tiles than compute units (28) 0.95.
+constexpr int kDtMinSlices = 40;
+// waits until at most `n` of this wavefront's vector memory operations are outstanding (n <= 32)
+__device__ __forceinline__ void wait_vm(int n) {
+    // s_waitcnt: vmcnt in bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima
+#define MOEI_WAIT_CASE(v) case v: __builtin_amdgcn_s_waitcnt(0x0f70 | ((v) & 15) | (((v) >> 4) << 14)); break;
+    switch (n) {
+        MOEI_WAIT_CASE(0) MOEI_WAIT_CASE(1) MOEI_WAIT_CASE(2) MOEI_WAIT_CASE(3) MOEI_WAIT_CASE(4) MOEI_WAIT_CASE(5)
+        MOEI_WAIT_CASE(6) MOEI_WAIT_CASE(7) MOEI_WAIT_CASE(8) MOEI_WAIT_CASE(9) MOEI_WAIT_CASE(10) MOEI_WAIT_CASE(11)
+        MOEI_WAIT_CASE(12) MOEI_WAIT_CASE(13) MOEI_WAIT_CASE(14) MOEI_WAIT_CASE(15) MOEI_WAIT_CASE(16) MOEI_WAIT_CASE(17)
+        MOEI_WAIT_CASE(18) MOEI_WAIT_CASE(19) MOEI_WAIT_CASE(20) MOEI_WAIT_CASE(21) MOEI_WAIT_CASE(22) MOEI_WAIT_CASE(23)
+        MOEI_WAIT_CASE(24) MOEI_WAIT_CASE(25) MOEI_WAIT_CASE(26) MOEI_WAIT_CASE(27) MOEI_WAIT_CASE(28) MOEI_WAIT_CASE(29)
+        MOEI_WAIT_CASE(30) MOEI_WAIT_CASE(31)
+        default: __builtin_amdgcn_s_waitcnt(0x8f70); break;  // 32
+    }
+#undef MOEI_WAIT_CASE
+}
+
+__global__ void __launch_bounds__(kWdThreads, 2) prefill_down_tile_kernel(MmArgs a) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    uint16_t* ring_w = reinterpret_cast<uint16_t*>(smem_raw);         // [kDwStagesW][64][256]
+    uint16_t* ring_a = ring_w + (size_t)kDwStagesW * kDwStageElemsW;  // [kDwStagesA][256][64], chunks swizzled
+    // all column blocks of an item on one XCD
+    const int pos = blockIdx.x % kXcds + kXcds * (blockIdx.x / kXcds / a.n_cb), cb = blockIdx.x / kXcds % a.n_cb;
+    if (pos >= a.meta[0]) return;
+    const PItem it = a.items[pos];
+    const int H = a.H, I = a.I;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int lrow = lane & 15, lgrp = lane >> 4;
+    const int cg = wv & 1, tq = wv >> 1;  // column group (128 columns), token quarter
+    const int col_wg = cb * kDwCols;
+    if (it.slot < 0 || it.slot >= a.n_slots_total) {  // not resident: the rows are zero, the flag says so
+        if (tid == 0) atomicOr(a.flags, 1);
+        for (int r = 0; r < it.ntok; ++r)
+            for (int c = tid; c < kDwCols; c += kWdThreads) a.yc[(size_t)(it.row0 + r) * H + col_wg + c] = 0.f;
+        return;
+    }
+    // 16-token blocks of this wavefront that hold tokens of the item (blocks tq, tq + 4, ...)
+    const int n_live = max(0, ((it.ntok + 15) / 16 - tq + 3) / 4);
+    const bool loads_w = wv < 4;  // else the activations
+    const uint16_t* wd = a.pool + (size_t)it.slot * a.slot_elems + 2 * H + col_wg;
+
+    // Weights: load j (of 8) of wavefront w fills rows 2 * (4 * j + w) .. + 2 of a stage (a row = 256
+    // columns = 32 pieces); this lane brings piece lane % 32 of row .. + lane / 32.  Activations: load
+    // j (of at most 8) fills rows 8 * (4 * j + w) .. + 8 (a row = 64 units = 8 pieces), chunk position
+    // lane % 8 of row .. + lane / 8; rows past the item's tokens are not loaded (what the ring holds
+    // there is multiplied at most within a token block that also holds tokens, never stored).  One
+    // source address per lane; the loads of a stage lie a fixed number of rows apart.
+    const uint16_t* src0;
+    const int arow = 8 * (wv & 3) + (lane >> 3);  // this lane's row of an activation load, before 32 * j
+    if (loads_w) {
+        const int r = 2 * (wv & 3) + (lane >> 5);
+        src0 = wd + (size_t)r * 3 * H + (lane & 31) * 8;
+    } else {
+        const int c = (lane & 7) ^ ((arow >> 1) & 7);  // rows 32 apart share the swizzle key
+        src0 = a.act + (size_t)it.row0 * I + c * 8;
+    }
+    const int nld = loads_w ? 8 : min(8, max(0, (it.ntok - 8 * (wv & 3) + 31) / 32));  // loads per stage of this wavefront
+    const uint32_t my_ring = lds_address(loads_w ? ring_w : ring_a) + (uint32_t)(wv & 3) * 1024;
+    auto issue = [&](int s) {  // the calling wavefront's share of stage s of its ring
+        if (loads_w) {
+            const uint32_t st = my_ring + (uint32_t)(s % kDwStagesW) * (kDwStageElemsW * 2);
+            const uint16_t* p = src0 + (size_t)s * kDwKS * 3 * H;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) load16_to_lds(p + (size_t)j * 8 * 3 * H, st + (uint32_t)j * 4096);
+        } else {
+            const uint32_t st = my_ring + (uint32_t)(s % kDwStagesA) * (kDwStageElemsA * 2);
+            const uint16_t* p = src0 + s * kDwKS;
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (j < nld) load16_to_lds(p + (uint32_t)min(arow + 32 * j, it.ntok - 1) * (uint32_t)I, st + (uint32_t)j * 4096);
+        }
+    };
+
+    f32x4 Y[4][8];
+#pragma unroll
+    for (int tb = 0; tb < 4; ++tb)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) Y[tb][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    struct Acts {
+        bf16x8 av[4];  // the token blocks' activations of a half stage
+    };
+    auto read_acts = [&](int t, Acts& o, auto nt_tag) {  // half step t: stage t / 2, units 32 * (t % 2) .. + 32
+        constexpr int NT = decltype(nt_tag)::value;
+        const uint16_t* sa = ring_a + (size_t)((t >> 1) % kDwStagesA) * kDwStageElemsA;
+#pragma unroll
+        for (int tb = 0; tb < NT; ++tb) o.av[tb] = ld_bf16x8(sa + wd_pos((4 * tb + tq) * 16 + lrow, 4 * (t & 1) + lgrp));
+    };
+    auto multiply = [&](int t, const Acts& o, auto nt_tag) {
+        constexpr int NT = decltype(nt_tag)::value;
+        const uint16_t* sw = ring_w + (size_t)((t >> 1) % kDwStagesW) * kDwStageElemsW;
+        uint4 w[8];  // units 8 * lgrp + j of the half stage, columns 8 * lrow .. + 8 of the wavefront's 128
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            w[j] = *reinterpret_cast<const uint4*>(sw + (size_t)(32 * (t & 1) + 8 * lgrp + j) * kDwCols + cg * 128 + lrow * 8);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            uint32_t dw[4];
+#pragma unroll
+            for (int p2 = 0; p2 < 4; ++p2) {
+                const uint32_t lo = reinterpret_cast<const uint32_t*>(&w[2 * p2])[i >> 1];
+                const uint32_t hi = reinterpret_cast<const uint32_t*>(&w[2 * p2 + 1])[i >> 1];
+                dw[p2] = (i & 1) ? __builtin_amdgcn_perm(hi, lo, 0x07060302u) : __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+            }
+            bf16x8 wt;
+            memcpy(&wt, dw, 16);
+#pragma unroll
+            for (int tb = 0; tb < NT; ++tb) Y[tb][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o.av[tb], wt, Y[tb][i], 0, 0, 0);
+        }
+    };
+    const int n_slices = I / kDwKS;  // I is a multiple of 64 here
+    // both rings start full; stage 0 of both has landed for all after the first barrier
+    if (loads_w) {
+        for (int s = 0; s < kDwStagesW; ++s)
+            if (s < n_slices) issue(s);
+        wait_vm((min(n_slices, kDwStagesW) - 1) * 8);
+    } else {
+        for (int s = 0; s < kDwStagesA; ++s)
+            if (s < n_slices) issue(s);
+        wait_vm((min(n_slices, kDwStagesA) - 1) * nld);
+    }
+    __syncthreads();
+    auto run = [&](auto nt_tag) {
+        constexpr int NT = decltype(nt_tag)::value;
+        Acts actA, actB;
+        if constexpr (NT > 0) read_acts(0, actA, nt_tag);
+        for (int s = 0; s < n_slices; ++s) {
+            // first half of stage s: its W_down rows have landed (stages 0 .. s + 1 have been issued);
+            // stage s - 1 has been read by all, its slot takes stage s + 2
+            if (s >= 1) {
+                if (loads_w) wait_vm(min(n_slices - 1 - s, 1) * 8);
+                __syncthreads();
+                if (loads_w && s + 2 < n_slices) issue(s + 2);
+            }
+            if constexpr (NT > 0) {
+                read_acts(2 * s + 1, actB, nt_tag);
+                multiply(2 * s, actA, nt_tag);
+            }
+            // second half: the activations of stage s + 1 (read during this half step) have landed; those of
+            // stage s have been read by all, their slot takes stage s + 2
+            if (s + 1 < n_slices) {
+                if (!loads_w) wait_vm(0);
+                __syncthreads();
+                if (!loads_w && s + 2 < n_slices) issue(s + 2);
+                if constexpr (NT > 0) read_acts(2 * s + 2, actA, nt_tag);
+            }
+            if constexpr (NT > 0) multiply(2 * s + 1, actB, nt_tag);
+        }
+    };
+    switch ((n_live + 1) / 2) {  // uniform over the wavefront
+        case 0: run(std::integral_constant<int, 0>{}); break;
+        case 1: run(std::integral_constant<int, 2>{}); break;
+        default: run(std::integral_constant<int, 4>{}); break;
+    }
+    // D[token 4*lgrp + v][column lrow] of matrix i is column col0 + 8*lrow + i
+    const int col0 = col_wg + cg * 128;
+#pragma unroll
+    for (int tb = 0; tb < 4; ++tb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int tok = (4 * tb + tq) * 16 + lgrp * 4 + v;
+            if (tok < it.ntok) {
+                float* dst = a.yc + (size_t)(it.row0 + tok) * H + col0 + lrow * 8;
+                *reinterpret_cast<float4*>(dst) = make_float4(Y[tb][0][v], Y[tb][1][v], Y[tb][2][v], Y[tb][3][v]);
+                *reinterpret_cast<float4*>(dst + 4) = make_float4(Y[tb][4][v], Y[tb][5][v], Y[tb][6][v], Y[tb][7][v]);
+            }
+        }
+}
+
 // ------------------------------------------------------------------ 4. y[t] = sum of the token's rows, in pick order
 // grid (n, groups of 1,024 columns, or one workgroup for all of them): the k picks' rows, then the shared experts' rows, each in its parts.  Bound by memory for long
 // prompts (2,048 tokens of the 26-layer shape 27 us, 5 TB/s) and by its trips there for short ones, so eight rows are requested
@@ -1533,7 +1714,7 @@ int down_parts(const moei_model_desc& d, int n) {
 int cus_per_xcd() { return std::max(1, compute_units() / kXcds); }
 
 template <int TM>
-int launch_mm(const moei_model_desc& d, MmArgs a, int max_items, int parts, hipStream_t s) {
+int launch_mm(const moei_model_desc& d, MmArgs a, int n, int max_items, int parts, hipStream_t s) {
     const size_t dn_smem = (size_t)2 * TM * kTileK * 2;
     int rc = pf_allow_lds(prefill_down_kernel<TM>, dn_smem);
     if (rc) return rc;
@@ -1554,11 +1735,16 @@ int launch_mm(const moei_model_desc& d, MmArgs a, int max_items, int parts, hipS
     MOEI_LAUNCH_CHECK();
     if (a.dn_split == 2 && d.I % kDwKS == 0 && d.H % kDwCols == 0) {
         const size_t dw_smem = (size_t)(kDwStagesW * kDwStageElemsW + kDwStagesA * kDwStageElemsA) * 2;
-        auto kernel = d.I < kDwMinSlices * kDwKS ? prefill_down_wide_kernel<true> : prefill_down_wide_kernel<false>;
+        a.n_cb = d.H / kDwCols;
+        // (the items if the experts' shares are even)
+        const int each = (n * d.k + d.E - 1) / d.E, items = d.E * ((each + kTileTokWide - 1) / kTileTokWide) + d.n_shared * ((n + kTileTokWide - 1) / kTileTokWide);
+        const bool tile_each = d.I >= kDtMinSlices * kDwKS && (long long)items * a.n_cb <= kXcds * a.cus;
+        auto kernel = tile_each ? prefill_down_tile_kernel
+                                : d.I < kDwMinSlices * kDwKS ? prefill_down_wide_kernel<true> : prefill_down_wide_kernel<false>;
         rc = pf_allow_lds(kernel, dw_smem);
         if (rc) return rc;
-        a.n_cb = d.H / kDwCols;
-        launch(K_PF_DOWN, kernel, dim3(kXcds * a.cus), dim3(kWdThreads), dw_smem, s, a);
+        const int grid = kXcds * (tile_each ? a.n_cb * ((max_items + kXcds - 1) / kXcds) : a.cus);
+        launch(K_PF_DOWN, kernel, dim3(grid), dim3(kWdThreads), dw_smem, s, a);
         MOEI_LAUNCH_CHECK();
         return MOEI_OK;
     }
@@ -1632,7 +1818,7 @@ int launch_prefill(const moei_model_desc& d, const PrefillScratch& ps, const voi
         a.k_per = (slices + parts - 1) / parts;
         parts = (slices + a.k_per - 1) / a.k_per;  // (none is empty)
     }
-    rc = tm == kTileTok ? launch_mm<kTileTok>(d, a, max_items, parts, s) : launch_mm<kTileTokBig>(d, a, max_items, parts, s);
+    rc = tm == kTileTok ? launch_mm<kTileTok>(d, a, n, max_items, parts, s) : launch_mm<kTileTokBig>(d, a, n, max_items, parts, s);
     if (rc) return rc;
     // long prompts have workgroups enough with one per token
     launch(K_PF_REDUCE, parts > 1 ? prefill_reduce_kernel<true> : prefill_reduce_kernel<false>,

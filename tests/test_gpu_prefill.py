@@ -181,6 +181,21 @@ def test_prefill_down_product_of_few_units(m, E, k, n_shared, H, I, n, resident,
     assert rel_max_err(o["Y"], o["rY"]) <= FFN_TOL_BF16_ACT
 
 
+# long experts of which every compute unit has a tile at most: a workgroup per tile from 40 stages of 64 units on, one fewer, one more; items of every
+# count of 16-token blocks; as many tiles as compute units and more of them than were expected; absent experts
+@pytest.mark.parametrize("E,k,n_shared,H,I,n,resident", [(1, 1, 1, 256, 2496, 270, None), (1, 1, 1, 256, 2560, 270, None), (3, 1, 0, 512, 2624, 50, None),
+                                                         (5, 2, 1, 768, 2560, 300, 2), (9, 3, 2, 256, 4160, 530, None), (32, 2, 0, 2048, 2560, 1100, 20)])
+def test_prefill_down_product_of_long_experts(m, E, k, n_shared, H, I, n, resident, monkeypatch):
+    monkeypatch.setenv("MOEI_PREFILL_TILE", "256")
+    cfg = mi.get_config("C2").scaled(L=1, E=E, k=k, n_shared=n_shared, H=H, I=I, N=4, prompt=16)
+    o = _prefill_case(m, cfg, n, layer=0, resident=resident, sample=24)
+    if resident is None:
+        _check(o)
+        return
+    assert o["flags"] & 2 and o["finite"] and (o["idx"] == o["ridx"]).all() and (o["eam"] == o["ream"]).all()
+    assert rel_max_err(o["Y"], o["rY"]) <= FFN_TOL_BF16_ACT
+
+
 # few experts of few tokens: the down kernel takes an expert's units in parts (a last one that is shorter, units that are no whole
 # slice, an item more than one expert has), with experts that are not resident too
 @pytest.mark.parametrize("E,k,n_shared,H,I,n,resident", [(4, 2, 0, 512, 1032, 5, None), (3, 2, 1, 640, 2056, 60, None), (2, 1, 0, 1024, 520, 90, None),
